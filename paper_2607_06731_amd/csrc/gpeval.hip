@@ -12,7 +12,9 @@
 //   k_class_scan     one workgroup: scans of both; class ranges (and for a
 //                    single request its per-class work-item tables).
 //   k_stage          one thread per program: stage each instruction as one
-//                    8-byte word {flags | selector | cell, payload} in a
+//                    8-byte word (the benchmark set: the address of its
+//                    handler and a payload, threaded.h; the whole command
+//                    table: {flags | selector | cell, payload}) in a
 //                    range of its own (unless k_validate did), folding
 //                    constant subtrees and a leaf into the operator after
 //                    it (stack moves and variables become cell moves);
@@ -29,7 +31,7 @@
 //                    targets are staged in LDS; each wavefront takes the
 //                    group's programs one at a time and runs one over the
 //                    64*K cases of the sub-tile (K per lane) with the value
-//                    stack in VGPRs; the fitness epilogue is fused (MSE:
+//                    stack in VGPRs (threaded code, interp_gfx950.h); the fitness epilogue is fused (MSE:
 //                    scaled square with Kahan accumulation; correlation:
 //                    shifted fp64 sums over valid pairs; integer reward:
 //                    int64 per case) and a wave shuffle tree gives one
@@ -698,6 +700,8 @@ __device__ bool cache_block_stage(bool mine, int r, int64_t s, int64_t e,
 
 #define GP_STAGING_FN __device__
 #include "staging.h"
+#include "threaded.h"
+#include "interp_gfx950.h"
 static_assert(kOpByteBadConst == kOpBadConst, "the LDS copy stores the walk's opcodes as they are");
 
 // Readers of the benchmark-set walk (stage_check_base): op (kOpBadConst
@@ -796,10 +800,10 @@ __global__ __launch_bounds__(kBucketBlock) void k_validate(
             uint2* dst = code + R.node_base + s;
             lds_f32* pvs = (lds_f32*)pv_mem + threadIdx.x;
             if (base && cached)
-                n_staged = stage_check_base(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
+                n_staged = stage_check_base<ThreadedWords>(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
                                             dst, pvs, status, maxd);
             else if (base)
-                n_staged = stage_check_base(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e,
+                n_staged = stage_check_base<ThreadedWords>(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e,
                                             allowed, n_vars, dst, pvs, status, maxd);
             else if (cached)
                 check_program(LdsNodes{cache, lo}, s, e, allowed, n_vars, R.n_consts, status, maxd,
@@ -1019,7 +1023,8 @@ __global__ __launch_bounds__(1024) void k_class_scan(
 // staged sizes inside the block, so ranges never overlap whatever the
 // offsets.
 //
-// Staged instruction (8 bytes, one scalar load):
+// Staged instruction of the flag form (8 bytes, one scalar load; calls within
+// the benchmark set use the threaded form instead, threaded.h):
 //   x = flags | sel << 8 | cell << 16, y = payload
 //   kFPush  save the top into stack cell `cell`, then the top = leaf
 //   kFUn    the top = unary sel (SIN..ABS as 0..5) of the top
@@ -1095,10 +1100,10 @@ __global__ __launch_bounds__(kBucketBlock) void k_stage(
             const int32_t n_vars = ds[R.dataset].n_vars;
             int st = 0, md = 0;
             if (base && cached)
-                stage_check_base(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
+                stage_check_base<ThreadedWords>(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
                                  code + start, pvs, st, md);
             else if (base)
-                stage_check_base(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e, allowed,
+                stage_check_base<ThreadedWords>(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e, allowed,
                                  n_vars, code + start, pvs, st, md);
             else if (cached)
                 stage_walk(LdsNodes{cache, lo}, s, e, GlobalConsts{R.consts}, code + start, m.slen,
@@ -1184,6 +1189,15 @@ struct EvalConst {
     int32_t reward_power;
     float reward_M;
 };
+
+// Pointers to memory that is constant while a kernel runs: loads at uniform
+// addresses are scalar loads, also past an asm statement (which the compiler
+// takes as writing any ordinary memory).
+template <class T> using const_ptr = const __attribute__((address_space(4))) T*;
+template <class T> __device__ __forceinline__ const_ptr<T> as_const(const T* p)
+{
+    return (const_ptr<T>)(uintptr_t)p;
+}
 
 // Error-free sum: s + e == a + b exactly (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e)
@@ -1357,10 +1371,9 @@ __device__ __forceinline__ void ext_unary(uint32_t sel, float (&t)[K])
     }
 }
 
-// EXT: the interpreter for the whole command table (POW, the unary
-// commands beyond the benchmark set, cell moves); without it the code is
-// the benchmark set's alone.
-template <int MAXD, int K, bool EXT>
+// The interpreter for the whole command table (POW, the unary commands
+// beyond the benchmark set, cell moves), over words of the flag form.
+template <int MAXD, int K>
 __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
                                             const float* __restrict__ xl, float (&tos)[K])
 {
@@ -1402,7 +1415,7 @@ __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
             }
         // unary: replaces the top
         const uint32_t uop = GP_SIN + sel;
-        if (EXT && sel >= kUnSquare) {
+        if (sel >= kUnSquare) {
             ext_unary<K>(sel, tos);
         } else {
             switch (uop) {
@@ -1469,7 +1482,7 @@ __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
             float sv[K];
 #pragma unroll
             for (int j = 0; j < K; ++j) sv[j] = GP_CHUNK_GET(slot, j);
-            if (EXT && sel == kBinPow) {
+            if (sel == kBinPow) {
 #pragma unroll
                 for (int j = 0; j < K; ++j) tos[j] = pow_value(sv[j], tos[j]);
             } else {
@@ -1479,7 +1492,7 @@ __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
             // top OP leaf; a constant leaf gets its own copy of the op
             // switch so the constant stays a scalar operand instead of
             // being broadcast into registers first
-            if (EXT && sel == kBinPow) {
+            if (sel == kBinPow) {
                 float lv[K];
                 GP_LEAF(f & kFConst, w.y, lv);
 #pragma unroll
@@ -1494,7 +1507,7 @@ __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
                 GP_LEAF(false, w.y, lv);
                 GP_BINARY_AB(GP_ADD + sel, tos, lv, tos);
             }
-        } else if (EXT && (f & kFMove)) {
+        } else if (f & kFMove) {
             // cell move; every cell number is scaled by J and masked to a
             // multiple of J inside the chunk
             constexpr uint32_t kCellMask = 32u - J;
@@ -1533,6 +1546,127 @@ __device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
             GP_LEAF(f & kFConst, w.y, tos);
         }
     } while ((int32_t)f >= 0);             // until kFLast (the sign bit)
+}
+
+// ------------------------------------------------- threaded interpreter
+// The constants its handlers read from vector registers v22..v25, made once
+// per kernel: opaque to the optimizer, which would otherwise rebuild them at
+// every run.
+struct ThreadConsts {
+    float inv_pi, sin_c3, log2e_hi, theta;
+};
+__device__ __forceinline__ float opaque(float v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ ThreadConsts thread_consts()
+{
+    return {opaque(kInvPi), opaque(kSinC3), opaque(kLog2eHi), opaque(0.001f)};
+}
+
+// Runs one program staged as threaded words (threaded.h) on K cases per
+// lane; `xl` is this lane's first case of the LDS input tile, the result is
+// the stack's one element.  Handlers that meet a value outside their fast
+// range return with a code; the out-of-line function is applied here, per
+// case, and the run resumes.
+typedef float f32x32 __attribute__((ext_vector_type(32)));
+
+#define GP_THREAD_TABLE(table)                                                             \
+    "s_getpc_b64 s[90:91]\n"                                                              \
+    "s_add_u32 s90, s90, " table "@rel32@lo+4\n"                                          \
+    "s_addc_u32 s91, s91, " table "@rel32@hi+12\n"
+// the first word, then its handler
+#define GP_THREAD_ENTER(table)                                                             \
+    "s_load_dwordx2 s[88:89], s[84:85], 0x0\n" GP_THREAD_TABLE(table)                      \
+    "s_mov_b32 s86, 8\n"                                                                  \
+    "s_waitcnt lgkmcnt(0)\n"                                                              \
+    "s_add_u32 s92, s90, s88\n"                                                           \
+    "s_addc_u32 s93, s91, 0\n"                                                            \
+    "s_swappc_b64 s[94:95], s[92:93]\n"
+// after a value was replaced: the finish code of the block that asked for it
+#define GP_THREAD_RESUME(table)                                                            \
+    GP_THREAD_TABLE(table)                                                                 \
+    "s_add_u32 s92, s90, s87\n"                                                           \
+    "s_addc_u32 s93, s91, 0\n"                                                            \
+    "s_swappc_b64 s[94:95], s[92:93]\n"
+#define GP_THREAD_INPUTS                                                                  \
+    "{s[84:85]}"(pc), "{v31}"(lane_addr), "{v22}"(tc.inv_pi), "{v23}"(tc.sin_c3),          \
+        "{v24}"(tc.log2e_hi), "{v25}"(tc.theta)
+#define GP_THREAD_CLOBBERS                                                                \
+    "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s90", "s91", "s92", "s93",   \
+        "s94", "s95", "s96", "s97", "v8", "v9", "v10", "v11", "v12", "v13", "v14", "v15", \
+        "v16", "v17", "v18", "v19", "vcc", "scc", "memory"
+
+template <int MAXD, int K>
+__device__ __forceinline__ void run_threaded(const uint2* code, const float* xl,
+                                             const ThreadConsts& tc, float (&tos)[K])
+{
+    static_assert((MAXD == 8 && K == 4) || (MAXD == 16 && K == 4) || (MAXD == 32 && K == 2),
+                  "the tables of interp_gfx950.h");
+    const uint64_t pa = (uint64_t)(uintptr_t)code;
+    const uint64_t pc = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(pa >> 32)) << 32 |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)pa);
+    const uint32_t lane_addr =
+        (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)xl;
+    f32x32 lo, hi;                             // the stack cells (hi unused at depth 8)
+    float t0, t1, t2, t3;
+    uint64_t w;
+    uint32_t off, resume, rc;
+    if constexpr (MAXD == 8)
+        asm volatile(GP_THREAD_ENTER("gp_threads_d8") : "+{v[36:67]}"(lo),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
+                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+    else if constexpr (MAXD == 16)
+        asm volatile(GP_THREAD_ENTER("gp_threads_d16") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
+                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+    else
+        asm volatile(GP_THREAD_ENTER("gp_threads_d32") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
+                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+    while (__builtin_expect(rc != 0u, 0)) {
+        float v[4] = {t0, t1, t2, t3};
+        if (rc == 1u) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) v[j] = sin_value(v[j]);
+        } else if (rc == 2u) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) v[j] = cos_value(v[j]);
+        } else if (rc == 3u) {
+#pragma unroll
+            for (int j = 0; j < K; ++j) v[j] = exp_value(v[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < K; ++j) v[j] = sqrt_value(v[j]);
+        }
+        t0 = v[0]; t1 = v[1]; t2 = v[2]; t3 = v[3];
+        // (uniform; said again where the loop made them look otherwise)
+        w = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(w >> 32)) << 32 |
+            (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+        off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+        resume = (uint32_t)__builtin_amdgcn_readfirstlane((int)resume);
+        if constexpr (MAXD == 8)
+            asm volatile(GP_THREAD_RESUME("gp_threads_d8") : "+{v[36:67]}"(lo),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
+                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+        else if constexpr (MAXD == 16)
+            asm volatile(GP_THREAD_RESUME("gp_threads_d16") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
+                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+        else
+            asm volatile(GP_THREAD_RESUME("gp_threads_d32") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
+                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
+                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
+                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+    }
+#pragma unroll
+    for (int j = 0; j < K; ++j) tos[j] = lo[j];
 }
 
 // ------------------------------------------------- correlation fitness
@@ -1653,7 +1787,7 @@ __device__ __forceinline__ void corr_wave_reduce(CorrLane& c)
 }
 
 template <int MAXD, int K, int FIT, bool EXT>
-__global__ __launch_bounds__(kWG) void k_eval(
+__global__ __launch_bounds__(kWG, !EXT && FIT == kFitMse ? (MAXD == 8 ? 6 : 4) : 1) void k_eval(
     const uint2* __restrict__ code, const ProgMeta* __restrict__ meta,
     const int32_t* __restrict__ order, const int32_t* __restrict__ class_info,
     uint32_t* __restrict__ work_counter, const DevDataset* __restrict__ ds,
@@ -1682,15 +1816,18 @@ __global__ __launch_bounds__(kWG) void k_eval(
     // deeper classes, which end last, finish sooner (alone, all wavefronts
     // of a kernel share one priority and nothing changes).
     if constexpr (MAXD >= 16) __builtin_amdgcn_s_setprio(1);
+    ThreadConsts tc;
+    if constexpr (!EXT) tc = thread_consts();
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int c = a.cls;
-    const int G = class_g[c];                     // <= a.G, the accumulators' capacity
-    const int cstart = class_info[2 * c];
-    const int32_t* __restrict__ cnt_c = seg_cnt + c * a.n_seg;
-    const int32_t* __restrict__ pos_c = seg_pos + c * a.n_seg;
-    const uint32_t* __restrict__ pre_c = item_pre + c * (a.n_seg + 1);
+    const int G = as_const(class_g)[c];           // <= a.G, the accumulators' capacity
+    const int cstart = as_const(class_info)[2 * c];
+    const const_ptr<int32_t> cnt_c = as_const(seg_cnt) + c * a.n_seg;
+    const const_ptr<int32_t> pos_c = as_const(seg_pos) + c * a.n_seg;
+    const const_ptr<uint32_t> pre_c = as_const(item_pre) + c * (a.n_seg + 1);
+    const const_ptr<int32_t> ord = as_const(order);
     const uint32_t n_items = pre_c[a.n_seg];
     int staged_d = -1;                            // dataset and first sub-tile in LDS
     int64_t staged = -1;
@@ -1717,10 +1854,10 @@ __global__ __launch_bounds__(kWG) void k_eval(
             const int mid = (sl + sh + 1) >> 1;
             if (pre_c[mid] <= item) sl = mid; else sh = mid - 1;
         }
-        const int d = seg_ds[sl];
+        const int d = as_const(seg_ds)[sl];
         // fields one by one: a struct copy indexed by the class would live
         // in scratch memory
-        const DevDataset* __restrict__ Dp = ds + d;
+        const const_ptr<DevDataset> Dp = as_const(ds) + d;
         const float* __restrict__ Xd = Dp->X;
         const float* __restrict__ yd = Dp->y;
         const int64_t ld_x = Dp->ld_x;
@@ -1792,8 +1929,7 @@ __global__ __launch_bounds__(kWG) void k_eval(
             for (;;) {
                 const int g = (int)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_next, 1u)) >> 6);
                 if (g >= gn) break;
-                const int pid = order[obase + g];
-                const ProgMeta m = meta[pid];
+                const uint2* pc = code + as_const(meta)[ord[obase + g]].start;
                 // fused residual, validity and scaled compensated square sum
                 // (MSE), or the sums of the correlation fitness
                 float hi = 0.f, lo_ = 0.f;
@@ -1806,7 +1942,10 @@ __global__ __launch_bounds__(kWG) void k_eval(
                 for (int b = 0; b < nw; ++b) {
                     const float* blk = xt + b * rows * SUB;
                     float tos[K];
-                    run_program<MAXD, K, EXT>(code + m.start, blk + lane, tos);
+                    if constexpr (EXT)
+                        run_program<MAXD, K>(pc, blk + lane, tos);
+                    else
+                        run_threaded<MAXD, K>(pc, blk + lane, tc, tos);
                     const int64_t base = (first + b) * SUB;
                     const float* yt = blk + n_vars * SUB;
                     if constexpr (FIT == kFitCorr) {
@@ -1935,12 +2074,14 @@ __global__ __launch_bounds__(kWG) void k_predict(
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int lane = tid & 63;
-    const int start = class_info[2 * a.cls];
-    const int count = class_info[2 * a.cls + 1];
+    const int start = as_const(class_info)[2 * a.cls];
+    const int count = as_const(class_info)[2 * a.cls + 1];
     const int n_groups = (count + kWaves - 1) / kWaves;
     const int64_t n_sub = (a.n_cases + SUB - 1) / SUB;
     const uint64_t n_items = (uint64_t)n_groups * (uint64_t)n_sub;
     int64_t staged = -1;
+    ThreadConsts tc;
+    if constexpr (!EXT) tc = thread_consts();
     for (;;) {
         if (tid == 0) s_item = atomicAdd(work_counter, 1u);
         __syncthreads();
@@ -1962,10 +2103,13 @@ __global__ __launch_bounds__(kWG) void k_predict(
         // interpreter below keeps its scalar branches
         const int g = __builtin_amdgcn_readfirstlane(grp * kWaves + wave);
         if (g < count) {
-            const int pid = order[start + g];
-            const ProgMeta m = meta[pid];
+            const int pid = as_const(order)[start + g];
+            const uint2* pc = code + as_const(meta)[pid].start;
             float tos[K];
-            run_program<MAXD, K, EXT>(code + m.start, xt + lane, tos);
+            if constexpr (EXT)
+                run_program<MAXD, K>(pc, xt + lane, tos);
+            else
+                run_threaded<MAXD, K>(pc, xt + lane, tc, tos);
 #pragma unroll
             for (int j = 0; j < K; ++j) {
                 const int64_t gi = base + lane + j * 64;

@@ -360,14 +360,48 @@ GP_STAGING_FN void check_program(Nodes nodes, int64_t s, int64_t e, uint32_t all
 // memory round trip serves the step.
 constexpr uint32_t kOpBadConst = 0xFEu;
 
+// The words of the flag form (above), as stage_check_base asks for them: `rt`
+// elements are on the stack before the instruction.
+struct StagedWords {
+    static __host__ __device__ uint32_t save(int rt) { return rt >= 1 ? (uint32_t)(rt - 1) : kDummyCell; }
+    static __host__ __device__ uint2 push_const(int rt, uint32_t bits)
+    {
+        return staged_word(kFPush | kFConst, 0u, save(rt), bits);
+    }
+    static __host__ __device__ uint2 push_row(int rt, uint32_t payload)
+    {
+        return staged_word(kFPush, 0u, save(rt), payload);
+    }
+    static __host__ __device__ uint2 push_unary(int rt, uint32_t sel, uint32_t payload)
+    {
+        return staged_word(kFPush | kFUn, sel, save(rt), payload);
+    }
+    static __host__ __device__ uint2 top_row(int, uint32_t sel, uint32_t payload)
+    {
+        return staged_word(kFLBin, sel, 0u, payload);
+    }
+    static __host__ __device__ uint2 top_const(int, uint32_t sel, uint32_t bits)
+    {
+        return staged_word(kFLBin | kFConst, sel, 0u, bits);
+    }
+    // second from top (element rt-2) is read from cell rt-2
+    static __host__ __device__ uint2 cells(int rt, uint32_t sel)
+    {
+        return staged_word(kFSBin, sel, (uint32_t)(rt - 2), 0u);
+    }
+    static __host__ __device__ uint2 unary(int, uint32_t sel) { return staged_word(kFUn, sel, 0u, 0u); }
+    // the same word as the program's last
+    static __host__ __device__ uint2 last(uint2 w) { return make_uint2(w.x | kFLast, w.y); }
+};
+
 // check_program and stage_walk in one pass, for a mask within
-// GP_BASE_OPS: the same checks in the same order (op, operand range,
+// GP_BASE_OPS (the words in the form `Words` makes them): the same checks in the same order (op, operand range,
 // underflow, depth at each node, then the final depth), the same maximum
 // depth and, for a valid program, the same words, stored to out[0, n) with
 // n returned (the staged count).  At most e - s words are stored, whatever
 // the program; for an invalid one they mean nothing.  A variable folds the
 // operator after it into its own word, so that operator is checked with it.
-template <class Reader>
+template <class Words = StagedWords, class Reader>
 GP_STAGING_FN int64_t stage_check_base(Reader rd, int64_t s, int64_t e, uint32_t allowed,
                                        int32_t n_vars, uint2* __restrict__ out, lds_f32* pvs,
                                        int& status, int& maxd)
@@ -376,7 +410,7 @@ GP_STAGING_FN int64_t stage_check_base(Reader rd, int64_t s, int64_t e, uint32_t
     int rt = 0, np = 0, md = 0, st = GP_PROG_OK;
     int64_t n = 0;
     // each word is stored as it is made; the last one is stored again at
-    // the end, with kFLast
+    // the end, marked as the last
     uint2 last = make_uint2(0u, 0u);
     auto put = [&](uint2 v) {
         out[n] = v;
@@ -401,8 +435,7 @@ GP_STAGING_FN int64_t stage_check_base(Reader rd, int64_t s, int64_t e, uint32_t
     // held-back constants become runtime elements, bottom up
     auto flush = [&]() {
         for (int i = 0; i < np; ++i) {
-            const uint32_t wr = rt >= 1 ? (uint32_t)(rt - 1) : kDummyCell;
-            put(staged_word(kFPush | kFConst, 0u, wr, __float_as_uint(pv(i))));
+            put(Words::push_const(rt, __float_as_uint(pv(i))));
             ++rt;
         }
         np = 0;
@@ -441,12 +474,11 @@ GP_STAGING_FN int64_t stage_check_base(Reader rd, int64_t s, int64_t e, uint32_t
                 ++k;
             }
             const uint32_t payload = arg * kVarPayload;
-            const uint32_t wr = rt >= 1 ? (uint32_t)(rt - 1) : kDummyCell;
             if (fb) {
                 // top = top OP x: the push and the pop cancel
-                put(staged_word(kFLBin, nx - GP_ADD, 0u, payload));
+                put(Words::top_row(rt, nx - GP_ADD, payload));
             } else {
-                put(staged_word(fu ? kFPush | kFUn : kFPush, fu ? nx - GP_SIN : 0u, wr, payload));
+                put(fu ? Words::push_unary(rt, nx - GP_SIN, payload) : Words::push_row(rt, payload));
                 ++rt;
             }
         } else if (op <= GP_DIV) {
@@ -457,23 +489,22 @@ GP_STAGING_FN int64_t stage_check_base(Reader rd, int64_t s, int64_t e, uint32_t
             } else if (np == 1) {
                 // top = top OP c: the runtime top is the left operand
                 np = 0;
-                put(staged_word(kFLBin | kFConst, op - GP_ADD, 0u, __float_as_uint(top)));
+                put(Words::top_const(rt, op - GP_ADD, __float_as_uint(top)));
             } else {
-                // second from top (element rt-2) is read from cell rt-2
-                put(staged_word(kFSBin, op - GP_ADD, (uint32_t)(rt - 2), 0u));
+                put(Words::cells(rt, op - GP_ADD));
                 --rt;
             }
         } else if (np >= 1) {
             top = unary_value(op, top);
             pv(np - 1) = top;
         } else {
-            put(staged_word(kFUn, op - GP_SIN, 0u, 0u));
+            put(Words::unary(rt, op - GP_SIN));
         }
     }
     if (st == GP_PROG_OK && rt + np != 1) st = GP_PROG_FINAL_DEPTH;
     if (st == GP_PROG_OK) {
         flush();                                 // a constant program: its value is pushed
-        out[n - 1] = make_uint2(last.x | kFLast, last.y);
+        out[n - 1] = Words::last(last);
     }
     status = st;
     maxd = md;
