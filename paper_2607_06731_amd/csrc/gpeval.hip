@@ -1,27 +1,27 @@
 // gpeval.hip -- gfx950 kernels and C ABI of the batched fitness evaluator.
 //
 // Path of one scoring call (all on the caller's stream):
-//   k_tables         one workgroup: check the dataset and request tables, lay
-//                    the requests out back to back, derive tile shapes.
-//   k_validate       one thread per program: validate (GCL stack and
-//                    variable discipline, 32-cell limit, opcode/operand
-//                    ranges, allowed ops), count staged instructions, depth
-//                    class and partition key; per-block key counts and
-//                    staged sizes.  With an op mask within the benchmark
-//                    set the same walk stages the program in place (below).
-//   k_class_scan     one workgroup: scans of both; class ranges (and for a
-//                    single request its per-class work-item tables).
-//   k_stage          one thread per program: stage each instruction as one
-//                    8-byte word (the benchmark set: the address of its
-//                    handler and a payload, threaded.h; the whole command
-//                    table: {flags | selector | cell, payload}) in a
-//                    range of its own (unless k_validate did), folding
+//   k_tables         calls of several requests: one workgroup checks the
+//                    dataset and request tables, lays the requests out back
+//                    to back and derives tile shapes (a single request's
+//                    entries travel as kernel arguments).
+//   k_stage_waves    one wavefront per program: validate (GCL stack
+//                    discipline, 32-cell limit, opcode/operand ranges,
+//                    allowed ops) and stage each instruction as one 8-byte
+//                    word (the address of its handler and a payload,
+//                    threaded.h) in the program's own node range, folding
 //                    constant subtrees and a leaf into the operator after
-//                    it (stack moves and variables become cell moves);
-//                    stable scatter of program ids by (depth class, length
+//                    it; depth class and partition key; key counts per block.
+//   k_order          stable scatter of program ids by (depth class, length
 //                    band): each depth class (max depth <= 8, <= 16, <= 32)
 //                    runs a kernel whose register stack is only as deep as
-//                    needed, longest programs first.
+//                    needed, longest programs first; class ranges and (for a
+//                    single request) its per-class work-item tables.
+//                    With an op mask beyond the benchmark set three kernels
+//                    take the place of these two: k_validate (one thread per
+//                    program: variables, stack moves, counts), k_class_scan
+//                    (one workgroup: scans of the counts) and k_stage (words
+//                    {flags | selector | cell, payload}, the scatter).
 //   k_seg_tables     several requests: per (class, request) program counts,
 //                    positions and work-item prefixes.
 //   k_eval<MAXD,K,FIT> persistent workgroups pull (program group, case tile)
@@ -113,13 +113,6 @@ constexpr int kK1 = 4;                  // cases per lane of the depth <= 16 cla
 constexpr int kMaxTiles = 32;            // case tiles per program (cap)
 constexpr int kBucketBlock = 128;        // programs per staging/partition block
 constexpr int kStageNodes = 6656;        // LDS node cache of a staging block (26 KB, 52 per program)
-// The short walk's cache (op masks within the benchmark set) holds an op
-// byte and a payload per node (30 KB for 6144 nodes, 48 per program),
-// which with the held constants keeps four staging blocks per CU.
-constexpr int kStageNodesEmit = 6144;
-constexpr uint32_t kOpByteBadConst = 0xFEu;   // its op byte of a constant out of range
-// Fourth word of a raw buffer resource on gfx9 parts (32-bit data format).
-constexpr int kBufferWord3 = 0x00020000;
 // Constants held back for folding per program while staging: a longer run
 // of constants is pushed (as runtime values) before the next one is held.
 // 16 keeps the staging block at four per CU (with the node cache).
@@ -223,6 +216,28 @@ struct DevDataset {
     int32_t window[kClasses];
 };
 
+// A dataset's derived entry (n_cases >= 1).
+__host__ __device__ inline DevDataset make_dataset(const gp_dataset& in, int32_t tile_lds, int32_t tile_max)
+{
+    DevDataset o;
+    const int e = scale_exponent(in.n_cases);
+    o.X = in.X;
+    o.y = in.y;
+    o.ld_x = in.ld_x;
+    o.n_cases = in.n_cases;
+    o.tax = in.tax_on_length;
+    o.unscale = ldexp(1.0, 2 * e) / (double)in.n_cases;
+    o.scale = ldexpf(1.0f, -e);
+    o.n_vars = in.n_vars;
+    for (int c = 0; c < kClasses; ++c) {
+        const TileShape t = tile_shape(in.n_cases, class_k(c, in.n_vars), in.n_vars, tile_lds, tile_max);
+        o.passes[c] = t.passes;
+        o.n_tiles[c] = t.n_tiles;
+        o.window[c] = t.window;
+    }
+    return o;
+}
+
 // Request entry as the kernels use it: the caller's entry with its
 // program and node offsets inside the whole call (derived each call).
 struct DevRequest {
@@ -244,7 +259,6 @@ struct DevRequest {
 // the single dataset `one` is used; with req_in == NULL the single request
 // `one_req`.  *bad becomes 1 for inconsistent tables; then no program is
 // staged and sizes are clamped so that every later index stays in range.
-// bad[1] (k_validate's restage flag) is cleared.
 __global__ __launch_bounds__(256) void k_tables(
     const gp_dataset* __restrict__ ds_in, int32_t n_ds, gp_dataset one,
     const gp_request* __restrict__ req_in, int32_t n_req, gp_request one_req,
@@ -257,30 +271,17 @@ __global__ __launch_bounds__(256) void k_tables(
     if (threadIdx.x == 0) s_bad = 0;
     __syncthreads();
     for (int d = threadIdx.x; d < n_ds; d += blockDim.x) {
-        const gp_dataset in = ds_in ? ds_in[d] : one;
-        DevDataset o;
+        gp_dataset in = ds_in ? ds_in[d] : one;
         const bool ok = in.n_cases >= 1 && in.n_cases <= max_cases && in.n_vars >= 0 &&
                         in.n_vars <= max_vars && in.y != nullptr &&
                         (in.n_vars == 0 || (in.X != nullptr && in.ld_x >= in.n_cases)) &&
                         __builtin_isfinite(in.tax_on_length);
-        if (!ok) atomicOr(&s_bad, 1);
-        const int64_t n = ok ? in.n_cases : 1;
-        const int e = scale_exponent(n);
-        o.X = in.X;
-        o.y = in.y;
-        o.ld_x = in.ld_x;
-        o.n_cases = n;
-        o.tax = in.tax_on_length;
-        o.unscale = ldexp(1.0, 2 * e) / (double)n;
-        o.scale = ldexpf(1.0f, -e);
-        o.n_vars = ok ? in.n_vars : 0;
-        for (int c = 0; c < kClasses; ++c) {
-            const TileShape t = tile_shape(n, class_k(c, o.n_vars), o.n_vars, tile_lds, tile_max);
-            o.passes[c] = t.passes;
-            o.n_tiles[c] = t.n_tiles;
-            o.window[c] = t.window;
+        if (!ok) {
+            atomicOr(&s_bad, 1);
+            in.n_cases = 1;
+            in.n_vars = 0;
         }
-        ds_out[d] = o;
+        ds_out[d] = make_dataset(in, tile_lds, tile_max);
     }
     // each thread takes a contiguous chunk of requests: check, clamp, sum
     const int chunk = (n_req + 255) / 256;
@@ -338,10 +339,7 @@ __global__ __launch_bounds__(256) void k_tables(
     }
     if (threadIdx.x == 0) seg_start[n_req] = n_programs;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        bad[0] = s_bad;
-        bad[1] = 0;                     // the restage flag, raised by k_validate
-    }
+    if (threadIdx.x == 0) *bad = s_bad;
 }
 
 // ------------------------------------------------------------------ sin/cos
@@ -534,6 +532,15 @@ __device__ __forceinline__ float unary_value(uint32_t op, float x)
     }
 }
 
+// Pointers to memory that is constant while a kernel runs: loads at uniform
+// addresses are scalar loads, also past an asm statement (which the compiler
+// takes as writing any ordinary memory).
+template <class T> using const_ptr = const __attribute__((address_space(4))) T*;
+template <class T> __device__ __forceinline__ const_ptr<T> as_const(const T* p)
+{
+    return (const_ptr<T>)(uintptr_t)p;
+}
+
 // ------------------------------------------------------------- staging
 // Request of program p: the last request whose first program is <= p.
 __device__ __forceinline__ int request_of(const int64_t* __restrict__ seg_start, int32_t n_seg,
@@ -550,7 +557,6 @@ __device__ __forceinline__ int request_of(const int64_t* __restrict__ seg_start,
 // LDS-qualified pointers (per-lane LDS addressing without generic loads).
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) float lds_f32;
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 // Node readers for the staging passes: straight from the request's array,
 // or from the block's LDS copy of its node range.
@@ -646,119 +652,26 @@ __device__ bool cache_block_nodes(bool mine, int r, int64_t s, int64_t e,
     return use;
 }
 
-// The short walk's LDS copy of the block's node range: the op byte of
-// each node (kOpByteBadConst for a constant whose index is out of range,
-// 0xFF for any opcode from 32 on) and its payload: the constant's value
-// bits for a constant in range, the argument otherwise.  The constants are
-// gathered here, many loads in flight per thread, so the walk reads only
-// LDS.  Every thread of the block must call it.
-__device__ bool cache_block_stage(bool mine, int r, int64_t s, int64_t e,
-                                  const DevRequest* __restrict__ reqs, lds_u8* ops,
-                                  lds_u32* pay, int64_t* lo)
-{
-    int rq = 0, n = 0;
-    const bool use = block_node_range(mine, r, s, e, kStageNodesEmit, &rq, lo, &n);
-    if (use) {
-        // one round: each thread has all its loads in flight at once (the
-        // block's cache, 48 nodes per program), then all its constants'
-        // gathers; raw buffer loads take a 32-bit lane offset plus the
-        // round-invariant row offset as a scalar, so the loads in flight
-        // cost one register each (loads past a range read 0)
-        constexpr int kU = kStageNodesEmit / kBucketBlock;
-        const int64_t nc = reqs[rq].n_consts;
-        const __amdgpu_buffer_rsrc_t nr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint32_t*>(reqs[rq].nodes + *lo), 0, n * 4, kBufferWord3);
-        const __amdgpu_buffer_rsrc_t cr = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(reqs[rq].consts), 0, (int)(nc * 4), kBufferWord3);
-        const int t4 = (int)threadIdx.x * 4;
-        uint32_t v[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u)
-            v[u] = __builtin_amdgcn_raw_buffer_load_b32(nr, t4, u * kBucketBlock * 4, 0);
-        uint32_t c[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const uint32_t a = v[u] >> 8;
-            c[u] = (v[u] & 0xFFu) == GP_CONST ? __builtin_amdgcn_raw_buffer_load_b32(cr, (int)(a * 4u), 0, 0)
-                                              : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const int i = u * kBucketBlock + (int)threadIdx.x;
-            if (i < n) {
-                const uint32_t op = v[u] & 0xFFu;
-                const bool cst = op == GP_CONST;
-                const bool bad = cst && (int64_t)(v[u] >> 8) >= nc;
-                ops[i] = (uint8_t)(bad ? kOpByteBadConst : (op < 32u ? op : 0xFFu));
-                pay[i] = cst ? (bad ? 0u : c[u]) : v[u] >> 8;
-            }
-        }
-    }
-    __syncthreads();
-    return use;
-}
-
 #define GP_STAGING_FN __device__
 #include "staging.h"
 #include "threaded.h"
 #include "interp_gfx950.h"
-static_assert(kOpByteBadConst == kOpBadConst, "the LDS copy stores the walk's opcodes as they are");
-
-// Readers of the benchmark-set walk (stage_check_base): op (kOpBadConst
-// for a constant out of range), payload word, constant value, from the
-// block's LDS copy (the payload holds the constant's value) or straight
-// from the request's arrays (the payload is the constant's index).
-struct LdsStageReader {
-    const lds_u8* o;
-    const lds_u32* p;
-    int64_t lo;
-    __device__ uint32_t op(int64_t k) const { return o[k - lo]; }
-    __device__ uint32_t pay(int64_t k) const { return p[k - lo]; }
-    __device__ float cval(int64_t, uint32_t pay) const { return __uint_as_float(pay); }
-};
-struct GlobalStageReader {
-    const uint32_t* __restrict__ n;
-    const float* __restrict__ c;
-    int64_t n_consts;
-    __device__ uint32_t op(int64_t k) const
-    {
-        const uint32_t w = n[k], op = (w & 0xFFu) < 32u ? (w & 0xFFu) : 0xFFu;
-        return op == GP_CONST && (int64_t)(w >> 8) >= n_consts ? kOpBadConst : op;
-    }
-    __device__ uint32_t pay(int64_t k) const { return n[k] >> 8; }
-    __device__ float cval(int64_t, uint32_t pay) const { return c[pay]; }
-};
-
-// LDS words of a staging block's node copy: the general walk's node
-// words, or the short walk's payloads followed by its op bytes.
-constexpr int kCacheWords = kStageNodes > kStageNodesEmit + kStageNodesEmit / 4
-                                ? kStageNodes : kStageNodesEmit + kStageNodesEmit / 4;
 
 // Pass 1, one thread per program (blocks of kBucketBlock): validate, count
 // staged instructions, derive the depth class and the partition key, and
 // accumulate per-block key counts and staged sizes for the scans that
 // follow.  The block's nodes are read from an LDS copy when they fit.
-// With an op mask within the benchmark set the same walk also stages the
-// program, at its own node offset in the request's part of `code` (staged
-// words never outnumber nodes, so the programs' ranges hold them, disjoint
-// while the offsets never decrease); a program whose offsets do decrease
-// sets *restage, and k_stage then stages every program again, packed.
 __global__ __launch_bounds__(kBucketBlock) void k_validate(
     int64_t n_programs, uint32_t allowed, const DevDataset* __restrict__ ds,
     const DevRequest* __restrict__ reqs, const int64_t* __restrict__ seg_start, int32_t n_seg,
     const int32_t* __restrict__ tables_bad, int32_t lpt, int32_t n_blk,
     ProgMeta* __restrict__ meta, uint8_t* __restrict__ cls, int32_t* __restrict__ pds,
-    int32_t* __restrict__ blk_counts, int64_t* __restrict__ blk_slen, uint2* __restrict__ code,
-    int32_t* __restrict__ restage)
+    int32_t* __restrict__ blk_counts, int64_t* __restrict__ blk_slen)
 {
     __shared__ int cnt[kKeys];
     __shared__ unsigned long long s_slen;
-    __shared__ uint32_t cache_mem[kCacheWords];
-    __shared__ float pv_mem[kHeldConsts * kBucketBlock];
+    __shared__ uint32_t cache_mem[kStageNodes];
     lds_u32* cache = (lds_u32*)cache_mem;
-    // a mask within the benchmark set: the short walk, which also stages
-    const bool base = (allowed & ~GP_BASE_OPS) == 0u;
-    lds_u8* ops = (lds_u8*)(cache + kStageNodesEmit);
     if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) s_slen = 0ull;
     const int64_t p = (int64_t)blockIdx.x * kBucketBlock + threadIdx.x;
@@ -775,14 +688,12 @@ __global__ __launch_bounds__(kBucketBlock) void k_validate(
         if (tab_ok) {
             s = R.offsets[q];
             e = R.offsets[q + 1];
-            if (e < s) *restage = 1;
         }
     }
     const bool range_ok = s >= 0 && e >= s && e <= R.n_nodes && e - s <= INT32_MAX - 1;
     const bool mine = have && tab_ok && range_ok && e > s;
     int64_t lo = 0;
-    const bool cached = base ? cache_block_stage(mine, r, s, e, reqs, ops, cache, &lo)
-                             : cache_block_nodes(mine, r, s, e, reqs, cache, &lo);
+    const bool cached = cache_block_nodes(mine, r, s, e, reqs, cache, &lo);
     long long slen = 0;                       // this program's staged size
     int pkey = 0xFF;                          // and its partition key
     if (have) {
@@ -797,15 +708,7 @@ __global__ __launch_bounds__(kBucketBlock) void k_validate(
             status = GP_PROG_EMPTY;
         } else {
             const int32_t n_vars = ds[R.dataset].n_vars;
-            uint2* dst = code + R.node_base + s;
-            lds_f32* pvs = (lds_f32*)pv_mem + threadIdx.x;
-            if (base && cached)
-                n_staged = stage_check_base<ThreadedWords>(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
-                                            dst, pvs, status, maxd);
-            else if (base)
-                n_staged = stage_check_base<ThreadedWords>(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e,
-                                            allowed, n_vars, dst, pvs, status, maxd);
-            else if (cached)
+            if (cached)
                 check_program(LdsNodes{cache, lo}, s, e, allowed, n_vars, R.n_consts, status, maxd,
                               n_staged);
             else
@@ -814,7 +717,7 @@ __global__ __launch_bounds__(kBucketBlock) void k_validate(
         }
         const int c = status == GP_PROG_OK ? depth_class(maxd) : -1;
         ProgMeta m;
-        m.start = R.node_base + s;            // where the short walk staged it
+        m.start = 0;                          // k_stage's
         m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : e - s);
         m.slen = c >= 0 ? (int32_t)n_staged : 0;
         meta[p] = m;
@@ -888,9 +791,506 @@ __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict
     item_pre[c * (n_seg + 1) + n_seg] = items;
 }
 
+// --------------------------------------------- staging by wavefronts
+// One wavefront stages one program of the benchmark set: lane l holds node
+// l of a 64-node chunk (longer programs take several chunks), and what the
+// serial walk of staging.h decides node by node has a form over lanes.
+//   depth after a node   leaves minus binary operators up to it (two ballots)
+//   elements that depend on a variable (the runtime depth)
+//                        the smallest depth since the last variable: a prefix
+//                        minimum, made one scan over the whole chunk by
+//                        subtracting 64 per variable passed
+//   held constants       depth minus runtime depth
+// From those each node knows the word it emits, if any, and the words before
+// it.  Folded operators are the only serial part: a loop over them, uniform
+// in the wavefront, whose operands are the values at the last node of each
+// depth.  (The serial walk, a program per lane, cost 275 instructions a node
+// for every wavefront, the union of what its 64 lanes were doing: 33 us for
+// 32 programs, 70 us for 10,000.)  The words are those of the serial walk
+// without its limit of 16 held constants; statuses, depths and values are
+// the same.
+//
+// LDS per wavefront: for each depth, one past the last node that left the
+// stack there in the chunks before, and the constant at it.
+constexpr int kDepthSlots = GP_MAX_STACK + 1;
+struct WaveTables {
+    uint32_t last[kDepthSlots];
+    float value[kDepthSlots];
+};
+
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+__device__ __forceinline__ int lane_value(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+}
+
+// Minimum over lanes 0..own (row shifts inside 16 lanes, then two row
+// broadcasts).
+__device__ __forceinline__ int prefix_min(int v)
+{
+    constexpr int big = INT_MAX;
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x111, 0xf, 0xf, false));   // row_shr:1
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x112, 0xf, 0xf, false));   // row_shr:2
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x114, 0xf, 0xf, false));   // row_shr:4
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x118, 0xf, 0xf, false));   // row_shr:8
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    v = min(v, __builtin_amdgcn_update_dpp(big, v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return v;
+}
+
+// Stages program nodes[0, len) into dst.  Every argument is uniform in the
+// wavefront.  status, cls (depth class) and the word count come back; dst
+// holds the words when the status is GP_PROG_OK (else nothing useful), never
+// more than len of them.
+__device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, int32_t len,
+                                          const float* __restrict__ consts, int64_t n_consts,
+                                          uint32_t allowed, int32_t n_vars,
+                                          uint2* __restrict__ dst, WaveTables* tb, int lane,
+                                          int* cls, int* n_words)
+{
+    int depth = 0, rt_in = 0, n = 0;       // after the chunks before: stack, runtime, words
+    bool prev_load = false;
+    float prev_value = 0.f;                // value at the chunk's previous node
+    int over8 = 0, over16 = 0;
+    uint2 held = make_uint2(0u, 0u);       // the last word so far, not yet stored
+    int held_at = -1;
+    const bool many = len > 64;
+    if (many && lane < kDepthSlots) tb->last[lane] = 0u;
+    for (int32_t c0 = 0; c0 < len; c0 += 64) {
+        const int32_t k = c0 + lane;
+        const bool live = k < len;
+        const uint32_t w = live ? nodes[k] : 0xFFu;
+        const uint32_t nx = k + 1 < len ? nodes[k + 1] & 0xFFu : 0xFFu;
+        const uint32_t op = w & 0xFFu, arg = w >> 8;
+        const bool leaf = op <= GP_CONST, bin = op - GP_ADD < 4u, un = op - GP_SIN < 6u;
+        const bool load = op == GP_LOAD, cst = op == GP_CONST;
+        const uint64_t leaves = __ballot(leaf), bins = __ballot(bin);
+        const int d0 = depth + (int)lanes_below(leaves) - (int)lanes_below(bins);
+        const int d1 = d0 + (leaf ? 1 : 0) - (bin ? 1 : 0);
+        // the checks of the serial walk; the first failing node names the status
+        int code = d1 > GP_MAX_STACK ? GP_PROG_TOO_DEEP : GP_PROG_OK;
+        code = d0 < (leaf ? 0 : (bin ? 2 : 1)) ? GP_PROG_UNDERFLOW : code;
+        code = cst && (int64_t)arg >= n_consts ? GP_PROG_BAD_CONST : code;
+        code = load && (int64_t)arg >= (int64_t)n_vars ? GP_PROG_BAD_VAR : code;
+        code = op < 32u && ((allowed >> (op & 31u)) & 1u) ? code : GP_PROG_BAD_OP;
+        const uint64_t bad = __ballot(live && code != GP_PROG_OK);
+        if (bad != 0ull) return lane_value(code, __builtin_ctzll(bad));
+        over8 |= __ballot(live && d1 > 8) != 0ull;
+        over16 |= __ballot(live && d1 > 16) != 0ull;
+
+        // runtime depth after and before each node
+        const uint64_t loads = __ballot(load);
+        const int sigma = (int)lanes_below(loads) + (load ? 1 : 0);
+        const int r1 = min(rt_in, prefix_min(live ? d1 - 64 * sigma : INT_MAX)) + 64 * sigma;
+        const int rp = __shfl_up(r1, 1);        // (every lane takes part)
+        const int r0 = lane == 0 ? rt_in : rp;
+        const int np = d0 - r0;
+        const bool after_load = lane == 0 ? prev_load : ((loads >> (lane - 1)) & 1ull) != 0ull;
+        const bool own = live && (load || (!after_load && ((bin && np < 2) || (un && np < 1))));
+
+        // constants, then the folded operators in order
+        float val = cst ? consts[arg] : 0.f;
+        // value at the last node before lane l that left the stack at depth d
+        auto at_depth = [&](int d, int l) {
+            const uint64_t m = __ballot(live && d1 == d) & ((1ull << l) - 1ull);
+            return m != 0ull ? lane_value(val, 63 - __builtin_clzll(m)) : tb->value[d];
+        };
+        uint64_t folds = __ballot(live && !after_load && ((bin && np >= 2) || (un && np >= 1)));
+        while (folds != 0ull) {
+            const int l = __builtin_ctzll(folds);
+            folds &= folds - 1ull;
+            const uint32_t fo = (uint32_t)lane_value((int)op, l);
+            const float b = l > 0 ? lane_value(val, l - 1) : prev_value;
+            float r;
+            if (fo <= GP_DIV) {
+                const float a = at_depth(lane_value(d0, l) - 1, l > 0 ? l - 1 : 0);
+                r = binary_value(fo, a, b);
+            } else {
+                r = unary_value(fo, b);
+            }
+            val = lane == l ? r : val;
+        }
+
+        // words: a variable flushes the constants held below it, then each
+        // node's own word
+        int pos = n + (int)lanes_below(__ballot(own));
+        int flushed = 0;
+        uint64_t flushes = __ballot(live && load && np > 0);
+        while (flushes != 0ull) {
+            const int l = __builtin_ctzll(flushes);
+            flushes &= flushes - 1ull;
+            const int cnt = lane_value(np, l), rt = lane_value(r0, l);
+            const int at = lane_value(pos, l);
+            for (int i = 0; i < cnt; ++i) {
+                const float v = at_depth(rt + 1 + i, l);
+                if (lane == 0) dst[at + i] = ThreadedWords::push_const(rt + i, __float_as_uint(v));
+            }
+            pos += lane >= l ? cnt : 0;
+            flushed += cnt;
+        }
+        const float pv = __shfl_up(val, 1);
+        const float top = lane == 0 ? prev_value : pv;
+        uint2 word;
+        if (load) {
+            const uint32_t payload = arg * kVarPayload;
+            const int rt = d0;                   // everything below is on the stack now
+            word = nx - GP_ADD < 4u   ? ThreadedWords::top_row(rt, nx - GP_ADD, payload)
+                   : nx - GP_SIN < 6u ? ThreadedWords::push_unary(rt, nx - GP_SIN, payload)
+                                      : ThreadedWords::push_row(rt, payload);
+        } else if (bin) {
+            word = np == 1 ? ThreadedWords::top_const(r0, op - GP_ADD, __float_as_uint(top))
+                           : ThreadedWords::cells(r0, op - GP_ADD);
+        } else {
+            word = ThreadedWords::unary(r0, un ? op - GP_SIN : 0u);
+        }
+        // the chunk's last own word is stored once it is known whether
+        // another follows
+        const uint64_t owns = __ballot(own);
+        if (owns != 0ull) {
+            if (held_at >= 0 && lane == 0) dst[held_at] = held;
+            const int l = 63 - __builtin_clzll(owns);
+            if (own && lane != l) dst[pos] = word;
+            held = make_uint2((uint32_t)lane_value((int)word.x, l), (uint32_t)lane_value((int)word.y, l));
+            held_at = lane_value(pos, l);
+        }
+        n += (int)__popcll(owns) + flushed;
+        const int end = min(63, len - 1 - c0);
+        depth = lane_value(d1, end);
+        rt_in = lane_value(r1, end);
+        prev_value = lane_value(val, end);
+        prev_load = ((loads >> end) & 1ull) != 0ull;
+        if (many && c0 + 64 < len) {
+            // the last node of each depth, for the chunks that follow
+            atomicMax(&tb->last[d1], (uint32_t)k + 1u);
+            if (tb->last[d1] == (uint32_t)k + 1u) tb->value[d1] = val;
+        }
+    }
+    if (depth != 1) return GP_PROG_FINAL_DEPTH;
+    if (rt_in == 0) {
+        // a constant program: its value is pushed
+        held = ThreadedWords::push_const(0, __float_as_uint(prev_value));
+        held_at = 0;
+        n = 1;
+    }
+    if (lane == 0) dst[held_at] = ThreadedWords::last(held);
+    *cls = over16 ? 2 : over8;
+    *n_words = n;
+    return GP_PROG_OK;
+}
+
+// Per staging block: programs per partition key, and whether some program's
+// offsets decrease.  The rows live in the partials' memory (8 bytes per
+// program at least), which nothing uses before the evaluation.
+struct StageRow {
+    uint16_t cnt[kKeys];
+    uint16_t down, pad;
+};
+static_assert(sizeof(StageRow) == 52, "StageRow layout");
+constexpr int kStageWaves = 8;
+constexpr int kStageBlocks = 1024;       // two workgroups of 8 wavefronts on every SIMD pair
+
+// Programs per staging block: one per wavefront up to 8,192 programs, then
+// as many as keep the grid at 1,024 blocks (a count fits 16 bits).
+inline int64_t stage_share(int64_t n_programs)
+{
+    const int64_t c = (n_programs + kStageBlocks - 1) / kStageBlocks;
+    return c < kStageWaves ? kStageWaves : (c > 32768 ? 32768 : c);
+}
+
+// What the two staging kernels share.  A call of one request brings its
+// request and dataset entries by value (block 0 writes the tables that the
+// later kernels read); a call of several has them in memory (k_tables).
+struct StageArgs {
+    int64_t n_programs, share;
+    uint32_t allowed;
+    int32_t single, lpt, n_seg;
+    DevRequest one_req;
+    DevDataset one_ds;
+    DevDataset* ds;
+    DevRequest* reqs;
+    int32_t* seg_ds;
+    int64_t* seg_start;
+    int32_t* bad;
+    ProgMeta* meta;
+    uint8_t* cls;
+    int32_t* pds;
+    int32_t* order;
+    uint2* code;
+    StageRow* rows;
+};
+
+struct ProgRange {
+    const uint32_t* nodes;
+    const float* consts;
+    int64_t n_consts, node_base, s, e;
+    int32_t* out_status;
+    int64_t n_nodes;
+    int32_t n_vars;
+    int r;
+};
+// Program p's request fields and node range (all uniform).
+__device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p, bool tab_ok)
+{
+    ProgRange g;
+    g.s = g.e = 0;
+    if (a.single) {
+        g.r = 0;
+        g.nodes = a.one_req.nodes;
+        g.consts = a.one_req.consts;
+        g.n_consts = a.one_req.n_consts;
+        g.node_base = 0;
+        g.n_nodes = a.one_req.n_nodes;
+        g.n_vars = a.one_ds.n_vars;
+        g.out_status = a.one_req.out_status ? a.one_req.out_status + p : nullptr;
+        g.s = as_const(a.one_req.offsets)[p];
+        g.e = as_const(a.one_req.offsets)[p + 1];
+        return g;
+    }
+    const const_ptr<int64_t> start = as_const((const int64_t*)a.seg_start);
+    int lo = 0, hi = a.n_seg - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (start[mid] <= p) lo = mid; else hi = mid - 1;
+    }
+    const const_ptr<DevRequest> R = as_const((const DevRequest*)a.reqs) + lo;
+    const int64_t q = p - start[lo];
+    g.r = lo;
+    g.nodes = R->nodes;
+    g.consts = R->consts;
+    g.n_consts = R->n_consts;
+    g.node_base = R->node_base;
+    g.n_nodes = R->n_nodes;
+    g.n_vars = as_const((const DevDataset*)a.ds)[R->dataset].n_vars;
+    g.out_status = R->out_status && q < R->n_programs ? R->out_status + q : nullptr;
+    if (tab_ok) {
+        g.s = as_const(R->offsets)[q];
+        g.e = as_const(R->offsets)[q + 1];
+    }
+    return g;
+}
+
+// Pass 1, one wavefront per program (benchmark-set masks): validate and
+// stage each program at its own node offset in the request's part of `code`
+// (its words never outnumber its nodes, so while offsets never decrease the
+// programs' ranges are disjoint), and count the partition keys per block.
+__global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
+{
+    __shared__ int cnt[kKeys];
+    __shared__ int s_down;
+    __shared__ WaveTables tables[kStageWaves];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_down = 0;
+    if (a.single && blockIdx.x == 0 && threadIdx.x == 0) {
+        a.ds[0] = a.one_ds;
+        a.reqs[0] = a.one_req;
+        a.seg_ds[0] = 0;
+        a.seg_start[0] = 0;
+        a.seg_start[1] = a.n_programs;
+        a.bad[0] = 0;
+    }
+    __syncthreads();
+    const bool tab_ok = a.single || as_const((const int32_t*)a.bad)[0] == 0;
+    const int64_t p0 = (int64_t)blockIdx.x * a.share;
+    const int64_t p1 = min(p0 + a.share, a.n_programs);
+    for (int64_t p = p0 + wave; p < p1; p += kStageWaves) {
+        const ProgRange g = program_range(a, p, tab_ok);
+        const bool range_ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
+        int status, c = -1, n = 0;
+        if (!tab_ok) status = GP_PROG_BAD_TABLE;
+        else if (!range_ok) status = GP_PROG_BAD_OFFSETS;
+        else if (g.e == g.s) status = GP_PROG_EMPTY;
+        else
+            status = stage_wave(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                g.n_vars, a.code + g.node_base + g.s, &tables[wave], lane, &c, &n);
+        if (status != GP_PROG_OK) {
+            c = -1;
+            n = 0;
+        }
+        if (lane == 0) {
+            if (g.e < g.s) s_down = 1;
+            ProgMeta m;
+            m.start = g.node_base + g.s;
+            m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
+            m.slen = n;
+            a.meta[p] = m;
+            a.pds[p] = g.r;
+            // partition key: depth class, then (single-request calls) length
+            // band from longest to shortest; with several requests the order
+            // inside a class stays the input order, so each request's
+            // programs stay together
+            int lb = 31 - __clz((uint32_t)(n > 0 ? n : 1));
+            lb = lb < kLenBuckets - 1 ? lb : kLenBuckets - 1;
+            const int key = c >= 0 ? c * kLenBuckets + (a.lpt ? kLenBuckets - 1 - lb : 0) : 0xFF;
+            a.cls[p] = (uint8_t)key;
+            if (c >= 0) atomicAdd(&cnt[key], 1);
+            if (g.out_status) *g.out_status = status;
+        }
+    }
+    __syncthreads();
+    StageRow* row = a.rows + blockIdx.x;
+    if (threadIdx.x < kKeys) row->cnt[threadIdx.x] = (uint16_t)cnt[threadIdx.x];
+    if (threadIdx.x == 0) row->down = (uint16_t)s_down;
+}
+
+// Pass 2, same blocks: every block sums the key counts of the blocks before
+// it (and of all), so the partition needs no scan of its own; program ids are
+// scattered stably by (depth class, length band); block 0 writes the class
+// ranges, clears the work counters and, for a single request, writes its
+// per-class tables (class_seg_tables with one segment).
+// Offsets that decrease somewhere let programs' node ranges overlap: then
+// every program is staged again here, packed in program order, unless the
+// staged programs need more than n_nodes words in total (no program of the
+// call is staged then).
+struct SegOut {
+    int32_t g_max, target_items;
+    int32_t* seg_cnt;
+    int32_t* seg_pos;
+    uint32_t* item_pre;
+    int32_t* class_g;
+    int32_t* class_info;
+    uint32_t* counters;
+};
+constexpr int kOrderWG = 256;
+__global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
+                                                    SegOut so)
+{
+    constexpr int kCols = (int)(sizeof(StageRow) / 4);        // pairs of counts
+    constexpr int kRowStep = kOrderWG / kCols;
+    __shared__ int s_all[2 * kCols], s_pre[2 * kCols];
+    __shared__ int s_base[kKeys];
+    __shared__ int s_chunk[kOrderWG / 64][kKeys];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (t < 2 * kCols) s_all[t] = s_pre[t] = 0;
+    __syncthreads();
+    if (t < kRowStep * kCols) {
+        const uint32_t* __restrict__ rows = reinterpret_cast<const uint32_t*>(a.rows);
+        const int c = t % kCols;
+        int all0 = 0, all1 = 0, pre0 = 0, pre1 = 0;
+        const int b = (int)blockIdx.x;
+#pragma unroll 8
+        for (int r = t / kCols; r < n_blk; r += kRowStep) {
+            const uint32_t v = rows[(int64_t)r * kCols + c];
+            all0 += (int)(v & 0xFFFFu);
+            all1 += (int)(v >> 16);
+            pre0 += r < b ? (int)(v & 0xFFFFu) : 0;
+            pre1 += r < b ? (int)(v >> 16) : 0;
+        }
+        atomicAdd(&s_all[2 * c], all0);
+        atomicAdd(&s_all[2 * c + 1], all1);
+        atomicAdd(&s_pre[2 * c], pre0);
+        atomicAdd(&s_pre[2 * c + 1], pre1);
+    }
+    __syncthreads();
+    const bool restage = s_all[kKeys] != 0;          // StageRow::down
+    const int64_t p0 = (int64_t)blockIdx.x * a.share;
+    const int64_t p1 = min(p0 + a.share, a.n_programs);
+    bool overflow = false;
+    if (restage) {
+        // staged words of all programs, and of those before this block
+        __shared__ unsigned long long s_words, s_before;
+        if (t == 0) s_words = s_before = 0ull;
+        __syncthreads();
+        unsigned long long all = 0, before = 0;
+        for (int64_t p = t; p < a.n_programs; p += kOrderWG) {
+            const unsigned long long v = (unsigned long long)a.meta[p].slen;
+            all += v;
+            if (p < p0) before += v;
+        }
+        atomicAdd(&s_words, all);
+        atomicAdd(&s_before, before);
+        __syncthreads();
+        overflow = (int64_t)s_words > code_capacity;
+        if (!overflow) {
+            __shared__ WaveTables tables[kOrderWG / 64];
+            for (int64_t p = p0 + __builtin_amdgcn_readfirstlane(wave); p < p1; p += kOrderWG / 64) {
+                int64_t start = (int64_t)s_before;
+                for (int64_t q = p0; q < p; ++q) start += a.meta[q].slen;
+                if (a.cls[p] >= kKeys) continue;
+                const ProgRange g = program_range(a, p, true);
+                int c = 0, n = 0;
+                (void)stage_wave(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                 g.n_vars, a.code + start, &tables[wave], lane, &c, &n);
+                if (lane == 0) a.meta[p].start = start;
+            }
+        }
+    }
+    if (t == 0) {
+        int run = 0;
+        for (int k = 0; k < kKeys; ++k) {
+            s_base[k] = run + s_pre[k];
+            run += s_all[k];
+        }
+    }
+    if (blockIdx.x == 0 && t < kClasses) {
+        int start = 0, count = 0;
+        for (int k = 0; k < kKeys; ++k) {
+            if (k / kLenBuckets < t) start += s_all[k];
+            if (k / kLenBuckets == t) count += s_all[k];
+        }
+        if (overflow) count = 0;
+        so.class_info[2 * t] = start;
+        so.class_info[2 * t + 1] = count;
+        so.counters[t] = 0u;
+        if (a.single) {
+            const int32_t tiles = a.one_ds.n_tiles[t];
+            const int G = class_group((double)count * (double)tiles, so.g_max, so.target_items);
+            so.seg_cnt[t] = count;
+            so.class_g[t] = G;
+            so.seg_pos[t] = 0;
+            so.item_pre[2 * t] = 0u;
+            so.item_pre[2 * t + 1] = (uint32_t)((count + G - 1) / G) * (uint32_t)tiles;
+        }
+    }
+    if (overflow) {
+        for (int64_t p = p0 + t; p < p1; p += kOrderWG) {
+            if (a.cls[p] >= kKeys) continue;
+            a.cls[p] = 0xFF;
+            int32_t* st = a.single ? a.one_req.out_status : a.reqs[a.pds[p]].out_status;
+            const int64_t q = a.single ? p : p - a.seg_start[a.pds[p]];
+            if (st && (a.single || q < a.reqs[a.pds[p]].n_programs)) st[q] = GP_PROG_BAD_OFFSETS;
+        }
+        return;
+    }
+    // stable scatter, one chunk of the block's programs at a time
+    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    for (int64_t c0 = p0; c0 < p1; c0 += kOrderWG) {
+        const int64_t p = c0 + t;
+        const int key = p < p1 ? (int)a.cls[p] : 0xFF;
+        if (lane < kKeys) s_chunk[wave][lane] = 0;
+        int rank = 0;
+        // one pass per distinct key in the wavefront
+        for (uint64_t todo = __ballot(key < kKeys); todo != 0ull;) {
+            const int first = __ffsll((unsigned long long)todo) - 1;
+            const int k0 = __shfl(key, first);
+            const uint64_t bm = __ballot(key == k0);
+            if (lane == first) s_chunk[wave][k0] = __popcll(bm);
+            if (key == k0) rank = __popcll(bm & below);
+            todo &= ~bm;
+        }
+        __syncthreads();
+        if (key < kKeys) {
+            for (int w2 = 0; w2 < wave; ++w2) rank += s_chunk[w2][key];
+            a.order[s_base[key] + rank] = (int32_t)p;
+        }
+        __syncthreads();
+        if (t < kKeys) {
+            for (int w2 = 0; w2 < kOrderWG / 64; ++w2) s_base[t] += s_chunk[w2][t];
+        }
+        __syncthreads();
+    }
+}
+
+// ------------------------------------ staging of the whole command table
 // Where a call of a single request gets its per-class work-item tables
 // (k_class_scan writes them when `single` is set).
-struct SegOut {
+struct ScanOut {
     int32_t single;
     int32_t g_max, target_items;
     const int32_t* seg_ds;
@@ -913,7 +1313,7 @@ __global__ __launch_bounds__(1024) void k_class_scan(
     const int32_t* __restrict__ blk_counts, const int64_t* __restrict__ blk_slen, int32_t n_blk,
     int64_t code_capacity, int32_t* __restrict__ blk_base, int64_t* __restrict__ blk_code,
     int32_t* __restrict__ class_info, uint32_t* __restrict__ work_counters,
-    int32_t* __restrict__ overflow, SegOut so)
+    int32_t* __restrict__ overflow, ScanOut so)
 {
     __shared__ int part[1024];
     __shared__ long long lpart[1024];
@@ -1015,16 +1415,13 @@ __global__ __launch_bounds__(1024) void k_class_scan(
     }
 }
 
-// Pass 2, same blocks as pass 1: each program's id is scattered (stably)
-// into the partition order.  Programs the short walk of pass 1 staged in
-// place stay there.  Otherwise (the whole command table, or node offsets
-// that decrease somewhere, so that programs' node ranges may overlap) each
-// program is staged here, at its block's base plus the exclusive scan of
-// staged sizes inside the block, so ranges never overlap whatever the
-// offsets.
+// Pass 2, same blocks as pass 1: each program is staged at its block's base
+// plus the exclusive scan of staged sizes inside the block, so ranges never
+// overlap whatever the offsets; its id is scattered (stably) into the
+// partition order.
 //
 // Staged instruction of the flag form (8 bytes, one scalar load; calls within
-// the benchmark set use the threaded form instead, threaded.h):
+// the benchmark set use the threaded form, threaded.h):
 //   x = flags | sel << 8 | cell << 16, y = payload
 //   kFPush  save the top into stack cell `cell`, then the top = leaf
 //   kFUn    the top = unary sel (SIN..ABS as 0..5) of the top
@@ -1037,10 +1434,10 @@ __global__ __launch_bounds__(1024) void k_class_scan(
 // resident wavefronts run at once small enough to stay in the scalar cache
 // while each program passes over its window.
 __global__ __launch_bounds__(kBucketBlock) void k_stage(
-    int64_t n_programs, const DevDataset* __restrict__ ds, const DevRequest* __restrict__ reqs,
+    int64_t n_programs, const DevRequest* __restrict__ reqs,
     const int64_t* __restrict__ seg_start, const int32_t* __restrict__ pds, int32_t n_blk,
     const int64_t* __restrict__ blk_code, const int32_t* __restrict__ blk_base,
-    const int32_t* __restrict__ overflow, const int32_t* __restrict__ restage, uint32_t allowed,
+    const int32_t* __restrict__ overflow,
     uint8_t* __restrict__ cls, ProgMeta* __restrict__ meta, uint2* __restrict__ code,
     int32_t* __restrict__ order)
 {
@@ -1061,58 +1458,43 @@ __global__ __launch_bounds__(kBucketBlock) void k_stage(
         }
         return;
     }
-    const bool base = (allowed & ~GP_BASE_OPS) == 0u;
-    if (!base || *restage) {
-        __shared__ uint32_t cache_mem[kCacheWords];
-        __shared__ float pv_mem[kHeldConsts * kBucketBlock];
-        lds_u32* cache = (lds_u32*)cache_mem;
-        lds_u8* ops = (lds_u8*)(cache + kStageNodesEmit);
-        ProgMeta m;
-        m.start = 0;
-        m.len = 0;
-        m.slen = 0;
-        if (p < n_programs) m = meta[p];
-        // inclusive scan of staged sizes inside the block
-        sc[t] = m.slen;
+    __shared__ uint32_t cache_mem[kStageNodes];
+    __shared__ float pv_mem[kHeldConsts * kBucketBlock];
+    lds_u32* cache = (lds_u32*)cache_mem;
+    ProgMeta m;
+    m.start = 0;
+    m.len = 0;
+    m.slen = 0;
+    if (p < n_programs) m = meta[p];
+    // inclusive scan of staged sizes inside the block
+    sc[t] = m.slen;
+    __syncthreads();
+    for (int off = 1; off < kBucketBlock; off <<= 1) {
+        const long long v = t >= off ? sc[t - off] : 0;
         __syncthreads();
-        for (int off = 1; off < kBucketBlock; off <<= 1) {
-            const long long v = t >= off ? sc[t - off] : 0;
-            __syncthreads();
-            sc[t] += v;
-            __syncthreads();
-        }
-        const int64_t start = blk_code[blockIdx.x] + sc[t] - m.slen;
-        int r = 0;
-        int64_t s = 0, e = 0;
-        DevRequest R{};
-        if (key < kKeys) {
-            r = pds[p];
-            R = reqs[r];
-            const int64_t q = p - seg_start[r];
-            s = R.offsets[q];
-            e = R.offsets[q + 1];
-        }
-        int64_t lo = 0;
-        const bool cached = base ? cache_block_stage(key < kKeys, r, s, e, reqs, ops, cache, &lo)
-                                 : cache_block_nodes(key < kKeys, r, s, e, reqs, cache, &lo);
-        if (key < kKeys) {
-            lds_f32* pvs = (lds_f32*)pv_mem + t;
-            const int32_t n_vars = ds[R.dataset].n_vars;
-            int st = 0, md = 0;
-            if (base && cached)
-                stage_check_base<ThreadedWords>(LdsStageReader{ops, cache, lo}, s, e, allowed, n_vars,
-                                 code + start, pvs, st, md);
-            else if (base)
-                stage_check_base<ThreadedWords>(GlobalStageReader{R.nodes, R.consts, R.n_consts}, s, e, allowed,
-                                 n_vars, code + start, pvs, st, md);
-            else if (cached)
-                stage_walk(LdsNodes{cache, lo}, s, e, GlobalConsts{R.consts}, code + start, m.slen,
-                           pvs);
-            else
-                stage_walk(GlobalNodes{R.nodes}, s, e, GlobalConsts{R.consts}, code + start,
-                           m.slen, pvs);
-            meta[p].start = start;
-        }
+        sc[t] += v;
+        __syncthreads();
+    }
+    const int64_t start = blk_code[blockIdx.x] + sc[t] - m.slen;
+    int r = 0;
+    int64_t s = 0, e = 0;
+    DevRequest R{};
+    if (key < kKeys) {
+        r = pds[p];
+        R = reqs[r];
+        const int64_t q = p - seg_start[r];
+        s = R.offsets[q];
+        e = R.offsets[q + 1];
+    }
+    int64_t lo = 0;
+    const bool cached = cache_block_nodes(key < kKeys, r, s, e, reqs, cache, &lo);
+    if (key < kKeys) {
+        lds_f32* pvs = (lds_f32*)pv_mem + t;
+        if (cached)
+            stage_walk(LdsNodes{cache, lo}, s, e, GlobalConsts{R.consts}, code + start, m.slen, pvs);
+        else
+            stage_walk(GlobalNodes{R.nodes}, s, e, GlobalConsts{R.consts}, code + start, m.slen, pvs);
+        meta[p].start = start;
     }
     // stable scatter into the partition order
     const int wave = t >> 6, lane = t & 63;
@@ -1189,15 +1571,6 @@ struct EvalConst {
     int32_t reward_power;
     float reward_M;
 };
-
-// Pointers to memory that is constant while a kernel runs: loads at uniform
-// addresses are scalar loads, also past an asm statement (which the compiler
-// takes as writing any ordinary memory).
-template <class T> using const_ptr = const __attribute__((address_space(4))) T*;
-template <class T> __device__ __forceinline__ const_ptr<T> as_const(const T* p)
-{
-    return (const_ptr<T>)(uintptr_t)p;
-}
 
 // Error-free sum: s + e == a + b exactly (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e)
@@ -2144,19 +2517,10 @@ struct ReduceArgs {
     int64_t n_programs;
     int32_t part_stride;    // tile stride of the partials (the program count)
     double max_score;
-    int32_t* restage;       // k_validate's restage flag, cleared for the next call
 };
-
-// The restage flag is cleared here as well as by k_tables, for plans that
-// run k_tables once, when they are captured.
-__device__ __forceinline__ void clear_restage(const ReduceArgs& a)
-{
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.restage = 0;
-}
 
 __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a)
 {
-    clear_restage(a);
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
     const int r = a.pds[p];
@@ -2186,7 +2550,6 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a)
 // constant output or target gives exactly zero: every shifted value is 0).
 __global__ __launch_bounds__(256) void k_reduce_corr(ReduceArgs a)
 {
-    clear_restage(a);
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
     const int r = a.pds[p];
@@ -2219,7 +2582,6 @@ __global__ __launch_bounds__(256) void k_reduce_corr(ReduceArgs a)
 // int64 totals added exactly, returned as a double (exact below 2^53).
 __global__ __launch_bounds__(256) void k_reduce_reward(ReduceArgs a)
 {
-    clear_restage(a);
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
     const int r = a.pds[p];
@@ -2277,7 +2639,7 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.seg_pos = off;    off = align_up(off + (size_t)kClasses * n_seg * 4);
     L.item_pre = off;   off = align_up(off + (size_t)kClasses * (n_seg + 1) * 4);
     L.pds = off;        off = align_up(off + (size_t)n_programs * 4);
-    L.bad = off;        off = align_up(off + 8);    // tables bad, restage
+    L.bad = off;        off = align_up(off + 4);
     L.overflow = off;   off = align_up(off + 4);
     L.total = off;
     return L;
@@ -2308,7 +2670,6 @@ struct Staged {
     uint32_t* item_pre;
     int32_t* pds;
     int32_t* bad;
-    int32_t* restage;
     int32_t* overflow;
 };
 
@@ -2339,7 +2700,6 @@ Staged carve(void* base, const Layout& L)
     st.item_pre = reinterpret_cast<uint32_t*>(ws + L.item_pre);
     st.pds = reinterpret_cast<int32_t*>(ws + L.pds);
     st.bad = reinterpret_cast<int32_t*>(ws + L.bad);
-    st.restage = st.bad + 1;
     st.overflow = reinterpret_cast<int32_t*>(ws + L.overflow);
     return st;
 }
@@ -2680,29 +3040,61 @@ int enqueue_tables(const Problem& pb, const Tuning& tu, const Staged& st, hipStr
     return GP_OK;
 }
 
-// tables_ready: the dataset and request tables in `st` are already those
-// of this problem and tuning (a plan derives them once, when captured:
-// its tables are kernel arguments, fixed for its life).
-int enqueue_stage(const Problem& pb, const Tuning& tu, const Staged& st, int32_t target_items,
-                  hipStream_t stream, bool tables_ready = false)
+// Calls within the benchmark set: wavefront staging (a single request brings
+// its tables by value; several have them derived by k_tables first).
+int enqueue_stage_waves(const Problem& pb, const Tuning& tu, const Staged& st, int32_t target_items,
+                        hipStream_t stream)
 {
+    int rc;
+    StageArgs a{};
+    a.n_programs = pb.n_programs;
+    a.share = stage_share(pb.n_programs);
+    a.allowed = pb.allowed;
+    a.single = pb.req_dev ? 0 : 1;
+    a.lpt = pb.n_req == 1 ? 1 : 0;
+    a.n_seg = pb.n_req;
+    a.ds = st.ds; a.reqs = st.req; a.seg_ds = st.seg_ds; a.seg_start = st.seg_start; a.bad = st.bad;
+    a.meta = st.meta; a.cls = st.cls; a.pds = st.pds; a.order = st.order; a.code = st.code;
+    a.rows = reinterpret_cast<StageRow*>(st.part);
+    if (a.single) {
+        const gp_request& q = pb.one_req;
+        a.one_req = DevRequest{q.nodes, q.offsets, q.consts, q.n_programs, q.n_nodes, q.n_consts, 0,
+                               q.out_fitness, q.out_status, 0};
+        a.one_ds = make_dataset(pb.one, tu.tile_lds, tu.tile_max);
+    } else if ((rc = enqueue_tables(pb, tu, st, stream)) != GP_OK) {
+        return rc;
+    }
+    const int32_t n_blk = (int32_t)((pb.n_programs + a.share - 1) / a.share);
+    hipLaunchKernelGGL(k_stage_waves, dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+    GP_HIP_TRY(hipGetLastError());
+    const SegOut so{group_capacity(pb, tu), target_items, st.seg_cnt, st.seg_pos, st.item_pre,
+                    st.class_g, st.class_info, st.counters};
+    hipLaunchKernelGGL(k_order, dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
+    GP_HIP_TRY(hipGetLastError());
+    return GP_OK;
+}
+
+int enqueue_stage(const Problem& pb, const Tuning& tu, const Staged& st, int32_t target_items,
+                  hipStream_t stream)
+{
+    if (!pb_ext(pb.allowed)) return enqueue_stage_waves(pb, tu, st, target_items, stream);
     const int32_t n_blk = (int32_t)((pb.n_programs + kBucketBlock - 1) / kBucketBlock);
     int rc;
-    if (!tables_ready && (rc = enqueue_tables(pb, tu, st, stream)) != GP_OK) return rc;
+    if ((rc = enqueue_tables(pb, tu, st, stream)) != GP_OK) return rc;
     const int32_t lpt = pb.n_req == 1 ? 1 : 0;
     hipLaunchKernelGGL(k_validate, dim3(n_blk), dim3(kBucketBlock), 0, stream, pb.n_programs,
                        pb.allowed, st.ds, st.req, st.seg_start, pb.n_req, st.bad, lpt, n_blk,
-                       st.meta, st.cls, st.pds, st.blk_counts, st.blk_slen, st.code, st.restage);
+                       st.meta, st.cls, st.pds, st.blk_counts, st.blk_slen);
     GP_HIP_TRY(hipGetLastError());
-    SegOut so{pb.n_req == 1 ? 1 : 0, group_capacity(pb, tu), target_items, st.seg_ds, st.ds,
-              st.seg_cnt, st.seg_pos, st.item_pre, st.class_g};
+    ScanOut so{pb.n_req == 1 ? 1 : 0, group_capacity(pb, tu), target_items, st.seg_ds, st.ds,
+               st.seg_cnt, st.seg_pos, st.item_pre, st.class_g};
     hipLaunchKernelGGL(k_class_scan, dim3(1), dim3(1024), 0, stream, st.blk_counts, st.blk_slen,
                        n_blk, pb.n_nodes, st.blk_base, st.blk_code, st.class_info, st.counters,
                        st.overflow, so);
     GP_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_stage, dim3(n_blk), dim3(kBucketBlock), 0, stream, pb.n_programs, st.ds,
+    hipLaunchKernelGGL(k_stage, dim3(n_blk), dim3(kBucketBlock), 0, stream, pb.n_programs,
                        st.req, st.seg_start, st.pds, n_blk, st.blk_code, st.blk_base, st.overflow,
-                       st.restage, pb.allowed, st.cls, st.meta, st.code, st.order);
+                       st.cls, st.meta, st.code, st.order);
     GP_HIP_TRY(hipGetLastError());
     return GP_OK;
 }
@@ -2728,12 +3120,12 @@ void launch_eval(bool ext, dim3 g, size_t lds, hipStream_t sc, const Staged& st,
 // The whole evaluation as stream work (no allocation, no synchronization:
 // safe to capture into a graph).
 int enqueue_eval(const Problem& pb, const Tuning& tu, const EvalLaunch& el, const Staged& st,
-                 SideStreams& side, hipStream_t stream, CallEvents& ce, bool tables_ready = false)
+                 SideStreams& side, hipStream_t stream, CallEvents& ce)
 {
     int rc;
     if ((rc = ce.mark(0, stream)) != GP_OK) return rc;
-    if ((rc = enqueue_stage(pb, tu, st, el.target_items, stream, tables_ready)) != GP_OK) return rc;
-    if (pb.n_req > 1) {
+    if ((rc = enqueue_stage(pb, tu, st, el.target_items, stream)) != GP_OK) return rc;
+    if (pb.req_dev) {
         hipLaunchKernelGGL(k_seg_tables, dim3(1), dim3(256), 0, stream, st.order, st.class_info,
                            st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(pb, tu),
                            el.target_items, st.seg_cnt, st.seg_pos, st.item_pre, st.class_g);
@@ -2807,7 +3199,6 @@ int enqueue_eval(const Problem& pb, const Tuning& tu, const EvalLaunch& el, cons
     ra.part = st.part; ra.part_bad = st.part_bad; ra.part_corr = st.part_corr;
     ra.n_programs = pb.n_programs; ra.part_stride = (int32_t)pb.n_programs;
     ra.max_score = pb.max_score;
-    ra.restage = st.restage;
     if ((rc = ce.mark(4, stream)) != GP_OK) return rc;
     if (pb.fit == kFitCorr)
         hipLaunchKernelGGL(k_reduce_corr, dim3((unsigned)((pb.n_programs + 255) / 256)), dim3(256),
@@ -2947,13 +3338,10 @@ int plan_build(gp_plan* p)
     // replays of a previous graph may still read the workspace
     if (p->exec) GP_HIP_TRY(hipDeviceSynchronize());
     plan_release_graph(p);
-    // the plan's tables (kernel arguments only) once, outside the graph
-    if ((rc = enqueue_tables(p->pb, p->tu, p->st, p->cap)) != GP_OK) return rc;
-    GP_HIP_TRY(hipStreamSynchronize(p->cap));
     GP_HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
     CallEvents none;
     (void)none.begin(false);
-    rc = enqueue_eval(p->pb, p->tu, p->el, p->st, p->side, p->cap, none, true);
+    rc = enqueue_eval(p->pb, p->tu, p->el, p->st, p->side, p->cap, none);
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(p->cap, &g);
     if (rc != GP_OK) {
@@ -3449,7 +3837,8 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
     pb.max_vars = n_vars; pb.max_cases = n_cases;
     pb.allowed = allowed_op_mask ? allowed_op_mask : GP_ALL_OPS;
     pb.need_out = 0;
-    const Layout L = make_layout(n_programs, n_nodes, 0, 1, 1);
+    // (one partial slot per program: the staging blocks' counts)
+    const Layout L = make_layout(n_programs, n_nodes, 1, 1, 1);
     Workspace* w = nullptr;
     if ((rc = get_workspace(stream, L.total, &w)) != GP_OK) return rc;
     const Staged st = carve(w->ptr, L);
