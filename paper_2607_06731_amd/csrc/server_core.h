@@ -153,6 +153,9 @@ struct Entry {
     size_t chunk;
 };
 
+// Node evaluations below which launches wait for each other (Core::hold).
+constexpr double kHoldNodeEvals = 2147483648.0;
+
 // One launch as the device sees it.
 struct Batch {
     std::vector<Entry> ent;
@@ -172,6 +175,7 @@ struct Slot {
     std::vector<ReqPtr> finishing;
     std::vector<std::pair<ReqPtr, uint32_t>> members;   // (request, generation)
     double t_launch_ms = 0.0;
+    double work = 0.0;                  // node evaluations of the launch in flight
 };
 
 struct Config {
@@ -498,10 +502,32 @@ struct Core {
         S.finishing = std::move(B.finishing);
         S.members = std::move(members);
         S.busy = true;
+        S.work = work;
         S.t_launch_ms = dev.now_ms();
         if (busy_slots++ == 0) busy_since_ms = S.t_launch_ms;
         n_launches += 1;
         n_chunks += (int64_t)B.ent.size();
+        return true;
+    }
+
+    // Whether what is ready waits for the launches in flight: while both are
+    // small (about 0.2 ms of the GPU together) requests that arrive meanwhile
+    // share the next launch; a launch of its own for each would leave most of
+    // the GPU idle (24 requests submitted in a row: 15-21 launches without
+    // this rule, since each ends before the next few are submitted).
+    bool hold() const
+    {
+        if (busy_slots == 0 || cfg.one_launch_per_request || ready.front()->solo) return false;
+        double work = 0.0;
+        for (const Slot& S : slots)
+            if (S.busy) work += S.work;
+        size_t chunks = 0;
+        for (const ReqPtr& R : ready) {
+            const double cases = (double)datasets[(size_t)R->ds].n_cases;
+            for (size_t c = R->next_chunk; c < R->chunks.size(); ++c, ++chunks)
+                work += (double)(R->offsets[R->chunks[c].e] - R->offsets[R->chunks[c].b]) * cases;
+            if (work >= kHoldNodeEvals || chunks >= (size_t)cfg.max_batch_chunks) return false;
+        }
         return true;
     }
 
@@ -552,7 +578,7 @@ struct Core {
         }
         progress = admit() || progress;
         for (int i = 0; i < (int)slots.size(); ++i) {
-            if (slots[(size_t)i].busy || ready.empty()) continue;
+            if (slots[(size_t)i].busy || ready.empty() || hold()) continue;
             if (launch(i)) progress = true;
             else if (!ready.empty()) progress = true;     // a failed enqueue requeued work
         }
