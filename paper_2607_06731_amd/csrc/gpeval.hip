@@ -13,34 +13,25 @@
 //                    constant subtrees and a leaf into the operator after
 //                    it; depth class and partition key; key counts per block.
 //   k_order          stable scatter of program ids by (depth class, length
-//                    band): each depth class (max depth <= 8, <= 16, <= 32)
-//                    runs a kernel whose register stack is only as deep as
-//                    needed, longest programs first; class ranges and (for a
-//                    single request) its per-class work-item tables.
-//                    With an op mask beyond the benchmark set three kernels
-//                    take the place of these two: k_validate (one thread per
-//                    program: variables, stack moves, counts), k_class_scan
-//                    (one workgroup: scans of the counts) and k_stage (words
-//                    {flags | selector | cell, payload}, the scatter).
+//                    band), longest first; class ranges and (for a single
+//                    request) its per-class work-item tables.
 //   k_seg_tables     several requests: per (class, request) program counts,
 //                    positions and work-item prefixes.
-//   k_eval<MAXD,K,FIT> persistent workgroups pull (program group, case tile)
-//                    items from an atomic counter (tile-major, or group-major
-//                    for the depth <= 8 class when the classes run one after
-//                    another); the tile's inputs and
+//   k_run<FIT>       persistent workgroups take (program chunk, case tiles)
+//                    items of every depth class (max depth <= 8, <= 16,
+//                    <= 32) from an atomic counter; the tiles' inputs and
 //                    targets are staged in LDS; each wavefront takes the
-//                    group's programs one at a time and runs one over the
-//                    64*K cases of the sub-tile (K per lane) with the value
-//                    stack in VGPRs (threaded code, interp_gfx950.h); the fitness epilogue is fused (MSE:
-//                    scaled square with Kahan accumulation; correlation:
-//                    shifted fp64 sums over valid pairs; integer reward:
-//                    int64 per case) and a wave shuffle tree gives one
+//                    chunk's programs one at a time and runs one over
+//                    sub-tiles of cases (4, 2 or 1 per lane) with the value
+//                    stack in VGPRs (threaded code, interp_gfx950.h); the
+//                    fitness epilogue is fused (MSE: scaled square with Kahan
+//                    accumulation; correlation: shifted fp64 sums over valid
+//                    pairs; integer reward: int64 per case; gp_predict: the
+//                    outputs themselves) and a wave shuffle tree gives one
 //                    partial per (program, tile).
 //   k_reduce[_corr|_reward]  one thread per program: its tile partials in
 //                    fixed order, then the score.
-// gp_predict runs the same staging and k_predict<MAXD,K,EXT> (per-case
-// outputs; EXT: the interpreter for the whole command table); gp_mc_rank
-// runs k_rank_sample and k_rank_assign.
+// gp_mc_rank runs k_rank_sample and k_rank_assign.
 //
 // Semantics follow the paper's GCL section (RPN stack machine, 32-element
 // stack, command table operand order) and the protected-operator readings
@@ -104,19 +95,14 @@ namespace {
     } while (0)
 
 // ------------------------------------------------------------------ layout
-constexpr int kWG = 256;                 // 4 wavefronts of 64
-constexpr int kWaves = kWG / 64;
 constexpr int kClasses = 3;              // max depth <= 8, <= 16, <= 32
 constexpr int kLenBuckets = 8;           // staged length 1, 2-3, ..., 64-127, 128+
 constexpr int kKeys = kClasses * kLenBuckets;
-constexpr int kK1 = 4;                  // cases per lane of the depth <= 16 class
 constexpr int kMaxTiles = 32;            // case tiles per program (cap)
-constexpr int kBucketBlock = 128;        // programs per staging/partition block
-constexpr int kStageNodes = 6656;        // LDS node cache of a staging block (26 KB, 52 per program)
-// Constants held back for folding per program while staging: a longer run
-// of constants is pushed (as runtime values) before the next one is held.
-// 16 keeps the staging block at four per CU (with the node cache).
+// The serial staging walks' limits (staging.h): constants held back for
+// folding per program, and their stride.
 constexpr int kHeldConsts = 16;
+constexpr int kBucketBlock = 1;
 constexpr int kMaxRequests = 4096;       // requests per batched call (tables are scanned by one workgroup)
 
 // Per-program record written by the staging passes.
@@ -127,16 +113,12 @@ struct ProgMeta {
 };
 static_assert(sizeof(ProgMeta) == 16, "ProgMeta layout");
 
-// Cases per lane for a depth class: deeper stacks hold fewer cases per
-// lane so that the register stack (MAXD * K VGPRs) stays bounded.  (8 cases
-// per lane for the shallow class measured slower on gfx950: occupancy drops
-// from 5 to 3 waves per SIMD and LDS input reads are exposed.)  Depends only
-// on the class and the dataset, never on the rest of the population.
-__host__ __device__ inline int class_k(int c, int n_vars)
-{
-    if (c == 0) return 4;
-    return c == 1 ? kK1 : 2;
-}
+// Cases per lane of a class's sub-tile, the unit in which its cases are
+// grouped into windows and tiles (and so its summation order).  Depends only
+// on the class, never on the rest of the population.  (Lane t holds cases t,
+// t + 64, t + 128, ... whatever the unit, so the interpreter may run two
+// sub-tiles at once.)
+__host__ __device__ inline int class_k(int c, int n_vars) { return c == 2 ? 2 : 4; }
 
 // Tile geometry for one class.  A sub-tile is 64*K cases (one wavefront, K
 // per lane).  The inputs and targets of `window` sub-tiles fit the LDS tile
@@ -486,8 +468,7 @@ __attribute__((noinline)) __device__ float sqrt_value(float x) { return sqrt_abs
 
 // The rest of the command table: ROCm's fp32 library functions, out of
 // line (the full-table interpreter calls them per case; constant folding
-// calls the same functions, so both give the same bits).  CUBE is formed
-// in fp64 (a*a is exact there) and rounded once; SQRT_RAW is the
+// calls the same functions, so both give the same bits).  SQRT_RAW is the
 // benchmark set's root with NaN below zero.
 __attribute__((noinline)) __device__ float cbrt_value(float x) { return cbrtf(x); }
 __attribute__((noinline)) __device__ float tan_value(float x) { return tanf(x); }
@@ -496,12 +477,7 @@ __attribute__((noinline)) __device__ float acos_value(float x) { return acosf(x)
 __attribute__((noinline)) __device__ float atan_value(float x) { return atanf(x); }
 __attribute__((noinline)) __device__ float tanh_value(float x) { return tanhf(x); }
 __attribute__((noinline)) __device__ float pow_value(float a, float b) { return powf(a, b); }
-__device__ __forceinline__ float cube_value(float x)
-{
-    const double d = (double)x;
-    return (float)(d * d * d);
-}
-__device__ __forceinline__ float sqrt_raw(float x)
+__attribute__((noinline)) __device__ float sqrt_raw_value(float x)
 {
     return x < 0.f ? __builtin_nanf("") : sqrt_abs(x);
 }
@@ -542,273 +518,122 @@ template <class T> __device__ __forceinline__ const_ptr<T> as_const(const T* p)
 }
 
 // ------------------------------------------------------------- staging
-// Request of program p: the last request whose first program is <= p.
-__device__ __forceinline__ int request_of(const int64_t* __restrict__ seg_start, int32_t n_seg,
-                                          int64_t p)
-{
-    int lo = 0, hi = n_seg - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (seg_start[mid] <= p) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// LDS-qualified pointers (per-lane LDS addressing without generic loads).
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) float lds_f32;
-
-// Node readers for the staging passes: straight from the request's array,
-// or from the block's LDS copy of its node range.
-struct GlobalNodes {
-    const uint32_t* __restrict__ p;
-    __device__ uint32_t operator()(int64_t k) const { return p[k]; }
-};
-struct LdsNodes {
-    const lds_u32* p;           // the block's node cache
-    int64_t lo;                 // first cached node
-    __device__ uint32_t operator()(int64_t k) const { return p[k - lo]; }
-};
-// Constant reader.
-struct GlobalConsts {
-    const float* __restrict__ p;
-    __device__ float operator()(uint32_t j) const { return p[j]; }
-};
-
-// The node range [min s, max e) of the block's programs, when they all
-// belong to one request and the range holds at most `cap` nodes.  `mine`:
-// this thread has a program with a valid node range.  Every thread of the
-// block must call it.  Returns true when the range is usable (then *req is
-// the request, *lo the first node and *n the node count).
-__device__ bool block_node_range(bool mine, int r, int64_t s, int64_t e, int cap, int* req,
-                                 int64_t* lo, int* n)
-{
-    __shared__ long long s_lo, s_hi;
-    __shared__ int s_r, s_mixed, s_any;
-    if (threadIdx.x == 0) {
-        s_lo = LLONG_MAX;
-        s_hi = LLONG_MIN;
-        s_r = -1;
-        s_mixed = 0;
-        s_any = 0;
-    }
-    __syncthreads();
-    // reduced inside each wavefront first: one LDS atomic per wavefront
-    // instead of one per thread
-    long long wlo = mine ? (long long)s : LLONG_MAX, whi = mine ? (long long)e : LLONG_MIN;
-    int wr = mine ? r : -1;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        wlo = min(wlo, __shfl_xor(wlo, off));
-        whi = max(whi, __shfl_xor(whi, off));
-        wr = max(wr, __shfl_xor(wr, off));
-    }
-    if ((threadIdx.x & 63) == 0 && wr >= 0) {
-        atomicMin(&s_lo, wlo);
-        atomicMax(&s_hi, whi);
-        atomicMax(&s_r, wr);
-        s_any = 1;
-    }
-    __syncthreads();
-    if (mine && r != s_r) s_mixed = 1;
-    __syncthreads();
-    const bool use = s_any && !s_mixed && s_hi - s_lo <= cap;
-    *req = s_r;
-    *lo = s_lo;
-    *n = use ? (int)(s_hi - s_lo) : 0;
-    return use;
-}
-
-// Cooperative, coalesced copy of the block's node range into LDS (see
-// block_node_range).  Every thread of the block must call it.  Returns true
-// when the copy is used (then *lo is the first cached node).
-__device__ bool cache_block_nodes(bool mine, int r, int64_t s, int64_t e,
-                                  const DevRequest* __restrict__ reqs, lds_u32* cache,
-                                  int64_t* lo)
-{
-    int rq = 0, n = 0;
-    const bool use = block_node_range(mine, r, s, e, kStageNodes, &rq, lo, &n);
-    if (use) {
-        // 16 independent loads in flight per thread and round: a plain copy
-        // loop would wait out the memory latency once per element
-        constexpr int kU = 16;
-        const uint32_t* __restrict__ src = reqs[rq].nodes + *lo;
-        const int step = (int)blockDim.x * kU;
-        for (int i0 = 0; i0 < n; i0 += step) {
-            uint32_t v[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int i = i0 + u * (int)blockDim.x + (int)threadIdx.x;
-                v[u] = i < n ? src[i] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int i = i0 + u * (int)blockDim.x + (int)threadIdx.x;
-                if (i < n) cache[i] = v[u];
-            }
-        }
-    }
-    __syncthreads();
-    return use;
-}
-
 #define GP_STAGING_FN __device__
 #include "staging.h"
 #include "threaded.h"
 #include "interp_gfx950.h"
 
-// Pass 1, one thread per program (blocks of kBucketBlock): validate, count
-// staged instructions, derive the depth class and the partition key, and
-// accumulate per-block key counts and staged sizes for the scans that
-// follow.  The block's nodes are read from an LDS copy when they fit.
-__global__ __launch_bounds__(kBucketBlock) void k_validate(
-    int64_t n_programs, uint32_t allowed, const DevDataset* __restrict__ ds,
-    const DevRequest* __restrict__ reqs, const int64_t* __restrict__ seg_start, int32_t n_seg,
-    const int32_t* __restrict__ tables_bad, int32_t lpt, int32_t n_blk,
-    ProgMeta* __restrict__ meta, uint8_t* __restrict__ cls, int32_t* __restrict__ pds,
-    int32_t* __restrict__ blk_counts, int64_t* __restrict__ blk_slen)
+// How a class's work is cut into items.  An item is G programs over m
+// consecutive case tiles, one workgroup's work between two barriers.
+// m is as large as the workgroup's LDS holds (item_tiles), capped so that at
+// least four (program, tiles) runs remain per wavefront of the GPU.
+// G (programs) is as large as g_max allows while the class still has about
+// target_items items, and at least one program per wavefront: larger groups
+// balance a workgroup's wavefronts (each takes the next program).  Neither
+// changes a result.
+constexpr int kRunWaves = 8;             // wavefronts of an evaluation workgroup
+constexpr int kRunWG = 64 * kRunWaves;
+constexpr double kGpuWaves = 6144.0;     // evaluation wavefronts resident on the GPU
+constexpr int kListed = 192;             // programs a workgroup lists between two barriers
+constexpr int kRunOn = 16;               // programs of an item that the next one may follow
+constexpr int kChunkMax = 64;            // programs of an item, at most
+constexpr int kWarmLines = 6;
+// prog_tiles: the class's (program, tile) pairs
+__device__ __forceinline__ int32_t cut_tiles(double prog_tiles)
 {
-    __shared__ int cnt[kKeys];
-    __shared__ unsigned long long s_slen;
-    __shared__ uint32_t cache_mem[kStageNodes];
-    lds_u32* cache = (lds_u32*)cache_mem;
-    if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
-    if (threadIdx.x == 0) s_slen = 0ull;
-    const int64_t p = (int64_t)blockIdx.x * kBucketBlock + threadIdx.x;
-    const bool have = p < n_programs;
-    const bool tab_ok = *tables_bad == 0;
-    int r = 0;
-    int64_t q = 0, s = 0, e = 0;
-    DevRequest R{};
-    if (have) {
-        r = request_of(seg_start, n_seg, p);
-        R = reqs[r];
-        q = p - seg_start[r];                 // index inside the request
-        pds[p] = r;
-        if (tab_ok) {
-            s = R.offsets[q];
-            e = R.offsets[q + 1];
-        }
-    }
-    const bool range_ok = s >= 0 && e >= s && e <= R.n_nodes && e - s <= INT32_MAX - 1;
-    const bool mine = have && tab_ok && range_ok && e > s;
-    int64_t lo = 0;
-    const bool cached = cache_block_nodes(mine, r, s, e, reqs, cache, &lo);
-    long long slen = 0;                       // this program's staged size
-    int pkey = 0xFF;                          // and its partition key
-    if (have) {
-        int status = GP_PROG_OK;
-        int maxd = 0;
-        int64_t n_staged = 0;
-        if (!tab_ok) {
-            status = GP_PROG_BAD_TABLE;
-        } else if (!range_ok) {
-            status = GP_PROG_BAD_OFFSETS;
-        } else if (e == s) {
-            status = GP_PROG_EMPTY;
-        } else {
-            const int32_t n_vars = ds[R.dataset].n_vars;
-            if (cached)
-                check_program(LdsNodes{cache, lo}, s, e, allowed, n_vars, R.n_consts, status, maxd,
-                              n_staged);
-            else
-                check_program(GlobalNodes{R.nodes}, s, e, allowed, n_vars, R.n_consts, status,
-                              maxd, n_staged);
-        }
-        const int c = status == GP_PROG_OK ? depth_class(maxd) : -1;
-        ProgMeta m;
-        m.start = 0;                          // k_stage's
-        m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : e - s);
-        m.slen = c >= 0 ? (int32_t)n_staged : 0;
-        meta[p] = m;
-        // partition key: depth class, then (single-request calls) length
-        // band from longest to shortest; with several requests the order
-        // inside a class stays the input order, so each request's programs
-        // stay together
-        int lb = 31 - __clz((uint32_t)(m.slen > 0 ? m.slen : 1));
-        lb = lb < kLenBuckets - 1 ? lb : kLenBuckets - 1;
-        const int key = c >= 0 ? c * kLenBuckets + (lpt ? kLenBuckets - 1 - lb : 0) : 0xFF;
-        cls[p] = (uint8_t)key;
-        pkey = key;
-        slen = m.slen;
-        if (R.out_status && q < R.n_programs) R.out_status[q] = status;
-    }
-    // per-key counts: one LDS atomic per distinct key in the wavefront
-    const int lane = threadIdx.x & 63;
-    for (uint64_t todo = __ballot(pkey < kKeys); todo != 0ull;) {
-        const int first = __ffsll((unsigned long long)todo) - 1;
-        const int k0 = __shfl(pkey, first);
-        const uint64_t same = __ballot(pkey == k0);
-        if (lane == first) atomicAdd(&cnt[k0], (int)__popcll(same));
-        todo &= ~same;
-    }
-    // the block's staged size, summed in each wavefront first
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) slen += __shfl_xor(slen, off);
-    if (lane == 0 && slen) atomicAdd(&s_slen, (unsigned long long)slen);
-    __syncthreads();
-    if (threadIdx.x < kKeys) blk_counts[threadIdx.x * n_blk + blockIdx.x] = cnt[threadIdx.x];
-    if (threadIdx.x == 0) blk_slen[blockIdx.x] = (int64_t)s_slen;
+    const double cap = prog_tiles / (4.0 * kGpuWaves);
+    return cap >= (double)kMaxTiles ? kMaxTiles : (cap < 1.0 ? 1 : (int32_t)cap);
 }
-
-// Programs per work item of a class with prog_tiles (program, case tile)
-// pairs: see class_seg_tables.
-__device__ __forceinline__ int class_group(double prog_tiles, int32_t g_max, int32_t target_items)
+// runs: the class's (program, m tiles) pairs
+__device__ __forceinline__ int32_t cut_programs(double runs, int32_t g_max, int32_t target_items)
 {
-    int G = g_max;
-    while (G > 4 && prog_tiles / G < (double)target_items) G >>= 1;
+    int32_t G = g_max;
+    while (G > kRunWaves && runs / (double)G < (double)target_items) G >>= 1;
     return G < 1 ? 1 : G;
 }
 
+// Cases of a class's sub-tile (64 per case held by a lane).
+__host__ __device__ constexpr int sub_cases(int c) { return c == 2 ? 128 : 256; }
+
+// Cases (a multiple of 256) whose inputs and targets fit the staged memory.
+__host__ __device__ inline int64_t staged_cases(int32_t lds_floats, int32_t n_vars)
+{
+    const int64_t n = lds_floats / (n_vars + 1) / 256 * 256;
+    return n < 256 ? 256 : n;
+}
+
+// Case tiles per item of one dataset: what the staged memory holds, spread
+// evenly over the dataset's tiles; 1 when a tile is larger than that (the
+// item then stages it piece by piece).
+__host__ __device__ inline int32_t item_tiles(int32_t passes, int32_t n_tiles, int c, int32_t n_vars,
+                                              int32_t lds_floats, int32_t m_cap)
+{
+    int64_t m = staged_cases(lds_floats, n_vars) / ((int64_t)passes * sub_cases(c));
+    m = m < m_cap ? m : m_cap;
+    m = m < 1 ? 1 : (m < n_tiles ? m : n_tiles);
+    const int32_t groups = (int32_t)((n_tiles + m - 1) / m);
+    return (n_tiles + groups - 1) / groups;
+}
+__host__ __device__ inline int32_t item_groups(int32_t n_tiles, int32_t m) { return (n_tiles + m - 1) / m; }
+
 // Per depth class c, from its programs per segment (seg_cnt[c * n_seg +
-// s]): the group size (programs per work item) and, per segment, where its
-// programs start inside the class's range of `order` and the prefix of work
-// items (groups times the segment dataset's case tiles).  Groups are as
-// large as g_max allows while the class still has about target_items items
-// (a small class gets smaller groups, so its few programs still spread over
-// the GPU); never below 4, one program per wavefront of a workgroup.
-// Grouping never changes a result.
+// s]): the cut (class_g[c], class_g[kClasses + c]) and, per segment, where
+// its programs start inside the class's range of `order` and the prefix of
+// work items.
 __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict__ seg_cnt,
                                  const int32_t* __restrict__ seg_ds,
                                  const DevDataset* __restrict__ ds, int32_t g_max,
-                                 int32_t target_items, int32_t* __restrict__ seg_pos,
-                                 uint32_t* __restrict__ item_pre, int32_t* __restrict__ class_g)
+                                 int32_t target_items, int32_t lds_floats,
+                                 int32_t* __restrict__ seg_pos, uint32_t* __restrict__ item_pre,
+                                 int32_t* __restrict__ class_g)
 {
     double prog_tiles = 0.0;
     for (int s = 0; s < n_seg; ++s)
         prog_tiles += (double)seg_cnt[c * n_seg + s] * (double)ds[seg_ds[s]].n_tiles[c];
-    const int G = class_group(prog_tiles, g_max, target_items);
+    const int32_t m_cap = cut_tiles(prog_tiles);
+    double runs = 0.0;
+    for (int s = 0; s < n_seg; ++s) {
+        const DevDataset& D = ds[seg_ds[s]];
+        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars, lds_floats, m_cap);
+        runs += (double)seg_cnt[c * n_seg + s] * (double)item_groups(D.n_tiles[c], m);
+    }
+    const int32_t G = cut_programs(runs, g_max, target_items);
     class_g[c] = G;
+    class_g[kClasses + c] = m_cap;
     int32_t pos = 0;
     uint32_t items = 0;
     for (int s = 0; s < n_seg; ++s) {
         const int32_t n = seg_cnt[c * n_seg + s];
+        const DevDataset& D = ds[seg_ds[s]];
+        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars, lds_floats, m_cap);
         seg_pos[c * n_seg + s] = pos;
         item_pre[c * (n_seg + 1) + s] = items;
         pos += n;
-        items += (uint32_t)((n + G - 1) / G) * (uint32_t)ds[seg_ds[s]].n_tiles[c];
+        items += (uint32_t)((n + G - 1) / G) * (uint32_t)item_groups(D.n_tiles[c], m);
     }
     item_pre[c * (n_seg + 1) + n_seg] = items;
 }
 
 // --------------------------------------------- staging by wavefronts
-// One wavefront stages one program of the benchmark set: lane l holds node
-// l of a 64-node chunk (longer programs take several chunks), and what the
-// serial walk of staging.h decides node by node has a form over lanes.
-//   depth after a node   leaves minus binary operators up to it (two ballots)
+// One wavefront stages one program: lane l holds node l of a 64-node chunk
+// (longer programs take several chunks), and what the serial walk of
+// staging.h decides node by node has a form over lanes.
+//   depth after a node   pushes minus pops up to it (two ballots)
 //   elements that depend on a variable (the runtime depth)
-//                        the smallest depth since the last variable: a prefix
-//                        minimum, made one scan over the whole chunk by
-//                        subtracting 64 per variable passed
+//                        the smallest depth since the last variable or
+//                        command that is not folded: a prefix minimum, made
+//                        one scan over the whole chunk by subtracting 64 per
+//                        such node passed
 //   held constants       depth minus runtime depth
 // From those each node knows the word it emits, if any, and the words before
-// it.  Folded operators are the only serial part: a loop over them, uniform
-// in the wavefront, whose operands are the values at the last node of each
-// depth.  (The serial walk, a program per lane, cost 275 instructions a node
-// for every wavefront, the union of what its 64 lanes were doing: 33 us for
-// 32 programs, 70 us for 10,000.)  The words are those of the serial walk
-// without its limit of 16 held constants; statuses, depths and values are
-// the same.
+// it.  Serial, uniform in the wavefront, are only the folded operators (their
+// operands are the values at the last node of each depth) and, with the
+// whole command table (EXT), the named variables' cells.  (The serial walk, a
+// program per lane, cost 275 instructions a node for every wavefront, the
+// union of what its 64 lanes were doing: 33 us for 32 programs, 70 us for
+// 10,000; with the whole table 64 + 75 us for 2,000.)  Statuses, depths and
+// values are the serial walk's; constants are held without its limit of 16.
 //
 // LDS per wavefront: for each depth, one past the last node that left the
 // stack there in the chunks before, and the constant at it.
@@ -847,6 +672,7 @@ __device__ __forceinline__ int prefix_min(int v)
 // wavefront.  status, cls (depth class) and the word count come back; dst
 // holds the words when the status is GP_PROG_OK (else nothing useful), never
 // more than len of them.
+template <bool EXT>
 __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, int32_t len,
                                           const float* __restrict__ consts, int64_t n_consts,
                                           uint32_t allowed, int32_t n_vars,
@@ -854,11 +680,13 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
                                           int* cls, int* n_words)
 {
     int depth = 0, rt_in = 0, n = 0;       // after the chunks before: stack, runtime, words
+    int live_in = 0;                       // held variables
     bool prev_load = false;
     float prev_value = 0.f;                // value at the chunk's previous node
     int over8 = 0, over16 = 0;
     uint2 held = make_uint2(0u, 0u);       // the last word so far, not yet stored
     int held_at = -1;
+    GclCheck gc;                           // the named variables' cells (EXT)
     const bool many = len > 64;
     if (many && lane < kDepthSlots) tb->last[lane] = 0u;
     for (int32_t c0 = 0; c0 < len; c0 += 64) {
@@ -867,31 +695,68 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
         const uint32_t w = live ? nodes[k] : 0xFFu;
         const uint32_t nx = k + 1 < len ? nodes[k + 1] & 0xFFu : 0xFFu;
         const uint32_t op = w & 0xFFu, arg = w >> 8;
-        const bool leaf = op <= GP_CONST, bin = op - GP_ADD < 4u, un = op - GP_SIN < 6u;
-        const bool load = op == GP_LOAD, cst = op == GP_CONST;
-        const uint64_t leaves = __ballot(leaf), bins = __ballot(bin);
-        const int d0 = depth + (int)lanes_below(leaves) - (int)lanes_below(bins);
-        const int d1 = d0 + (leaf ? 1 : 0) - (bin ? 1 : 0);
+        const bool leaf = op <= GP_CONST, load = op == GP_LOAD, cst = op == GP_CONST;
+        const bool bin = op - GP_ADD < 4u, un = op - GP_SIN < 6u;       // folded operators
+        const bool pw = EXT && op == GP_POW;
+        const bool copy = EXT && op == GP_COPY, paste = EXT && op == GP_PASTE;
+        const bool push = leaf || (EXT && op == GP_DUP) || paste;
+        const bool pop = bin || pw || (EXT && op == GP_DEL);
+        const uint64_t pushes = __ballot(push), pops = __ballot(pop);
+        const int d0 = depth + (int)lanes_below(pushes) - (int)lanes_below(pops);
+        const int d1 = d0 + (push ? 1 : 0) - (pop ? 1 : 0);
+        int used = d1;                           // cells in use after the node
+        uint32_t cells = 0u;                     // a variable move's cells
+        bool unpaired = false;
+        int copies = 0, pastes = 0;
+        if constexpr (EXT) {
+            const uint64_t cm = __ballot(copy), pm = __ballot(paste);
+            used += live_in + (int)lanes_below(cm) - (int)lanes_below(pm) + (copy ? 1 : 0) - (paste ? 1 : 0);
+            copies = (int)__popcll(cm);
+            pastes = (int)__popcll(pm);
+            // (past a program's first broken node the state means nothing)
+            for (uint64_t mv = cm | pm; mv != 0ull; mv &= mv - 1ull) {
+                const int l = __builtin_ctzll(mv);
+                const uint32_t name = (uint32_t)lane_value((int)arg, l);
+                const bool is_copy = ((cm >> l) & 1ull) != 0ull;
+                const bool held_var = name < GP_GCL_VARS && ((gc.held >> name) & 1u);
+                const bool ok = name < GP_GCL_VARS && held_var != is_copy;
+                uint32_t c = 0u;
+                if (ok && is_copy) {
+                    c = 31u - (uint32_t)gc.copy(name);
+                } else if (ok) {
+                    const int q = gc.var_pos(name), from = gc.paste(name);
+                    c = (31u - (uint32_t)q) | ((31u - (uint32_t)(from >= 0 ? from : q)) << 8);
+                }
+                cells = lane == l ? c : cells;
+                unpaired = lane == l ? !ok : unpaired;
+            }
+        }
         // the checks of the serial walk; the first failing node names the status
-        int code = d1 > GP_MAX_STACK ? GP_PROG_TOO_DEEP : GP_PROG_OK;
-        code = d0 < (leaf ? 0 : (bin ? 2 : 1)) ? GP_PROG_UNDERFLOW : code;
+        int need = leaf || paste ? 0 : (bin || pw || (EXT && op == GP_SWAP) ? 2 : 1);
+        int code = used > GP_MAX_STACK ? GP_PROG_TOO_DEEP : GP_PROG_OK;
+        code = unpaired ? GP_PROG_BAD_PAIR : code;
+        code = d0 < need ? GP_PROG_UNDERFLOW : code;
         code = cst && (int64_t)arg >= n_consts ? GP_PROG_BAD_CONST : code;
         code = load && (int64_t)arg >= (int64_t)n_vars ? GP_PROG_BAD_VAR : code;
         code = op < 32u && ((allowed >> (op & 31u)) & 1u) ? code : GP_PROG_BAD_OP;
         const uint64_t bad = __ballot(live && code != GP_PROG_OK);
         if (bad != 0ull) return lane_value(code, __builtin_ctzll(bad));
-        over8 |= __ballot(live && d1 > 8) != 0ull;
-        over16 |= __ballot(live && d1 > 16) != 0ull;
+        over8 |= __ballot(live && used > 8) != 0ull;
+        over16 |= __ballot(live && used > 16) != 0ull;
 
         // runtime depth after and before each node
-        const uint64_t loads = __ballot(load);
-        const int sigma = (int)lanes_below(loads) + (load ? 1 : 0);
+        const bool beyond = EXT && live && op >= GP_DUP;
+        const uint64_t loads = __ballot(load), solid = EXT ? __ballot(load || beyond) : loads;
+        const int sigma = (int)lanes_below(solid) + (load || beyond ? 1 : 0);
         const int r1 = min(rt_in, prefix_min(live ? d1 - 64 * sigma : INT_MAX)) + 64 * sigma;
         const int rp = __shfl_up(r1, 1);        // (every lane takes part)
         const int r0 = lane == 0 ? rt_in : rp;
         const int np = d0 - r0;
         const bool after_load = lane == 0 ? prev_load : ((loads >> (lane - 1)) & 1ull) != 0ull;
-        const bool own = live && (load || (!after_load && ((bin && np < 2) || (un && np < 1))));
+        const bool fused = after_load && (bin || un || pw);
+        bool own = load || (!fused && ((bin && np < 2) || (un && np < 1)));
+        if constexpr (EXT) own = own || (beyond && !fused && !(op == GP_DEL && d0 < 2));
+        own = own && live;
 
         // constants, then the folded operators in order
         float val = cst ? consts[arg] : 0.f;
@@ -900,7 +765,7 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
             const uint64_t m = __ballot(live && d1 == d) & ((1ull << l) - 1ull);
             return m != 0ull ? lane_value(val, 63 - __builtin_clzll(m)) : tb->value[d];
         };
-        uint64_t folds = __ballot(live && !after_load && ((bin && np >= 2) || (un && np >= 1)));
+        uint64_t folds = __ballot(live && !fused && ((bin && np >= 2) || (un && np >= 1)));
         while (folds != 0ull) {
             const int l = __builtin_ctzll(folds);
             folds &= folds - 1ull;
@@ -916,11 +781,11 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
             val = lane == l ? r : val;
         }
 
-        // words: a variable flushes the constants held below it, then each
-        // node's own word
+        // words: a variable (or a command that is not folded) flushes the
+        // constants held below it, then each node's own word
         int pos = n + (int)lanes_below(__ballot(own));
         int flushed = 0;
-        uint64_t flushes = __ballot(live && load && np > 0);
+        uint64_t flushes = __ballot(live && np > 0 && (load || (beyond && !(pw && np == 1))));
         while (flushes != 0ull) {
             const int l = __builtin_ctzll(flushes);
             flushes &= flushes - 1ull;
@@ -939,14 +804,23 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
         if (load) {
             const uint32_t payload = arg * kVarPayload;
             const int rt = d0;                   // everything below is on the stack now
-            word = nx - GP_ADD < 4u   ? ThreadedWords::top_row(rt, nx - GP_ADD, payload)
-                   : nx - GP_SIN < 6u ? ThreadedWords::push_unary(rt, nx - GP_SIN, payload)
-                                      : ThreadedWords::push_row(rt, payload);
-        } else if (bin) {
-            word = np == 1 ? ThreadedWords::top_const(r0, op - GP_ADD, __float_as_uint(top))
-                           : ThreadedWords::cells(r0, op - GP_ADD);
+            word = nx - GP_ADD < 4u            ? ThreadedWords::top_row(rt, nx - GP_ADD, payload)
+                   : EXT && nx == GP_POW       ? ThreadedWords::top_row(rt, kBinPow, payload)
+                   : nx - GP_SIN < 6u          ? ThreadedWords::push_unary(rt, nx - GP_SIN, payload)
+                                               : ThreadedWords::push_row(rt, payload);
+        } else if (bin || pw) {
+            const uint32_t sel = pw ? kBinPow : op - GP_ADD;
+            word = np == 1 ? ThreadedWords::top_const(r0, sel, __float_as_uint(top))
+                           : ThreadedWords::cells(pw ? d0 : r0, sel);
+        } else if (EXT && beyond && !op_is_unary(op)) {
+            const uint32_t off = op == GP_DUP    ? kThDup
+                                 : op == GP_SWAP ? kThSwap
+                                 : op == GP_DEL  ? kThDel
+                                 : copy          ? kThCopy
+                                                 : kThPaste;
+            word = ThreadedWords::move(d0, off, cells);
         } else {
-            word = ThreadedWords::unary(r0, un ? op - GP_SIN : 0u);
+            word = ThreadedWords::unary(beyond ? d0 : r0, un || beyond ? uop_sel(op) : 0u);
         }
         // the chunk's last own word is stored once it is known whether
         // another follows
@@ -964,6 +838,7 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
         rt_in = lane_value(r1, end);
         prev_value = lane_value(val, end);
         prev_load = ((loads >> end) & 1ull) != 0ull;
+        live_in += copies - pastes;
         if (many && c0 + 64 < len) {
             // the last node of each depth, for the chunks that follow
             atomicMax(&tb->last[d1], (uint32_t)k + 1u);
@@ -971,11 +846,13 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
         }
     }
     if (depth != 1) return GP_PROG_FINAL_DEPTH;
+    if (live_in != 0) return GP_PROG_BAD_PAIR;
     if (rt_in == 0) {
-        // a constant program: its value is pushed
+        // what is left is a constant: its value is pushed
+        if (held_at >= 0 && lane == 0) dst[held_at] = held;
         held = ThreadedWords::push_const(0, __float_as_uint(prev_value));
-        held_at = 0;
-        n = 1;
+        held_at = n;
+        ++n;
     }
     if (lane == 0) dst[held_at] = ThreadedWords::last(held);
     *cls = over16 ? 2 : over8;
@@ -1074,10 +951,11 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
     return g;
 }
 
-// Pass 1, one wavefront per program (benchmark-set masks): validate and
+// Pass 1, one wavefront per program: validate and
 // stage each program at its own node offset in the request's part of `code`
 // (its words never outnumber its nodes, so while offsets never decrease the
 // programs' ranges are disjoint), and count the partition keys per block.
+template <bool EXT>
 __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
 {
     __shared__ int cnt[kKeys];
@@ -1107,8 +985,8 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
         else if (!range_ok) status = GP_PROG_BAD_OFFSETS;
         else if (g.e == g.s) status = GP_PROG_EMPTY;
         else
-            status = stage_wave(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                g.n_vars, a.code + g.node_base + g.s, &tables[wave], lane, &c, &n);
+            status = stage_wave<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                     g.n_vars, a.code + g.node_base + g.s, &tables[wave], lane, &c, &n);
         if (status != GP_PROG_OK) {
             c = -1;
             n = 0;
@@ -1142,22 +1020,23 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
 // Pass 2, same blocks: every block sums the key counts of the blocks before
 // it (and of all), so the partition needs no scan of its own; program ids are
 // scattered stably by (depth class, length band); block 0 writes the class
-// ranges, clears the work counters and, for a single request, writes its
+// ranges, clears the work counter and, for a single request, writes its
 // per-class tables (class_seg_tables with one segment).
 // Offsets that decrease somewhere let programs' node ranges overlap: then
 // every program is staged again here, packed in program order, unless the
 // staged programs need more than n_nodes words in total (no program of the
 // call is staged then).
 struct SegOut {
-    int32_t g_max, target_items;
+    int32_t g_max, target_items, lds_floats;
     int32_t* seg_cnt;
     int32_t* seg_pos;
     uint32_t* item_pre;
     int32_t* class_g;
     int32_t* class_info;
-    uint32_t* counters;
+    uint32_t* counter;
 };
 constexpr int kOrderWG = 256;
+template <bool EXT>
 __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
                                                     SegOut so)
 {
@@ -1215,7 +1094,7 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
                 if (a.cls[p] >= kKeys) continue;
                 const ProgRange g = program_range(a, p, true);
                 int c = 0, n = 0;
-                (void)stage_wave(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                (void)stage_wave<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
                                  g.n_vars, a.code + start, &tables[wave], lane, &c, &n);
                 if (lane == 0) a.meta[p].start = start;
             }
@@ -1237,15 +1116,23 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         if (overflow) count = 0;
         so.class_info[2 * t] = start;
         so.class_info[2 * t + 1] = count;
-        so.counters[t] = 0u;
+        if (t == 0) *so.counter = 0u;
         if (a.single) {
             const int32_t tiles = a.one_ds.n_tiles[t];
-            const int G = class_group((double)count * (double)tiles, so.g_max, so.target_items);
+            const int32_t m_cap = cut_tiles((double)count * (double)tiles);
+            const int32_t m = item_tiles(a.one_ds.passes[t], tiles, t, a.one_ds.n_vars, so.lds_floats, m_cap);
+            const int32_t groups = item_groups(tiles, m);
+            // (items over the same cases follow each other without a barrier, so
+            // small ones cost nothing and end the launch evenly)
+            const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars);
+            const int32_t G = cut_programs((double)count * (double)groups,
+                                           whole && so.g_max > kRunOn ? kRunOn : so.g_max, so.target_items);
             so.seg_cnt[t] = count;
             so.class_g[t] = G;
+            so.class_g[kClasses + t] = m_cap;
             so.seg_pos[t] = 0;
             so.item_pre[2 * t] = 0u;
-            so.item_pre[2 * t + 1] = (uint32_t)((count + G - 1) / G) * (uint32_t)tiles;
+            so.item_pre[2 * t + 1] = (uint32_t)((count + G - 1) / G) * (uint32_t)groups;
         }
     }
     if (overflow) {
@@ -1287,247 +1174,17 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
     }
 }
 
-// ------------------------------------ staging of the whole command table
-// Where a call of a single request gets its per-class work-item tables
-// (k_class_scan writes them when `single` is set).
-struct ScanOut {
-    int32_t single;
-    int32_t g_max, target_items;
-    const int32_t* seg_ds;
-    const DevDataset* ds;
-    int32_t* seg_cnt;
-    int32_t* seg_pos;
-    uint32_t* item_pre;
-    int32_t* class_g;
-};
-
-// One workgroup: exclusive scans of the per-block key counts (key-major
-// order) into blk_base and of the per-block staged sizes into blk_code;
-// class_info[2c] = first position of depth class c, [2c+1] = its size (its
-// keys are contiguous); also clears the per-class work counters.  Staged
-// code never exceeds the call's node count unless programs' node ranges
-// overlap; then *overflow is set, nothing is staged and every class is
-// left empty.  With a single request it also writes the request's
-// per-class tables (class_seg_tables).
-__global__ __launch_bounds__(1024) void k_class_scan(
-    const int32_t* __restrict__ blk_counts, const int64_t* __restrict__ blk_slen, int32_t n_blk,
-    int64_t code_capacity, int32_t* __restrict__ blk_base, int64_t* __restrict__ blk_code,
-    int32_t* __restrict__ class_info, uint32_t* __restrict__ work_counters,
-    int32_t* __restrict__ overflow, ScanOut so)
-{
-    __shared__ int part[1024];
-    __shared__ long long lpart[1024];
-    const int t = threadIdx.x;
-    // a single request's dataset tiles, loaded while the scan runs
-    const int32_t tiles = so.single && t < kClasses ? so.ds[so.seg_ds[0]].n_tiles[t] : 0;
-    const int total = kKeys * n_blk;
-    const int chunk = (total + 1023) / 1024;
-    const int lo = t * chunk, hi = min(total, lo + chunk);
-    // loads in batches of 8, so that a thread's loads are in flight together
-    int sum = 0;
-    {
-        int i = lo;
-        for (; i + 8 <= hi; i += 8) {
-            int v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = blk_counts[i + u];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) sum += v[u];
-        }
-        for (; i < hi; ++i) sum += blk_counts[i];
-    }
-    part[t] = sum;
-    const int chunk2 = (n_blk + 1023) / 1024;
-    const int lo2 = t * chunk2, hi2 = min(n_blk, lo2 + chunk2);
-    long long sum2 = 0;
-    for (int i = lo2; i < hi2; ++i) sum2 += blk_slen[i];
-    lpart[t] = sum2;
-    __syncthreads();
-    // inclusive Hillis-Steele scans of the chunk sums
-    for (int off = 1; off < 1024; off <<= 1) {
-        const int v = t >= off ? part[t - off] : 0;
-        const long long v2 = t >= off ? lpart[t - off] : 0;
-        __syncthreads();
-        part[t] += v;
-        lpart[t] += v2;
-        __syncthreads();
-    }
-    int run = part[t] - sum;
-    {
-        int i = lo;
-        for (; i + 8 <= hi; i += 8) {
-            int v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = blk_counts[i + u];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                blk_base[i + u] = run;
-                run += v[u];
-            }
-        }
-        for (; i < hi; ++i) {
-            blk_base[i] = run;
-            run += blk_counts[i];
-        }
-    }
-    long long run2 = lpart[t] - sum2;
-    for (int i = lo2; i < hi2; ++i) {
-        blk_code[i] = run2;
-        run2 += blk_slen[i];
-    }
-    if (t < kClasses) {
-        // exclusive prefix of entry i from the scanned chunk sums (LDS)
-        // and the entries before it in its chunk, loaded all at once
-        auto prefix = [&](int i) {
-            if (i >= total) return part[1023];
-            const int owner = i / chunk;
-            int b = owner > 0 ? part[owner - 1] : 0;
-            const int j0 = owner * chunk;
-            if (chunk <= 32) {
-                int v[32];
-#pragma unroll
-                for (int u = 0; u < 32; ++u) v[u] = j0 + u < i ? blk_counts[j0 + u] : 0;
-#pragma unroll
-                for (int u = 0; u < 32; ++u) b += v[u];
-            } else {
-                for (int j = j0; j < i; ++j) b += blk_counts[j];
-            }
-            return b;
-        };
-        const bool ovf = lpart[1023] > code_capacity;
-        const int start = prefix(t * kLenBuckets * n_blk);
-        const int end = prefix((t + 1) * kLenBuckets * n_blk);
-        class_info[2 * t] = start;
-        class_info[2 * t + 1] = ovf ? 0 : end - start;
-        work_counters[t] = 0u;
-        if (t == 0) *overflow = ovf ? 1 : 0;
-        if (so.single) {
-            // one request holds the whole class (class_seg_tables with one
-            // segment)
-            const int32_t n = ovf ? 0 : end - start;
-            const int G = class_group((double)n * (double)tiles, so.g_max, so.target_items);
-            so.seg_cnt[t] = n;
-            so.class_g[t] = G;
-            so.seg_pos[t] = 0;
-            so.item_pre[2 * t] = 0u;
-            so.item_pre[2 * t + 1] = (uint32_t)((n + G - 1) / G) * (uint32_t)tiles;
-        }
-    }
-}
-
-// Pass 2, same blocks as pass 1: each program is staged at its block's base
-// plus the exclusive scan of staged sizes inside the block, so ranges never
-// overlap whatever the offsets; its id is scattered (stably) into the
-// partition order.
-//
-// Staged instruction of the flag form (8 bytes, one scalar load; calls within
-// the benchmark set use the threaded form, threaded.h):
-//   x = flags | sel << 8 | cell << 16, y = payload
-//   kFPush  save the top into stack cell `cell`, then the top = leaf
-//   kFUn    the top = unary sel (SIN..ABS as 0..5) of the top
-//   kFSBin  the top = stack cell `cell`  OP_sel  top  (ADD..DIV as 0..3)
-//   kFLBin  the top = top  OP_sel  leaf
-//   kFLast  (with any of the above) the program's last instruction
-// A leaf is the constant with bits y when kFConst is set, else the input
-// row at LDS byte offset y (variable index * 1024, halved at two cases per
-// lane).  Eight bytes (not sixteen) keep the code of the programs that the
-// resident wavefronts run at once small enough to stay in the scalar cache
-// while each program passes over its window.
-__global__ __launch_bounds__(kBucketBlock) void k_stage(
-    int64_t n_programs, const DevRequest* __restrict__ reqs,
-    const int64_t* __restrict__ seg_start, const int32_t* __restrict__ pds, int32_t n_blk,
-    const int64_t* __restrict__ blk_code, const int32_t* __restrict__ blk_base,
-    const int32_t* __restrict__ overflow,
-    uint8_t* __restrict__ cls, ProgMeta* __restrict__ meta, uint2* __restrict__ code,
-    int32_t* __restrict__ order)
-{
-    __shared__ long long sc[kBucketBlock];
-    constexpr int kW = kBucketBlock / 64;
-    __shared__ int wcnt[kW][kKeys];
-    const int t = threadIdx.x;
-    const int64_t p = (int64_t)blockIdx.x * kBucketBlock + t;
-    int key = p < n_programs ? (int)cls[p] : 0xFF;
-    if (*overflow) {
-        // overlapping node ranges: no program of this call is staged
-        if (key < kKeys) {
-            cls[p] = 0xFF;
-            const int r = pds[p];
-            const DevRequest& R = reqs[r];
-            const int64_t q = p - seg_start[r];
-            if (R.out_status && q < R.n_programs) R.out_status[q] = GP_PROG_BAD_OFFSETS;
-        }
-        return;
-    }
-    __shared__ uint32_t cache_mem[kStageNodes];
-    __shared__ float pv_mem[kHeldConsts * kBucketBlock];
-    lds_u32* cache = (lds_u32*)cache_mem;
-    ProgMeta m;
-    m.start = 0;
-    m.len = 0;
-    m.slen = 0;
-    if (p < n_programs) m = meta[p];
-    // inclusive scan of staged sizes inside the block
-    sc[t] = m.slen;
-    __syncthreads();
-    for (int off = 1; off < kBucketBlock; off <<= 1) {
-        const long long v = t >= off ? sc[t - off] : 0;
-        __syncthreads();
-        sc[t] += v;
-        __syncthreads();
-    }
-    const int64_t start = blk_code[blockIdx.x] + sc[t] - m.slen;
-    int r = 0;
-    int64_t s = 0, e = 0;
-    DevRequest R{};
-    if (key < kKeys) {
-        r = pds[p];
-        R = reqs[r];
-        const int64_t q = p - seg_start[r];
-        s = R.offsets[q];
-        e = R.offsets[q + 1];
-    }
-    int64_t lo = 0;
-    const bool cached = cache_block_nodes(key < kKeys, r, s, e, reqs, cache, &lo);
-    if (key < kKeys) {
-        lds_f32* pvs = (lds_f32*)pv_mem + t;
-        if (cached)
-            stage_walk(LdsNodes{cache, lo}, s, e, GlobalConsts{R.consts}, code + start, m.slen, pvs);
-        else
-            stage_walk(GlobalNodes{R.nodes}, s, e, GlobalConsts{R.consts}, code + start, m.slen, pvs);
-        meta[p].start = start;
-    }
-    // stable scatter into the partition order
-    const int wave = t >> 6, lane = t & 63;
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    int rank = 0;
-    if (lane < kKeys) wcnt[wave][lane] = 0;
-    // one pass per distinct key in the wavefront
-    for (uint64_t todo = __ballot(key < kKeys); todo != 0ull;) {
-        const int first = __ffsll((unsigned long long)todo) - 1;
-        const int k0 = __shfl(key, first);
-        const uint64_t bm = __ballot(key == k0);
-        if (lane == first) wcnt[wave][k0] = __popcll(bm);
-        if (key == k0) rank = __popcll(bm & below);
-        todo &= ~bm;
-    }
-    __syncthreads();
-    if (key < kKeys) {
-        for (int w2 = 0; w2 < wave; ++w2) rank += wcnt[w2][key];
-        order[blk_base[key * n_blk + blockIdx.x] + rank] = (int32_t)p;
-    }
-}
-
 // One workgroup, calls of several requests: the programs of each depth
 // class inside each segment (seg_cnt[c * n_seg + s]; the partition keeps
 // each class in program order, so they are the class's entries between two
 // lower bounds of the segment's program range), then class_seg_tables per
-// class.  (A single request's tables come from k_class_scan.)
+// class.  (A single request's tables come from k_order.)
 __global__ __launch_bounds__(256) void k_seg_tables(
     const int32_t* __restrict__ order, const int32_t* __restrict__ class_info,
     const int64_t* __restrict__ seg_start, int32_t n_seg, const int32_t* __restrict__ tables_bad,
     const int32_t* __restrict__ seg_ds, const DevDataset* __restrict__ ds, int32_t g_max,
-    int32_t target_items, int32_t* __restrict__ seg_cnt, int32_t* __restrict__ seg_pos,
-    uint32_t* __restrict__ item_pre, int32_t* __restrict__ class_g)
+    int32_t target_items, int32_t lds_floats, int32_t* __restrict__ seg_cnt,
+    int32_t* __restrict__ seg_pos, uint32_t* __restrict__ item_pre, int32_t* __restrict__ class_g)
 {
     const bool bad = *tables_bad != 0;              // then no program was staged
     for (int i = threadIdx.x; i < kClasses * n_seg; i += blockDim.x) {
@@ -1547,31 +1204,11 @@ __global__ __launch_bounds__(256) void k_seg_tables(
     }
     __syncthreads();
     if (threadIdx.x < kClasses)
-        class_seg_tables(threadIdx.x, n_seg, seg_cnt, seg_ds, ds, g_max, target_items, seg_pos,
-                         item_pre, class_g);
+        class_seg_tables(threadIdx.x, n_seg, seg_cnt, seg_ds, ds, g_max, target_items, lds_floats,
+                         seg_pos, item_pre, class_g);
 }
 
 // ------------------------------------------------------------ evaluation
-// Scalars of one class launch (pointers travel as restrict-qualified kernel
-// parameters so that uniform loads of programs and metadata become scalar
-// memory loads).
-struct EvalConst {
-    int32_t cls;
-    int32_t G;              // programs per work item
-    int32_t part_stride;    // partial of (program p, tile t) at t * part_stride + p
-    int32_t max_vars;       // largest n_vars of the call
-    int32_t n_seg;
-    int32_t tile_floats;    // LDS floats for input windows
-    int32_t group_major;    // depth <= 8 class: a group's case tiles are consecutive items
-    // single-dataset form (gp_predict)
-    int64_t ld_x;
-    int64_t n_cases;
-    int32_t n_vars;
-    // integer reward mode
-    int32_t reward_power;
-    float reward_M;
-};
-
 // Error-free sum: s + e == a + b exactly (Knuth's TwoSum).
 __device__ __forceinline__ void two_sum(float a, float b, float& s, float& e)
 {
@@ -1619,308 +1256,6 @@ __device__ __forceinline__ void mse_case(float f, float ys, float s, float& hi, 
     hi = u;
 }
 
-// The value stack below the top lives in VGPR arrays of 32 floats ("chunks"):
-// chunk c holds cases [c*J, (c+1)*J) of every slot, element index
-// slot*J + (case mod J), J = 32 / MAXD.  A uniform dynamic index into a
-// 32-element vector compiles to GPR-index-mode moves (smaller vectors would
-// be expanded into compare/select chains).  `ix` is a staged cell number
-// scaled by J, modulo 32 (so always inside the chunk).
-#define GP_CHUNK_PUT(ix, j, v)                                                     \
-    do {                                                                           \
-        const uint32_t i_ = (ix) + ((j) % J);                                      \
-        if ((j) / J == 0) c0[i_] = (v);                                            \
-        else if ((j) / J == 1) c1[i_] = (v);                                       \
-        else if ((j) / J == 2) c2[i_] = (v);                                       \
-        else c3[i_] = (v);                                                         \
-    } while (0)
-#define GP_CHUNK_GET(ix, j)                                                        \
-    (((j) / J == 0) ? c0[(ix) + ((j) % J)]                                         \
-     : ((j) / J == 1) ? c1[(ix) + ((j) % J)]                                       \
-     : ((j) / J == 2) ? c2[(ix) + ((j) % J)] : c3[(ix) + ((j) % J)])
-
-// out[j] = a[j] OP b[j] for the four binary ops (b = top of stack, a = the
-// element below it; SUB and DIV take a - b and a / b, GCL command table).
-#define GP_BINARY_AB(bop, a, b, out)                                               \
-    do {                                                                           \
-        switch (bop) {                                                             \
-        case GP_ADD:                                                               \
-            _Pragma("unroll") for (int j = 0; j < K; ++j) out[j] = a[j] + b[j];    \
-            break;                                                                 \
-        case GP_SUB:                                                               \
-            _Pragma("unroll") for (int j = 0; j < K; ++j) out[j] = a[j] - b[j];    \
-            break;                                                                 \
-        case GP_MUL:                                                               \
-            _Pragma("unroll") for (int j = 0; j < K; ++j) out[j] = a[j] * b[j];    \
-            break;                                                                 \
-        default:                                                                   \
-            _Pragma("unroll") for (int j = 0; j < K; ++j)                          \
-                out[j] = div_protected(a[j], b[j]);                                \
-            break;                                                                 \
-        }                                                                          \
-    } while (0)
-#define GP_BINARY(bop, a, top) GP_BINARY_AB(bop, a, top, top)
-
-// Runs one staged program on K cases per lane; xl points at this lane's
-// first case of the LDS input tile.  A sub-tile's cases are laid out case-
-// major: case j of lane t is element j*64 + t of a variable's row (row
-// stride 64*K floats), so each of the K reads of a LOAD is a conflict-free,
-// lane-contiguous LDS access.  The top of the stack is returned in tos[].
-// Loads a leaf for K cases: the constant with bits `payload` when is_const,
-// else the input row whose byte offset at four cases per lane is `payload`
-// (halved at two cases per lane).
-#define GP_LEAF(is_const, payload, out)                                            \
-    do {                                                                           \
-        if (is_const) {                                                            \
-            const float c_ = __uint_as_float(payload);                             \
-            _Pragma("unroll") for (int j = 0; j < K; ++j) out[j] = c_;             \
-        } else {                                                                   \
-            const float* xp_ = reinterpret_cast<const float*>(                     \
-                reinterpret_cast<const char*>(xl) + ((payload) >> kRowShift));     \
-            _Pragma("unroll") for (int j = 0; j < K; ++j) out[j] = xp_[j * 64];    \
-        }                                                                          \
-    } while (0)
-
-// Whether any lane of the wavefront holds, among its K values, one with
-// |v| > limit or a NaN: one compare per value into a lane mask, the masks
-// OR-ed on the scalar unit.
-template <int K>
-__device__ __forceinline__ bool wave_any_above(const float (&v)[K], float limit)
-{
-    // the largest magnitude on the vector unit (a NaN drops out of the
-    // maximum: the fast formulas propagate it), one compare into a mask
-    float m = fabsf(v[0]);
-#pragma unroll
-    for (int j = 1; j < K; ++j) m = __builtin_fmaxf(m, fabsf(v[j]));
-    return __ballot(m > limit) != 0ull;
-}
-
-// The commands beyond the benchmark set on the top values (unary
-// selectors kUnSquare..15), per case, with the functions constant folding
-// uses.
-template <int K>
-__device__ __forceinline__ void ext_unary(uint32_t sel, float (&t)[K])
-{
-    switch (sel) {
-    case kUnSquare:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = t[j] * t[j];
-        break;
-    case kUnSquare + 1:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = -t[j];
-        break;
-    case kUnSquare + 2:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = cube_value(t[j]);
-        break;
-    case kUnSquare + 3:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = cbrt_value(t[j]);
-        break;
-    case kUnSquare + 4:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = tan_value(t[j]);
-        break;
-    case kUnSquare + 5:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = asin_value(t[j]);
-        break;
-    case kUnSquare + 6:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = acos_value(t[j]);
-        break;
-    case kUnSquare + 7:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = atan_value(t[j]);
-        break;
-    case kUnSquare + 8:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = tanh_value(t[j]);
-        break;
-    default:
-#pragma unroll
-        for (int j = 0; j < K; ++j) t[j] = sqrt_raw(t[j]);
-        break;
-    }
-}
-
-// The interpreter for the whole command table (POW, the unary commands
-// beyond the benchmark set, cell moves), over words of the flag form.
-template <int MAXD, int K>
-__device__ __forceinline__ void run_program(const uint2* __restrict__ pc,
-                                            const float* __restrict__ xl, float (&tos)[K])
-{
-    constexpr int J = 32 / MAXD;                  // cases per 32-float chunk
-    static_assert(K % J == 0 && K / J <= 4, "chunking");
-    // staged cell numbers times J, by one shift of the word (bits 14-15 of
-    // a staged word are zero)
-    constexpr uint32_t kLogJ = J == 4 ? 2u : (J == 2 ? 1u : 0u);
-    static_assert((1 << kLogJ) == J, "J is 1, 2 or 4");
-    // variable payloads are row offsets at four cases per lane
-    constexpr uint32_t kRowShift = K == 4 ? 0u : 1u;
-    static_assert(K == 4 || K == 2, "row offsets for 4 or 2 cases per lane");
-    float c0[32], c1[32], c2[32], c3[32];
-#pragma unroll
-    for (int j = 0; j < K; ++j) tos[j] = 0.f;
-
-    // Dispatch on flag bits, unary forms first (the most frequent); the
-    // program's last instruction carries kFLast in the sign bit (no separate
-    // trip count).  The loop is bound by scalar instructions per dispatch,
-    // so the word is fetched with a 32-bit offset (one add per step) and
-    // range tests run on the vector unit.  Stack indices are masked to the
-    // 32-element chunk: the register index can never leave the chunk,
-    // whatever the staged word says.
-    uint32_t f;
-    uint32_t off = 0;                          // byte offset of the next word
-    do {
-        const uint2 w = *reinterpret_cast<const uint2*>(
-            reinterpret_cast<const char*>(pc) + off);
-        off += 8u;
-        f = w.x;
-        const uint32_t sel = (f >> 8) & 0xFu;
-        const uint32_t slot = (f >> (16u - kLogJ)) & 31u;
-        if (f & kFUn) {
-            if (f & kFPush) {
-                // f(leaf): the old top is saved first
-#pragma unroll
-                for (int j = 0; j < K; ++j) GP_CHUNK_PUT(slot, j, tos[j]);
-                GP_LEAF(f & kFConst, w.y, tos);
-            }
-        // unary: replaces the top
-        const uint32_t uop = GP_SIN + sel;
-        if (sel >= kUnSquare) {
-            ext_unary<K>(sel, tos);
-        } else {
-            switch (uop) {
-            case GP_SIN:
-                // the fast kernel when every case of the wavefront has
-                // |x| <= 2^17; otherwise per case, the library function
-                // (with its large-argument reduction) beyond the fast range
-                if (__builtin_expect(wave_any_above<K>(tos, kTrigFastLimit), 0)) {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = sin_value(tos[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = sin_fast(tos[j]);
-                }
-                break;
-            case GP_COS:
-                if (__builtin_expect(wave_any_above<K>(tos, kTrigFastLimit), 0)) {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = cos_value(tos[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = cos_fast(tos[j]);
-                }
-                break;
-            case GP_EXP:
-                // same split as sin/cos, at |x| <= 87 (per case values equal
-                // exp_value's either way)
-                if (__builtin_expect(wave_any_above<K>(tos, kExpFastLimit), 0)) {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = exp_value(tos[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = exp_fast(tos[j]);
-                }
-                break;
-            case GP_LOG:
-#pragma unroll
-                for (int j = 0; j < K; ++j) tos[j] = log_protected(tos[j]);
-                break;
-            case GP_SQRT: {
-                // the hardware root directly unless some case of the
-                // wavefront is below the scaling threshold (or NaN);
-                // sqrt_abs gives the same value for the others
-                float mn = fabsf(tos[0]);
-#pragma unroll
-                for (int j = 1; j < K; ++j) mn = __builtin_fminf(mn, fabsf(tos[j]));
-                if (__builtin_expect(__ballot(!(mn >= kSqrtTiny)) != 0ull, 0)) {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = sqrt_value(tos[j]);
-                } else {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) tos[j] = __builtin_amdgcn_sqrtf(fabsf(tos[j]));
-                }
-                break;
-            }
-            default:
-#pragma unroll
-                for (int j = 0; j < K; ++j) tos[j] = fabsf(tos[j]);
-                break;
-            }
-            }
-        } else if (f & kFSBin) {
-            // a = second from top (stack slot `slot`), b = top
-            float sv[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j) sv[j] = GP_CHUNK_GET(slot, j);
-            if (sel == kBinPow) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) tos[j] = pow_value(sv[j], tos[j]);
-            } else {
-                GP_BINARY(GP_ADD + sel, sv, tos);
-            }
-        } else if (f & kFLBin) {
-            // top OP leaf; a constant leaf gets its own copy of the op
-            // switch so the constant stays a scalar operand instead of
-            // being broadcast into registers first
-            if (sel == kBinPow) {
-                float lv[K];
-                GP_LEAF(f & kFConst, w.y, lv);
-#pragma unroll
-                for (int j = 0; j < K; ++j) tos[j] = pow_value(tos[j], lv[j]);
-            } else if (f & kFConst) {
-                float cv[K];
-#pragma unroll
-                for (int j = 0; j < K; ++j) cv[j] = __uint_as_float(w.y);
-                GP_BINARY_AB(GP_ADD + sel, tos, cv, tos);
-            } else {
-                float lv[K];
-                GP_LEAF(false, w.y, lv);
-                GP_BINARY_AB(GP_ADD + sel, tos, lv, tos);
-            }
-        } else if (f & kFMove) {
-            // cell move; every cell number is scaled by J and masked to a
-            // multiple of J inside the chunk
-            constexpr uint32_t kCellMask = 32u - J;
-            const uint32_t rs = slot & kCellMask;
-            const uint32_t ws = (w.y << kLogJ) & kCellMask;
-            float tv[K];
-#pragma unroll
-            for (int j = 0; j < K; ++j) tv[j] = tos[j];
-            if (sel & kMvRead) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) tv[j] = GP_CHUNK_GET(rs, j);
-            }
-            if (sel & kMvWrite) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) GP_CHUNK_PUT(ws, j, tos[j]);
-            }
-            if (sel & kMvTop) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) tos[j] = tv[j];
-            }
-            if (sel & kMvCompact) {
-                const uint32_t cs = ((w.y >> 8) << kLogJ) & kCellMask;
-                const uint32_t cd = ((w.y >> 16) << kLogJ) & kCellMask;
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    const float v = GP_CHUNK_GET(cs, j);
-                    GP_CHUNK_PUT(cd, j, v);
-                }
-            }
-        } else {
-            // the old top moves into the stack (slot MAXD-1 never holds a
-            // live element, so a push onto an empty stack writes there),
-            // the leaf becomes the top
-#pragma unroll
-            for (int j = 0; j < K; ++j) GP_CHUNK_PUT(slot, j, tos[j]);
-            GP_LEAF(f & kFConst, w.y, tos);
-        }
-    } while ((int32_t)f >= 0);             // until kFLast (the sign bit)
-}
-
 // ------------------------------------------------- threaded interpreter
 // The constants its handlers read from vector registers v22..v25, made once
 // per kernel: opaque to the optimizer, which would otherwise rebuild them at
@@ -1939,10 +1274,11 @@ __device__ __forceinline__ ThreadConsts thread_consts()
 }
 
 // Runs one program staged as threaded words (threaded.h) on K cases per
-// lane; `xl` is this lane's first case of the LDS input tile, the result is
-// the stack's one element.  Handlers that meet a value outside their fast
-// range return with a code; the out-of-line function is applied here, per
-// case, and the run resumes.
+// lane; `xl` is this lane's first case of the staged inputs, whose rows are
+// `scale` * 256 cases long; the result is the stack's one element.  Handlers
+// that meet a value outside their fast range, and the library commands,
+// return with a code; the out-of-line function is applied here, per case,
+// and the run resumes.
 typedef float f32x32 __attribute__((ext_vector_type(32)));
 
 #define GP_THREAD_TABLE(table)                                                             \
@@ -1963,83 +1299,77 @@ typedef float f32x32 __attribute__((ext_vector_type(32)));
     "s_add_u32 s92, s90, s87\n"                                                           \
     "s_addc_u32 s93, s91, 0\n"                                                            \
     "s_swappc_b64 s[94:95], s[92:93]\n"
-#define GP_THREAD_INPUTS                                                                  \
-    "{s[84:85]}"(pc), "{v31}"(lane_addr), "{v22}"(tc.inv_pi), "{v23}"(tc.sin_c3),          \
-        "{v24}"(tc.log2e_hi), "{v25}"(tc.theta)
-#define GP_THREAD_CLOBBERS                                                                \
-    "s68", "s69", "s70", "s71", "s72", "s73", "s74", "s75", "s90", "s91", "s92", "s93",   \
-        "s94", "s95", "s96", "s97", "v8", "v9", "v10", "v11", "v12", "v13", "v14", "v15", \
-        "v16", "v17", "v18", "v19", "vcc", "scc", "memory"
+#define GP_THREAD_ASM(kind, table, io)                                                     \
+    asm volatile(GP_THREAD_##kind(table)                                                   \
+                 : "+{v[36:67]}"(cells), io "{v4}"(t[0]), io "{v5}"(t[1]), io "{v6}"(t[2]),    \
+                   io "{v7}"(t[3]), "={v12}"(u[0]), "={v13}"(u[1]), "={v14}"(u[2]),         \
+                   "={v15}"(u[3]), io "{s[88:89]}"(w), io "{s86}"(off), io "{s87}"(resume), \
+                   "={s83}"(rc)                                                            \
+                 : "{s[84:85]}"(pc), "{s82}"(scale), "{v31}"(lane_addr),                   \
+                   "{v22}"(tc.inv_pi), "{v23}"(tc.sin_c3), "{v24}"(tc.log2e_hi),           \
+                   "{v25}"(tc.theta)                                                       \
+                 : "v8", "v9", "v10", "v11", "v16", "v17", "v18", "s68", "s69", "s70",     \
+                   "s71", "s72", "s73", "s74", "s75", "s90", "s91", "s92", "s93", "s94",   \
+                   "s95", "s96", "s97", "s98", "vcc", "scc", "memory")
+
+// The function a result code asks for, on the K values v (u: the exponents).
+template <int K>
+__device__ __forceinline__ void threaded_call(uint32_t rc, float (&v)[4], const float (&u)[4])
+{
+#define GP_CALL(code, expr)                                                                \
+    case code:                                                                             \
+        _Pragma("unroll") for (int j = 0; j < K; ++j) v[j] = expr;                         \
+        break;
+    switch (rc) {
+        GP_CALL(kCallSin, sin_value(v[j]))
+        GP_CALL(kCallCos, cos_value(v[j]))
+        GP_CALL(kCallExp, exp_value(v[j]))
+        GP_CALL(kCallSqrt, sqrt_value(v[j]))
+        GP_CALL(kCallCbrt, cbrt_value(v[j]))
+        GP_CALL(kCallTan, tan_value(v[j]))
+        GP_CALL(kCallAsin, asin_value(v[j]))
+        GP_CALL(kCallAcos, acos_value(v[j]))
+        GP_CALL(kCallAtan, atan_value(v[j]))
+        GP_CALL(kCallTanh, tanh_value(v[j]))
+        GP_CALL(kCallSqrtRaw, sqrt_raw_value(v[j]))
+    default:
+        _Pragma("unroll") for (int j = 0; j < K; ++j) v[j] = pow_value(v[j], u[j]);
+        break;
+    }
+#undef GP_CALL
+}
 
 template <int MAXD, int K>
-__device__ __forceinline__ void run_threaded(const uint2* code, const float* xl,
+__device__ __forceinline__ void run_threaded(const uint2* code, const float* xl, uint32_t scale,
                                              const ThreadConsts& tc, float (&tos)[K])
 {
-    static_assert((MAXD == 8 && K == 4) || (MAXD == 16 && K == 4) || (MAXD == 32 && K == 2),
+    static_assert((MAXD == 8 && K == 4) || (MAXD == 16 && K == 2) || (MAXD == 32 && K == 1),
                   "the tables of interp_gfx950.h");
     const uint64_t pa = (uint64_t)(uintptr_t)code;
     const uint64_t pc = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(pa >> 32)) << 32 |
                         (uint32_t)__builtin_amdgcn_readfirstlane((int)pa);
     const uint32_t lane_addr =
         (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)xl;
-    f32x32 lo, hi;                             // the stack cells (hi unused at depth 8)
-    float t0, t1, t2, t3;
+    f32x32 cells;                              // the stack
+    float t[4], u[4];
     uint64_t w;
     uint32_t off, resume, rc;
-    if constexpr (MAXD == 8)
-        asm volatile(GP_THREAD_ENTER("gp_threads_d8") : "+{v[36:67]}"(lo),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
-                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
-    else if constexpr (MAXD == 16)
-        asm volatile(GP_THREAD_ENTER("gp_threads_d16") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
-                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
-    else
-        asm volatile(GP_THREAD_ENTER("gp_threads_d32") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "={s[88:89]}"(w),
-                     "={s86}"(off), "={s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+    if constexpr (MAXD == 8) GP_THREAD_ASM(ENTER, "gp_threads_d8", "=");
+    else if constexpr (MAXD == 16) GP_THREAD_ASM(ENTER, "gp_threads_d16", "=");
+    else GP_THREAD_ASM(ENTER, "gp_threads_d32", "=");
     while (__builtin_expect(rc != 0u, 0)) {
-        float v[4] = {t0, t1, t2, t3};
-        if (rc == 1u) {
-#pragma unroll
-            for (int j = 0; j < K; ++j) v[j] = sin_value(v[j]);
-        } else if (rc == 2u) {
-#pragma unroll
-            for (int j = 0; j < K; ++j) v[j] = cos_value(v[j]);
-        } else if (rc == 3u) {
-#pragma unroll
-            for (int j = 0; j < K; ++j) v[j] = exp_value(v[j]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < K; ++j) v[j] = sqrt_value(v[j]);
-        }
-        t0 = v[0]; t1 = v[1]; t2 = v[2]; t3 = v[3];
+        threaded_call<K>(rc, t, u);
         // (uniform; said again where the loop made them look otherwise)
         w = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(w >> 32)) << 32 |
             (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
         off = (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
         resume = (uint32_t)__builtin_amdgcn_readfirstlane((int)resume);
-        if constexpr (MAXD == 8)
-            asm volatile(GP_THREAD_RESUME("gp_threads_d8") : "+{v[36:67]}"(lo),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
-                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
-        else if constexpr (MAXD == 16)
-            asm volatile(GP_THREAD_RESUME("gp_threads_d16") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
-                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
-        else
-            asm volatile(GP_THREAD_RESUME("gp_threads_d32") : "+{v[36:67]}"(lo), "+{v[68:99]}"(hi),
-                     "+{v4}"(t0), "+{v5}"(t1), "+{v6}"(t2), "+{v7}"(t3), "+{s[88:89]}"(w),
-                     "+{s86}"(off), "+{s87}"(resume), "={s83}"(rc)
-                     : GP_THREAD_INPUTS : GP_THREAD_CLOBBERS);
+        if constexpr (MAXD == 8) GP_THREAD_ASM(RESUME, "gp_threads_d8", "+");
+        else if constexpr (MAXD == 16) GP_THREAD_ASM(RESUME, "gp_threads_d16", "+");
+        else GP_THREAD_ASM(RESUME, "gp_threads_d32", "+");
     }
 #pragma unroll
-    for (int j = 0; j < K; ++j) tos[j] = lo[j];
+    for (int j = 0; j < K; ++j) tos[j] = cells[j];
 }
 
 // ------------------------------------------------- correlation fitness
@@ -2063,7 +1393,7 @@ struct CorrLane {
     int32_t n, c1, c2;
 };
 
-enum : int { kFitMse = 0, kFitCorr = 1, kFitReward = 2 };
+enum : int { kFitMse = 0, kFitCorr = 1, kFitReward = 2, kFitPredict = 3 };
 constexpr int kCorrMaxG = 32;            // programs per work item in correlation mode (LDS)
 
 __device__ __forceinline__ void corr_zero(CorrPart& c)
@@ -2159,337 +1489,497 @@ __device__ __forceinline__ void corr_wave_reduce(CorrLane& c)
     }
 }
 
-template <int MAXD, int K, int FIT, bool EXT>
-__global__ __launch_bounds__(kWG, !EXT && FIT == kFitMse ? (MAXD == 8 ? 6 : 4) : 1) void k_eval(
-    const uint2* __restrict__ code, const ProgMeta* __restrict__ meta,
-    const int32_t* __restrict__ order, const int32_t* __restrict__ class_info,
-    uint32_t* __restrict__ work_counter, const DevDataset* __restrict__ ds,
-    const int32_t* __restrict__ seg_ds, const int32_t* __restrict__ seg_cnt,
-    const int32_t* __restrict__ seg_pos, const uint32_t* __restrict__ item_pre,
-    const int32_t* __restrict__ class_g, float2* __restrict__ part, uint8_t* __restrict__ part_bad,
-    CorrPart* __restrict__ part_corr, EvalConst a)
+// ------------------------------------------------------------------ k_run
+// Arguments of the evaluation kernel.
+struct RunArgs {
+    const uint2* code;
+    const ProgMeta* meta;
+    const int32_t* order;
+    const int32_t* class_info;
+    uint32_t* work_counter;
+    const DevDataset* ds;
+    const int32_t* seg_ds;
+    const int32_t* seg_cnt;
+    const int32_t* seg_pos;
+    const uint32_t* item_pre;
+    const int32_t* class_g;
+    float2* part;
+    uint8_t* part_bad;
+    CorrPart* part_corr;    // the same memory as part, correlation mode
+    float* out;             // gp_predict: per-case outputs
+    int64_t ld_out;
+    int32_t part_stride;    // partial of (program p, tile t) at t * part_stride + p
+    int32_t n_seg;
+    int32_t lds_floats;     // staged inputs and targets, at most
+    int32_t reward_power;
+    float reward_M;
+};
+
+// One workgroup's item as its wavefronts see it (uniform).
+struct Item {
+    int64_t first;          // first case staged
+    int32_t cases;          // cases staged (the last sub-tile may be partial)
+    int32_t stride;         // cases per row of the staged memory (multiple of 256)
+    int32_t n_vars;
+    int32_t window;         // cases summed before each wavefront tree
+    int32_t tile_cases;     // cases per partial; 0: the tile goes on past this piece
+    int32_t tile;           // first tile
+    int32_t obase, count;   // programs: order[obase .. obase + count)
+    int32_t ynf;            // some staged target is NaN or infinite
+    float scale;
+};
+
+// What a wavefront accumulates for one program.
+template <int FIT> struct Sums;
+template <> struct Sums<kFitMse> {
+    float hi, lo;           // this lane's Kahan pair of the window
+    float H, L;             // the tile's windows, added in order
+    bool bad, tile_bad;
+};
+template <> struct Sums<kFitCorr> {
+    CorrLane cl;
+    double cs, ct;          // the window's shift
+    bool have_shift;
+};
+template <> struct Sums<kFitReward> {
+    long long rl;
+};
+template <> struct Sums<kFitPredict> {};
+
+// NJ cases per lane from case `pos` of the staged piece: the fitness
+// epilogue (MSE: scaled square with Kahan accumulation; correlation: shifted
+// fp64 sums over valid pairs; integer reward: int64 per case), or the
+// outputs themselves.
+template <int FIT, int NJ>
+__device__ __forceinline__ void add_cases(const float (&f)[NJ], const float* yt, int left, int lane,
+                                          const RunArgs& a, const Item& it, Sums<FIT>& s, float* out)
 {
-    static_assert(K == 2 || K == 4 || K == 8, "cases per lane");
-    static_assert(MAXD == 8 || MAXD == 16 || MAXD == 32, "stack class");
-    constexpr int J = 32 / MAXD;                  // cases per 32-float chunk
-    static_assert(K % J == 0 && K / J <= 4, "chunking");
-    constexpr int SUB = 64 * K;                   // cases per sub-tile
-    extern __shared__ float lds[];
-    float* xt = lds;                              // window: [W][n_vars + 1][SUB]
-    float2* acc = reinterpret_cast<float2*>(lds + a.tile_floats);            // [G]
-    uint32_t* accbad = reinterpret_cast<uint32_t*>(acc + a.G);               // [G]
-    // correlation mode: one CorrPart per program instead (the tile floats are
-    // a multiple of 2, so the array is 8-byte aligned)
-    CorrPart* cacc = reinterpret_cast<CorrPart*>(lds + a.tile_floats);       // [G]
-    // integer reward mode: one int64 total per program
-    long long* racc = reinterpret_cast<long long*>(lds + a.tile_floats);     // [G]
-    __shared__ uint32_t s_item, s_next;
-    // With the classes overlapped, a deeper class's workgroups run beside
-    // the depth <= 8 class's; their wavefronts issue first there, so the
-    // deeper classes, which end last, finish sooner (alone, all wavefronts
-    // of a kernel share one priority and nothing changes).
-    if constexpr (MAXD >= 16) __builtin_amdgcn_s_setprio(1);
-    ThreadConsts tc;
-    if constexpr (!EXT) tc = thread_consts();
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int c = a.cls;
-    const int G = as_const(class_g)[c];           // <= a.G, the accumulators' capacity
-    const int cstart = as_const(class_info)[2 * c];
-    const const_ptr<int32_t> cnt_c = as_const(seg_cnt) + c * a.n_seg;
-    const const_ptr<int32_t> pos_c = as_const(seg_pos) + c * a.n_seg;
-    const const_ptr<uint32_t> pre_c = as_const(item_pre) + c * (a.n_seg + 1);
-    const const_ptr<int32_t> ord = as_const(order);
-    const uint32_t n_items = pre_c[a.n_seg];
-    int staged_d = -1;                            // dataset and first sub-tile in LDS
-    int64_t staged = -1;
-    int ynf = 0;                                  // the staged window holds a NaN/inf target
-
-    for (;;) {
-        if (tid == 0) s_item = atomicAdd(work_counter, 1u);
-        if (tid < G) {
-            if constexpr (FIT == kFitCorr) {
-                corr_zero(cacc[tid]);
-            } else if constexpr (FIT == kFitReward) {
-                racc[tid] = 0;
-            } else {
-                acc[tid] = make_float2(0.f, 0.f);
-                accbad[tid] = 0u;
+    if constexpr (FIT == kFitPredict) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (lane + j * 64 < left) out[lane + j * 64] = f[j];
+    } else if constexpr (FIT == kFitMse) {
+        // a whole sub-tile in range with finite targets: no per-case tests
+        // (wave-uniform branches)
+        if (left >= NJ * 64 && !it.ynf) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                mse_case<false>(f[j], yt[lane + j * 64], it.scale, s.hi, s.lo, s.bad);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (lane + j * 64 < left)
+                    mse_case<true>(f[j], yt[lane + j * 64], it.scale, s.hi, s.lo, s.bad);
+        }
+    } else if constexpr (FIT == kFitCorr) {
+        // the shift: the window's first valid pair, in the order (sub-tile,
+        // case, lane)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            if (!s.have_shift) {
+                const float yj = yt[lane + j * 64];
+                const bool v = lane + j * 64 < left && __builtin_isfinite(f[j]) && __builtin_isfinite(yj);
+                const unsigned long long mk = __ballot(v);
+                if (mk != 0ull) {
+                    const int src = __builtin_ctzll(mk);
+                    s.cs = (double)lane_value(f[j], src);
+                    s.ct = (double)lane_value(yj, src);
+                    s.have_shift = true;
+                }
             }
         }
-        __syncthreads();
-        const uint32_t item = __builtin_amdgcn_readfirstlane(s_item);
-        if (item >= n_items) break;
-        // segment of this item: last s with pre_c[s] <= item
-        int sl = 0, sh = a.n_seg - 1;
-        while (sl < sh) {
-            const int mid = (sl + sh + 1) >> 1;
-            if (pre_c[mid] <= item) sl = mid; else sh = mid - 1;
-        }
-        const int d = as_const(seg_ds)[sl];
-        // fields one by one: a struct copy indexed by the class would live
-        // in scratch memory
-        const const_ptr<DevDataset> Dp = as_const(ds) + d;
-        const float* __restrict__ Xd = Dp->X;
-        const float* __restrict__ yd = Dp->y;
-        const int64_t ld_x = Dp->ld_x;
-        const int64_t n_cases = Dp->n_cases;
-        const int n_vars = Dp->n_vars;
-        const float scale = Dp->scale;
-        const int passes = Dp->passes[c];
-        const int window = Dp->window[c];
-        const int count = cnt_c[sl];
-        const int n_groups = (count + G - 1) / G;
-        // item order inside a segment: tile-major (tile t of every group,
-        // then tile t + 1), or, for the depth <= 8 class when the classes
-        // run one after another, group-major (a group's case tiles are
-        // consecutive items, so workgroups running at the same time read
-        // the group's instruction words while they are in the cache).  The
-        // order changes no result.
-        const uint32_t local = item - pre_c[sl];
-        const uint32_t n_tiles = (uint32_t)Dp->n_tiles[c];
-        const bool gm = MAXD == 8 && a.group_major != 0;
-        const int tile = gm ? (int)(local % n_tiles) : (int)(local / (uint32_t)n_groups);
-        const int grp = gm ? (int)(local / n_tiles) : (int)(local % (uint32_t)n_groups);
-        const int g0 = grp * G;
-        const int gn = min(G, count - g0);
-        const int obase = cstart + pos_c[sl] + g0;
-        const int64_t n_sub = (n_cases + SUB - 1) / SUB;
-        const int rows = n_vars + 1;              // inputs, then the targets
-
-        for (int w0 = 0; w0 < passes; w0 += window) {
-            const int64_t first = (int64_t)tile * passes + w0;      // first sub-tile
-            if (first >= n_sub) break;
-            const int nw = (int)min((int64_t)min(window, passes - w0), n_sub - first);
-            if (first != staged || d != staged_d) {
-                // lane t's case j of a sub-tile is element j*64 + t of a
-                // row: conflict-free, lane-contiguous reads.  MSE mode
-                // stores the targets pre-scaled (an exact power of two).
-                int nf = 0;
-                for (int i = tid; i < nw * rows * SUB; i += kWG) {
-                    const int blk = i / (rows * SUB);
-                    const int r = i - blk * rows * SUB;
-                    const int v = r / SUB, cc = r - v * SUB;
-                    const int64_t gi = (first + blk) * SUB + cc;
-                    float val = 0.f;
-                    if (gi < n_cases) {
-                        if (v < n_vars) {
-                            val = Xd[(int64_t)v * ld_x + gi];
-                        } else {
-                            val = FIT == kFitMse ? yd[gi] * scale : yd[gi];
-                            nf |= !__builtin_isfinite(val);
-                        }
-                    }
-                    xt[i] = val;
-                }
-                // (block-uniform branch: every thread reaches the barrier)
-                ynf = __syncthreads_or(nf);
-                staged = first;
-                staged_d = d;
-            }
-            if (tid == 0) s_next = 0u;
-            __syncthreads();
-            // each wavefront takes the group's programs one at a time and
-            // runs each over the whole window.  The loop has no lane-0-only
-            // region at its head or tail: every lane adds one to the claim
-            // counter (a wavefront's 64 claims are one block of 64, so the
-            // block index is the program), and every lane writes the same
-            // accumulator value after the wavefront tree.  A lane-0-only
-            // claim followed by a lane-0-only update lets the optimizer rotate
-            // the two into one region that lane 0 alone runs between
-            // iterations, so the other lanes would re-read a stale claim.
-            for (;;) {
-                const int g = (int)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_next, 1u)) >> 6);
-                if (g >= gn) break;
-                const uint2* pc = code + as_const(meta)[ord[obase + g]].start;
-                // fused residual, validity and scaled compensated square sum
-                // (MSE), or the sums of the correlation fitness
-                float hi = 0.f, lo_ = 0.f;
-                bool bad = false;
-                CorrLane cl;
-                if constexpr (FIT == kFitCorr) corr_zero(cl);
-                double cs = 0.0, ct = 0.0;                // the wavefront's shift
-                bool have_shift = false;
-                long long rl = 0;
-                for (int b = 0; b < nw; ++b) {
-                    const float* blk = xt + b * rows * SUB;
-                    float tos[K];
-                    if constexpr (EXT)
-                        run_program<MAXD, K>(pc, blk + lane, tos);
-                    else
-                        run_threaded<MAXD, K>(pc, blk + lane, tc, tos);
-                    const int64_t base = (first + b) * SUB;
-                    const float* yt = blk + n_vars * SUB;
-                    if constexpr (FIT == kFitCorr) {
-                        // the shift: the window's first valid pair, in the
-                        // order (sub-tile, j, lane)
 #pragma unroll
-                        for (int j = 0; j < K; ++j) {
-                            if (!have_shift) {
-                                const float yj = yt[lane + j * 64];
-                                const bool v = base + lane + j * 64 < n_cases &&
-                                               __builtin_isfinite(tos[j]) && __builtin_isfinite(yj);
-                                const unsigned long long mk = __ballot(v);
-                                if (mk != 0ull) {
-                                    const int src = __builtin_ctzll(mk);
-                                    cs = (double)__int_as_float(__builtin_amdgcn_readlane(
-                                        __float_as_int(tos[j]), src));
-                                    ct = (double)__int_as_float(__builtin_amdgcn_readlane(
-                                        __float_as_int(yj), src));
-                                    have_shift = true;
-                                }
-                            }
-                        }
-                    }
-                    if constexpr (FIT == kFitMse) {
-                        // a whole sub-tile in range with finite targets: no
-                        // per-case tests (wave-uniform branches)
-                        if (base + SUB <= n_cases && !ynf) {
+        for (int j = 0; j < NJ; ++j)
+            if (lane + j * 64 < left) corr_case(s.cl, f[j], yt[lane + j * 64], s.cs, s.ct);
+    } else {
 #pragma unroll
-                            for (int j = 0; j < K; ++j)
-                                mse_case<false>(tos[j], yt[lane + j * 64], scale, hi, lo_, bad);
-                        } else {
-#pragma unroll
-                            for (int j = 0; j < K; ++j)
-                                if (base + lane + j * 64 < n_cases)
-                                    mse_case<true>(tos[j], yt[lane + j * 64], scale, hi, lo_,
-                                                   bad);
-                        }
-                    } else {
-#pragma unroll
-                    for (int j = 0; j < K; ++j) {
-                        if (base + lane + j * 64 < n_cases) {
-                            const float f = tos[j];
-                            if constexpr (FIT == kFitCorr) {
-                                corr_case(cl, f, yt[lane + j * 64], cs, ct);
-                            } else {
-                                rl += pair_reward(f, yt[lane + j * 64], a.reward_M,
-                                                  a.reward_power);
-                            }
-                        }
-                    }
-                    }
-                }
-                if constexpr (FIT == kFitCorr) {
-                    corr_wave_reduce(cl);
-                    // the windows add up in order, whichever wavefront ran
-                    // them (every lane holds the same sums and writes the
-                    // same merged value)
-                    {
-                        CorrPart w;
-                        w.s = cs; w.t = ct;
-                        w.sd = cl.sd; w.sdd = cl.sdd; w.se = cl.se; w.see = cl.see;
-                        w.sde = cl.sde;
-                        w.n = cl.n; w.c1 = cl.c1; w.c2 = cl.c2;
-                        corr_merge(cacc[g], w);
-                    }
-                } else if constexpr (FIT == kFitReward) {
-                    // integers: exact in any order (every lane holds the
-                    // same total and writes the same sum)
-#pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) rl += __shfl_xor(rl, off);
-                    racc[g] += rl;
-                } else {
-                // wavefront tree: every lane ends with the same pair
-#pragma unroll
-                for (int off = 32; off >= 1; off >>= 1) {
-                    const float h2 = __shfl_xor(hi, off);
-                    const float l2 = __shfl_xor(lo_, off);
-                    acc_pair(hi, lo_, h2, l2);
-                }
-                const bool wave_bad = __ballot(bad) != 0ull;
-                // one wavefront per program and window: the windows add up
-                // in order, whichever wavefront ran them (every lane writes
-                // the same pair)
-                {
-                    float h = acc[g].x, l = acc[g].y;
-                    acc_pair(h, l, hi, lo_);
-                    acc[g] = make_float2(h, l);
-                    if (wave_bad) accbad[g] = 1u;
-                }
-                }
-            }
-            __syncthreads();
-        }
-        if (tid < gn) {
-            const int pid = order[obase + tid];
-            // tile-major partials: the reduction reads neighbours' together
-            const int64_t slot = (int64_t)tile * a.part_stride + pid;
-            if constexpr (FIT == kFitCorr) {
-                part_corr[slot] = cacc[tid];
-            } else if constexpr (FIT == kFitReward) {
-                reinterpret_cast<long long*>(part)[slot] = racc[tid];
-            } else {
-                part[slot] = acc[tid];
-                part_bad[slot] = (uint8_t)(accbad[tid] != 0u);
-            }
-        }
-        __syncthreads();
+        for (int j = 0; j < NJ; ++j)
+            if (lane + j * 64 < left)
+                s.rl += pair_reward(f[j], yt[lane + j * 64], a.reward_M, a.reward_power);
     }
 }
 
-// ------------------------------------------------------------ k_predict
-// Per-case outputs f_p(x_i) of the programs of one depth class: persistent
-// workgroups pull (group of four programs, sub-tile) items; each wavefront
-// runs one program of the group and each lane writes its K values.
-template <int MAXD, int K, bool EXT>
-__global__ __launch_bounds__(kWG) void k_predict(
-    const uint2* __restrict__ code, const ProgMeta* __restrict__ meta,
-    const int32_t* __restrict__ order, const int32_t* __restrict__ class_info,
-    uint32_t* __restrict__ work_counter, const float* __restrict__ X,
-    float* __restrict__ out, int64_t ld_out, EvalConst a)
+// Runs one program of depth class C over the staged piece; acc is its
+// running tile sum in LDS (correlation always; the others only when a tile
+// goes on past the piece).
+template <int FIT, int C>
+__device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float* xt, const RunArgs& a,
+                                          const Item& it, const ThreadConsts& tc, int lane, void* acc,
+                                          uint32_t* acc_bad)
 {
-    constexpr int SUB = 64 * K;
-    extern __shared__ float lds[];
-    float* xt = lds;                              // [n_vars][SUB]
-    __shared__ uint32_t s_item;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-    const int lane = tid & 63;
-    const int start = as_const(class_info)[2 * a.cls];
-    const int count = as_const(class_info)[2 * a.cls + 1];
-    const int n_groups = (count + kWaves - 1) / kWaves;
-    const int64_t n_sub = (a.n_cases + SUB - 1) / SUB;
-    const uint64_t n_items = (uint64_t)n_groups * (uint64_t)n_sub;
-    int64_t staged = -1;
-    ThreadConsts tc;
-    if constexpr (!EXT) tc = thread_consts();
-    for (;;) {
-        if (tid == 0) s_item = atomicAdd(work_counter, 1u);
-        __syncthreads();
-        const uint64_t item = __builtin_amdgcn_readfirstlane(s_item);
-        if (item >= n_items) break;
-        const int64_t sub = (int64_t)(item / (uint64_t)n_groups);
-        const int grp = (int)(item % (uint64_t)n_groups);
-        const int64_t base = sub * SUB;
-        if (sub != staged) {
-            for (int i = tid; i < a.n_vars * SUB; i += kWG) {
-                const int v = i / SUB, c = i - v * SUB;
-                const int64_t gi = base + c;
-                xt[i] = gi < a.n_cases ? X[(int64_t)v * a.ld_x + gi] : 0.f;
-            }
-            staged = sub;
+    constexpr int SUB = sub_cases(C);
+    constexpr int NJ = SUB / 64;
+    const float* yt = xt + (int64_t)it.n_vars * it.stride;
+    Sums<FIT> s;
+    const bool goes_on = it.tile_cases == 0;
+    if constexpr (FIT == kFitMse) {
+        s.hi = s.lo = 0.f;
+        s.bad = s.tile_bad = false;
+        s.H = s.L = 0.f;
+        if (goes_on) {
+            const float2 v = *static_cast<const float2*>(acc);
+            s.H = v.x;
+            s.L = v.y;
+            s.tile_bad = *acc_bad != 0u;
         }
-        __syncthreads();
-        // wave-uniform (readfirstlane tells the compiler), so the
-        // interpreter below keeps its scalar branches
-        const int g = __builtin_amdgcn_readfirstlane(grp * kWaves + wave);
-        if (g < count) {
-            const int pid = as_const(order)[start + g];
-            const uint2* pc = code + as_const(meta)[pid].start;
-            float tos[K];
-            if constexpr (EXT)
-                run_program<MAXD, K>(pc, xt + lane, tos);
-            else
-                run_threaded<MAXD, K>(pc, xt + lane, tc, tos);
+    } else if constexpr (FIT == kFitCorr) {
+        corr_zero(s.cl);
+        s.cs = s.ct = 0.0;
+        s.have_shift = false;
+        if (!goes_on) corr_zero(*static_cast<CorrPart*>(acc));
+    } else if constexpr (FIT == kFitReward) {
+        s.rl = 0;
+    }
+    int wleft = it.window;
+    int tleft = goes_on ? INT_MAX : it.tile_cases;
+    int tile = it.tile;
+    float* out = nullptr;
+    if constexpr (FIT == kFitPredict) out = a.out + (int64_t)pid * a.ld_out + it.first;
+
+    // after `SUB` cases ending at case `end`: close the window and the tile
+    auto close = [&](int end) {
+        if constexpr (FIT == kFitPredict) return;
+        wleft -= SUB;
+        tleft -= SUB;
+        const bool stop = end >= it.cases;
+        const bool tile_end = tleft == 0 || (stop && !goes_on);
+        if (wleft == 0 || tile_end || stop) {
+            wleft = it.window;
+            if constexpr (FIT == kFitMse) {
+                // wavefront tree: every lane ends with the same pair
 #pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const int64_t gi = base + lane + j * 64;
-                if (gi < a.n_cases) out[(int64_t)pid * ld_out + gi] = tos[j];
+                for (int off = 32; off >= 1; off >>= 1) {
+                    const float h2 = __shfl_xor(s.hi, off);
+                    const float l2 = __shfl_xor(s.lo, off);
+                    acc_pair(s.hi, s.lo, h2, l2);
+                }
+                s.tile_bad = s.tile_bad || __ballot(s.bad) != 0ull;
+                acc_pair(s.H, s.L, s.hi, s.lo);
+                s.hi = s.lo = 0.f;
+                s.bad = false;
+            } else if constexpr (FIT == kFitCorr) {
+                corr_wave_reduce(s.cl);
+                // (every lane holds the same sums and writes the same value)
+                CorrPart w;
+                w.s = s.cs; w.t = s.ct;
+                w.sd = s.cl.sd; w.sdd = s.cl.sdd; w.se = s.cl.se; w.see = s.cl.see;
+                w.sde = s.cl.sde;
+                w.n = s.cl.n; w.c1 = s.cl.c1; w.c2 = s.cl.c2;
+                corr_merge(*static_cast<CorrPart*>(acc), w);
+                corr_zero(s.cl);
+                s.cs = s.ct = 0.0;
+                s.have_shift = false;
             }
         }
-        __syncthreads();
+        if (tile_end) {
+            const int64_t slot = (int64_t)tile * a.part_stride + pid;
+            if constexpr (FIT == kFitMse) {
+                if (lane == 0) {
+                    a.part[slot] = make_float2(s.H, s.L);
+                    a.part_bad[slot] = (uint8_t)s.tile_bad;
+                }
+                s.H = s.L = 0.f;
+                s.tile_bad = false;
+            } else if constexpr (FIT == kFitCorr) {
+                if (lane == 0) a.part_corr[slot] = *static_cast<const CorrPart*>(acc);
+                corr_zero(*static_cast<CorrPart*>(acc));
+            } else if constexpr (FIT == kFitReward) {
+                // integers: exact in any order
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) s.rl += __shfl_xor(s.rl, off);
+                if (lane == 0) reinterpret_cast<long long*>(a.part)[slot] = s.rl;
+                s.rl = 0;
+            }
+            ++tile;
+            tleft = it.tile_cases;
+            wleft = it.window;
+        }
+    };
+
+    for (int pos = 0; pos < it.cases;) {
+        const float* xl = xt + pos + lane;
+        float f[NJ];
+        constexpr int K = C == 0 ? 4 : (C == 1 ? 2 : 1);
+#pragma unroll
+        for (int h = 0; h < NJ; h += K) {
+            float v[K];
+            run_threaded<C == 0 ? 8 : (C == 1 ? 16 : 32), K>(pc, xl + h * 64, it.stride >> 8, tc, v);
+#pragma unroll
+            for (int j = 0; j < K; ++j) f[h + j] = v[j];
+        }
+        add_cases<FIT, NJ>(f, yt + pos, it.cases - pos, lane, a, it, s, out + pos);
+        close(pos + SUB);
+        pos += SUB;
+    }
+    if (goes_on) {
+        if constexpr (FIT == kFitMse) {
+            *static_cast<float2*>(acc) = make_float2(s.H, s.L);
+            *acc_bad = s.tile_bad ? 1u : 0u;
+        } else if constexpr (FIT == kFitReward) {
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) s.rl += __shfl_xor(s.rl, off);
+            *static_cast<long long*>(acc) += s.rl;
+        }
+    }
+}
+
+// Loads the first lines (64 bytes, 8 words) of a program's code into the
+// scalar cache together; met one by one they cost a wavefront a wait each.
+__device__ __forceinline__ void warm_code(const uint2* pc, int words)
+{
+    const const_ptr<uint2> code = as_const(pc);
+    const int top = words - 1;
+    uint32_t w[kWarmLines];
+#pragma unroll
+    for (int l = 0; l < kWarmLines; ++l) w[l] = code[min(8 * l, top)].x;
+#pragma unroll
+    for (int l = 0; l < kWarmLines; ++l) asm volatile("" ::"s"(w[l]));
+}
+
+// LDS bytes of a workgroup's running sums: one per program of a chunk (a tile
+// in pieces), or per wavefront.
+constexpr size_t acc_bytes(int fit)
+{
+    return fit == kFitCorr     ? (size_t)kCorrMaxG * sizeof(CorrPart)
+           : fit == kFitReward ? (size_t)kChunkMax * sizeof(long long)
+           : fit == kFitMse    ? (size_t)kChunkMax * (sizeof(float2) + sizeof(uint32_t))
+                               : 0;
+}
+
+// Lists programs order[obase .. obase + count) of a chunk (count <= G <= 64) in
+// LDS, by one wavefront: looked up one by one, a wavefront would wait for
+// three loads in turn before each.  The lanes left over touch the programs'
+// code, a cache line each, so it is in this XCD's L2.
+__device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int count, int G, int lane, uint4* list)
+{
+    const int per = 64 / G, g = lane / per, k = lane - g * per;
+    uint32_t touched = 0;
+    if (g < count) {
+        const int pid = a.order[obase + g];
+        const ProgMeta pm = a.meta[pid];
+        const uint64_t at = (uint64_t)(uintptr_t)(a.code + pm.start);
+        if (k == 0) list[g] = make_uint4((uint32_t)at, (uint32_t)(at >> 32), (uint32_t)pid, (uint32_t)pm.slen);
+        for (int l = k; l * 16 < pm.slen; l += per) touched ^= a.code[pm.start + l * 16].x;
+    }
+    return touched;     // (to be consumed where the wait for it does no harm)
+}
+
+// Evaluation of every depth class in one launch.  Persistent workgroups take
+// items (a chunk of programs of one class x a run of its case tiles) from a
+// counter, the deepest class first and inside a class the longest programs
+// first, so the launch ends on short ones.  The item's inputs and targets are
+// staged in LDS, and each wavefront takes programs one at a time and runs
+// each over all staged cases.  The wavefront that takes a chunk's first
+// program claims the workgroup's next item and, when that is over the same
+// cases, lists its programs behind the chunk's: wavefronts go on without
+// meeting, up to kListed programs between two barriers.  (Barriers after
+// every item left 44% of the wavefronts' time waiting; a class's kernel of its
+// own left the GPU to each tail in turn and cost 13 us when it was empty.)
+// Bound by vector issue (threaded.h): 80 registers hold 32 of stack, 16 of
+// temporaries and the epilogue's, for six wavefronts per SIMD; the
+// correlation and reward sums take more.
+template <int FIT>
+__global__ __launch_bounds__(kRunWG, FIT == kFitCorr || FIT == kFitReward ? 4 : 6) void k_run(RunArgs a)
+{
+    extern __shared__ float lds[];
+    float* xt = lds;                              // [n_vars + 1][stride]: inputs, then targets
+    char* accs = reinterpret_cast<char*>(lds + a.lds_floats);
+    __shared__ uint32_t s_next, s_end, s_pending; // programs taken and listed; the next item
+    __shared__ uint4 s_prog[kListed];             // listed programs: code, id, words
+    const ThreadConsts tc = thread_consts();
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const const_ptr<uint32_t> pre = as_const(a.item_pre);
+    const int ns = a.n_seg;
+    const uint32_t n2 = pre[2 * (ns + 1) + ns], n1 = pre[(ns + 1) + ns], n0 = pre[ns];
+    const uint32_t n_items = n2 + n1 + n0;
+    int staged_d = -1, staged_n = 0, ynf = 0;     // what the staged memory holds
+    int64_t staged = -1;
+
+    for (uint32_t item = blockIdx.x; item < n_items;) {
+        const int c = item < n2 ? 2 : (item < n2 + n1 ? 1 : 0);
+        const uint32_t c0 = c == 2 ? 0u : (c == 1 ? n2 : n2 + n1);
+        const uint32_t ci = item - c0;
+        // segment of this item: last s with pre_c[s] <= ci
+        const const_ptr<uint32_t> pre_c = pre + c * (ns + 1);
+        int sl = 0, sh = ns - 1;
+        while (sl < sh) {
+            const int mid = (sl + sh + 1) >> 1;
+            if (pre_c[mid] <= ci) sl = mid; else sh = mid - 1;
+        }
+        const int d = as_const(a.seg_ds)[sl];
+        const const_ptr<DevDataset> D = as_const(a.ds) + d;
+        const int G = as_const(a.class_g)[c], m_cap = as_const(a.class_g)[kClasses + c];
+        const int passes = D->passes[c], n_tiles = D->n_tiles[c], n_vars = D->n_vars;
+        const int sub = sub_cases(c);
+        const int64_t n_cases = D->n_cases;
+        const int m = item_tiles(passes, n_tiles, c, n_vars, a.lds_floats, m_cap);
+        const int count = as_const(a.seg_cnt)[c * ns + sl];
+        const uint32_t groups = (uint32_t)((count + G - 1) / G);
+        const uint32_t local = ci - pre_c[sl];
+        const int tg = (int)(local / groups), grp = (int)(local % groups);
+        // items of the same programs' segment, class and cases: [item0, item1)
+        const uint32_t item0 = item - (uint32_t)grp, item1 = item0 + groups;
+        const int seg0 = as_const(a.class_info)[2 * c] + as_const(a.seg_pos)[c * ns + sl];
+        Item it;
+        it.n_vars = n_vars;
+        it.scale = D->scale;
+        it.window = D->window[c] * sub;
+        it.tile = tg * m;
+        it.count = min(G, count - grp * G);
+        it.obase = seg0 + grp * G;
+        // the item's cases, and how many of them are staged at once
+        const int64_t tile_cases = (int64_t)passes * sub;
+        const int64_t first = tile_cases * it.tile;
+        const int64_t last = min(first + tile_cases * min(m, n_tiles - it.tile), n_cases);
+        const int64_t cap = staged_cases(a.lds_floats, n_vars);
+        const bool whole = tile_cases <= cap;
+        const int64_t step = whole ? last - first : max(cap / it.window, (int64_t)1) * it.window;
+        it.tile_cases = whole ? (int)tile_cases : 0;
+        if (!whole && FIT != kFitPredict) {
+            // running sums of the chunk's programs over the tile's pieces
+            for (int g = tid; g < it.count; g += kRunWG) {
+                if constexpr (FIT == kFitCorr) corr_zero(reinterpret_cast<CorrPart*>(accs)[g]);
+                else if constexpr (FIT == kFitReward) reinterpret_cast<long long*>(accs)[g] = 0;
+                else {
+                    reinterpret_cast<float2*>(accs)[g] = make_float2(0.f, 0.f);
+                    reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax)[g] = 0u;
+                }
+            }
+        }
+        uint32_t touched = 0;
+        if (wave == kRunWaves - 1) touched = list_chunk(a, it.obase, it.count, G, lane, s_prog);
+        for (int64_t f0 = first; f0 < last; f0 += step) {
+            it.first = f0;
+            it.cases = (int)min(step, last - f0);
+            it.stride = (it.cases + 255) & ~255;
+            if (tid == 0) {
+                s_next = 0u;
+                s_end = (uint32_t)it.count;
+            }
+            if (f0 != staged || d != staged_d || it.cases != staged_n) {
+                // one wavefront per 256 cases of a row; MSE mode stores the
+                // targets pre-scaled (an exact power of two)
+                const float* __restrict__ X = D->X;
+                const float* __restrict__ y = D->y;
+                const int64_t ld_x = D->ld_x;
+                const int nb = it.stride >> 8, units = (n_vars + 1) * nb;
+                int nf = 0;
+                for (int u = wave; u < units; u += kRunWaves) {
+                    const int v = u / nb, b = u - v * nb;
+                    const bool target = v == n_vars;
+                    const float* __restrict__ src = (target ? y : X + (int64_t)v * ld_x) + f0 + b * 256;
+                    const int left = it.cases - b * 256;
+                    float val[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) val[j] = lane + j * 64 < left ? src[lane + j * 64] : 0.f;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (target) {
+                            if (FIT == kFitMse) val[j] *= it.scale;
+                            nf |= !__builtin_isfinite(val[j]);
+                        }
+                        xt[u * 256 + lane + j * 64] = val[j];
+                    }
+                }
+                // (block-uniform branch: every thread reaches the barrier)
+                ynf = __syncthreads_or(nf);
+                staged = f0;
+                staged_d = d;
+                staged_n = it.cases;
+            } else {
+                __syncthreads();
+            }
+            asm volatile("" ::"v"(touched));
+            it.ynf = ynf;
+            // The claim has no lane-0-only region: every lane adds one to the
+            // counter (a wavefront's 64 claims are one block of 64, so the
+            // block index is the program).  A lane-0-only claim followed by a
+            // lane-0-only update lets the optimizer rotate the two into one
+            // region that lane 0 alone runs between iterations, so the other
+            // lanes would re-read a stale claim.
+            auto claim = [&] { return (int)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_next, 1u)) >> 6); };
+            auto listed = [&] {
+                return (int)__builtin_amdgcn_readfirstlane(
+                    __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+            };
+            auto run = [&](int g, bool more) {
+                if (f0 == first && g % G == 0) {
+                    // the chunk's first program: the workgroup's next item
+                    uint32_t next = n_items;
+                    if (n_items > gridDim.x) {
+                        if (lane == 0) next = gridDim.x + atomicAdd(a.work_counter, 1u);
+                        next = __builtin_amdgcn_readfirstlane(next);
+                    }
+                    if (more && whole && next < item1 && g + 2 * G <= kListed) {
+                        const int at = (int)(next - item0) * G, n = min(G, count - at);
+                        const uint32_t t = list_chunk(a, seg0 + at, n, G, lane, s_prog + g + G);
+                        asm volatile("" ::"v"(t));
+                        // (a wavefront's LDS writes land in order)
+                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                        if (lane == 0)
+                            __hip_atomic_store(&s_end, (uint32_t)(g + G + n), __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    } else if (lane == 0) {
+                        s_pending = next;
+                    }
+                }
+                const uint4 pr = s_prog[g];
+                const int pid = __builtin_amdgcn_readfirstlane((int)pr.z);
+                const int words = __builtin_amdgcn_readfirstlane((int)pr.w);
+                const uint2* pc = reinterpret_cast<const uint2*>(
+                    (uintptr_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)pr.y) << 32 |
+                                (uint32_t)__builtin_amdgcn_readfirstlane((int)pr.x)));
+                warm_code(pc, words);
+                const int slot = whole ? wave : g;
+                void* acc = nullptr;
+                uint32_t* acc_bad = nullptr;
+                if constexpr (FIT == kFitCorr) acc = reinterpret_cast<CorrPart*>(accs) + slot;
+                else if constexpr (FIT == kFitReward) acc = reinterpret_cast<long long*>(accs) + slot;
+                else if constexpr (FIT == kFitMse) {
+                    acc = reinterpret_cast<float2*>(accs) + slot;
+                    acc_bad = reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax) + slot;
+                }
+                if (c == 0) run_piece<FIT, 0>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
+                else if (c == 1) run_piece<FIT, 1>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
+                else run_piece<FIT, 2>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
+            };
+            // A wavefront that comes to the end of the list waits at the
+            // barrier; a program listed meanwhile under its number is still
+            // its own, run after the barrier (nothing is listed any more
+            // then: a wavefront that lists goes on to the list's end).
+            bool after = false;
+            int g = claim();
+            for (;;) {
+                const int end = listed();
+                if (g < end) {
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    run(g, !after);
+                    if (!after) { g = claim(); continue; }
+                    break;
+                }
+                if (after) break;
+                __syncthreads();
+                after = true;
+            }
+            __syncthreads();
+        }
+        if (!whole && FIT != kFitPredict) {
+            for (int g = tid; g < it.count; g += kRunWG) {
+                // tile-major partials: the reduction reads neighbours' together
+                const int64_t slot = (int64_t)it.tile * a.part_stride + s_prog[g].z;
+                if constexpr (FIT == kFitCorr) a.part_corr[slot] = reinterpret_cast<CorrPart*>(accs)[g];
+                else if constexpr (FIT == kFitReward)
+                    reinterpret_cast<long long*>(a.part)[slot] = reinterpret_cast<long long*>(accs)[g];
+                else {
+                    a.part[slot] = reinterpret_cast<float2*>(accs)[g];
+                    a.part_bad[slot] =
+                        (uint8_t)(reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax)[g] != 0u);
+                }
+            }
+        }
+        item = __builtin_amdgcn_readfirstlane(s_pending);
+        if (!whole) __syncthreads();
     }
 }
 
@@ -2600,10 +2090,9 @@ __global__ __launch_bounds__(256) void k_reduce_reward(ReduceArgs a)
 
 // ----------------------------------------------------------- workspaces
 struct Layout {
-    size_t code, meta, cls, order, blk_counts, blk_base, blk_slen, blk_code, class_info, class_g;
-    size_t counters;
+    size_t code, meta, cls, order, class_info, class_g, counter;
     size_t part, part_bad;
-    size_t ds, req, seg_ds, seg_start, seg_cnt, seg_pos, item_pre, pds, bad, overflow, total;
+    size_t ds, req, seg_ds, seg_start, seg_cnt, seg_pos, item_pre, pds, bad, total;
 };
 
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
@@ -2612,20 +2101,15 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
                    int32_t n_seg, int fit = kFitMse)
 {
     Layout L;
-    const int64_t n_blk = (n_programs + kBucketBlock - 1) / kBucketBlock;
     size_t off = 0;
     // a staged program never holds more instructions than nodes
     L.code = off;       off = align_up(off + (size_t)(n_nodes + 1) * sizeof(uint2));
     L.meta = off;       off = align_up(off + (size_t)n_programs * sizeof(ProgMeta));
     L.cls = off;        off = align_up(off + (size_t)n_programs);
     L.order = off;      off = align_up(off + (size_t)n_programs * 4);
-    L.blk_counts = off; off = align_up(off + (size_t)kKeys * n_blk * 4);
-    L.blk_base = off;   off = align_up(off + (size_t)kKeys * n_blk * 4);
-    L.blk_slen = off;   off = align_up(off + (size_t)n_blk * 8);
-    L.blk_code = off;   off = align_up(off + (size_t)n_blk * 8);
     L.class_info = off; off = align_up(off + 2 * kClasses * 4);
-    L.class_g = off;    off = align_up(off + kClasses * 4);
-    L.counters = off;   off = align_up(off + kClasses * 4);
+    L.class_g = off;    off = align_up(off + 2 * kClasses * 4);
+    L.counter = off;    off = align_up(off + 4);
     // per (program, tile) partials: a compensated pair and a bad flag
     // (MSE), the correlation sums, or an int64 reward total
     const size_t part_elem = fit == kFitCorr ? sizeof(CorrPart) : sizeof(float2);
@@ -2640,7 +2124,6 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.item_pre = off;   off = align_up(off + (size_t)kClasses * (n_seg + 1) * 4);
     L.pds = off;        off = align_up(off + (size_t)n_programs * 4);
     L.bad = off;        off = align_up(off + 4);
-    L.overflow = off;   off = align_up(off + 4);
     L.total = off;
     return L;
 }
@@ -2651,13 +2134,9 @@ struct Staged {
     ProgMeta* meta;
     uint8_t* cls;
     int32_t* order;
-    int32_t* blk_counts;
-    int32_t* blk_base;
-    int64_t* blk_slen;
-    int64_t* blk_code;
     int32_t* class_info;
     int32_t* class_g;
-    uint32_t* counters;
+    uint32_t* counter;
     float2* part;
     uint8_t* part_bad;
     CorrPart* part_corr;            // the same memory as part, correlation mode
@@ -2670,7 +2149,6 @@ struct Staged {
     uint32_t* item_pre;
     int32_t* pds;
     int32_t* bad;
-    int32_t* overflow;
 };
 
 Staged carve(void* base, const Layout& L)
@@ -2681,13 +2159,9 @@ Staged carve(void* base, const Layout& L)
     st.meta = reinterpret_cast<ProgMeta*>(ws + L.meta);
     st.cls = reinterpret_cast<uint8_t*>(ws + L.cls);
     st.order = reinterpret_cast<int32_t*>(ws + L.order);
-    st.blk_counts = reinterpret_cast<int32_t*>(ws + L.blk_counts);
-    st.blk_base = reinterpret_cast<int32_t*>(ws + L.blk_base);
-    st.blk_slen = reinterpret_cast<int64_t*>(ws + L.blk_slen);
-    st.blk_code = reinterpret_cast<int64_t*>(ws + L.blk_code);
     st.class_info = reinterpret_cast<int32_t*>(ws + L.class_info);
     st.class_g = reinterpret_cast<int32_t*>(ws + L.class_g);
-    st.counters = reinterpret_cast<uint32_t*>(ws + L.counters);
+    st.counter = reinterpret_cast<uint32_t*>(ws + L.counter);
     st.part = reinterpret_cast<float2*>(ws + L.part);
     st.part_corr = reinterpret_cast<CorrPart*>(ws + L.part);
     st.part_bad = reinterpret_cast<uint8_t*>(ws + L.part_bad);
@@ -2700,37 +2174,13 @@ Staged carve(void* base, const Layout& L)
     st.item_pre = reinterpret_cast<uint32_t*>(ws + L.item_pre);
     st.pds = reinterpret_cast<int32_t*>(ws + L.pds);
     st.bad = reinterpret_cast<int32_t*>(ws + L.bad);
-    st.overflow = reinterpret_cast<int32_t*>(ws + L.overflow);
     return st;
 }
-
-// Side streams and fork/join events used when depth classes run
-// concurrently.  Default priority, non-blocking.
-struct SideStreams {
-    hipStream_t s[2] = {nullptr, nullptr};
-    hipEvent_t fork = nullptr, join[2] = {nullptr, nullptr};
-    int create()
-    {
-        for (auto& x : s) GP_HIP_TRY(hipStreamCreateWithFlags(&x, hipStreamNonBlocking));
-        GP_HIP_TRY(hipEventCreateWithFlags(&fork, hipEventDisableTiming));
-        for (auto& e : join) GP_HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        return GP_OK;
-    }
-    void destroy()
-    {
-        for (auto& x : s) if (x) (void)hipStreamDestroy(x);
-        if (fork) (void)hipEventDestroy(fork);
-        for (auto& e : join) if (e) (void)hipEventDestroy(e);
-        s[0] = s[1] = nullptr;
-        fork = join[0] = join[1] = nullptr;
-    }
-};
 
 // Per-(device, caller stream) state of gp_eval / gp_predict.
 struct Workspace {
     void* ptr = nullptr;
     size_t bytes = 0;
-    SideStreams side;
 };
 
 std::mutex g_ws_mutex;
@@ -2742,10 +2192,6 @@ int get_workspace(hipStream_t stream, size_t bytes, Workspace** out)
     GP_HIP_TRY(hipGetDevice(&dev));
     std::lock_guard<std::mutex> lk(g_ws_mutex);
     Workspace& w = g_ws[std::make_pair(dev, stream)];
-    if (!w.side.s[0]) {
-        int rc = w.side.create();
-        if (rc != GP_OK) return rc;
-    }
     if (w.bytes < bytes) {
         if (w.ptr) {
             // earlier work on this stream may still use the old buffer
@@ -2906,104 +2352,52 @@ struct Tuning {
     int tile_max = kMaxTiles;   // case tiles per program, at most
 };
 
-struct EvalPtrs {
-    const uint2* code;
-    const ProgMeta* meta;
-    const int32_t* order;
-    const int32_t* class_info;
-    uint32_t* work_counter;
-    const float* X;
-    const float* y;
-    float2* part;
-    uint8_t* part_bad;
-};
-
-template <int MAXD, int K>
-size_t eval_tile_floats(int n_vars, int tile_lds)
-{
-    // every dataset's window fits the budget; a single sub-tile of a dataset
-    // with very many variables may need more
-    const size_t one = (size_t)(n_vars + 1) * 64 * K;
-    const size_t budget = (size_t)tile_lds / sizeof(float);
-    return one > budget ? one : budget;
-}
-
-template <int MAXD, int K, int FIT>
-size_t eval_lds_bytes(int n_vars, int G, int tile_lds)
-{
-    const size_t acc = FIT == kFitCorr     ? (size_t)G * sizeof(CorrPart)
-                       : FIT == kFitReward ? (size_t)G * sizeof(long long)
-                                           : (size_t)G * (sizeof(float2) + sizeof(uint32_t));
-    return eval_tile_floats<MAXD, K>(n_vars, tile_lds) * sizeof(float) + acc;
-}
-
-// Whether a call runs the interpreter built for the whole command table
-// (its op mask reaches beyond the benchmark set).
+// Whether a call's op mask reaches beyond the benchmark set (its staging then
+// follows named variables and stack moves).
 inline bool pb_ext(uint32_t allowed) { return (allowed & ~GP_BASE_OPS) != 0u; }
 
-// Grid size of one class kernel (LDS attribute set outside any capture).
-template <int MAXD, int K, int FIT, bool EXT>
-int eval_grid(int n_vars, int G, const Tuning& tu, int cus, int* grid, size_t* lds_out,
-              int* refill = nullptr)
+// Programs per work item at most: the tuning's value, capped by the LDS of the
+// running sums.
+int group_capacity(const Problem& pb, const Tuning& tu)
 {
-    const int wg_per_cu = tu.wg_per_cu;
-    const size_t lds = eval_lds_bytes<MAXD, K, FIT>(n_vars, G, tu.tile_lds);
-    if (lds > 64 * 1024) {
-        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_eval<MAXD, K, FIT, EXT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
-    int per_cu = 0;
-    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_eval<MAXD, K, FIT, EXT>, kWG, lds));
-    if (per_cu < 1) return set_error(GP_E_TOO_LARGE, "n_vars=%d needs %zu bytes of LDS per workgroup", n_vars, lds);
-    if (wg_per_cu > 0 && wg_per_cu < per_cu) per_cu = wg_per_cu;
-    // overlapped classes: the depth <= 8 class (launched first) runs one
-    // workgroup per CU below its limit, so that the registers and LDS left
-    // over hold a deeper class's workgroup from the start instead of its
-    // whole run waiting for the first class to drain (and k_eval gives the
-    // deeper classes' wavefronts issue priority)
-    if (MAXD == 8 && tu.concurrent == 2 && per_cu > 1) {
-        --per_cu;
-        // the slot comes back once the deeper classes are done: a second
-        // launch of one workgroup per CU on the stream of the last of them
-        // joins the same work queue
-        if (refill) *refill = cus;
-    }
-    *grid = cus * per_cu;
-    *lds_out = lds;
-    return GP_OK;
+    return std::min(tu.G, pb.fit == kFitCorr ? kCorrMaxG : kChunkMax);
 }
 
 struct EvalLaunch {
     int32_t stride = 1;
     int32_t target_items = 1;   // work items per class worth keeping large groups for
-    int grid[kClasses] = {0, 0, 0};
-    int refill0 = 0;            // workgroups of the depth <= 8 class's second launch
-    size_t lds[kClasses] = {0, 0, 0};
+    int32_t lds_floats = 0;     // staged inputs and targets
+    int grid = 0;
+    size_t lds = 0;
     Layout layout;
 };
 
-// Programs per work item at most (the LDS accumulators' capacity): the
-// tuning's value, capped in correlation mode (larger per-program sums).
-int group_capacity(const Problem& pb, const Tuning& tu)
-{
-    return pb.fit == kFitCorr && tu.G > kCorrMaxG ? kCorrMaxG : tu.G;
-}
+// LDS for staged inputs that leaves room for three workgroups per CU (160 KB).
+constexpr int kRunLds = 48 * 1024;
 
-template <int FIT, bool EXT>
-int eval_grids(const Problem& pb, const Tuning& tu, int G, int cus, EvalLaunch* el)
-{
-    int rc;
-    if ((rc = eval_grid<8, 4, FIT, EXT>(pb.max_vars, G, tu, cus, &el->grid[0], &el->lds[0],
-                                        &el->refill0)) != GP_OK) return rc;
-    if ((rc = eval_grid<16, kK1, FIT, EXT>(pb.max_vars, G, tu, cus, &el->grid[1], &el->lds[1])) != GP_OK) return rc;
-    return eval_grid<32, 2, FIT, EXT>(pb.max_vars, G, tu, cus, &el->grid[2], &el->lds[2]);
-}
-
+// Grid and LDS of the evaluation kernel (LDS attribute set outside any
+// capture).
 template <int FIT>
-int eval_grids(const Problem& pb, const Tuning& tu, int G, int cus, EvalLaunch* el)
+int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
-    return pb_ext(pb.allowed) ? eval_grids<FIT, true>(pb, tu, G, cus, el)
-                              : eval_grids<FIT, false>(pb, tu, G, cus, el);
+    // at least one sub-tile of the widest dataset, and every window (a
+    // window of sub-tiles of 128 cases may round up by a third)
+    const int64_t one = (int64_t)(pb.max_vars + 1) * 256;
+    const int64_t want = std::max<int64_t>(kRunLds / 4, (int64_t)tu.tile_lds / 3);
+    const size_t acc = acc_bytes(FIT);
+    el->lds_floats = (int32_t)std::max(one, want);
+    el->lds = (size_t)el->lds_floats * sizeof(float) + acc;
+    if (el->lds > 64 * 1024) {
+        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)el->lds));
+    }
+    int per_cu = 0;
+    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_run<FIT>, kRunWG, el->lds));
+    if (per_cu < 1)
+        return set_error(GP_E_TOO_LARGE, "n_vars=%d needs %zu bytes of LDS per workgroup", pb.max_vars, el->lds);
+    if (tu.wg_per_cu > 0 && tu.wg_per_cu < per_cu) per_cu = tu.wg_per_cu;
+    el->grid = cus * per_cu;
+    return GP_OK;
 }
 
 int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
@@ -3018,11 +2412,12 @@ int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
         const int32_t t = max_tiles(pb.max_cases, class_k(c, pb.max_vars), tu.tile_max);
         if (t > el->stride) el->stride = t;
     }
-    el->target_items = 4 * 6 * cus;     // ~4 items per workgroup slot
-    const int G = group_capacity(pb, tu);
-    if (pb.fit == kFitCorr) rc = eval_grids<kFitCorr>(pb, tu, G, cus, el);
-    else if (pb.fit == kFitReward) rc = eval_grids<kFitReward>(pb, tu, G, cus, el);
-    else rc = eval_grids<kFitMse>(pb, tu, G, cus, el);
+    if (pb.fit == kFitPredict) el->stride = 1;      // (only the staging blocks' counts)
+    el->target_items = 4 * 3 * cus;     // ~4 items per workgroup slot
+    if (pb.fit == kFitCorr) rc = run_grid<kFitCorr>(pb, tu, cus, el);
+    else if (pb.fit == kFitReward) rc = run_grid<kFitReward>(pb, tu, cus, el);
+    else if (pb.fit == kFitPredict) rc = run_grid<kFitPredict>(pb, tu, cus, el);
+    else rc = run_grid<kFitMse>(pb, tu, cus, el);
     if (rc != GP_OK) return rc;
     el->layout = make_layout(pb.n_programs, pb.n_nodes, el->stride, pb.n_ds, pb.n_req, pb.fit);
     return GP_OK;
@@ -3040,10 +2435,10 @@ int enqueue_tables(const Problem& pb, const Tuning& tu, const Staged& st, hipStr
     return GP_OK;
 }
 
-// Calls within the benchmark set: wavefront staging (a single request brings
-// its tables by value; several have them derived by k_tables first).
-int enqueue_stage_waves(const Problem& pb, const Tuning& tu, const Staged& st, int32_t target_items,
-                        hipStream_t stream)
+// Validation, staging and partition (a single request brings its tables by
+// value; several have them derived by k_tables first).
+int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, const Staged& st,
+                  hipStream_t stream)
 {
     int rc;
     StageArgs a{};
@@ -3065,170 +2460,77 @@ int enqueue_stage_waves(const Problem& pb, const Tuning& tu, const Staged& st, i
         return rc;
     }
     const int32_t n_blk = (int32_t)((pb.n_programs + a.share - 1) / a.share);
-    hipLaunchKernelGGL(k_stage_waves, dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+    const SegOut so{group_capacity(pb, tu), el.target_items, el.lds_floats, st.seg_cnt, st.seg_pos,
+                    st.item_pre, st.class_g, st.class_info, st.counter};
+    if (pb_ext(pb.allowed)) {
+        hipLaunchKernelGGL((k_stage_waves<true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+        GP_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL((k_order<true>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
+    } else {
+        hipLaunchKernelGGL((k_stage_waves<false>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+        GP_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL((k_order<false>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
+    }
     GP_HIP_TRY(hipGetLastError());
-    const SegOut so{group_capacity(pb, tu), target_items, st.seg_cnt, st.seg_pos, st.item_pre,
-                    st.class_g, st.class_info, st.counters};
-    hipLaunchKernelGGL(k_order, dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
-    GP_HIP_TRY(hipGetLastError());
+    if (pb.req_dev) {
+        hipLaunchKernelGGL(k_seg_tables, dim3(1), dim3(256), 0, stream, st.order, st.class_info,
+                           st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(pb, tu),
+                           el.target_items, el.lds_floats, st.seg_cnt, st.seg_pos, st.item_pre,
+                           st.class_g);
+        GP_HIP_TRY(hipGetLastError());
+    }
     return GP_OK;
 }
 
-int enqueue_stage(const Problem& pb, const Tuning& tu, const Staged& st, int32_t target_items,
-                  hipStream_t stream)
+// The evaluation kernel (out: gp_predict's per-case outputs).
+int enqueue_run(const Problem& pb, const EvalLaunch& el, const Staged& st, hipStream_t stream,
+                float* out = nullptr, int64_t ld_out = 0)
 {
-    if (!pb_ext(pb.allowed)) return enqueue_stage_waves(pb, tu, st, target_items, stream);
-    const int32_t n_blk = (int32_t)((pb.n_programs + kBucketBlock - 1) / kBucketBlock);
-    int rc;
-    if ((rc = enqueue_tables(pb, tu, st, stream)) != GP_OK) return rc;
-    const int32_t lpt = pb.n_req == 1 ? 1 : 0;
-    hipLaunchKernelGGL(k_validate, dim3(n_blk), dim3(kBucketBlock), 0, stream, pb.n_programs,
-                       pb.allowed, st.ds, st.req, st.seg_start, pb.n_req, st.bad, lpt, n_blk,
-                       st.meta, st.cls, st.pds, st.blk_counts, st.blk_slen);
-    GP_HIP_TRY(hipGetLastError());
-    ScanOut so{pb.n_req == 1 ? 1 : 0, group_capacity(pb, tu), target_items, st.seg_ds, st.ds,
-               st.seg_cnt, st.seg_pos, st.item_pre, st.class_g};
-    hipLaunchKernelGGL(k_class_scan, dim3(1), dim3(1024), 0, stream, st.blk_counts, st.blk_slen,
-                       n_blk, pb.n_nodes, st.blk_base, st.blk_code, st.class_info, st.counters,
-                       st.overflow, so);
-    GP_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_stage, dim3(n_blk), dim3(kBucketBlock), 0, stream, pb.n_programs,
-                       st.req, st.seg_start, st.pds, n_blk, st.blk_code, st.blk_base, st.overflow,
-                       st.cls, st.meta, st.code, st.order);
+    RunArgs a{};
+    a.code = st.code; a.meta = st.meta; a.order = st.order; a.class_info = st.class_info;
+    a.work_counter = st.counter; a.ds = st.ds; a.seg_ds = st.seg_ds; a.seg_cnt = st.seg_cnt;
+    a.seg_pos = st.seg_pos; a.item_pre = st.item_pre; a.class_g = st.class_g;
+    a.part = st.part; a.part_bad = st.part_bad; a.part_corr = st.part_corr;
+    a.out = out; a.ld_out = ld_out;
+    a.part_stride = (int32_t)pb.n_programs;       // tile stride of the partials
+    a.n_seg = pb.n_req;
+    a.lds_floats = el.lds_floats;
+    a.reward_power = pb.reward_power;
+    a.reward_M = (float)pb.max_score;
+    const dim3 g(el.grid), b(kRunWG);
+    if (pb.fit == kFitCorr) hipLaunchKernelGGL(k_run<kFitCorr>, g, b, el.lds, stream, a);
+    else if (pb.fit == kFitReward) hipLaunchKernelGGL(k_run<kFitReward>, g, b, el.lds, stream, a);
+    else if (pb.fit == kFitPredict) hipLaunchKernelGGL(k_run<kFitPredict>, g, b, el.lds, stream, a);
+    else hipLaunchKernelGGL(k_run<kFitMse>, g, b, el.lds, stream, a);
     GP_HIP_TRY(hipGetLastError());
     return GP_OK;
-}
-
-// One class kernel of the evaluation (EXT: the interpreter for the whole
-// command table, picked by the op mask).
-template <int MD, int KK, int FIT>
-void launch_eval(bool ext, dim3 g, size_t lds, hipStream_t sc, const Staged& st, int c,
-                 const EvalConst& ea)
-{
-    if (ext)
-        hipLaunchKernelGGL((k_eval<MD, KK, FIT, true>), g, dim3(kWG), lds, sc, st.code, st.meta,
-                           st.order, st.class_info, st.counters + c, st.ds, st.seg_ds, st.seg_cnt,
-                           st.seg_pos, st.item_pre, st.class_g, st.part, st.part_bad, st.part_corr,
-                           ea);
-    else
-        hipLaunchKernelGGL((k_eval<MD, KK, FIT, false>), g, dim3(kWG), lds, sc, st.code, st.meta,
-                           st.order, st.class_info, st.counters + c, st.ds, st.seg_ds, st.seg_cnt,
-                           st.seg_pos, st.item_pre, st.class_g, st.part, st.part_bad, st.part_corr,
-                           ea);
 }
 
 // The whole evaluation as stream work (no allocation, no synchronization:
 // safe to capture into a graph).
 int enqueue_eval(const Problem& pb, const Tuning& tu, const EvalLaunch& el, const Staged& st,
-                 SideStreams& side, hipStream_t stream, CallEvents& ce)
+                 hipStream_t stream, CallEvents& ce)
 {
     int rc;
     if ((rc = ce.mark(0, stream)) != GP_OK) return rc;
-    if ((rc = enqueue_stage(pb, tu, st, el.target_items, stream)) != GP_OK) return rc;
-    if (pb.req_dev) {
-        hipLaunchKernelGGL(k_seg_tables, dim3(1), dim3(256), 0, stream, st.order, st.class_info,
-                           st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(pb, tu),
-                           el.target_items, st.seg_cnt, st.seg_pos, st.item_pre, st.class_g);
-        GP_HIP_TRY(hipGetLastError());
-    }
-
-    EvalConst ea{};
-    ea.G = group_capacity(pb, tu);
-    ea.part_stride = (int32_t)pb.n_programs;      // tile stride of the partials
-    ea.max_vars = pb.max_vars;
-    ea.n_seg = pb.n_req;
-    ea.reward_power = pb.reward_power;
-    ea.reward_M = (float)pb.max_score;
-    // group-major items in the depth <= 8 class pay when that class has the
-    // GPU to itself; overlapped with the other classes, tile-major is faster
-    ea.group_major = tu.concurrent ? 0 : 1;
-    if (tu.concurrent) {
-        GP_HIP_TRY(hipEventRecord(side.fork, stream));
-        for (auto& x : side.s) GP_HIP_TRY(hipStreamWaitEvent(x, side.fork, 0));
-    }
-    const bool ext = pb_ext(pb.allowed);
-    for (int c = 0; c < kClasses; ++c) {
-        if ((rc = ce.mark(1 + c, stream)) != GP_OK) return rc;
-        const hipStream_t sc = (tu.concurrent && c > 0) ? side.s[c - 1] : stream;
-        ea.cls = c;
-        const dim3 g(el.grid[c]);
-#define GP_LAUNCH_EVAL(MD, KK)                                                                 \
-        do {                                                                                   \
-            if (pb.fit == kFitCorr)                                                            \
-                launch_eval<MD, KK, kFitCorr>(ext, g, el.lds[c], sc, st, c, ea);               \
-            else if (pb.fit == kFitReward)                                                     \
-                launch_eval<MD, KK, kFitReward>(ext, g, el.lds[c], sc, st, c, ea);             \
-            else                                                                               \
-                launch_eval<MD, KK, kFitMse>(ext, g, el.lds[c], sc, st, c, ea);                \
-        } while (0)
-        if (c == 0) {
-            ea.tile_floats = (int32_t)eval_tile_floats<8, 4>(pb.max_vars, tu.tile_lds);
-            GP_LAUNCH_EVAL(8, 4);
-        } else if (c == 1) {
-            ea.tile_floats = (int32_t)eval_tile_floats<16, kK1>(pb.max_vars, tu.tile_lds);
-            GP_LAUNCH_EVAL(16, kK1);
-        } else {
-            ea.tile_floats = (int32_t)eval_tile_floats<32, 2>(pb.max_vars, tu.tile_lds);
-            GP_LAUNCH_EVAL(32, 2);
-        }
-#undef GP_LAUNCH_EVAL
-        GP_HIP_TRY(hipGetLastError());
-    }
-    if (el.refill0 > 0 && tu.concurrent == 2) {
-        // the depth <= 8 class takes back its slot after the depth <= 16
-        // class (same work counter: the items are shared, each taken once)
-        ea.cls = 0;
-        ea.tile_floats = (int32_t)eval_tile_floats<8, 4>(pb.max_vars, tu.tile_lds);
-        const dim3 g(el.refill0);
-        const int c = 0;
-        const hipStream_t sc = side.s[0];
-        if (pb.fit == kFitCorr) launch_eval<8, 4, kFitCorr>(ext, g, el.lds[c], sc, st, c, ea);
-        else if (pb.fit == kFitReward) launch_eval<8, 4, kFitReward>(ext, g, el.lds[c], sc, st, c, ea);
-        else launch_eval<8, 4, kFitMse>(ext, g, el.lds[c], sc, st, c, ea);
-        GP_HIP_TRY(hipGetLastError());
-    }
-    if (tu.concurrent) {
-        for (int i = 0; i < 2; ++i) {
-            GP_HIP_TRY(hipEventRecord(side.join[i], side.s[i]));
-            GP_HIP_TRY(hipStreamWaitEvent(stream, side.join[i], 0));
-        }
-    }
+    if ((rc = enqueue_stage(pb, tu, el, st, stream)) != GP_OK) return rc;
+    if ((rc = ce.mark(1, stream)) != GP_OK) return rc;
+    if ((rc = enqueue_run(pb, el, st, stream)) != GP_OK) return rc;
+    // one launch evaluates every class: the class phases share its time
+    for (int i = 2; i <= 4; ++i)
+        if ((rc = ce.mark(i, stream)) != GP_OK) return rc;
     ReduceArgs ra{};
     ra.meta = st.meta; ra.cls = st.cls; ra.pds = st.pds; ra.reqs = st.req;
     ra.seg_start = st.seg_start; ra.ds = st.ds;
     ra.part = st.part; ra.part_bad = st.part_bad; ra.part_corr = st.part_corr;
     ra.n_programs = pb.n_programs; ra.part_stride = (int32_t)pb.n_programs;
     ra.max_score = pb.max_score;
-    if ((rc = ce.mark(4, stream)) != GP_OK) return rc;
-    if (pb.fit == kFitCorr)
-        hipLaunchKernelGGL(k_reduce_corr, dim3((unsigned)((pb.n_programs + 255) / 256)), dim3(256),
-                           0, stream, ra);
-    else if (pb.fit == kFitReward)
-        hipLaunchKernelGGL(k_reduce_reward, dim3((unsigned)((pb.n_programs + 255) / 256)),
-                           dim3(256), 0, stream, ra);
-    else
-        hipLaunchKernelGGL(k_reduce, dim3((unsigned)((pb.n_programs + 255) / 256)), dim3(256), 0,
-                           stream, ra);
+    const dim3 g((unsigned)((pb.n_programs + 255) / 256)), b(256);
+    if (pb.fit == kFitCorr) hipLaunchKernelGGL(k_reduce_corr, g, b, 0, stream, ra);
+    else if (pb.fit == kFitReward) hipLaunchKernelGGL(k_reduce_reward, g, b, 0, stream, ra);
+    else hipLaunchKernelGGL(k_reduce, g, b, 0, stream, ra);
     GP_HIP_TRY(hipGetLastError());
     if ((rc = ce.mark(5, stream)) != GP_OK) return rc;
-    return GP_OK;
-}
-
-template <int MAXD, int K, bool EXT>
-int launch_predict(const EvalPtrs& p, float* out, int64_t ld_out, const EvalConst& args,
-                   hipStream_t stream, int cus)
-{
-    const size_t lds = (size_t)args.n_vars * 64 * K * sizeof(float);
-    if (lds > 64 * 1024) {
-        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_predict<MAXD, K, EXT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    }
-    int per_cu = 0;
-    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_predict<MAXD, K, EXT>, kWG, lds));
-    if (per_cu < 1) return set_error(GP_E_TOO_LARGE, "n_vars=%d needs %zu bytes of LDS per workgroup", args.n_vars, lds);
-    hipLaunchKernelGGL((k_predict<MAXD, K, EXT>), dim3(cus * per_cu), dim3(kWG), lds, stream, p.code,
-                       p.meta, p.order, p.class_info, p.work_counter, p.X, out, ld_out, args);
-    GP_HIP_TRY(hipGetLastError());
     return GP_OK;
 }
 
@@ -3297,7 +2599,6 @@ struct gp_plan {
     void* ws = nullptr;
     size_t ws_bytes = 0;
     Staged st;
-    SideStreams side;
     hipStream_t cap = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -3341,7 +2642,7 @@ int plan_build(gp_plan* p)
     GP_HIP_TRY(hipStreamBeginCapture(p->cap, hipStreamCaptureModeThreadLocal));
     CallEvents none;
     (void)none.begin(false);
-    rc = enqueue_eval(p->pb, p->tu, p->el, p->st, p->side, p->cap, none);
+    rc = enqueue_eval(p->pb, p->tu, p->el, p->st, p->cap, none);
     hipGraph_t g = nullptr;
     const hipError_t ec = hipStreamEndCapture(p->cap, &g);
     if (rc != GP_OK) {
@@ -3369,10 +2670,10 @@ int time_config(gp_plan* p, const Tuning& t, hipStream_t stream, hipEvent_t e0, 
     (void)none.begin(false);
     float ms[8];
     runs = std::min(std::max(runs, 1), 8);
-    if (warm && (rc = enqueue_eval(p->pb, t, el, st, p->side, stream, none)) != GP_OK) return rc;
+    if (warm && (rc = enqueue_eval(p->pb, t, el, st, stream, none)) != GP_OK) return rc;
     for (int r = 0; r < runs; ++r) {
         GP_HIP_TRY(hipEventRecord(e0, stream));
-        if ((rc = enqueue_eval(p->pb, t, el, st, p->side, stream, none)) != GP_OK) return rc;
+        if ((rc = enqueue_eval(p->pb, t, el, st, stream, none)) != GP_OK) return rc;
         GP_HIP_TRY(hipEventRecord(e1, stream));
         GP_HIP_TRY(hipEventSynchronize(e1));
         GP_HIP_TRY(hipEventElapsedTime(&ms[r], e0, e1));
@@ -3515,7 +2816,7 @@ int eval_problem(const Problem& pb, hipStream_t stream)
     const Staged st = carve(w->ptr, el.layout);
     CallEvents ce;
     if ((rc = ce.begin(true)) != GP_OK) return rc;
-    if ((rc = enqueue_eval(pb, tu, el, st, w->side, stream, ce)) != GP_OK) return rc;
+    if ((rc = enqueue_eval(pb, tu, el, st, stream, ce)) != GP_OK) return rc;
     ce.commit();
     return GP_OK;
 }
@@ -3579,10 +2880,9 @@ int eval_problem_noalloc(const Problem& pb, hipStream_t stream)
         return set_error(GP_E_TOO_LARGE, "the call needs %zu bytes of workspace; the fixed array holds %zu",
                          el.layout.total, kScratchBytes);
     const Staged st = carve(base, el.layout);
-    SideStreams unused;
     CallEvents ce;
     if ((rc = ce.begin(false)) != GP_OK) return rc;
-    return enqueue_eval(pb, tu, el, st, unused, stream, ce);
+    return enqueue_eval(pb, tu, el, st, stream, ce);
 }
 
 // ------------------------------------------------- Monte-Carlo ranking
@@ -3822,8 +3122,6 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
     // work items (program, sub-tile) are counted in 32 bits
     if ((double)n_programs * (double)((n_cases + 511) / 512) > 2.0e9)
         return set_error(GP_E_TOO_LARGE, "n_programs * n_cases too large for one gp_predict call");
-    int cus = 0;
-    if ((rc = device_cus(&cus)) != GP_OK) return rc;
     Problem pb{};
     pb.one_req.nodes = nodes; pb.one_req.offsets = offsets; pb.one_req.consts = consts;
     pb.one_req.n_programs = n_programs; pb.one_req.n_nodes = n_nodes;
@@ -3837,27 +3135,15 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
     pb.max_vars = n_vars; pb.max_cases = n_cases;
     pb.allowed = allowed_op_mask ? allowed_op_mask : GP_ALL_OPS;
     pb.need_out = 0;
-    // (one partial slot per program: the staging blocks' counts)
-    const Layout L = make_layout(n_programs, n_nodes, 1, 1, 1);
+    pb.fit = kFitPredict;
+    Tuning tu;
+    EvalLaunch el;
+    if ((rc = configure_eval(pb, tu, &el)) != GP_OK) return rc;
     Workspace* w = nullptr;
-    if ((rc = get_workspace(stream, L.total, &w)) != GP_OK) return rc;
-    const Staged st = carve(w->ptr, L);
-    if ((rc = enqueue_stage(pb, Tuning(), st, 1, stream)) != GP_OK) return rc;
-    EvalPtrs ep{st.code, st.meta, st.order, st.class_info, nullptr, X, nullptr, nullptr, nullptr};
-    EvalConst ea{};
-    ea.ld_x = ld_x; ea.n_cases = n_cases; ea.n_vars = n_vars;
-    for (int c = 0; c < kClasses; ++c) {
-        ea.cls = c;
-        ep.work_counter = st.counters + c;
-        const bool ext = pb_ext(pb.allowed);
-        if (c == 0) rc = ext ? launch_predict<8, 4, true>(ep, out, ld_out, ea, stream, cus)
-                             : launch_predict<8, 4, false>(ep, out, ld_out, ea, stream, cus);
-        else if (c == 1) rc = ext ? launch_predict<16, kK1, true>(ep, out, ld_out, ea, stream, cus)
-                                  : launch_predict<16, kK1, false>(ep, out, ld_out, ea, stream, cus);
-        else rc = ext ? launch_predict<32, 2, true>(ep, out, ld_out, ea, stream, cus)
-                      : launch_predict<32, 2, false>(ep, out, ld_out, ea, stream, cus);
-        if (rc != GP_OK) return rc;
-    }
+    if ((rc = get_workspace(stream, el.layout.total, &w)) != GP_OK) return rc;
+    const Staged st = carve(w->ptr, el.layout);
+    if ((rc = enqueue_stage(pb, tu, el, st, stream)) != GP_OK) return rc;
+    if ((rc = enqueue_run(pb, el, st, stream, out, ld_out)) != GP_OK) return rc;
     hipLaunchKernelGGL(k_fill_invalid, dim3((unsigned)n_programs), dim3(256), 0, stream, st.cls,
                        n_cases, out, ld_out);
     GP_HIP_TRY(hipGetLastError());
@@ -3891,8 +3177,7 @@ int gp_plan_create(gp_plan** plan, const gp_problem* problem, const gp_tuning* t
         if (tuning->max_tiles > 0) p->tu.tile_max = tuning->max_tiles;
     }
     if (hipGetDevice(&p->device) != hipSuccess ||
-        hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking) != hipSuccess ||
-        p->side.create() != GP_OK) {
+        hipStreamCreateWithFlags(&p->cap, hipStreamNonBlocking) != hipSuccess) {
         gp_plan_destroy(p);
         return set_error(GP_E_HIP, "plan stream setup failed");
     }
@@ -3956,7 +3241,6 @@ void gp_plan_destroy(gp_plan* plan)
     if (plan->cap) (void)hipStreamSynchronize(plan->cap);
     (void)hipDeviceSynchronize();
     plan_release_graph(plan);
-    plan->side.destroy();
     if (plan->cap) (void)hipStreamDestroy(plan->cap);
     if (plan->ws) (void)hipFree(plan->ws);
     delete plan;
@@ -4033,7 +3317,6 @@ __attribute__((visibility("hidden"))) void gp_internal_release_stream_workspace(
     if (it == g_ws.end()) return;
     (void)hipStreamSynchronize(stream);
     if (it->second.ptr) (void)hipFree(it->second.ptr);
-    it->second.side.destroy();
     g_ws.erase(it);
 }
 
@@ -4045,7 +3328,6 @@ void gp_release_workspaces(void)
     for (auto& kv : g_ws) {
         (void)hipStreamSynchronize(kv.first.second);
         if (kv.second.ptr) (void)hipFree(kv.second.ptr);
-        kv.second.side.destroy();
     }
     g_ws.clear();
 }
