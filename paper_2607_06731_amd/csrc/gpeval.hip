@@ -1285,9 +1285,14 @@ typedef float f32x32 __attribute__((ext_vector_type(32)));
     "s_getpc_b64 s[90:91]\n"                                                              \
     "s_add_u32 s90, s90, " table "@rel32@lo+4\n"                                          \
     "s_addc_u32 s91, s91, " table "@rel32@hi+12\n"
+// Loads still in flight when the statement starts would land in registers that
+// the handlers use: the compiler does not wait for a load whose result is not
+// read (a spilled value read back and not needed on this path), and takes the
+// register as free.
+#define GP_THREAD_SETTLE "s_waitcnt vmcnt(0) lgkmcnt(0)\n"
 // the first word, then its handler
 #define GP_THREAD_ENTER(table)                                                             \
-    "s_load_dwordx2 s[88:89], s[84:85], 0x0\n" GP_THREAD_TABLE(table)                      \
+    GP_THREAD_SETTLE "s_load_dwordx2 s[88:89], s[84:85], 0x0\n" GP_THREAD_TABLE(table)                      \
     "s_mov_b32 s86, 8\n"                                                                  \
     "s_waitcnt lgkmcnt(0)\n"                                                              \
     "s_add_u32 s92, s90, s88\n"                                                           \
@@ -1295,7 +1300,7 @@ typedef float f32x32 __attribute__((ext_vector_type(32)));
     "s_swappc_b64 s[94:95], s[92:93]\n"
 // after a value was replaced: the finish code of the block that asked for it
 #define GP_THREAD_RESUME(table)                                                            \
-    GP_THREAD_TABLE(table)                                                                 \
+    GP_THREAD_SETTLE GP_THREAD_TABLE(table)                                                                 \
     "s_add_u32 s92, s90, s87\n"                                                           \
     "s_addc_u32 s93, s91, 0\n"                                                            \
     "s_swappc_b64 s[94:95], s[92:93]\n"
