@@ -109,8 +109,9 @@ constexpr int kMaxRequests = 4096;       // requests per batched call (tables ar
 struct ProgMeta {
     int64_t start;      // first staged instruction
     int32_t len;        // node count (the length taxed)
-    int32_t slen;       // staged instructions (0: not staged)
+    int32_t slen;       // staged instructions (0: not staged), and kNarrow
 };
+constexpr int32_t kNarrow = INT32_MIN;   // class 2, but the words need at most 8 cells
 static_assert(sizeof(ProgMeta) == 16, "ProgMeta layout");
 
 // Cases per lane of a class's sub-tile, the unit in which its cases are
@@ -668,12 +669,87 @@ __device__ __forceinline__ int prefix_min(int v)
     return v;
 }
 
-// Stages program nodes[0, len) into dst.  Every argument is uniform in the
-// wavefront.  status, cls (depth class) and the word count come back; dst
+// Operands in Sethi-Ullman order: a binary operator whose right operand needs
+// more stack cells than the left one takes it first, so an operator over
+// operands of equal need is the only one that takes a cell more, and a program
+// of 128 nodes needs at most 7.  (In the order written, an eighth of the
+// programs of up to 64 nodes need more than 8 cells, a third of those of up to
+// 128 -- half of all nodes -- and run at two or one cases per lane.)  The results are the same: no operator's operands change, only which
+// of them is ready first.  The walk takes a wavefront 4 us, which datasets of
+// fewer than 2,048 cases do not give back (1,000 programs x 1,024 cases: 43 us
+// without it, 49 with it; 60,000 x 16,384: 1,719 and 1,609).
+constexpr int kReorderMax = 128;         // nodes: two per lane
+constexpr int64_t kReorderCases = 2048;
+constexpr uint32_t kReversed = 1u << 8;  // on - and / of the reordered program: the top is the left operand
+
+// Reorders a valid program; false: nothing to gain, or the program moves stack
+// elements.  The walk keeps (size, need) of the subtrees on the stack in the
+// lanes of one register; a node's place moves by the other operand's size for
+// each reordered operator above it.
+template <bool EXT>
+__device__ __forceinline__ bool reorder(const uint32_t* __restrict__ nodes, int len, int lane, uint32_t* out)
+{
+    uint32_t w[2];
+    int pos[2];
+    uint64_t leaves[2], bins[2], may[2], rev[2];
+    bool moves = false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int k = h * 64 + lane;
+        w[h] = k < len ? nodes[k] : 0xFFu;
+        pos[h] = k;
+        const uint32_t op = w[h] & 0xFFu;
+        leaves[h] = __ballot(op <= GP_CONST);
+        may[h] = __ballot(op - GP_ADD < 4u);
+        bins[h] = may[h] | (EXT ? __ballot(op == GP_POW) : 0ull);
+        rev[h] = 0ull;
+        if (EXT)
+            moves |= __ballot(k < len && op >= GP_DUP && op != GP_POW && !op_is_unary(op)) != 0ull;
+    }
+    if (moves) return false;
+    int st = 0, sp = 0;
+    for (int i = 0; i < len; ++i) {
+        const uint64_t bit = 1ull << (i & 63);
+        const bool hi = i >= 64;
+        if (((hi ? leaves[1] : leaves[0]) & bit) != 0ull) {
+            st = lane == sp++ ? 1 | 1 << 16 : st;
+        } else if (((hi ? bins[1] : bins[0]) & bit) == 0ull) {
+            st += lane == sp - 1 ? 1 : 0;
+        } else {
+            const int r = lane_value(st, sp - 1), l = lane_value(st, sp - 2);
+            const int sr = r & 0xFFFF, sl = l & 0xFFFF, nr = r >> 16, nl = l >> 16;
+            int need = nl > nr ? nl : nr + 1;
+            if (nr > nl && ((hi ? may[1] : may[0]) & bit) != 0ull) {
+                need = nr;
+                const int b = i - sr - sl;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t k = (uint32_t)(h * 64 + lane - b);
+                    pos[h] += k < (uint32_t)sl ? sr : (k - (uint32_t)sl < (uint32_t)sr ? -sl : 0);
+                }
+                rev[0] |= hi ? 0ull : bit;
+                rev[1] |= hi ? bit : 0ull;
+            }
+            --sp;
+            st = lane == sp - 1 ? (sl + sr + 1) | need << 16 : st;
+        }
+    }
+    if ((rev[0] | rev[1]) == 0ull) return false;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t op = w[h] & 0xFFu;
+        const bool turned = ((rev[h] >> lane) & 1ull) != 0ull && (op == GP_SUB || op == GP_DIV);
+        if (h * 64 + lane < len) out[pos[h]] = op - GP_ADD < 4u ? op | (turned ? kReversed : 0u) : w[h];
+    }
+    return true;
+}
+
+// Stages program nodes[0, len) into dst; with `turned` the nodes are those of
+// reorder() (in LDS).  Every argument is uniform in the wavefront.  status, cls (depth class) and the word count come back; dst
 // holds the words when the status is GP_PROG_OK (else nothing useful), never
 // more than len of them.
 template <bool EXT>
-__device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, int32_t len,
+__device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, const uint32_t* turned, int32_t len,
                                           const float* __restrict__ consts, int64_t n_consts,
                                           uint32_t allowed, int32_t n_vars,
                                           uint2* __restrict__ dst, WaveTables* tb, int lane,
@@ -692,11 +768,18 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
     for (int32_t c0 = 0; c0 < len; c0 += 64) {
         const int32_t k = c0 + lane;
         const bool live = k < len;
-        const uint32_t w = live ? nodes[k] : 0xFFu;
-        const uint32_t nx = k + 1 < len ? nodes[k + 1] & 0xFFu : 0xFFu;
-        const uint32_t op = w & 0xFFu, arg = w >> 8;
+        uint32_t w = 0xFFu, nw = 0xFFu;
+        if (turned) {
+            if (live) w = turned[k];
+            if (k + 1 < len) nw = turned[k + 1];
+        } else {
+            if (live) w = nodes[k];
+            if (k + 1 < len) nw = nodes[k + 1];
+        }
+        const uint32_t op = w & 0xFFu, arg = w >> 8, nx = nw & 0xFFu;
         const bool leaf = op <= GP_CONST, load = op == GP_LOAD, cst = op == GP_CONST;
         const bool bin = op - GP_ADD < 4u, un = op - GP_SIN < 6u;       // folded operators
+        const bool rev = turned && bin && arg != 0u, next_rev = turned && nx - GP_ADD < 4u && nw > 0xFFu;
         const bool pw = EXT && op == GP_POW;
         const bool copy = EXT && op == GP_COPY, paste = EXT && op == GP_PASTE;
         const bool push = leaf || (EXT && op == GP_DUP) || paste;
@@ -765,6 +848,7 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
             const uint64_t m = __ballot(live && d1 == d) & ((1ull << l) - 1ull);
             return m != 0ull ? lane_value(val, 63 - __builtin_clzll(m)) : tb->value[d];
         };
+        const uint64_t revs = __ballot(rev);
         uint64_t folds = __ballot(live && !fused && ((bin && np >= 2) || (un && np >= 1)));
         while (folds != 0ull) {
             const int l = __builtin_ctzll(folds);
@@ -774,7 +858,8 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
             float r;
             if (fo <= GP_DIV) {
                 const float a = at_depth(lane_value(d0, l) - 1, l > 0 ? l - 1 : 0);
-                r = binary_value(fo, a, b);
+                const bool t = ((revs >> l) & 1ull) != 0ull;
+                r = binary_value(fo, t ? b : a, t ? a : b);
             } else {
                 r = unary_value(fo, b);
             }
@@ -804,14 +889,19 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
         if (load) {
             const uint32_t payload = arg * kVarPayload;
             const int rt = d0;                   // everything below is on the stack now
-            word = nx - GP_ADD < 4u            ? ThreadedWords::top_row(rt, nx - GP_ADD, payload)
+            word = next_rev                    ? ThreadedWords::row_top(rt, nx - GP_ADD, payload)
+                   : nx - GP_ADD < 4u          ? ThreadedWords::top_row(rt, nx - GP_ADD, payload)
                    : EXT && nx == GP_POW       ? ThreadedWords::top_row(rt, kBinPow, payload)
                    : nx - GP_SIN < 6u          ? ThreadedWords::push_unary(rt, nx - GP_SIN, payload)
                                                : ThreadedWords::push_row(rt, payload);
         } else if (bin || pw) {
             const uint32_t sel = pw ? kBinPow : op - GP_ADD;
-            word = np == 1 ? ThreadedWords::top_const(r0, sel, __float_as_uint(top))
-                           : ThreadedWords::cells(pw ? d0 : r0, sel);
+            if (rev)
+                word = np == 1 ? ThreadedWords::const_top(r0, sel, __float_as_uint(top))
+                               : ThreadedWords::cells_top(r0, sel);
+            else
+                word = np == 1 ? ThreadedWords::top_const(r0, sel, __float_as_uint(top))
+                               : ThreadedWords::cells(pw ? d0 : r0, sel);
         } else if (EXT && beyond && !op_is_unary(op)) {
             const uint32_t off = op == GP_DUP    ? kThDup
                                  : op == GP_SWAP ? kThSwap
@@ -858,6 +948,42 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, in
     *cls = over16 ? 2 : over8;
     *n_words = n;
     return GP_PROG_OK;
+}
+
+// Stages one program: in the order written, and where that needs more than 8
+// cells again in Sethi-Ullman order.  cls: the depth class by the order written
+// decides the unit in which cases are summed (class_k), so the class of a
+// program with more than 16 cells stays, and *narrow says that its words fit
+// the first class's handlers.
+template <bool EXT>
+__device__ __forceinline__ int stage_program(const uint32_t* __restrict__ nodes, int32_t len,
+                                             const float* __restrict__ consts, int64_t n_consts,
+                                             uint32_t allowed, int32_t n_vars, uint2* __restrict__ dst,
+                                             WaveTables* tb, int64_t n_cases, uint32_t* turned, int lane, int* cls,
+                                             int* n_words, bool* narrow)
+{
+    const uint32_t* from = nullptr;
+    int first = -1;
+    *narrow = false;
+    for (;;) {
+        int c = 0;
+        const int status = stage_wave<EXT>(nodes, from, len, consts, n_consts, allowed, n_vars, dst, tb, lane, &c,
+                                           n_words);
+        if (first >= 0) {
+            *cls = first == 2 ? 2 : c;
+            *narrow = first == 2 && c == 0;
+            return status;
+        }
+        *cls = c;
+        if (status != GP_PROG_OK || c == 0 || n_cases < kReorderCases || len > kReorderMax ||
+            !reorder<EXT>(nodes, len, lane, turned))
+            return status;
+        first = c;
+        from = turned;
+        // the words are written again, the nodes read back by other lanes
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    }
 }
 
 // Per staging block: programs per partition key, and whether some program's
@@ -907,6 +1033,7 @@ struct ProgRange {
     int64_t n_consts, node_base, s, e;
     int32_t* out_status;
     int64_t n_nodes;
+    int64_t n_cases;
     int32_t n_vars;
     int r;
 };
@@ -923,6 +1050,7 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
         g.node_base = 0;
         g.n_nodes = a.one_req.n_nodes;
         g.n_vars = a.one_ds.n_vars;
+        g.n_cases = a.one_ds.n_cases;
         g.out_status = a.one_req.out_status ? a.one_req.out_status + p : nullptr;
         g.s = as_const(a.one_req.offsets)[p];
         g.e = as_const(a.one_req.offsets)[p + 1];
@@ -943,6 +1071,7 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
     g.node_base = R->node_base;
     g.n_nodes = R->n_nodes;
     g.n_vars = as_const((const DevDataset*)a.ds)[R->dataset].n_vars;
+    g.n_cases = as_const((const DevDataset*)a.ds)[R->dataset].n_cases;
     g.out_status = R->out_status && q < R->n_programs ? R->out_status + q : nullptr;
     if (tab_ok) {
         g.s = as_const(R->offsets)[q];
@@ -961,6 +1090,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
     __shared__ int cnt[kKeys];
     __shared__ int s_down;
     __shared__ WaveTables tables[kStageWaves];
+    __shared__ uint32_t turned[kStageWaves][kReorderMax];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
@@ -981,12 +1111,14 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
         const ProgRange g = program_range(a, p, tab_ok);
         const bool range_ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
         int status, c = -1, n = 0;
+        bool narrow = false;
         if (!tab_ok) status = GP_PROG_BAD_TABLE;
         else if (!range_ok) status = GP_PROG_BAD_OFFSETS;
         else if (g.e == g.s) status = GP_PROG_EMPTY;
         else
-            status = stage_wave<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                     g.n_vars, a.code + g.node_base + g.s, &tables[wave], lane, &c, &n);
+            status = stage_program<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                        g.n_vars, a.code + g.node_base + g.s, &tables[wave], g.n_cases, turned[wave], lane,
+                                        &c, &n, &narrow);
         if (status != GP_PROG_OK) {
             c = -1;
             n = 0;
@@ -996,7 +1128,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
             ProgMeta m;
             m.start = g.node_base + g.s;
             m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
-            m.slen = n;
+            m.slen = narrow ? n | kNarrow : n;
             a.meta[p] = m;
             a.pds[p] = g.r;
             // partition key: depth class, then (single-request calls) length
@@ -1078,7 +1210,7 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         __syncthreads();
         unsigned long long all = 0, before = 0;
         for (int64_t p = t; p < a.n_programs; p += kOrderWG) {
-            const unsigned long long v = (unsigned long long)a.meta[p].slen;
+            const unsigned long long v = (unsigned long long)(a.meta[p].slen & ~kNarrow);
             all += v;
             if (p < p0) before += v;
         }
@@ -1088,14 +1220,17 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         overflow = (int64_t)s_words > code_capacity;
         if (!overflow) {
             __shared__ WaveTables tables[kOrderWG / 64];
+            __shared__ uint32_t turned[kOrderWG / 64][kReorderMax];
             for (int64_t p = p0 + __builtin_amdgcn_readfirstlane(wave); p < p1; p += kOrderWG / 64) {
                 int64_t start = (int64_t)s_before;
-                for (int64_t q = p0; q < p; ++q) start += a.meta[q].slen;
+                for (int64_t q = p0; q < p; ++q) start += a.meta[q].slen & ~kNarrow;
                 if (a.cls[p] >= kKeys) continue;
                 const ProgRange g = program_range(a, p, true);
                 int c = 0, n = 0;
-                (void)stage_wave<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                 g.n_vars, a.code + start, &tables[wave], lane, &c, &n);
+                bool narrow = false;
+                (void)stage_program<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                         g.n_vars, a.code + start, &tables[wave], g.n_cases, turned[wave], lane, &c, &n,
+                                         &narrow);
                 if (lane == 0) a.meta[p].start = start;
             }
         }
@@ -1604,7 +1739,8 @@ __device__ __forceinline__ void add_cases(const float (&f)[NJ], const float* yt,
     }
 }
 
-// Runs one program of depth class C over the staged piece; acc is its
+// Runs one program of depth class C (3: of class 2, with the first class's
+// handlers) over the staged piece; acc is its
 // running tile sum in LDS (correlation always; the others only when a tile
 // goes on past the piece).
 template <int FIT, int C>
@@ -1612,7 +1748,7 @@ __device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float*
                                           const Item& it, const ThreadConsts& tc, int lane, void* acc,
                                           uint32_t* acc_bad)
 {
-    constexpr int SUB = sub_cases(C);
+    constexpr int SUB = sub_cases(C == 3 ? 2 : C);
     constexpr int NJ = SUB / 64;
     const float* yt = xt + (int64_t)it.n_vars * it.stride;
     Sums<FIT> s;
@@ -1703,6 +1839,20 @@ __device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float*
 
     for (int pos = 0; pos < it.cases;) {
         const float* xl = xt + pos + lane;
+        if constexpr (C == 3) {
+            // two sub-tiles at once (pos is a multiple of 256, like a row)
+            float f[4];
+            run_threaded<8, 4>(pc, xl, it.stride >> 8, tc, f);
+            const float f0[2] = {f[0], f[1]}, f1[2] = {f[2], f[3]};
+            add_cases<FIT, 2>(f0, yt + pos, it.cases - pos, lane, a, it, s, out + pos);
+            close(pos + SUB);
+            pos += SUB;
+            if (pos >= it.cases) break;
+            add_cases<FIT, 2>(f1, yt + pos, it.cases - pos, lane, a, it, s, out + pos);
+            close(pos + SUB);
+            pos += SUB;
+            continue;
+        }
         float f[NJ];
         constexpr int K = C == 0 ? 4 : (C == 1 ? 2 : 1);
 #pragma unroll
@@ -1764,7 +1914,8 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
         const ProgMeta pm = a.meta[pid];
         const uint64_t at = (uint64_t)(uintptr_t)(a.code + pm.start);
         if (k == 0) list[g] = make_uint4((uint32_t)at, (uint32_t)(at >> 32), (uint32_t)pid, (uint32_t)pm.slen);
-        for (int l = k; l * 16 < pm.slen; l += per) touched ^= a.code[pm.start + l * 16].x;
+        const int words = pm.slen & ~kNarrow;
+        for (int l = k; l * 16 < words; l += per) touched ^= a.code[pm.start + l * 16].x;
     }
     return touched;     // (to be consumed where the wait for it does no harm)
 }
@@ -1931,11 +2082,11 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr || FIT == kFitReward ? 4 : 
                 }
                 const uint4 pr = s_prog[g];
                 const int pid = __builtin_amdgcn_readfirstlane((int)pr.z);
-                const int words = __builtin_amdgcn_readfirstlane((int)pr.w);
+                const int slen = __builtin_amdgcn_readfirstlane((int)pr.w);
                 const uint2* pc = reinterpret_cast<const uint2*>(
                     (uintptr_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)pr.y) << 32 |
                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)pr.x)));
-                warm_code(pc, words);
+                warm_code(pc, slen & ~kNarrow);
                 const int slot = whole ? wave : g;
                 void* acc = nullptr;
                 uint32_t* acc_bad = nullptr;
@@ -1947,6 +2098,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr || FIT == kFitReward ? 4 : 
                 }
                 if (c == 0) run_piece<FIT, 0>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
                 else if (c == 1) run_piece<FIT, 1>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
+                else if (slen < 0) run_piece<FIT, 3>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
                 else run_piece<FIT, 2>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
             };
             // A wavefront that comes to the end of the list waits at the

@@ -352,12 +352,48 @@ asm volatile(R"(
  .endif
  .endr
 .endm
-// any operands: the IEEE quotient (scaled reciprocal, one Newton step, two
-// residual corrections, fix-up), 1 where |divisor| <= 0.001
-.macro GP_DIVP K, a
+// cell \a = cell \a+1 / cell \a
+.macro GP_DIVR K, a
  .irp j,0,1,2,3
  .if \j < \K
-  v_div_scale_f32 v[4+((\j+3)&3)], s[96:97], v[GP_CB+\K*(\a+1)+\j], v[GP_CB+\K*(\a+1)+\j], v[GP_CB+\K*\a+\j]
+  v_rcp_f32_e32 v[8+((\j+1)&3)], v[GP_CB+\K*\a+\j]
+ .endif
+ .endr
+ .if \K == 1
+  s_nop 0
+ .endif
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_fma_f32 v[12+((\j+2)&3)], -v[GP_CB+\K*\a+\j], v[8+((\j+1)&3)], 1.0
+ .endif
+ .endr
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_fmac_f32_e32 v[8+((\j+1)&3)], v[12+((\j+2)&3)], v[8+((\j+1)&3)]
+ .endif
+ .endr
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_mul_f32_e32 v[4+((\j+3)&3)], v[GP_CB+\K*(\a+1)+\j], v[8+((\j+1)&3)]
+ .endif
+ .endr
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_fma_f32 v[12+((\j+2)&3)], -v[GP_CB+\K*\a+\j], v[4+((\j+3)&3)], v[GP_CB+\K*(\a+1)+\j]
+ .endif
+ .endr
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_fma_f32 v[GP_CB+\K*\a+\j], v[12+((\j+2)&3)], v[8+((\j+1)&3)], v[4+((\j+3)&3)]
+ .endif
+ .endr
+.endm
+// cell \r = cell \n / cell \d, any operands: the IEEE quotient (scaled reciprocal, one Newton step, two
+// residual corrections, fix-up), 1 where |divisor| <= 0.001
+.macro GP_DIVP K, n, d, r
+ .irp j,0,1,2,3
+ .if \j < \K
+  v_div_scale_f32 v[4+((\j+3)&3)], s[96:97], v[GP_CB+\K*\d+\j], v[GP_CB+\K*\d+\j], v[GP_CB+\K*\n+\j]
  .endif
  .endr
  .irp j,0,1,2,3
@@ -367,7 +403,7 @@ asm volatile(R"(
  .endr
  .irp j,0,1,2,3
  .if \j < \K
-  v_cmp_nle_f32_e64 s[68+2*\j:69+2*\j], |v[GP_CB+\K*(\a+1)+\j]|, v25
+  v_cmp_nle_f32_e64 s[68+2*\j:69+2*\j], |v[GP_CB+\K*\d+\j]|, v25
  .endif
  .endr
  .irp j,0,1,2,3
@@ -382,7 +418,7 @@ asm volatile(R"(
  .endr
  .irp j,0,1,2,3
  .if \j < \K
-  v_div_scale_f32 v16, vcc, v[GP_CB+\K*\a+\j], v[GP_CB+\K*(\a+1)+\j], v[GP_CB+\K*\a+\j]
+  v_div_scale_f32 v16, vcc, v[GP_CB+\K*\n+\j], v[GP_CB+\K*\d+\j], v[GP_CB+\K*\n+\j]
   v_mul_f32_e32 v17, v16, v[8+((\j+1)&3)]
   v_fma_f32 v18, -v[4+((\j+3)&3)], v17, v16
   v_fmac_f32_e32 v17, v18, v[8+((\j+1)&3)]
@@ -392,12 +428,12 @@ asm volatile(R"(
  .endr
  .irp j,0,1,2,3
  .if \j < \K
-  v_div_fixup_f32 v[12+((\j+2)&3)], v[12+((\j+2)&3)], v[GP_CB+\K*(\a+1)+\j], v[GP_CB+\K*\a+\j]
+  v_div_fixup_f32 v[12+((\j+2)&3)], v[12+((\j+2)&3)], v[GP_CB+\K*\d+\j], v[GP_CB+\K*\n+\j]
  .endif
  .endr
  .irp j,0,1,2,3
  .if \j < \K
-  v_cndmask_b32_e64 v[GP_CB+\K*\a+\j], 1.0, v[12+((\j+2)&3)], s[68+2*\j:69+2*\j]
+  v_cndmask_b32_e64 v[GP_CB+\K*\r+\j], 1.0, v[12+((\j+2)&3)], s[68+2*\j:69+2*\j]
  .endif
  .endr
 .endm
@@ -452,11 +488,11 @@ asm volatile(R"(
 // the first decides the result's sign: the top is the first source of + and
 // *, a constant the first of all.)
 .macro GP_PUSHES tab, K, blk, d, last
- .org \tab + 68544 + 3136*(\blk) + 0
+ .org \tab + 81600 + 3776*(\blk) + 0
   GP_CONST_CELL \K, \d
   GP_LOADNEXT \last
   GP_NEXT \last
- .org \tab + 68544 + 3136*(\blk) + 64
+ .org \tab + 81600 + 3776*(\blk) + 64
   GP_ROW \K, \d
   GP_LOADNEXT \last
   GP_NEXT \last
@@ -464,7 +500,7 @@ asm volatile(R"(
 // vcc / branch to the cold division unless every |operand| <= 2^60, every
 // |dividend| > 2^-60 and every |divisor| > 0.001 (then nothing overflows, no
 // step is denormal and no case is protected)
-.macro GP_DIVRANGE tab, K, blk, a
+.macro GP_DIVRANGE tab, K, blk, a, num, den, cold
  .if \K == 4
   v_max3_f32 v4, |v[GP_CB+4*\a]|, |v[GP_CB+4*\a+1]|, |v[GP_CB+4*\a+2]|
   v_max3_f32 v4, v4, |v[GP_CB+4*\a+3]|, |v[GP_CB+4*\a+4]|
@@ -477,36 +513,47 @@ asm volatile(R"(
   v_max_f32_e64 v4, |v[GP_CB+\a]|, |v[GP_CB+\a+1]|
  .endif
   v_cmp_nge_f32_e32 vcc, 0x5d800000, v4
-  GP_MAGNITUDE \K, \a, min, 5
-  s_cbranch_vccnz \tab\()_\blk\()_cdiv
-  GP_MAGNITUDE \K, (\a+1), min, 6
+  GP_MAGNITUDE \K, \num, min, 5
+  s_cbranch_vccnz \tab\()_\blk\()_\cold
+  GP_MAGNITUDE \K, \den, min, 6
   v_mul_f32_e32 v5, 0x5883126f, v5
   v_min_f32_e32 v5, v5, v6
   v_cmp_nlt_f32_e32 vcc, 0x3a83126f, v5
-  s_cbranch_vccnz \tab\()_\blk\()_cdiv
+  s_cbranch_vccnz \tab\()_\blk\()_\cold
 .endm
 .macro GP_CELLS tab, K, blk, a, last
- .org \tab + 68544 + 3136*(\blk) + 128
+ .org \tab + 81600 + 3776*(\blk) + 128
   GP_LOADNEXT \last
   GP_ALL2 v_add_f32_e32, \K, \a, (\a+1), \a
   GP_NEXT \last
- .org \tab + 68544 + 3136*(\blk) + 192
+ .org \tab + 81600 + 3776*(\blk) + 192
   GP_LOADNEXT \last
   GP_ALL2 v_sub_f32_e32, \K, \a, \a, (\a+1)
   GP_NEXT \last
- .org \tab + 68544 + 3136*(\blk) + 256
+ .org \tab + 81600 + 3776*(\blk) + 256
   GP_LOADNEXT \last
   GP_ALL2 v_mul_f32_e32, \K, \a, (\a+1), \a
   GP_NEXT \last
- .org \tab + 68544 + 3136*(\blk) + 320
+ .org \tab + 81600 + 3776*(\blk) + 320
   GP_LOADNEXT \last
 \tab\()_\blk\()_div:
-  GP_DIVRANGE \tab, \K, \blk, \a
+  GP_DIVRANGE \tab, \K, \blk, \a, \a, (\a+1), cdiv
   GP_DIV \K, \a
+  GP_NEXT \last
+// top minus, top over the element below
+ .org \tab + 81600 + 3776*(\blk) + 608
+  GP_LOADNEXT \last
+  GP_ALL2 v_sub_f32_e32, \K, \a, (\a+1), \a
+  GP_NEXT \last
+ .org \tab + 81600 + 3776*(\blk) + 672
+  GP_LOADNEXT \last
+\tab\()_\blk\()_divr:
+  GP_DIVRANGE \tab, \K, \blk, \a, (\a+1), \a, cdivr
+  GP_DIVR \K, \a
   GP_NEXT \last
 .endm
 .macro GP_CONSTOP tab, K, blk, c, last, off, op
- .org \tab + 68544 + 3136*(\blk) + 0+\off
+ .org \tab + 81600 + 3776*(\blk) + 0+\off
   v_mov_b32_e32 v4, s89
   GP_LOADNEXT \last
  .irp j,0,1,2,3
@@ -517,7 +564,7 @@ asm volatile(R"(
   GP_NEXT \last
 .endm
 .macro GP_ROWOP tab, K, blk, c, last, off, op
- .org \tab + 68544 + 3136*(\blk) + 0+\off
+ .org \tab + 81600 + 3776*(\blk) + 0+\off
   GP_ROW \K, (\c+1)
   GP_LOADNEXT \last
   s_waitcnt lgkmcnt(0)
@@ -525,29 +572,46 @@ asm volatile(R"(
   GP_JUMP \last
 .endm
 .macro GP_LEAFOPS tab, K, blk, c, last, target
-  GP_CONSTOP \tab, \K, \blk, \c, \last, 608, v_add_f32_e32
-  GP_CONSTOP \tab, \K, \blk, \c, \last, 672, v_subrev_f32_e32
-  GP_CONSTOP \tab, \K, \blk, \c, \last, 736, v_mul_f32_e32
- .org \tab + 68544 + 3136*(\blk) + 800
+  GP_CONSTOP \tab, \K, \blk, \c, \last, 960, v_add_f32_e32
+  GP_CONSTOP \tab, \K, \blk, \c, \last, 1024, v_subrev_f32_e32
+  GP_CONSTOP \tab, \K, \blk, \c, \last, 1088, v_mul_f32_e32
+ .org \tab + 81600 + 3776*(\blk) + 1152
   GP_CONST_CELL \K, (\c+1)
   GP_LOADNEXT \last
   s_branch \tab\()_\target\()_div
-  GP_ROWOP \tab, \K, \blk, \c, \last, 832, v_add_f32_e32
-  GP_ROWOP \tab, \K, \blk, \c, \last, 928, v_sub_f32_e32
-  GP_ROWOP \tab, \K, \blk, \c, \last, 1024, v_mul_f32_e32
- .org \tab + 68544 + 3136*(\blk) + 1120
+  GP_ROWOP \tab, \K, \blk, \c, \last, 1184, v_add_f32_e32
+  GP_ROWOP \tab, \K, \blk, \c, \last, 1280, v_sub_f32_e32
+  GP_ROWOP \tab, \K, \blk, \c, \last, 1376, v_mul_f32_e32
+ .org \tab + 81600 + 3776*(\blk) + 1472
   GP_ROW \K, (\c+1)
   GP_LOADNEXT \last
   s_waitcnt lgkmcnt(0)
   s_branch \tab\()_\target\()_div
+// a constant, a row minus or over the top
+  GP_CONSTOP \tab, \K, \blk, \c, \last, 1536, v_sub_f32_e32
+ .org \tab + 81600 + 3776*(\blk) + 1600
+  GP_CONST_CELL \K, (\c+1)
+  GP_LOADNEXT \last
+  s_branch \tab\()_\target\()_divr
+ .org \tab + 81600 + 3776*(\blk) + 1632
+  GP_ROW \K, (\c+1)
+  GP_LOADNEXT \last
+  s_waitcnt lgkmcnt(0)
+  GP_ALL2 v_sub_f32_e32, \K, \c, (\c+1), \c
+  GP_JUMP \last
+ .org \tab + 81600 + 3776*(\blk) + 1728
+  GP_ROW \K, (\c+1)
+  GP_LOADNEXT \last
+  s_waitcnt lgkmcnt(0)
+  s_branch \tab\()_\target\()_divr
 .endm
 .macro GP_UN tab, blk, u, off, last
- .org \tab + 68544 + 3136*(\blk) + 0+\off
+ .org \tab + 81600 + 3776*(\blk) + 0+\off
   GP_LOADNEXT \last
 \tab\()_\blk\()_un\u:
 .endm
 .macro GP_UNARIES tab, K, blk, c, last
-  GP_UN \tab, \blk, 0, 1184, \last
+  GP_UN \tab, \blk, 0, 1792, \last
   GP_SUMTEST \K, \c, 0x48000000
   s_cbranch_vccnz \tab\()_\blk\()_chk1
 \tab\()_\blk\()_go1:
@@ -559,7 +623,7 @@ asm volatile(R"(
   GP_LOGP \K, \c
   GP_NEXT \last
  .endif
-  GP_UN \tab, \blk, 1, 1600, \last
+  GP_UN \tab, \blk, 1, 2208, \last
   GP_SUMTEST \K, \c, 0x48000000
   s_cbranch_vccnz \tab\()_\blk\()_chk2
 \tab\()_\blk\()_go2:
@@ -568,13 +632,20 @@ asm volatile(R"(
  .if (\K == 1) && ((\blk == 0) || (\c >= 1))
 \tab\()_\blk\()_cdiv:
  .if \blk == 0
-  GP_DIVP \K, 0
+  GP_DIVP \K, 0, 1, 0
  .else
-  GP_DIVP \K, (\c-1)
+  GP_DIVP \K, (\c-1), \c, (\c-1)
+ .endif
+  GP_NEXT \last
+\tab\()_\blk\()_cdivr:
+ .if \blk == 0
+  GP_DIVP \K, 1, 0, 0
+ .else
+  GP_DIVP \K, \c, (\c-1), (\c-1)
  .endif
   GP_NEXT \last
  .endif
-  GP_UN \tab, \blk, 2, 2080, \last
+  GP_UN \tab, \blk, 2, 2688, \last
   GP_SUMTEST \K, \c, 0x42ae0000
   s_cbranch_vccnz \tab\()_\blk\()_chk3
 \tab\()_\blk\()_go3:
@@ -583,13 +654,13 @@ asm volatile(R"(
  .if \K == 1
   GP_TOCALLER \tab, \K, \blk, \c
  .endif
-  GP_UN \tab, \blk, 3, 2400, \last
+  GP_UN \tab, \blk, 3, 3008, \last
   GP_MAGNITUDE \K, \c, min, 4
   v_cmp_nlt_f32_e32 vcc, 0x3a83126f, v4
   s_cbranch_vccnz \tab\()_\blk\()_clog
   GP_LOG \K, \c
   GP_NEXT \last
-  GP_UN \tab, \blk, 4, 2592, \last
+  GP_UN \tab, \blk, 4, 3200, \last
   GP_MAGNITUDE \K, \c, min, 4
   v_cmp_nle_f32_e32 vcc, 0x0d800000, v4
   s_cbranch_vccnz \tab\()_\blk\()_slow4
@@ -599,7 +670,7 @@ asm volatile(R"(
  .endif
  .endr
   GP_NEXT \last
-  GP_UN \tab, \blk, 5, 2688, \last
+  GP_UN \tab, \blk, 5, 3296, \last
  .irp j,0,1,2,3
  .if \j < \K
   v_and_b32_e32 v[GP_CB+\K*\c+\j], 0x7fffffff, v[GP_CB+\K*\c+\j]
@@ -609,7 +680,7 @@ asm volatile(R"(
 .endm
 .macro GP_PUSHUNS tab, K, blk, d, last, target
  .irp u,0,1,2,3,4,5
- .org \tab + 68544 + 3136*(\blk) + 2752+64*\u
+ .org \tab + 81600 + 3776*(\blk) + 3360+64*\u
   GP_ROW \K, \d
   GP_LOADNEXT \last
   s_waitcnt lgkmcnt(0)
@@ -630,7 +701,7 @@ asm volatile(R"(
  .endr
 .endm
 .macro GP_LEAVE blk
-  s_mov_b32 s87, 2016*(33-\blk) + 0
+  s_mov_b32 s87, 2400*(33-\blk) + 0
   s_waitcnt lgkmcnt(0)
   s_setpc_b64 s[94:95]
 .endm
@@ -663,7 +734,7 @@ asm volatile(R"(
 .endm
 .macro GP_SLOW tab, K, blk, c, last
 // after a call: the values back into the top
- .org \tab + 2016*(33-\blk) + 0
+ .org \tab + 2400*(33-\blk) + 0
  .irp j,0,1,2,3
  .if \j < \K
   v_mov_b32_e32 v[GP_CB+\K*\c+\j], v[4+\j]
@@ -671,36 +742,40 @@ asm volatile(R"(
  .endr
   GP_JUMP \last
  .if \K > 1
- .org \tab + 2016*(33-\blk) + 32
+ .org \tab + 2400*(33-\blk) + 32
   GP_TOCALLER \tab, \K, \blk, \c
- .org \tab + 2016*(33-\blk) + 96
+ .org \tab + 2400*(33-\blk) + 96
   GP_CHECKS \tab, \K, \blk, \c
  .endif
 .endm
 .macro GP_COLDDIV tab, K, blk, a, last
  .if \K > 1
- .org \tab + 2016*(33-\blk) + 224
+ .org \tab + 2400*(33-\blk) + 224
 \tab\()_\blk\()_cdiv:
-  GP_DIVP \K, \a
+  GP_DIVP \K, \a, (\a+1), \a
+  GP_NEXT \last
+ .org \tab + 2400*(33-\blk) + 608
+\tab\()_\blk\()_cdivr:
+  GP_DIVP \K, (\a+1), \a, \a
   GP_NEXT \last
  .endif
 .endm
 .macro GP_COLDLOG tab, K, blk, c, last
  .if \K > 1
- .org \tab + 2016*(33-\blk) + 608
+ .org \tab + 2400*(33-\blk) + 992
 \tab\()_\blk\()_clog:
   GP_LOGP \K, \c
   GP_NEXT \last
  .endif
 .endm
 .macro GP_DUP tab, K, blk, d
- .org \tab + 2016*(33-\blk) + 800
+ .org \tab + 2400*(33-\blk) + 1184
   GP_LOADNEXT 0
   GP_COPY_CELL \K, \d, (\d-1)
   GP_NEXT 0
 .endm
 .macro GP_SWAPDEL tab, K, blk, d
- .org \tab + 2016*(33-\blk) + 864
+ .org \tab + 2400*(33-\blk) + 1248
   GP_LOADNEXT 0
  .irp j,0,1,2,3
  .if \j < \K
@@ -708,7 +783,7 @@ asm volatile(R"(
  .endif
  .endr
   GP_NEXT 0
- .org \tab + 2016*(33-\blk) + 928
+ .org \tab + 2400*(33-\blk) + 1312
   GP_LOADNEXT 0
   GP_NEXT 0
 .endm
@@ -720,7 +795,7 @@ asm volatile(R"(
 .endm
 // COPY: the variable's cell = the top
 .macro GP_COPYVAR tab, K, maxd, blk, c
- .org \tab + 2016*(33-\blk) + 960
+ .org \tab + 2400*(33-\blk) + 1344
   GP_VARCELL \K, \maxd, s96, 0
   GP_LOADNEXT 0
   s_set_gpr_idx_on s96, gpr_idx(DST)
@@ -735,7 +810,7 @@ asm volatile(R"(
 // PASTE: push the variable in cell byte 0; then the cell of byte 1 moves into
 // it (the same cell when nothing moves)
 .macro GP_PASTE tab, K, maxd, blk, d, last
- .org \tab + 2016*(33-\blk) + 1056
+ .org \tab + 2400*(33-\blk) + 1440
   GP_VARCELL \K, \maxd, s96, 0
   GP_VARCELL \K, \maxd, s97, 8
   GP_LOADNEXT \last
@@ -768,11 +843,11 @@ asm volatile(R"(
   GP_NEXT \last
 .endm
 .macro GP_EXTUN tab, K, blk, c, last
- .org \tab + 2016*(33-\blk) + 1216
+ .org \tab + 2400*(33-\blk) + 1600
   GP_LOADNEXT \last
   GP_ALL2 v_mul_f32_e32, \K, \c, \c, \c
   GP_NEXT \last
- .org \tab + 2016*(33-\blk) + 1280
+ .org \tab + 2400*(33-\blk) + 1664
   GP_LOADNEXT \last
  .irp j,0,1,2,3
  .if \j < \K
@@ -780,18 +855,18 @@ asm volatile(R"(
  .endif
  .endr
   GP_NEXT \last
- .org \tab + 2016*(33-\blk) + 1344
+ .org \tab + 2400*(33-\blk) + 1728
   GP_LOADNEXT \last
   GP_CUBE \K, \c
   GP_NEXT \last
- .org \tab + 2016*(33-\blk) + 1472
+ .org \tab + 2400*(33-\blk) + 1856
   GP_LOADNEXT \last
   GP_MAGNITUDE \K, \c, min, 4
   v_cmp_nle_f32_e32 vcc, 0x0d800000, v4
   s_cbranch_vccnz \tab\()_\blk\()_slow11
   GP_SQRTRAW \K, \c
   GP_NEXT \last
- .org \tab + 2016*(33-\blk) + 1664
+ .org \tab + 2400*(33-\blk) + 2048
  .irp n,5,6,7,8,9,10
   s_mov_b32 s83, \n
   s_branch \tab\()_\blk\()_lib
@@ -808,7 +883,7 @@ asm volatile(R"(
 // POW of the cells \a, \a+1 (the top): both to the caller, the result into \a
 // (the finish code of the block one element less deep)
 .macro GP_POWCELLS tab, K, blk, a, last, lower
- .org \tab + 2016*(33-\blk) + 1792
+ .org \tab + 2400*(33-\blk) + 2176
   GP_LOADNEXT \last
 \tab\()_\blk\()_pow:
  .irp j,0,1,2,3
@@ -821,11 +896,11 @@ asm volatile(R"(
   GP_LEAVE \lower
 .endm
 .macro GP_POWLEAF tab, K, blk, c, last, target
- .org \tab + 2016*(33-\blk) + 1888
+ .org \tab + 2400*(33-\blk) + 2272
   GP_CONST_CELL \K, (\c+1)
   GP_LOADNEXT \last
   s_branch \tab\()_\target\()_pow
- .org \tab + 2016*(33-\blk) + 1952
+ .org \tab + 2400*(33-\blk) + 2336
   GP_ROW \K, (\c+1)
   GP_LOADNEXT \last
   s_waitcnt lgkmcnt(0)
@@ -906,7 +981,7 @@ asm volatile(R"(
  .p2align 8
  .skip 32
 \tab\()_first:
- .set \tab, \tab\()_first - 2016*(33 - \maxd - 1)
+ .set \tab, \tab\()_first - 2400*(33 - \maxd - 1)
  .if \maxd == 32
   GP_COLDBLOCK \tab, \K, 32, 32, 33, 34
   GP_EIGHTDOWN GP_COLDBLOCK, \tab, \K, \maxd, 24, 25, 26, 27, 28, 29, 30, 31, 32, 33
@@ -924,7 +999,7 @@ asm volatile(R"(
   GP_SLOW \tab, \K, 0, 0, 1
   GP_COLDDIV \tab, \K, 0, 0, 1
   GP_COLDLOG \tab, \K, 0, 0, 1
- .org \tab + 2016*(33-0) + 928
+ .org \tab + 2400*(33-0) + 1312
   GP_NEXT 1
   GP_PASTE \tab, \K, \maxd, 0, 0, 1
   GP_EXTUN \tab, \K, 0, 0, 1

@@ -39,24 +39,27 @@
 // or the cells of a variable move.
 #pragma once
 
-constexpr uint32_t kThHot = 3136u, kThCold = 2016u;     // bytes of a block
+constexpr uint32_t kThHot = 3776u, kThCold = 2400u;     // bytes of a block
 constexpr uint32_t kThHot0 = 34u * kThCold;             // hot blocks start here, upwards
 constexpr uint32_t kThPushC = 0u;            // push a constant
 constexpr uint32_t kThPushV = 64u;           // push an input row
 constexpr uint32_t kThBin = 128u;            // + - * /: two stack cells (64 bytes each, / longer)
-constexpr uint32_t kThBinC = 608u;           // top OP constant (64 bytes each)
-constexpr uint32_t kThBinV = 832u;          // top OP input row (96 bytes each)
-constexpr uint32_t kThPushUn = 2752u;        // push f(input row) (64 bytes each)
+constexpr uint32_t kThBinC = 960u;           // top OP constant (64 bytes each)
+constexpr uint32_t kThBinV = 1184u;          // top OP input row (96 bytes each)
+// - and / with the top as the left operand: two cells; a constant; a row
+constexpr uint32_t kThSubR = 608u, kThDivR = 672u, kThSubCR = 1536u, kThDivCR = 1600u;
+constexpr uint32_t kThSubVR = 1632u, kThDivVR = 1728u;
+constexpr uint32_t kThPushUn = 3360u;        // push f(input row) (64 bytes each)
 // sin cos exp ln sqrt abs of the top: offsets in units of 32, one byte each
-constexpr uint64_t kThUnary = 0x54514B413225ull;
+constexpr uint64_t kThUnary = 0x67645E544538ull;
 // beyond the benchmark set: offsets in the cold block, marked
 constexpr uint32_t kThColdBit = 0x8000u;
-constexpr uint32_t kThDup = kThColdBit + 800u, kThSwap = kThColdBit + 864u, kThDel = kThColdBit + 928u;
-constexpr uint32_t kThCopy = kThColdBit + 960u, kThPaste = kThColdBit + 1056u;
-constexpr uint32_t kThSquare = kThColdBit + 1216u, kThSign = kThColdBit + 1280u, kThCube = kThColdBit + 1344u;
-constexpr uint32_t kThSqrtRaw = kThColdBit + 1472u;
-constexpr uint32_t kThLibrary = kThColdBit + 1664u;     // cbrt tan asin acos atan tanh: 8 bytes each
-constexpr uint32_t kThPow = kThColdBit + 1792u, kThPowC = kThColdBit + 1888u, kThPowV = kThColdBit + 1952u;
+constexpr uint32_t kThDup = kThColdBit + 1184u, kThSwap = kThColdBit + 1248u, kThDel = kThColdBit + 1312u;
+constexpr uint32_t kThCopy = kThColdBit + 1344u, kThPaste = kThColdBit + 1440u;
+constexpr uint32_t kThSquare = kThColdBit + 1600u, kThSign = kThColdBit + 1664u, kThCube = kThColdBit + 1728u;
+constexpr uint32_t kThSqrtRaw = kThColdBit + 1856u;
+constexpr uint32_t kThLibrary = kThColdBit + 2048u;     // cbrt tan asin acos atan tanh: 8 bytes each
+constexpr uint32_t kThPow = kThColdBit + 2176u, kThPowC = kThColdBit + 2272u, kThPowV = kThColdBit + 2336u;
 
 // Result codes of a handler that hands values to the caller (0: the program
 // has ended).
@@ -99,6 +102,20 @@ struct ThreadedWords {
     static __host__ __device__ uint2 cells(int rt, uint32_t sel)
     {
         return make_uint2(at(rt, sel == kBinPow ? kThPow : kThBin + 64u * sel), 0u);
+    }
+    // the same with the operands exchanged: the row, the constant, the top is
+    // the left one (sel 1: -, else /; + and * do not tell)
+    static __host__ __device__ uint2 row_top(int rt, uint32_t sel, uint32_t payload)
+    {
+        return make_uint2(at(rt, sel == 1u ? kThSubVR : kThDivVR), payload);
+    }
+    static __host__ __device__ uint2 const_top(int rt, uint32_t sel, uint32_t bits)
+    {
+        return make_uint2(at(rt, sel == 1u ? kThSubCR : kThDivCR), bits);
+    }
+    static __host__ __device__ uint2 cells_top(int rt, uint32_t sel)
+    {
+        return make_uint2(at(rt, sel == 1u ? kThSubR : kThDivR), 0u);
     }
     static __host__ __device__ uint2 unary(int rt, uint32_t sel) { return make_uint2(at(rt, un(sel)), 0u); }
     // DUP, SWAP, DEL: `off` is the command's; COPY and PASTE with their cells

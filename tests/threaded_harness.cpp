@@ -73,7 +73,7 @@ struct Reader {
 // offset of a flag word's operator in its block, and its change of depth
 static uint32_t offset_of(uint32_t f, int* change)
 {
-    static const uint32_t un[6] = {1184, 1600, 2080, 2400, 2592, 2688};
+    static const uint32_t un[6] = {1792, 2208, 2688, 3008, 3200, 3296};
     const uint32_t sel = (f >> 8) & 0xFu;
     *change = 0;
     if (f & kFUn) {
@@ -128,7 +128,7 @@ int main(int argc, char** argv)
             const uint32_t at = b[k].x - kThHot0, blk = at / kThHot, o = at % kThHot;
             const int need = change < 0 ? 2 : (change > 0 ? 0 : 1);
             // a leaf taken as an operand sits in the cell above the top
-            const bool leaf_op = o >= kThBinC && o < kThBinV + 352u;
+            const bool leaf_op = o >= kThBinC && o < kThSubCR;
             if (o != want || b[k].y != a[k].y || blk != (last ? 0u : (uint32_t)(d + 1)) ||
                 last != (k == n1 - 1) || d < need || d + (change > 0) > maxd ||
                 (leaf_op && d + 1 > maxd))
