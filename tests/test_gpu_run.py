@@ -151,3 +151,22 @@ def test_full_table_around_a_chunk(length):
     nan = np.isnan(want)
     assert np.array_equal(np.isnan(out), nan)
     assert np.array_equal(out.view(np.uint32)[~nan], want.view(np.uint32)[~nan])
+
+
+@pytest.mark.parametrize("power", [1, 2, 3, 8])
+@pytest.mark.parametrize("M", [10000.0, -7.0, 2.0 ** 21, 2.0 ** 21 + 1, 2.0 ** 24])
+def test_rewards_at_the_fast_range(power, M):
+    """Ratios of values around the bounds of the reward's fast form, among
+    themselves and alone among ordinary values, signs mixed: integers, exact."""
+    gp = _gp()
+    rng = np.random.default_rng(power)
+    v = _edges(2.0 ** -10, 2.0 ** -60, 2.0 ** 60, 1.0, 3.0)
+    a, b = (g.ravel() for g in np.meshgrid(v, v))
+    o = rng.uniform(-4, 4, 256 * a.size).astype(np.float32)
+    y = rng.uniform(-4, 4, o.size).astype(np.float32)
+    at = np.arange(a.size) * 256 + rng.integers(0, 256, a.size)
+    o[at], y[at] = a, b
+    nodes, off = np.array([synth.LOAD], np.uint32), np.array([0, 1], np.int64)
+    for x, t in ((a, b), (o, y), (o[1:256], y[1:256])):
+        R = gp.evaluate_reward(nodes, off, np.ones(1, np.float32), x[None, :], t, M, power)
+        assert R[0] == oracle.case_rewards(x, t, M, power).sum()
