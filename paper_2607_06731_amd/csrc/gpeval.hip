@@ -96,7 +96,11 @@ namespace {
 
 // ------------------------------------------------------------------ layout
 constexpr int kClasses = 3;              // max depth <= 8, <= 16, <= 32
-constexpr int kLenBuckets = 8;           // staged length 1, 2-3, ..., 64-127, 128+
+// Bands of a program's cost, four per octave from 8 to 128 words' worth: an
+// item's programs are of one band, so its wavefronts end together.  (Eight
+// bands of one octave of length each: at 10,000 programs x 4,096 cases the
+// wavefronts waited 14% of the time at barriers for the longest.)
+constexpr int kLenBuckets = 16;
 constexpr int kKeys = kClasses * kLenBuckets;
 constexpr int kMaxTiles = 32;            // case tiles per program (cap)
 // The serial staging walks' limits (staging.h): constants held back for
@@ -754,8 +758,9 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, co
                                           const float* __restrict__ consts, int64_t n_consts,
                                           uint32_t allowed, int32_t n_vars,
                                           uint2* __restrict__ dst, WaveTables* tb, int lane,
-                                          int* cls, int* n_words)
+                                          int* cls, int* n_words, int* cost)
 {
+    int extra = 0;                         // what the operators take beyond a word each
     int depth = 0, rt_in = 0, n = 0;       // after the chunks before: stack, runtime, words
     int live_in = 0;                       // held variables
     bool prev_load = false;
@@ -825,6 +830,11 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, co
         code = op < 32u && ((allowed >> (op & 31u)) & 1u) ? code : GP_PROG_BAD_OP;
         const uint64_t bad = __ballot(live && code != GP_PROG_OK);
         if (bad != 0ull) return lane_value(code, __builtin_ctzll(bad));
+        // (clocks per word and four cases: 24 for the cheapest, division, sine and
+        // cosine four to five times that, the other functions two to three)
+        extra += 3 * (int)__popcll(__ballot(op == GP_DIV)) + 4 * (int)__popcll(__ballot(op - GP_SIN < 2u)) +
+                 2 * (int)__popcll(__ballot(op - GP_SIN - 2u < 3u));
+        if constexpr (EXT) extra += 12 * (int)__popcll(__ballot(pw || (live && op >= GP_CBRT && op_is_unary(op))));
         over8 |= __ballot(live && used > 8) != 0ull;
         over16 |= __ballot(live && used > 16) != 0ull;
 
@@ -948,6 +958,7 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, co
     if (lane == 0) dst[held_at] = ThreadedWords::last(held);
     *cls = over16 ? 2 : over8;
     *n_words = n;
+    *cost = n + extra;
     return GP_PROG_OK;
 }
 
@@ -961,7 +972,7 @@ __device__ __forceinline__ int stage_program(const uint32_t* __restrict__ nodes,
                                              const float* __restrict__ consts, int64_t n_consts,
                                              uint32_t allowed, int32_t n_vars, uint2* __restrict__ dst,
                                              WaveTables* tb, int64_t n_cases, uint32_t* turned, int lane, int* cls,
-                                             int* n_words, bool* narrow)
+                                             int* n_words, int* cost, bool* narrow)
 {
     const uint32_t* from = nullptr;
     int first = -1;
@@ -969,7 +980,7 @@ __device__ __forceinline__ int stage_program(const uint32_t* __restrict__ nodes,
     for (;;) {
         int c = 0;
         const int status = stage_wave<EXT>(nodes, from, len, consts, n_consts, allowed, n_vars, dst, tb, lane, &c,
-                                           n_words);
+                                           n_words, cost);
         if (first >= 0) {
             *cls = first == 2 ? 2 : c;
             *narrow = first == 2 && c == 0;
@@ -988,13 +999,12 @@ __device__ __forceinline__ int stage_program(const uint32_t* __restrict__ nodes,
 }
 
 // Per staging block: programs per partition key, and whether some program's
-// offsets decrease.  The rows live in the partials' memory (8 bytes per
-// program at least), which nothing uses before the evaluation.
+// offsets decrease.
 struct StageRow {
     uint16_t cnt[kKeys];
     uint16_t down, pad;
 };
-static_assert(sizeof(StageRow) == 52, "StageRow layout");
+static_assert(sizeof(StageRow) == 100, "StageRow layout");
 constexpr int kStageWaves = 8;
 constexpr int kStageBlocks = 1024;       // two workgroups of 8 wavefronts on every SIMD pair
 
@@ -1004,6 +1014,12 @@ inline int64_t stage_share(int64_t n_programs)
 {
     const int64_t c = (n_programs + kStageBlocks - 1) / kStageBlocks;
     return c < kStageWaves ? kStageWaves : (c > 32768 ? 32768 : c);
+}
+
+inline int64_t stage_blocks(int64_t n_programs)
+{
+    const int64_t share = stage_share(n_programs);
+    return (n_programs + share - 1) / share;
 }
 
 // What the two staging kernels share.  A call of one request brings its
@@ -1111,7 +1127,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
     for (int64_t p = p0 + wave; p < p1; p += kStageWaves) {
         const ProgRange g = program_range(a, p, tab_ok);
         const bool range_ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
-        int status, c = -1, n = 0;
+        int status, c = -1, n = 0, cost = 0;
         bool narrow = false;
         if (!tab_ok) status = GP_PROG_BAD_TABLE;
         else if (!range_ok) status = GP_PROG_BAD_OFFSETS;
@@ -1119,7 +1135,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
         else
             status = stage_program<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
                                         g.n_vars, a.code + g.node_base + g.s, &tables[wave], g.n_cases, turned[wave], lane,
-                                        &c, &n, &narrow);
+                                        &c, &n, &cost, &narrow);
         if (status != GP_PROG_OK) {
             c = -1;
             n = 0;
@@ -1132,12 +1148,13 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
             m.slen = narrow ? n | kNarrow : n;
             a.meta[p] = m;
             a.pds[p] = g.r;
-            // partition key: depth class, then (single-request calls) length
-            // band from longest to shortest; with several requests the order
+            // partition key: depth class, then (single-request calls) cost
+            // band from dearest to cheapest; with several requests the order
             // inside a class stays the input order, so each request's
             // programs stay together
-            int lb = 31 - __clz((uint32_t)(n > 0 ? n : 1));
-            lb = lb < kLenBuckets - 1 ? lb : kLenBuckets - 1;
+            const uint32_t w = (uint32_t)(cost > 1 ? cost : 1), z = __clz(w);
+            int lb = (int)(((31u - z) << 2) + ((w << z) >> 29 & 3u)) - 12;      // 4 log2(w / 8)
+            lb = lb < 0 ? 0 : (lb < kLenBuckets ? lb : kLenBuckets - 1);
             const int key = c >= 0 ? c * kLenBuckets + (a.lpt ? kLenBuckets - 1 - lb : 0) : 0xFF;
             a.cls[p] = (uint8_t)key;
             if (c >= 0) atomicAdd(&cnt[key], 1);
@@ -1152,7 +1169,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
 
 // Pass 2, same blocks: every block sums the key counts of the blocks before
 // it (and of all), so the partition needs no scan of its own; program ids are
-// scattered stably by (depth class, length band); block 0 writes the class
+// scattered stably by (depth class, cost band); block 0 writes the class
 // ranges, clears the work counter and, for a single request, writes its
 // per-class tables (class_seg_tables with one segment).
 // Offsets that decrease somewhere let programs' node ranges overlap: then
@@ -1227,11 +1244,11 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
                 for (int64_t q = p0; q < p; ++q) start += a.meta[q].slen & ~kNarrow;
                 if (a.cls[p] >= kKeys) continue;
                 const ProgRange g = program_range(a, p, true);
-                int c = 0, n = 0;
+                int c = 0, n = 0, cost = 0;
                 bool narrow = false;
                 (void)stage_program<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
                                          g.n_vars, a.code + start, &tables[wave], g.n_cases, turned[wave], lane, &c, &n,
-                                         &narrow);
+                                         &cost, &narrow);
                 if (lane == 0) a.meta[p].start = start;
             }
         }
@@ -2319,7 +2336,7 @@ __global__ __launch_bounds__(256) void k_reduce_reward(ReduceArgs a)
 
 // ----------------------------------------------------------- workspaces
 struct Layout {
-    size_t code, meta, cls, order, class_info, class_g, counter;
+    size_t code, meta, cls, order, class_info, class_g, counter, rows;
     size_t part, part_bad;
     size_t ds, req, seg_ds, seg_start, seg_cnt, seg_pos, item_pre, pds, bad, total;
 };
@@ -2353,6 +2370,7 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.item_pre = off;   off = align_up(off + (size_t)kClasses * (n_seg + 1) * 4);
     L.pds = off;        off = align_up(off + (size_t)n_programs * 4);
     L.bad = off;        off = align_up(off + 4);
+    L.rows = off;       off = align_up(off + (size_t)stage_blocks(n_programs) * sizeof(StageRow));
     L.total = off;
     return L;
 }
@@ -2366,6 +2384,7 @@ struct Staged {
     int32_t* class_info;
     int32_t* class_g;
     uint32_t* counter;
+    StageRow* rows;
     float2* part;
     uint8_t* part_bad;
     CorrPart* part_corr;            // the same memory as part, correlation mode
@@ -2391,6 +2410,7 @@ Staged carve(void* base, const Layout& L)
     st.class_info = reinterpret_cast<int32_t*>(ws + L.class_info);
     st.class_g = reinterpret_cast<int32_t*>(ws + L.class_g);
     st.counter = reinterpret_cast<uint32_t*>(ws + L.counter);
+    st.rows = reinterpret_cast<StageRow*>(ws + L.rows);
     st.part = reinterpret_cast<float2*>(ws + L.part);
     st.part_corr = reinterpret_cast<CorrPart*>(ws + L.part);
     st.part_bad = reinterpret_cast<uint8_t*>(ws + L.part_bad);
@@ -2653,7 +2673,7 @@ int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
 }
 
 // Dataset/segment tables, validation, staging and the stable (depth class,
-// length) partition.
+// cost) partition.
 int enqueue_tables(const Problem& pb, const Tuning& tu, const Staged& st, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_tables, dim3(1), dim3(256), 0, stream, pb.ds_dev, pb.n_ds, pb.one,
@@ -2679,7 +2699,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     a.n_seg = pb.n_req;
     a.ds = st.ds; a.reqs = st.req; a.seg_ds = st.seg_ds; a.seg_start = st.seg_start; a.bad = st.bad;
     a.meta = st.meta; a.cls = st.cls; a.pds = st.pds; a.order = st.order; a.code = st.code;
-    a.rows = reinterpret_cast<StageRow*>(st.part);
+    a.rows = st.rows;
     if (a.single) {
         const gp_request& q = pb.one_req;
         a.one_req = DevRequest{q.nodes, q.offsets, q.consts, q.n_programs, q.n_nodes, q.n_consts, 0,
@@ -2688,7 +2708,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     } else if ((rc = enqueue_tables(pb, tu, st, stream)) != GP_OK) {
         return rc;
     }
-    const int32_t n_blk = (int32_t)((pb.n_programs + a.share - 1) / a.share);
+    const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
     const SegOut so{group_capacity(pb, tu), el.target_items, el.lds_floats, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
     if (pb_ext(pb.allowed)) {
