@@ -17,7 +17,7 @@
 //                    request) its per-class work-item tables.
 //   k_seg_tables     several requests: per (class, request) program counts,
 //                    positions and work-item prefixes.
-//   k_run<FIT>       persistent workgroups take (program chunk, case tiles)
+//   k_run<FIT, SPLIT>       persistent workgroups take (program chunk, case tiles)
 //                    items of every depth class (max depth <= 8, <= 16,
 //                    <= 32) from an atomic counter; the tiles' inputs and
 //                    targets are staged in LDS; each wavefront takes the
@@ -584,7 +584,8 @@ __host__ __device__ inline int32_t item_tiles(int32_t passes, int32_t n_tiles, i
 __host__ __device__ inline int32_t item_groups(int32_t n_tiles, int32_t m) { return (n_tiles + m - 1) / m; }
 
 // Per depth class c, from its programs per segment (seg_cnt[c * n_seg +
-// s]): the cut (class_g[c], class_g[kClasses + c]) and, per segment, where
+// s]): the cut (class_g[c], class_g[kClasses + c]; class_g[2 kClasses + c]: cases
+// are split) and, per segment, where
 // its programs start inside the class's range of `order` and the prefix of
 // work items.
 __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict__ seg_cnt,
@@ -607,6 +608,7 @@ __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict
     const int32_t G = cut_programs(runs, g_max, target_items);
     class_g[c] = G;
     class_g[kClasses + c] = m_cap;
+    class_g[2 * kClasses + c] = 0;
     int32_t pos = 0;
     uint32_t items = 0;
     for (int s = 0; s < n_seg; ++s) {
@@ -1177,7 +1179,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
 // staged programs need more than n_nodes words in total (no program of the
 // call is staged then).
 struct SegOut {
-    int32_t g_max, target_items, lds_floats;
+    int32_t g_max, target_items, lds_floats, split, free_outputs;
     int32_t* seg_cnt;
     int32_t* seg_pos;
     uint32_t* item_pre;
@@ -1185,6 +1187,33 @@ struct SegOut {
     int32_t* class_info;
     uint32_t* counter;
 };
+
+// A class of fewer (program, tile) pairs than the GPU holds wavefronts ends
+// with its longest program: its pairs are split into units of 256 cases, which
+// wavefronts take one by one, leaving the program's outputs in LDS; the one
+// that finishes a program's last unit sums them up, in the order of a whole
+// run.  gp_predict has nothing to sum and splits always.  Returns the programs
+// per item, 0 for no split.  (us per call: 1,000 programs x 1,024 cases 44 ->
+// 35; the whole command table, 2,000 x 2,048, 94 -> 74; outputs of 1,000 x 16,384
+// 110 -> 101.  10,000 x 4,096, 6.5 pairs per wavefront: 268 either way.)
+constexpr int kSplitMax = 8;             // programs per item
+__device__ inline int32_t split_programs(const DevDataset& D, int c, int32_t count, const SegOut& so)
+{
+    const int64_t tile = (int64_t)D.passes[c] * sub_cases(c);
+    const int32_t stride = (int32_t)((min(tile, D.n_cases) + 255) & ~(int64_t)255), units = stride >> 8;
+    if (units < 2) return 0;
+    int32_t most = min(so.g_max, kSplitMax);
+    if (!so.free_outputs) {
+        if ((double)count * (double)D.n_tiles[c] > kGpuWaves) return 0;
+        most = min(most, (so.lds_floats - (D.n_vars + 1) * stride) / stride);
+        if (most < 1) return 0;
+    }
+    int32_t G = max(kRunWaves / units, 1);
+    while (G > most) G >>= 1;
+    while (2 * G <= most && (double)count * (double)D.n_tiles[c] / G > (double)(so.target_items / 4)) G *= 2;
+    return G;
+}
+
 constexpr int kOrderWG = 256;
 template <bool EXT>
 __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
@@ -1278,11 +1307,14 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
             // (items over the same cases follow each other without a barrier, so
             // small ones cost nothing and end the launch evenly)
             const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars);
-            const int32_t G = cut_programs((double)count * (double)groups,
+            int32_t G = cut_programs((double)count * (double)groups,
                                            whole && so.g_max > kRunOn ? kRunOn : so.g_max, so.target_items);
             so.seg_cnt[t] = count;
+            const int32_t split = so.split && whole && m == 1 ? split_programs(a.one_ds, t, count, so) : 0;
+            if (split) G = split;
             so.class_g[t] = G;
             so.class_g[kClasses + t] = m_cap;
+            so.class_g[2 * kClasses + t] = split != 0;
             so.seg_pos[t] = 0;
             so.item_pre[2 * t] = 0u;
             so.item_pre[2 * t + 1] = (uint32_t)((count + G - 1) / G) * (uint32_t)groups;
@@ -1819,15 +1851,23 @@ __device__ __forceinline__ void add_cases(const float (&f)[NJ], const float* yt,
     }
 }
 
+enum : int { kAll = 0, kKeep = 1, kSum = 2 };
 // Runs one program of depth class C (3: of class 2, with the first class's
-// handlers) over the staged piece; acc is its
+// handlers) over cases [from, to) of the staged piece, or keeps their outputs
+// (kKeep) or sums the kept ones (kSum); acc is its
 // running tile sum in LDS (correlation always; the others only when a tile
 // goes on past the piece).
-template <int FIT, int C>
+template <int FIT, int C, bool SPLIT>
 __device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float* xt, const RunArgs& a,
                                           const Item& it, const ThreadConsts& tc, int lane, void* acc,
-                                          uint32_t* acc_bad)
+                                          uint32_t* acc_bad, int from, int to, int mode, float* kept)
 {
+    if (!SPLIT || FIT == kFitPredict) mode = kAll;
+    if (!SPLIT) {
+        from = 0;
+        to = it.cases;
+    }
+
     constexpr int SUB = sub_cases(C == 3 ? 2 : C);
     constexpr int NJ = SUB / 64;
     const float* yt = xt + (int64_t)it.n_vars * it.stride;
@@ -1917,12 +1957,23 @@ __device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float*
         }
     };
 
-    for (int pos = 0; pos < it.cases;) {
+    for (int pos = from; pos < to;) {
         const float* xl = xt + pos + lane;
+        float* kl = kept + pos + lane;
         if constexpr (C == 3) {
             // two sub-tiles at once (pos is a multiple of 256, like a row)
             float f[4];
-            run_threaded<8, 4>(pc, xl, it.stride >> 8, tc, f);
+            if (mode != kSum) run_threaded<8, 4>(pc, xl, it.stride >> 8, tc, f);
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f[j] = kl[j * 64];
+            }
+            if (mode == kKeep) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) kl[j * 64] = f[j];
+                pos += 2 * SUB;
+                continue;
+            }
             const float f0[2] = {f[0], f[1]}, f1[2] = {f[2], f[3]};
             add_cases<FIT, 2>(f0, yt + pos, it.cases - pos, lane, a, it, s, out + pos);
             close(pos + SUB);
@@ -1935,12 +1986,23 @@ __device__ __forceinline__ void run_piece(const uint2* pc, int pid, const float*
         }
         float f[NJ];
         constexpr int K = C == 0 ? 4 : (C == 1 ? 2 : 1);
+        if (mode != kSum) {
 #pragma unroll
-        for (int h = 0; h < NJ; h += K) {
-            float v[K];
-            run_threaded<C == 0 ? 8 : (C == 1 ? 16 : 32), K>(pc, xl + h * 64, it.stride >> 8, tc, v);
+            for (int h = 0; h < NJ; h += K) {
+                float v[K];
+                run_threaded<C == 0 ? 8 : (C == 1 ? 16 : 32), K>(pc, xl + h * 64, it.stride >> 8, tc, v);
 #pragma unroll
-            for (int j = 0; j < K; ++j) f[h + j] = v[j];
+                for (int j = 0; j < K; ++j) f[h + j] = v[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) f[j] = kl[j * 64];
+        }
+        if (mode == kKeep) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) kl[j * 64] = f[j];
+            pos += SUB;
+            continue;
         }
         add_cases<FIT, NJ>(f, yt + pos, it.cases - pos, lane, a, it, s, out + pos);
         close(pos + SUB);
@@ -2014,7 +2076,7 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
 // Bound by vector issue (threaded.h): 80 registers hold 32 of stack, 16 of
 // temporaries and the epilogue's, for six wavefronts per SIMD; the
 // correlation sums take more.
-template <int FIT>
+template <int FIT, bool SPLIT>
 __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs a)
 {
     extern __shared__ float lds[];
@@ -2022,6 +2084,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
     char* accs = reinterpret_cast<char*>(lds + a.lds_floats);
     __shared__ uint32_t s_next, s_end, s_pending; // programs taken and listed; the next item
     __shared__ uint4 s_prog[kListed];             // listed programs: code, id, words
+    __shared__ uint32_t s_done[kSplitMax];        // units of a program that are done
     const ThreadConsts tc = thread_consts();
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2046,6 +2109,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int d = as_const(a.seg_ds)[sl];
         const const_ptr<DevDataset> D = as_const(a.ds) + d;
         const int G = as_const(a.class_g)[c], m_cap = as_const(a.class_g)[kClasses + c];
+        const bool split = SPLIT && as_const(a.class_g)[2 * kClasses + c] != 0;
         const int passes = D->passes[c], n_tiles = D->n_tiles[c], n_vars = D->n_vars;
         const int sub = sub_cases(c);
         const int64_t n_cases = D->n_cases;
@@ -2102,6 +2166,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 s_next = 0u;
                 s_end = (uint32_t)it.count;
             }
+            if (split && tid < kSplitMax) s_done[tid] = 0u;
             if (f0 != staged || d != staged_d || it.cases != staged_n) {
                 // one wavefront per 256 cases of a row; MSE mode stores the
                 // targets pre-scaled (an exact power of two)
@@ -2148,27 +2213,8 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 return (int)__builtin_amdgcn_readfirstlane(
                     __hip_atomic_load(&s_end, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             };
-            auto run = [&](int g, bool more) {
-                if (f0 == first && g % G == 0) {
-                    // the chunk's first program: the workgroup's next item
-                    uint32_t next = n_items;
-                    if (n_items > gridDim.x) {
-                        if (lane == 0) next = gridDim.x + atomicAdd(a.work_counter, 1u);
-                        next = __builtin_amdgcn_readfirstlane(next);
-                    }
-                    if (more && whole && next < item1 && g + 2 * G <= kListed) {
-                        const int at = (int)(next - item0) * G, n = min(G, count - at);
-                        const uint32_t t = list_chunk(a, seg0 + at, n, G, lane, s_prog + g + G);
-                        asm volatile("" ::"v"(t));
-                        // (a wavefront's LDS writes land in order)
-                        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                        if (lane == 0)
-                            __hip_atomic_store(&s_end, (uint32_t)(g + G + n), __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_WORKGROUP);
-                    } else if (lane == 0) {
-                        s_pending = next;
-                    }
-                }
+            // the program at place g of the list, over cases [from, to)
+            auto run_cases = [&](int g, int from, int to, int mode, float* kept) {
                 const uint4 pr = s_prog[g];
                 const int pid = __builtin_amdgcn_readfirstlane((int)pr.z);
                 const int slen = __builtin_amdgcn_readfirstlane((int)pr.w);
@@ -2185,28 +2231,85 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                     acc = reinterpret_cast<float2*>(accs) + slot;
                     acc_bad = reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax) + slot;
                 }
-                if (c == 0) run_piece<FIT, 0>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
-                else if (c == 1) run_piece<FIT, 1>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
-                else if (slen < 0) run_piece<FIT, 3>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
-                else run_piece<FIT, 2>(pc, pid, xt, a, it, tc, lane, acc, acc_bad);
+                if (c == 0) run_piece<FIT, 0, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
+                else if (c == 1) run_piece<FIT, 1, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
+                else if (slen < 0) run_piece<FIT, 3, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
+                else run_piece<FIT, 2, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
             };
+            auto take_next = [&] {
+                uint32_t next = n_items;
+                if (n_items > gridDim.x) {
+                    if (lane == 0) next = gridDim.x + atomicAdd(a.work_counter, 1u);
+                    next = __builtin_amdgcn_readfirstlane(next);
+                }
+                return next;
+            };
+            // the chunk's first program: the workgroup's next item, listed behind
+            // the chunk when it is over the same cases
+            auto follow = [&](int g, bool more) {
+                const uint32_t next = take_next();
+                if (more && whole && next < item1 && g + 2 * G <= kListed) {
+                    const int at = (int)(next - item0) * G, n = min(G, count - at);
+                    const uint32_t t = list_chunk(a, seg0 + at, n, G, lane, s_prog + g + G);
+                    asm volatile("" ::"v"(t));
+                    // (a wavefront's LDS writes land in order)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    if (lane == 0)
+                        __hip_atomic_store(&s_end, (uint32_t)(g + G + n), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                } else if (lane == 0) {
+                    s_pending = next;
+                }
+            };
+            // A claim is a program, or with split cases one of its units of 256
+            // cases (and the sum, for the wavefront that ends the last unit).
             // A wavefront that comes to the end of the list waits at the
             // barrier; a program listed meanwhile under its number is still
             // its own, run after the barrier (nothing is listed any more
             // then: a wavefront that lists goes on to the list's end).
-            bool after = false;
-            int g = claim();
+            const int units = it.stride >> 8;
+            bool after = false, sum = false;
+            int t = claim();
             for (;;) {
-                const int end = listed();
-                if (g < end) {
+                int g = t, from = 0, to = it.cases, mode = kAll;
+                float* kept = xt;
+                if (split) {
+                    if (t >= it.count * units) break;
+                    if (t == 0 && !sum) follow(0, false);
+                    g = t / units;
+                    if (FIT != kFitPredict) kept += (int64_t)(n_vars + 1 + g) * it.stride;
+                    if (sum) {
+                        mode = kSum;
+                    } else {
+                        from = (t - g * units) * 256;
+                        to = min(from + 256, it.cases);
+                        mode = FIT == kFitPredict ? kAll : kKeep;
+                    }
+                } else {
+                    const int end = listed();
+                    if (t >= end) {
+                        if (after) break;
+                        __syncthreads();
+                        after = true;
+                        continue;
+                    }
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                    run(g, !after);
-                    if (!after) { g = claim(); continue; }
-                    break;
+                    if (f0 == first && t % G == 0) follow(t, !after);
                 }
+                run_cases(g, from, to, mode, kept);
+                if (SPLIT && mode == kKeep) {
+                    // (every lane adds one, as in the claims)
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    const int done = (int)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_done[g], 1u)) >> 6);
+                    sum = done == units - 1;
+                    if (sum) {
+                        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                        continue;
+                    }
+                }
+                sum = false;
                 if (after) break;
-                __syncthreads();
-                after = true;
+                t = claim();
             }
             __syncthreads();
         }
@@ -2354,7 +2457,7 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.cls = off;        off = align_up(off + (size_t)n_programs);
     L.order = off;      off = align_up(off + (size_t)n_programs * 4);
     L.class_info = off; off = align_up(off + 2 * kClasses * 4);
-    L.class_g = off;    off = align_up(off + 2 * kClasses * 4);
+    L.class_g = off;    off = align_up(off + 3 * kClasses * 4);
     L.counter = off;    off = align_up(off + 4);
     // per (program, tile) partials: a compensated pair and a bad flag
     // (MSE), the correlation sums, or an int64 reward total
@@ -2616,6 +2719,7 @@ struct EvalLaunch {
     int32_t stride = 1;
     int32_t target_items = 1;   // work items per class worth keeping large groups for
     int32_t lds_floats = 0;     // staged inputs and targets
+    int32_t split = 0;          // cases may be split over wavefronts
     int grid = 0;
     size_t lds = 0;
     Layout layout;
@@ -2626,7 +2730,7 @@ constexpr int kRunLds = 48 * 1024;
 
 // Grid and LDS of the evaluation kernel (LDS attribute set outside any
 // capture).
-template <int FIT>
+template <int FIT, bool SPLIT>
 int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
     // at least one sub-tile of the widest dataset, and every window (a
@@ -2637,11 +2741,11 @@ int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
     el->lds_floats = (int32_t)std::max(one, want);
     el->lds = (size_t)el->lds_floats * sizeof(float) + acc;
     if (el->lds > 64 * 1024) {
-        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT>),
+        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT, SPLIT>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)el->lds));
     }
     int per_cu = 0;
-    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_run<FIT>, kRunWG, el->lds));
+    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_run<FIT, SPLIT>, kRunWG, el->lds));
     if (per_cu < 1)
         return set_error(GP_E_TOO_LARGE, "n_vars=%d needs %zu bytes of LDS per workgroup", pb.max_vars, el->lds);
     if (tu.wg_per_cu > 0 && tu.wg_per_cu < per_cu) per_cu = tu.wg_per_cu;
@@ -2661,12 +2765,18 @@ int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
         const int32_t t = max_tiles(pb.max_cases, class_k(c, pb.max_vars), tu.tile_max);
         if (t > el->stride) el->stride = t;
     }
-    if (pb.fit == kFitPredict) el->stride = 1;      // (only the staging blocks' counts)
     el->target_items = 4 * 3 * cus;     // ~4 items per workgroup slot
-    if (pb.fit == kFitCorr) rc = run_grid<kFitCorr>(pb, tu, cus, el);
-    else if (pb.fit == kFitReward) rc = run_grid<kFitReward>(pb, tu, cus, el);
-    else if (pb.fit == kFitPredict) rc = run_grid<kFitPredict>(pb, tu, cus, el);
-    else rc = run_grid<kFitMse>(pb, tu, cus, el);
+    // (classes are split one by one, see split_programs; a kernel of its own, as
+    // the forms for units cost the ordinary ones 3% in registers)
+    const int32_t tiles =
+        tile_shape(pb.max_cases, class_k(0, pb.max_vars), pb.max_vars, tu.tile_lds, tu.tile_max).n_tiles;
+    el->split = pb.req_dev == nullptr && pb.max_cases > 256 &&
+                (pb.fit == kFitPredict || (double)pb.n_programs * (double)tiles <= kGpuWaves);
+    if (pb.fit == kFitPredict) el->stride = 1;      // (only the staging blocks' counts)
+    if (pb.fit == kFitCorr) rc = el->split ? run_grid<kFitCorr, true>(pb, tu, cus, el) : run_grid<kFitCorr, false>(pb, tu, cus, el);
+    else if (pb.fit == kFitReward) rc = el->split ? run_grid<kFitReward, true>(pb, tu, cus, el) : run_grid<kFitReward, false>(pb, tu, cus, el);
+    else if (pb.fit == kFitPredict) rc = el->split ? run_grid<kFitPredict, true>(pb, tu, cus, el) : run_grid<kFitPredict, false>(pb, tu, cus, el);
+    else rc = el->split ? run_grid<kFitMse, true>(pb, tu, cus, el) : run_grid<kFitMse, false>(pb, tu, cus, el);
     if (rc != GP_OK) return rc;
     el->layout = make_layout(pb.n_programs, pb.n_nodes, el->stride, pb.n_ds, pb.n_req, pb.fit);
     return GP_OK;
@@ -2709,7 +2819,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
         return rc;
     }
     const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
-    const SegOut so{group_capacity(pb, tu), el.target_items, el.lds_floats, st.seg_cnt, st.seg_pos,
+    const SegOut so{group_capacity(pb, tu), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
     if (pb_ext(pb.allowed)) {
         hipLaunchKernelGGL((k_stage_waves<true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
@@ -2731,6 +2841,13 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     return GP_OK;
 }
 
+template <int FIT>
+void launch_run(const EvalLaunch& el, dim3 g, dim3 b, hipStream_t stream, const RunArgs& a)
+{
+    if (el.split) hipLaunchKernelGGL((k_run<FIT, true>), g, b, el.lds, stream, a);
+    else hipLaunchKernelGGL((k_run<FIT, false>), g, b, el.lds, stream, a);
+}
+
 // The evaluation kernel (out: gp_predict's per-case outputs).
 int enqueue_run(const Problem& pb, const EvalLaunch& el, const Staged& st, hipStream_t stream,
                 float* out = nullptr, int64_t ld_out = 0)
@@ -2748,10 +2865,10 @@ int enqueue_run(const Problem& pb, const EvalLaunch& el, const Staged& st, hipSt
     a.reward_M = (float)pb.max_score;
     a.reward_less = a.reward_M / 11.0f;
     const dim3 g(el.grid), b(kRunWG);
-    if (pb.fit == kFitCorr) hipLaunchKernelGGL(k_run<kFitCorr>, g, b, el.lds, stream, a);
-    else if (pb.fit == kFitReward) hipLaunchKernelGGL(k_run<kFitReward>, g, b, el.lds, stream, a);
-    else if (pb.fit == kFitPredict) hipLaunchKernelGGL(k_run<kFitPredict>, g, b, el.lds, stream, a);
-    else hipLaunchKernelGGL(k_run<kFitMse>, g, b, el.lds, stream, a);
+    if (pb.fit == kFitCorr) launch_run<kFitCorr>(el, g, b, stream, a);
+    else if (pb.fit == kFitReward) launch_run<kFitReward>(el, g, b, stream, a);
+    else if (pb.fit == kFitPredict) launch_run<kFitPredict>(el, g, b, stream, a);
+    else launch_run<kFitMse>(el, g, b, stream, a);
     GP_HIP_TRY(hipGetLastError());
     return GP_OK;
 }
