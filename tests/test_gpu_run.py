@@ -170,3 +170,28 @@ def test_rewards_at_the_fast_range(power, M):
     for x, t in ((a, b), (o, y), (o[1:256], y[1:256])):
         R = gp.evaluate_reward(nodes, off, np.ones(1, np.float32), x[None, :], t, M, power)
         assert R[0] == oracle.case_rewards(x, t, M, power).sum()
+
+
+@pytest.mark.parametrize("n", [1, 2, 255, 1023, 1024, 1025, 5000])
+@pytest.mark.parametrize("S", [1, 2, 9, 10, 99, 100, 255, 256, 257])
+def test_ranking_with_small_and_large_samples(n, S):
+    """Bands, children and the sorted sample on both sides of the sample size
+    that one kernel sorts and of a workgroup's individuals, with ties,
+    infinities and NaN: exact, against the ranking oracle."""
+    import torch
+    from oracle import ranking
+    gp = _gp()
+    rng = np.random.default_rng(1000 * n + S)
+    f = np.round(rng.normal(0, 3, n), 1)
+    f[rng.random(n) < 0.1] = np.nan
+    f[rng.random(n) < 0.1] = np.inf
+    ft = torch.from_numpy(f).cuda()
+    band = torch.empty(n, dtype=torch.int32, device="cuda")
+    ch = torch.empty(n, dtype=torch.float32, device="cuda")
+    keys = torch.empty(S, dtype=torch.float64, device="cuda")
+    for higher in (False, True):
+        gp.gp_mc_rank(ft, higher, 77, band, ch, keys, sample_size=S)
+        want = ranking.mc_rank(f, higher, 77, S)
+        assert np.array_equal(band.cpu().numpy(), want[0])
+        assert np.array_equal(ch.cpu().numpy(), want[1])
+        assert np.array_equal(keys.cpu().numpy(), want[2])
