@@ -349,8 +349,8 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
  * paper's loop uploads a new population each generation and scores it,
  * Sec. "Dividing Tasks Between CPU and GPU").  A plan owns its workspace,
  * captures the whole pipeline (validation and staging, the partition by
- * stack depth class and program length -- longest first --, the persistent
- * per-class evaluation kernels and the fp64 reduction) into a hipGraph
+ * stack depth class and estimated cost -- dearest first --, the persistent
+ * evaluation kernel and the fp64 reduction) into a hipGraph
  * once, and replays it with gp_plan_launch.  The caller rewrites the
  * program/data buffers in place between launches (same pointers, same
  * sizes) or calls gp_plan_update for new pointers or sizes (re-capture).
@@ -363,9 +363,9 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
  * and the defaults (24 KiB, 32 tiles) give gp_eval's bits; other values may
  * differ from gp_eval in the last bits (within the fitness tolerance).
  * With autotune != 0, gp_plan_create times candidate knobs on the given
- * inputs (coordinate descent over the five knobs, two sweeps, the median
+ * inputs (coordinate descent over the knobs, two sweeps, the median
  * of five runs per candidate, then a run-off of the three fastest: this
- * runs the evaluation about 140 times and synchronizes `stream`) and keeps
+ * runs the evaluation about 110 times and synchronizes `stream`) and keeps
  * the fastest; results are cached per workload shape (device, cases, variables,
  * programs, mean length, requests) in the process and, if the environment
  * variable GPEVAL_TUNE_CACHE names a file, there too.
@@ -383,11 +383,8 @@ typedef struct {
     int32_t programs_per_item;   /* most programs per work item, 1..128 (default 64);
                                     a depth class with few programs uses fewer */
     int32_t wg_per_cu;           /* persistent workgroups per CU, 0 = occupancy limit */
-    int32_t concurrent_classes;  /* 1: depth classes run on forked streams; 2: as 1,
-                                    and the depth <= 8 class runs one workgroup
-                                    per CU below its limit, so that the deeper
-                                    classes (whose wavefronts issue first) run
-                                    beside it from the start */
+    int32_t concurrent_classes;  /* 0..2, accepted and reported: every depth class
+                                    runs in one launch, so it changes nothing */
     int32_t tile_lds_bytes;      /* LDS budget of an input window, 4096..65536
                                     (default 24576) */
     int32_t max_tiles;           /* case tiles per program, at most, 1..32
@@ -536,8 +533,9 @@ int gp_workspace_size(int64_t n_programs, int64_t n_nodes, int32_t n_requests,
  * gp_eval calls on the calling thread record HIP events on their stream
  * around each phase; gp_timing_read() synchronizes on the recorded events
  * and accumulates milliseconds per phase since the last reset:
- *   ms[0] prepare + depth-class partition, ms[1..3] evaluation of depth
- *   classes <= 8, <= 16, <= 32, ms[4] fp64 reduction, ms[5] whole call.
+ *   ms[0] prepare + depth-class partition, ms[1] evaluation (one launch for
+ *   every depth class; ms[2] and ms[3] are empty), ms[4] fp64 reduction,
+ *   ms[5] whole call.
  * *n_calls gets the number of timed calls.  gp_timing_enable(0) stops
  * recording; gp_timing_reset() clears the sums.  Returns GP_OK or GP_E_HIP.
  */

@@ -563,20 +563,21 @@ __device__ __forceinline__ int32_t cut_programs(double runs, int32_t g_max, int3
 // Cases of a class's sub-tile (64 per case held by a lane).
 __host__ __device__ constexpr int sub_cases(int c) { return c == 2 ? 128 : 256; }
 
-// Cases (a multiple of 256) whose inputs and targets fit the staged memory.
-__host__ __device__ inline int64_t staged_cases(int32_t lds_floats, int32_t n_vars)
+// Cases (a multiple of 256) whose rows (the inputs, and the targets) fit the
+// staged memory.
+__host__ __device__ inline int64_t staged_cases(int32_t lds_floats, int32_t rows)
 {
-    const int64_t n = lds_floats / (n_vars + 1) / 256 * 256;
+    const int64_t n = lds_floats / (rows < 1 ? 1 : rows) / 256 * 256;
     return n < 256 ? 256 : n;
 }
 
 // Case tiles per item of one dataset: what the staged memory holds, spread
 // evenly over the dataset's tiles; 1 when a tile is larger than that (the
 // item then stages it piece by piece).
-__host__ __device__ inline int32_t item_tiles(int32_t passes, int32_t n_tiles, int c, int32_t n_vars,
+__host__ __device__ inline int32_t item_tiles(int32_t passes, int32_t n_tiles, int c, int32_t rows,
                                               int32_t lds_floats, int32_t m_cap)
 {
-    int64_t m = staged_cases(lds_floats, n_vars) / ((int64_t)passes * sub_cases(c));
+    int64_t m = staged_cases(lds_floats, rows) / ((int64_t)passes * sub_cases(c));
     m = m < m_cap ? m : m_cap;
     m = m < 1 ? 1 : (m < n_tiles ? m : n_tiles);
     const int32_t groups = (int32_t)((n_tiles + m - 1) / m);
@@ -603,7 +604,7 @@ __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict
     double runs = 0.0;
     for (int s = 0; s < n_seg; ++s) {
         const DevDataset& D = ds[seg_ds[s]];
-        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars, lds_floats, m_cap);
+        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars + 1, lds_floats, m_cap);
         runs += (double)seg_cnt[c * n_seg + s] * (double)item_groups(D.n_tiles[c], m);
     }
     const int32_t G = cut_programs(runs, g_max, target_items);
@@ -615,7 +616,7 @@ __device__ void class_seg_tables(int c, int32_t n_seg, const int32_t* __restrict
     for (int s = 0; s < n_seg; ++s) {
         const int32_t n = seg_cnt[c * n_seg + s];
         const DevDataset& D = ds[seg_ds[s]];
-        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars, lds_floats, m_cap);
+        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars + 1, lds_floats, m_cap);
         seg_pos[c * n_seg + s] = pos;
         item_pre[c * (n_seg + 1) + s] = items;
         pos += n;
@@ -1180,7 +1181,7 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
 // staged programs need more than n_nodes words in total (no program of the
 // call is staged then).
 struct SegOut {
-    int32_t g_max, target_items, lds_floats, split, free_outputs;
+    int32_t g_max, target_items, lds_floats, split, free_outputs, y_row;
     int32_t* seg_cnt;
     int32_t* seg_pos;
     uint32_t* item_pre;
@@ -1303,11 +1304,11 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         if (a.single) {
             const int32_t tiles = a.one_ds.n_tiles[t];
             const int32_t m_cap = cut_tiles((double)count * (double)tiles);
-            const int32_t m = item_tiles(a.one_ds.passes[t], tiles, t, a.one_ds.n_vars, so.lds_floats, m_cap);
+            const int32_t m = item_tiles(a.one_ds.passes[t], tiles, t, a.one_ds.n_vars + so.y_row, so.lds_floats, m_cap);
             const int32_t groups = item_groups(tiles, m);
             // (items over the same cases follow each other without a barrier, so
             // small ones cost nothing and end the launch evenly)
-            const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars);
+            const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars + so.y_row);
             int32_t G = cut_programs((double)count * (double)groups,
                                            whole && so.g_max > kRunOn ? kRunOn : so.g_max, so.target_items);
             so.seg_cnt[t] = count;
@@ -2036,12 +2037,14 @@ __device__ __forceinline__ void warm_code(const uint2* pc, int words)
 
 // LDS bytes of a workgroup's running sums: one per program of a chunk (a tile
 // in pieces), or per wavefront.
-constexpr size_t acc_bytes(int fit)
+constexpr int chunk_max(int fit, bool wide) { return wide ? kRunWaves : (fit == kFitCorr ? kCorrMaxG : kChunkMax); }
+constexpr size_t acc_bytes(int fit, bool wide)
 {
-    return fit == kFitCorr     ? (size_t)kCorrMaxG * sizeof(CorrPart)
-           : fit == kFitReward ? (size_t)kChunkMax * sizeof(long long)
-           : fit == kFitMse    ? (size_t)kChunkMax * (sizeof(float2) + sizeof(uint32_t))
-                               : 0;
+    return (size_t)chunk_max(fit, wide) *
+           (fit == kFitCorr     ? sizeof(CorrPart)
+            : fit == kFitReward ? sizeof(long long)
+            : fit == kFitMse    ? sizeof(float2) + sizeof(uint32_t)
+                                : 0);
 }
 
 // Lists programs order[obase .. obase + count) of a chunk (count <= G <= 64) in
@@ -2074,17 +2077,21 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
 // meeting, up to kListed programs between two barriers.  (Barriers after
 // every item left 44% of the wavefronts' time waiting; a class's kernel of its
 // own left the GPU to each tail in turn and cost 13 us when it was empty.)
+// WIDE: datasets of so many variables that a sub-tile leaves no room for the
+// long list (and, for gp_predict, for the targets).
 // Bound by vector issue (threaded.h): 80 registers hold 32 of stack, 16 of
 // temporaries and the epilogue's, for six wavefronts per SIMD; the
 // correlation sums take more.
-template <int FIT, bool SPLIT>
+template <int FIT, bool SPLIT, bool WIDE>
 __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs a)
 {
     extern __shared__ float lds[];
     float* xt = lds;                              // [n_vars + 1][stride]: inputs, then targets
     char* accs = reinterpret_cast<char*>(lds + a.lds_floats);
     __shared__ uint32_t s_next, s_end, s_pending; // programs taken and listed; the next item
-    __shared__ uint4 s_prog[kListed];             // listed programs: code, id, words
+    constexpr int kList = WIDE ? 2 * kRunWaves : kListed, kChunk = chunk_max(FIT, WIDE);
+    constexpr int kRowY = WIDE && FIT == kFitPredict ? 0 : 1;     // the targets are staged
+    __shared__ uint4 s_prog[kList];             // listed programs: code, id, words
     __shared__ uint32_t s_done[kSplitMax];        // units of a program that are done
     const ThreadConsts tc = thread_consts();
     const int tid = threadIdx.x, lane = tid & 63;
@@ -2114,7 +2121,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int passes = D->passes[c], n_tiles = D->n_tiles[c], n_vars = D->n_vars;
         const int sub = sub_cases(c);
         const int64_t n_cases = D->n_cases;
-        const int m = item_tiles(passes, n_tiles, c, n_vars, a.lds_floats, m_cap);
+        const int m = item_tiles(passes, n_tiles, c, n_vars + kRowY, a.lds_floats, m_cap);
         const int count = as_const(a.seg_cnt)[c * ns + sl];
         const uint32_t groups = (uint32_t)((count + G - 1) / G);
         const uint32_t local = ci - pre_c[sl];
@@ -2142,7 +2149,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int64_t tile_cases = (int64_t)passes * sub;
         const int64_t first = tile_cases * it.tile;
         const int64_t last = min(first + tile_cases * min(m, n_tiles - it.tile), n_cases);
-        const int64_t cap = staged_cases(a.lds_floats, n_vars);
+        const int64_t cap = staged_cases(a.lds_floats, n_vars + kRowY);
         const bool whole = tile_cases <= cap;
         const int64_t step = whole ? last - first : max(cap / it.window, (int64_t)1) * it.window;
         it.tile_cases = whole ? (int)tile_cases : 0;
@@ -2153,7 +2160,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 else if constexpr (FIT == kFitReward) reinterpret_cast<long long*>(accs)[g] = 0;
                 else {
                     reinterpret_cast<float2*>(accs)[g] = make_float2(0.f, 0.f);
-                    reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax)[g] = 0u;
+                    reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunk)[g] = 0u;
                 }
             }
         }
@@ -2174,7 +2181,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 const float* __restrict__ X = D->X;
                 const float* __restrict__ y = D->y;
                 const int64_t ld_x = D->ld_x;
-                const int nb = it.stride >> 8, units = (n_vars + 1) * nb;
+                const int nb = it.stride >> 8, units = (n_vars + kRowY) * nb;
                 int nf = 0;
                 for (int u = wave; u < units; u += kRunWaves) {
                     const int v = u / nb, b = u - v * nb;
@@ -2230,7 +2237,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 else if constexpr (FIT == kFitReward) acc = reinterpret_cast<long long*>(accs) + slot;
                 else if constexpr (FIT == kFitMse) {
                     acc = reinterpret_cast<float2*>(accs) + slot;
-                    acc_bad = reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax) + slot;
+                    acc_bad = reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunk) + slot;
                 }
                 if (c == 0) run_piece<FIT, 0, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
                 else if (c == 1) run_piece<FIT, 1, SPLIT>(pc, pid, xt, a, it, tc, lane, acc, acc_bad, from, to, mode, kept);
@@ -2249,7 +2256,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
             // the chunk when it is over the same cases
             auto follow = [&](int g, bool more) {
                 const uint32_t next = take_next();
-                if (more && whole && next < item1 && g + 2 * G <= kListed) {
+                if (more && whole && next < item1 && g + 2 * G <= kList) {
                     const int at = (int)(next - item0) * G, n = min(G, count - at);
                     const uint32_t t = list_chunk(a, seg0 + at, n, G, lane, s_prog + g + G);
                     asm volatile("" ::"v"(t));
@@ -2324,7 +2331,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 else {
                     a.part[slot] = reinterpret_cast<float2*>(accs)[g];
                     a.part_bad[slot] =
-                        (uint8_t)(reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunkMax)[g] != 0u);
+                        (uint8_t)(reinterpret_cast<uint32_t*>(reinterpret_cast<float2*>(accs) + kChunk)[g] != 0u);
                 }
             }
         }
@@ -2699,8 +2706,7 @@ int check_problem(const Problem& pb)
 struct Tuning {
     int G = 64;             // programs per work item, at most (small classes use fewer)
     int wg_per_cu = 0;      // persistent workgroups per CU (0: occupancy limit)
-    int concurrent = 0;     // depth classes on forked streams (2: and the depth <= 8
-                            // class leaves one workgroup slot per CU to the others)
+    int concurrent = 0;     // accepted and reported; every class runs in one launch
     int tile_lds = kTileLds;    // LDS bytes of an input window
     int tile_max = kMaxTiles;   // case tiles per program, at most
 };
@@ -2709,49 +2715,65 @@ struct Tuning {
 // follows named variables and stack moves).
 inline bool pb_ext(uint32_t allowed) { return (allowed & ~GP_BASE_OPS) != 0u; }
 
-// Programs per work item at most: the tuning's value, capped by the LDS of the
-// running sums.
-int group_capacity(const Problem& pb, const Tuning& tu)
-{
-    return std::min(tu.G, pb.fit == kFitCorr ? kCorrMaxG : kChunkMax);
-}
 
 struct EvalLaunch {
     int32_t stride = 1;
     int32_t target_items = 1;   // work items per class worth keeping large groups for
     int32_t lds_floats = 0;     // staged inputs and targets
     int32_t split = 0;          // cases may be split over wavefronts
+    int32_t wide = 0;           // a sub-tile takes nearly all LDS (k_run's WIDE)
+    int32_t y_row = 1;          // the targets are staged
+    int32_t chunk = 0;          // programs per work item, at most
     int grid = 0;
     size_t lds = 0;
     Layout layout;
 };
+
+// Programs per work item at most: the tuning's value, capped by the LDS of the
+// running sums.
+int group_capacity(const Tuning& tu, const EvalLaunch& el) { return std::min(tu.G, el.chunk); }
 
 // LDS for staged inputs that leaves room for three workgroups per CU (160 KB).
 constexpr int kRunLds = 48 * 1024;
 
 // Grid and LDS of the evaluation kernel (LDS attribute set outside any
 // capture).
-template <int FIT, bool SPLIT>
+template <int FIT, bool SPLIT, bool WIDE>
 int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
     // at least one sub-tile of the widest dataset, and every window (a
     // window of sub-tiles of 128 cases may round up by a third)
-    const int64_t one = (int64_t)(pb.max_vars + 1) * 256;
+    el->y_row = WIDE && FIT == kFitPredict ? 0 : 1;
+    el->wide = WIDE;
+    el->chunk = chunk_max(FIT, WIDE);
+    const int64_t one = (int64_t)std::max(pb.max_vars + el->y_row, 1) * 256;
     const int64_t want = std::max<int64_t>(kRunLds / 4, (int64_t)tu.tile_lds / 3);
-    const size_t acc = acc_bytes(FIT);
     el->lds_floats = (int32_t)std::max(one, want);
-    el->lds = (size_t)el->lds_floats * sizeof(float) + acc;
+    el->lds = (size_t)el->lds_floats * sizeof(float) + acc_bytes(FIT, WIDE);
     if (el->lds > 64 * 1024) {
-        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT, SPLIT>),
+        GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT, SPLIT, WIDE>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)el->lds));
     }
     int per_cu = 0;
-    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_run<FIT, SPLIT>, kRunWG, el->lds));
+    GP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_run<FIT, SPLIT, WIDE>, kRunWG, el->lds));
     if (per_cu < 1)
         return set_error(GP_E_TOO_LARGE, "n_vars=%d needs %zu bytes of LDS per workgroup", pb.max_vars, el->lds);
     if (tu.wg_per_cu > 0 && tu.wg_per_cu < per_cu) per_cu = tu.wg_per_cu;
     el->grid = cus * per_cu;
     return GP_OK;
+}
+
+// (Classes are split one by one, see split_programs; a kernel of its own, as
+// the forms for units cost the ordinary ones 3% in registers.)
+constexpr int32_t kWideVars = 128;       // from here on a sub-tile takes most of the LDS
+template <int FIT>
+int run_grid_for(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
+{
+    if (pb.max_vars >= kWideVars) {
+        el->split = 0;
+        return run_grid<FIT, false, true>(pb, tu, cus, el);
+    }
+    return el->split ? run_grid<FIT, true, false>(pb, tu, cus, el) : run_grid<FIT, false, false>(pb, tu, cus, el);
 }
 
 int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
@@ -2767,17 +2789,15 @@ int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
         if (t > el->stride) el->stride = t;
     }
     el->target_items = 4 * 3 * cus;     // ~4 items per workgroup slot
-    // (classes are split one by one, see split_programs; a kernel of its own, as
-    // the forms for units cost the ordinary ones 3% in registers)
     const int32_t tiles =
         tile_shape(pb.max_cases, class_k(0, pb.max_vars), pb.max_vars, tu.tile_lds, tu.tile_max).n_tiles;
     el->split = pb.req_dev == nullptr && pb.max_cases > 256 &&
                 (pb.fit == kFitPredict || (double)pb.n_programs * (double)tiles <= kGpuWaves);
     if (pb.fit == kFitPredict) el->stride = 1;      // (only the staging blocks' counts)
-    if (pb.fit == kFitCorr) rc = el->split ? run_grid<kFitCorr, true>(pb, tu, cus, el) : run_grid<kFitCorr, false>(pb, tu, cus, el);
-    else if (pb.fit == kFitReward) rc = el->split ? run_grid<kFitReward, true>(pb, tu, cus, el) : run_grid<kFitReward, false>(pb, tu, cus, el);
-    else if (pb.fit == kFitPredict) rc = el->split ? run_grid<kFitPredict, true>(pb, tu, cus, el) : run_grid<kFitPredict, false>(pb, tu, cus, el);
-    else rc = el->split ? run_grid<kFitMse, true>(pb, tu, cus, el) : run_grid<kFitMse, false>(pb, tu, cus, el);
+    if (pb.fit == kFitCorr) rc = run_grid_for<kFitCorr>(pb, tu, cus, el);
+    else if (pb.fit == kFitReward) rc = run_grid_for<kFitReward>(pb, tu, cus, el);
+    else if (pb.fit == kFitPredict) rc = run_grid_for<kFitPredict>(pb, tu, cus, el);
+    else rc = run_grid_for<kFitMse>(pb, tu, cus, el);
     if (rc != GP_OK) return rc;
     el->layout = make_layout(pb.n_programs, pb.n_nodes, el->stride, pb.n_ds, pb.n_req, pb.fit);
     return GP_OK;
@@ -2820,7 +2840,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
         return rc;
     }
     const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
-    const SegOut so{group_capacity(pb, tu), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, st.seg_cnt, st.seg_pos,
+    const SegOut so{group_capacity(tu, el), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, el.y_row, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
     if (pb_ext(pb.allowed)) {
         hipLaunchKernelGGL((k_stage_waves<true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
@@ -2834,7 +2854,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     GP_HIP_TRY(hipGetLastError());
     if (pb.req_dev) {
         hipLaunchKernelGGL(k_seg_tables, dim3(1), dim3(256), 0, stream, st.order, st.class_info,
-                           st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(pb, tu),
+                           st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(tu, el),
                            el.target_items, el.lds_floats, st.seg_cnt, st.seg_pos, st.item_pre,
                            st.class_g);
         GP_HIP_TRY(hipGetLastError());
@@ -2845,8 +2865,9 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
 template <int FIT>
 void launch_run(const EvalLaunch& el, dim3 g, dim3 b, hipStream_t stream, const RunArgs& a)
 {
-    if (el.split) hipLaunchKernelGGL((k_run<FIT, true>), g, b, el.lds, stream, a);
-    else hipLaunchKernelGGL((k_run<FIT, false>), g, b, el.lds, stream, a);
+    if (el.wide) hipLaunchKernelGGL((k_run<FIT, false, true>), g, b, el.lds, stream, a);
+    else if (el.split) hipLaunchKernelGGL((k_run<FIT, true, false>), g, b, el.lds, stream, a);
+    else hipLaunchKernelGGL((k_run<FIT, false, false>), g, b, el.lds, stream, a);
 }
 
 // The evaluation kernel (out: gp_predict's per-case outputs).
@@ -3052,9 +3073,9 @@ int time_config(gp_plan* p, const Tuning& t, hipStream_t stream, hipEvent_t e0, 
 }
 
 // Time candidate knobs on the real inputs and keep the fastest: coordinate
-// descent over five axes (programs per work item, workgroups per CU, depth
-// classes on forked streams, the LDS budget of an input window, the cap on
-// case tiles per program), each axis tried in turn with the others at their
+// descent over the axes (programs per work item, workgroups per CU, the LDS
+// budget of an input window, the cap on case tiles per program; the classes
+// share one launch, so `concurrent` has nothing to try), each axis tried in turn with the others at their
 // best so far, two sweeps, each candidate the median of five runs; then the
 // three fastest candidates are timed again in turns (five rounds, one run
 // each per round, so drift hits them alike) and the lowest median wins.
@@ -3077,7 +3098,7 @@ int plan_autotune(gp_plan* p, hipStream_t stream)
     GP_HIP_TRY(hipEventCreate(&e0));
     GP_HIP_TRY(hipEventCreate(&e1));
     const int kAxes = 5;
-    const std::vector<int> values[kAxes] = {{32, 64, 128}, {0, 3, 4}, {0, 1, 2},
+    const std::vector<int> values[kAxes] = {{32, 64, 128}, {0, 3, 4}, {0},
                                             {12 * 1024, 24 * 1024, 40 * 1024}, {2, 8, 32}};
     auto field = [](Tuning& t, int a) -> int& {
         return a == 0 ? t.G : a == 1 ? t.wg_per_cu : a == 2 ? t.concurrent

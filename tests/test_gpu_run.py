@@ -42,7 +42,7 @@ def _sums(n_vars, copies):
 @pytest.mark.parametrize("n_cases,n_vars,copies", [
     (1, 1, 1), (63, 2, 3), (128, 3, 1), (255, 2, 9), (256, 2, 40), (257, 5, 9), (511, 3, 9),
     (513, 11, 9), (1537, 3, 30), (3073, 5, 9), (4099, 1, 9), (40961, 3, 9), (100003, 7, 3),
-    (700, 60, 5), (20000, 60, 3), (300, 127, 2)])
+    (700, 60, 5), (20000, 60, 3), (300, 127, 2), (300, 128, 3), (2100, 156, 2)])
 def test_sums_over_all_classes(n_cases, n_vars, copies):
     gp = _gp()
     rng = np.random.default_rng(n_cases + n_vars)
@@ -195,3 +195,28 @@ def test_ranking_with_small_and_large_samples(n, S):
         assert np.array_equal(band.cpu().numpy(), want[0])
         assert np.array_equal(ch.cpu().numpy(), want[1])
         assert np.array_equal(keys.cpu().numpy(), want[2])
+
+
+def test_the_widest_datasets():
+    """158 variables are the most a score takes (a sub-tile of every row fills
+    the LDS), 159 the most outputs take."""
+    gp = _gp()
+    rng = np.random.default_rng(4)
+    X = rng.uniform(-3, 3, (159, 700)).astype(np.float32)
+    y = rng.uniform(-9, 9, 700).astype(np.float32)
+    consts = np.ones(1, np.float32)
+    for n_vars in (158, 159):
+        nodes, offsets, use = _sums(n_vars, 2)
+        want = []
+        for v in use:
+            f = X[v[-1]]
+            for k in v[-2::-1]:
+                f = X[k] + f
+            want.append(f)
+        want = np.stack(want)
+        assert np.array_equal(gp.predict(nodes, offsets, consts, X[:n_vars], synth.MASK_2), want)
+        if n_vars == 158:
+            F = gp.evaluate(nodes, offsets, consts, X[:158], y, 0.0, synth.MASK_2)
+            np.testing.assert_allclose(F, ((want.astype(np.float64) - y) ** 2).mean(axis=1), rtol=2.0 ** -21)
+            R = gp.evaluate_reward(nodes, offsets, consts, X[:158], y, 11000.0, 1)
+            assert np.array_equal(R, [oracle.case_rewards(f, y, 11000.0, 1).sum() for f in want])
