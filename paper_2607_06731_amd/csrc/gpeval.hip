@@ -1106,16 +1106,20 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
 // (its words never outnumber its nodes, so while offsets never decrease the
 // programs' ranges are disjoint), and count the partition keys per block.
 template <bool EXT>
-__global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
+__global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a)
 {
     __shared__ int cnt[kKeys];
     __shared__ int s_down;
+    __shared__ uint32_t s_taken;
     __shared__ WaveTables tables[kStageWaves];
     __shared__ uint32_t turned[kStageWaves][kReorderMax];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
-    if (threadIdx.x == 0) s_down = 0;
+    if (threadIdx.x == 0) {
+        s_down = 0;
+        s_taken = 0u;
+    }
     if (a.single && blockIdx.x == 0 && threadIdx.x == 0) {
         a.ds[0] = a.one_ds;
         a.reqs[0] = a.one_req;
@@ -1128,7 +1132,10 @@ __global__ __launch_bounds__(64 * kStageWaves) void k_stage_waves(StageArgs a)
     const bool tab_ok = a.single || as_const((const int32_t*)a.bad)[0] == 0;
     const int64_t p0 = (int64_t)blockIdx.x * a.share;
     const int64_t p1 = min(p0 + a.share, a.n_programs);
-    for (int64_t p = p0 + wave; p < p1; p += kStageWaves) {
+    for (;;) {
+        // (all lanes add one, as in k_run's claims)
+        const int64_t p = p0 + (int64_t)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_taken, 1u)) >> 6);
+        if (p >= p1) break;
         const ProgRange g = program_range(a, p, tab_ok);
         const bool range_ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
         int status, c = -1, n = 0, cost = 0;
