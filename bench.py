@@ -125,12 +125,12 @@ def oracle_threads(n_programs):
 
 
 def kernel_source_digest():
-    """SHA-256 over the code of the kernel sources (gpeval.hip, then
-    staging.h) with comments and blank space left out, so an edit of a
+    """SHA-256 over the code of the kernel sources (gpeval.hip, staging.h,
+    threaded.h, interp_gfx950.h) with comments and blank space left out, so an edit of a
     comment keeps the counters that were taken on the same code, and any
     change of the code drops them."""
     texts = []
-    for name in ("gpeval.hip", "staging.h"):
+    for name in ("gpeval.hip", "staging.h", "threaded.h", "interp_gfx950.h"):
         with open(os.path.join(ROOT, "paper_2607_06731_amd", "csrc", name)) as f:
             texts.append(f.read())
     return code_digest(texts)
@@ -158,7 +158,7 @@ def measured_counters(workload):
     import re
     if workload != "generation":
         return {}
-    summary = os.path.join(ROOT, "profiles", "k_eval_generation_counters.md")
+    summary = os.path.join(ROOT, "profiles", "k_run_generation_counters.md")
     try:
         text = open(summary).read()
         digest = kernel_source_digest()
@@ -342,11 +342,12 @@ def throughput(args):
     ms_step = ms_total / args.steps
     gpops = node_evals / (ms_step * 1e-3) / 1e9
 
-    # dominant kernel: evaluation of the depth <= 8 class
+    # dominant kernel: the evaluation, one launch over every depth class (the
+    # eval_d8 phase holds all of it)
     status, maxd, _ = gp.gp_validate(w.pop.nodes, w.pop.offsets, w.pop.consts.size,
                                      w.data.n_vars, w.allowed_mask)
     lens = w.pop.lengths
-    cls0 = (status == 0) & (maxd <= 8)
+    cls0 = status == 0
     evals0 = int(lens[cls0].sum()) * w.data.n_cases
     ms0 = phases["eval_d8"] / max(n_calls, 1)
     counters = measured_counters(args.workload) if args.fitness == "mse" else {}
@@ -358,12 +359,12 @@ def throughput(args):
     # the operators' own arithmetic (OP_VALU lane operations per case)
     mix0 = executed_operator_mix(w.pop.nodes, w.pop.offsets, cls0)
     math0 = int(sum(int(mix0[k]) * OP_VALU[k] for k in range(12))) * w.data.n_cases
-    # algorithmic bytes of the launch: each input read once (the class's
+    # algorithmic bytes of the launch: each input read once (the programs'
     # nodes, offsets, the cases and targets) and one value per program out
     algo0 = (4 * int(lens[cls0].sum()) + 16 * int(cls0.sum())
              + 4 * (w.data.n_vars + 1) * w.data.n_cases)
     traffic = counters.get("traffic_bytes_per_launch")
-    roofline = {"bound": "alu", "kernel": "k_eval<8,4> (depth<=8 class)",
+    roofline = {"bound": "alu", "kernel": "k_run (every depth class)",
                 "achieved": round(achieved, 4), "peak": round(PEAK_LANE_OPS / 1e12, 4),
                 "unit": "T node-evals/s vs T fp32 VALU lane-ops/s",
                 "frac": round(achieved * 1e12 / PEAK_LANE_OPS, 4),
