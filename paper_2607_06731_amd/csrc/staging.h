@@ -1,10 +1,10 @@
 // staging.h -- the interpreter's staged program format and the staging
 // walk: validation with the instruction count (check_program) and emission
 // (stage_walk), and for op masks within the benchmark set both in one
-// shorter pass (stage_check_base).  Included by gpeval.hip for the
-// device passes (k_validate, k_stage) and by a host test harness, so the
+// shorter pass (stage_check_base).  Host test harnesses run the walks, so the
 // count, the emission and the meaning of the staged words can be checked
-// without a GPU.
+// without a GPU; the device's staging (k_stage_waves) shares the command
+// tables and the named variables' cells.
 //
 // The includer provides, before this header: gpeval.h, uint2 and
 // make_uint2, __float_as_uint, the LDS float type lds_f32, kHeldConsts and
@@ -13,7 +13,7 @@
 // qualifier of the walks: __device__ in the library).
 #pragma once
 
-// Staged instruction flags (see k_stage).  A leaf directly followed by a
+// Staged instruction flags.  A leaf directly followed by a
 // binary op folds into "top = top OP leaf"; a leaf directly followed by a
 // unary op folds into "save top; top = f(leaf)".  The leaf's load and the
 // op still run for every case: only the push/pop and one dispatch go.
@@ -150,7 +150,7 @@ struct GclCheck {
     }
 };
 
-// Emits the staged instructions of one valid program (k_validate counts
+// Emits the staged instructions of one valid program (the check counts
 // them with the same rules as it validates).  Constants are held back on a
 // shadow stack and folded: an operator whose operands are all held-back
 // constants is computed here, once, with the interpreter's own scalar
@@ -171,7 +171,7 @@ GP_STAGING_FN int64_t stage_walk(Nodes nodes, int64_t s, int64_t e, Consts const
     // held-back constant i of this thread is pvs[i * kBucketBlock] (LDS:
     // a per-lane index into a register array would become a select chain)
 #define pv(i) pvs[(i) * kBucketBlock]
-    // never writes past the range k_validate sized (`cap` entries)
+    // never writes past the range that was sized (`cap` entries)
     auto put = [&](int64_t i, uint2 v) {
         if (i < cap) out[i] = v;
     };
