@@ -669,6 +669,11 @@ struct StageRow {
 static_assert(sizeof(StageRow) == 100, "StageRow layout");
 constexpr int kStageWaves = 8;
 constexpr int kStageBlocks = 1024;       // two workgroups of 8 wavefronts on every SIMD pair
+constexpr int kStageRound = 1024;        // programs that a block looks through for those left to it
+constexpr int kLaneWG = 256;
+// Keys beyond the partition's: an invalid program, one whose offsets decrease,
+// one that k_stage_lanes leaves to k_stage_waves.
+constexpr uint8_t kKeyInvalid = 0xFF, kKeyDown = 0xFE, kKeyLeft = 0xFD;
 
 // Programs per staging block: one per wavefront up to 8,192 programs, then
 // as many as keep the grid at 1,024 blocks (a count fits 16 bits).
@@ -684,13 +689,29 @@ inline int64_t stage_blocks(int64_t n_programs)
     return (n_programs + share - 1) / share;
 }
 
-// What the two staging kernels share.  A call of one request brings its
+// Nodes of a program that one lane stages, at most (0: every program takes a
+// wavefront).  A wavefront's walk costs about the same for any program of up to 64
+// nodes, 64 lanes' walks the time of the longest: lanes win where programs are
+// short, but only when there are enough of them to fill the GPU with lanes, from
+// about 4,000 per node of mean length.  (us per call over 100 cases by
+// wavefronts and by lanes; programs of 1-3 nodes: 10,000 53.8 and 51.7, 1,000,000
+// 1,101 and 430; of 3-8: 20,000 76.5 and 73.3, 10,000 54.7 and 60.7; of 3-20: 50,000
+// 125 and 115, 20,000 79 and 91; of 3-64: 200,000 453 and 396, 100,000 266 and 266,
+// 50,000 172 and 215.)
+constexpr int32_t kLaneNodes = 64;
+inline int32_t lane_nodes(int64_t n_programs, int64_t n_nodes)
+{
+    return (double)n_programs * (double)n_programs >= 4000.0 * (double)n_nodes ? kLaneNodes : 0;
+}
+
+// What the staging kernels share.  A call of one request brings its
 // request and dataset entries by value (block 0 writes the tables that the
 // later kernels read); a call of several has them in memory (k_tables).
 struct StageArgs {
     int64_t n_programs, share;
     uint32_t allowed;
     int32_t single, lpt, n_seg;
+    int32_t lane_nodes;             // nodes of a program that one lane stages, at most
     DevRequest one_req;
     DevDataset one_ds;
     DevDataset* ds;
@@ -759,6 +780,61 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
     return g;
 }
 
+// The status that program g's range alone gives (GP_PROG_OK: look at its nodes).
+__device__ __forceinline__ int range_status(const ProgRange& g, bool tab_ok)
+{
+    const bool ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
+    return !tab_ok ? GP_PROG_BAD_TABLE : (!ok ? GP_PROG_BAD_OFFSETS : (g.e == g.s ? GP_PROG_EMPTY : GP_PROG_OK));
+}
+
+// Program p's record and status, by one lane; returns its partition key: depth
+// class, then (single-request calls) cost band from dearest to cheapest; with
+// several requests the order inside a class stays the input order, so each
+// request's programs stay together.
+__device__ __forceinline__ int put_program(const StageArgs& a, int64_t p, const ProgRange& g, int status, int c,
+                                           int n, int cost, bool narrow)
+{
+    if (status != GP_PROG_OK) {
+        c = -1;
+        n = 0;
+    }
+    ProgMeta m;
+    m.start = g.node_base + g.s;
+    m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
+    m.slen = narrow ? n | kNarrow : n;
+    a.meta[p] = m;
+    a.pds[p] = g.r;
+    const uint32_t w = (uint32_t)(cost > 1 ? cost : 1), z = __clz(w);
+    int lb = (int)(((31u - z) << 2) + ((w << z) >> 29 & 3u)) - 12;      // 4 log2(w / 8)
+    lb = lb < 0 ? 0 : (lb < kLenBuckets ? lb : kLenBuckets - 1);
+    const int key = c >= 0 ? c * kLenBuckets + (a.lpt ? kLenBuckets - 1 - lb : 0) : kKeyInvalid;
+    a.cls[p] = (uint8_t)key;
+    if (g.out_status) *g.out_status = status;
+    return key;
+}
+
+// Pass 1 of calls of many programs, before k_stage_waves: a lane stages a program
+// of up to a.lane_nodes nodes (stage_lane) and leaves others to it.
+template <bool EXT>
+__global__ __launch_bounds__(kLaneWG) void k_stage_lanes(StageArgs a)
+{
+    __shared__ float held[kLaneWG / 64][kLaneHeld * kLaneStride];
+    const int64_t p = (int64_t)blockIdx.x * kLaneWG + threadIdx.x;
+    if (p >= a.n_programs) return;
+    const bool tab_ok = a.single || as_const((const int32_t*)a.bad)[0] == 0;
+    const ProgRange g = program_range(a, p, tab_ok);
+    int status = range_status(g, tab_ok), c = -1, n = 0, cost = 0;
+    if (status == GP_PROG_OK)
+        status = g.e - g.s > a.lane_nodes
+                     ? kLeftToWave
+                     : stage_lane<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                       g.n_vars, a.code + g.node_base + g.s,
+                                       (lds_f32*)&held[threadIdx.x >> 6][threadIdx.x & 63], g.n_cases, &c, &n, &cost);
+    if (status == kLeftToWave) a.cls[p] = kKeyLeft;
+    else (void)put_program(a, p, g, status, c, n, cost, false);
+    if (g.e < g.s) a.cls[p] = kKeyDown;
+}
+
 // Pass 1, one wavefront per program: validate and
 // stage each program at its own node offset in the request's part of `code`
 // (its words never outnumber its nodes, so while offsets never decrease the
@@ -767,12 +843,14 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
 // several times a plain one's time.  64 registers, so that all 1,024 blocks are
 // resident (at 80 a quarter of them waited for a second round).  A call of
 // 100,000 programs x 4,096 cases: 1,137 us without the two, 1,099 with them.
-template <bool EXT>
+// LANES: k_stage_lanes has run; what it left is listed and staged here.
+template <bool EXT, bool LANES>
 __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a)
 {
     __shared__ int cnt[kKeys];
     __shared__ int s_down;
-    __shared__ uint32_t s_taken;
+    __shared__ uint32_t s_taken, s_left;
+    __shared__ uint16_t left[LANES ? kStageRound : 1];
     __shared__ WaveTables tables[kStageWaves];
     __shared__ uint32_t turned[kStageWaves][kReorderMax];
     const int lane = threadIdx.x & 63;
@@ -780,7 +858,7 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
     if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         s_down = 0;
-        s_taken = 0u;
+        s_taken = s_left = 0u;
     }
     if (a.single && blockIdx.x == 0 && threadIdx.x == 0) {
         a.ds[0] = a.one_ds;
@@ -794,44 +872,40 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
     const bool tab_ok = a.single || as_const((const int32_t*)a.bad)[0] == 0;
     const int64_t p0 = (int64_t)blockIdx.x * a.share;
     const int64_t p1 = min(p0 + a.share, a.n_programs);
-    for (;;) {
-        // (all lanes add one, as in k_run's claims)
-        const int64_t p = p0 + (int64_t)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_taken, 1u)) >> 6);
-        if (p >= p1) break;
-        const ProgRange g = program_range(a, p, tab_ok);
-        const bool range_ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
-        int status, c = -1, n = 0, cost = 0;
-        bool narrow = false;
-        if (!tab_ok) status = GP_PROG_BAD_TABLE;
-        else if (!range_ok) status = GP_PROG_BAD_OFFSETS;
-        else if (g.e == g.s) status = GP_PROG_EMPTY;
-        else
-            status = stage_program<EXT, false>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                        g.n_vars, a.code + g.node_base + g.s, &tables[wave], g.n_cases, turned[wave], lane,
-                                        &c, &n, &cost, &narrow);
-        if (status != GP_PROG_OK) {
-            c = -1;
-            n = 0;
+    for (int64_t r0 = p0, r1; r0 < p1; r0 = r1) {
+        r1 = LANES ? min(r0 + kStageRound, p1) : p1;
+        if (LANES) {
+            if (r0 != p0) {
+                __syncthreads();
+                if (threadIdx.x == 0) s_taken = s_left = 0u;
+                __syncthreads();
+            }
+            for (int64_t p = r0 + threadIdx.x; p < r1; p += 64 * kStageWaves) {
+                const int key = a.cls[p];
+                if (key < kKeys) atomicAdd(&cnt[key], 1);
+                if (key == kKeyDown) s_down = 1;
+                if (key == kKeyLeft) left[atomicAdd(&s_left, 1u)] = (uint16_t)(p - r0);
+            }
+            __syncthreads();
         }
-        if (lane == 0) {
-            if (g.e < g.s) s_down = 1;
-            ProgMeta m;
-            m.start = g.node_base + g.s;
-            m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
-            m.slen = narrow ? n | kNarrow : n;
-            a.meta[p] = m;
-            a.pds[p] = g.r;
-            // partition key: depth class, then (single-request calls) cost
-            // band from dearest to cheapest; with several requests the order
-            // inside a class stays the input order, so each request's
-            // programs stay together
-            const uint32_t w = (uint32_t)(cost > 1 ? cost : 1), z = __clz(w);
-            int lb = (int)(((31u - z) << 2) + ((w << z) >> 29 & 3u)) - 12;      // 4 log2(w / 8)
-            lb = lb < 0 ? 0 : (lb < kLenBuckets ? lb : kLenBuckets - 1);
-            const int key = c >= 0 ? c * kLenBuckets + (a.lpt ? kLenBuckets - 1 - lb : 0) : 0xFF;
-            a.cls[p] = (uint8_t)key;
-            if (c >= 0) atomicAdd(&cnt[key], 1);
-            if (g.out_status) *g.out_status = status;
+        const int64_t todo = LANES ? (int64_t)s_left : r1 - r0;
+        for (;;) {
+            // (all lanes add one, as in k_run's claims)
+            const int64_t t = (int64_t)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_taken, 1u)) >> 6);
+            if (t >= todo) break;
+            const int64_t p = r0 + (LANES ? (int64_t)__builtin_amdgcn_readfirstlane((int)left[t]) : t);
+            const ProgRange g = program_range(a, p, tab_ok);
+            int status = range_status(g, tab_ok), c = -1, n = 0, cost = 0;
+            bool narrow = false;
+            if (status == GP_PROG_OK)
+                status = stage_program<EXT, false>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
+                                                   g.n_vars, a.code + g.node_base + g.s, &tables[wave], g.n_cases,
+                                                   turned[wave], lane, &c, &n, &cost, &narrow);
+            if (lane == 0) {
+                if (g.e < g.s) s_down = 1;
+                const int key = put_program(a, p, g, status, c, n, cost, narrow);
+                if (key < kKeys) atomicAdd(&cnt[key], 1);
+            }
         }
     }
     __syncthreads();
@@ -994,7 +1068,7 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
     if (overflow) {
         for (int64_t p = p0 + t; p < p1; p += kOrderWG) {
             if (a.cls[p] >= kKeys) continue;
-            a.cls[p] = 0xFF;
+            a.cls[p] = kKeyInvalid;
             int32_t* st = a.single ? a.one_req.out_status : a.reqs[a.pds[p]].out_status;
             const int64_t q = a.single ? p : p - a.seg_start[a.pds[p]];
             if (st && (a.single || q < a.reqs[a.pds[p]].n_programs)) st[q] = GP_PROG_BAD_OFFSETS;
@@ -2484,18 +2558,36 @@ int enqueue_tables(const Problem& pb, const Tuning& tu, const Staged& st, hipStr
     return GP_OK;
 }
 
+template <bool EXT>
+int launch_stage(const StageArgs& a, int32_t n_blk, int64_t n_nodes, const SegOut& so, hipStream_t stream)
+{
+    if (a.lane_nodes > 0) {
+        hipLaunchKernelGGL((k_stage_lanes<EXT>), dim3((unsigned)((a.n_programs + kLaneWG - 1) / kLaneWG)), dim3(kLaneWG),
+                           0, stream, a);
+        GP_HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL((k_stage_waves<EXT, true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+    } else {
+        hipLaunchKernelGGL((k_stage_waves<EXT, false>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
+    }
+    GP_HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL((k_order<EXT>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, n_nodes, so);
+    GP_HIP_TRY(hipGetLastError());
+    return GP_OK;
+}
+
 // Validation, staging and partition (a single request brings its tables by
 // value; several have them derived by k_tables first).
 int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, const Staged& st,
                   hipStream_t stream)
 {
-    int rc;
+    int rc = GP_OK;
     StageArgs a{};
     a.n_programs = pb.n_programs;
     a.share = stage_share(pb.n_programs);
     a.allowed = pb.allowed;
     a.single = pb.req_dev ? 0 : 1;
     a.lpt = pb.n_req == 1 ? 1 : 0;
+    a.lane_nodes = lane_nodes(pb.n_programs, pb.n_nodes);
     a.n_seg = pb.n_req;
     a.ds = st.ds; a.reqs = st.req; a.seg_ds = st.seg_ds; a.seg_start = st.seg_start; a.bad = st.bad;
     a.meta = st.meta; a.cls = st.cls; a.pds = st.pds; a.order = st.order; a.code = st.code;
@@ -2511,16 +2603,9 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
     const SegOut so{group_capacity(tu, el), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, el.y_row, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
-    if (pb_ext(pb.allowed)) {
-        hipLaunchKernelGGL((k_stage_waves<true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
-        GP_HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL((k_order<true>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
-    } else {
-        hipLaunchKernelGGL((k_stage_waves<false>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
-        GP_HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL((k_order<false>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, pb.n_nodes, so);
-    }
-    GP_HIP_TRY(hipGetLastError());
+    if (pb_ext(pb.allowed)) rc = launch_stage<true>(a, n_blk, pb.n_nodes, so, stream);
+    else rc = launch_stage<false>(a, n_blk, pb.n_nodes, so, stream);
+    if (rc != GP_OK) return rc;
     if (pb.req_dev) {
         hipLaunchKernelGGL(k_seg_tables, dim3(1), dim3(256), 0, stream, st.order, st.class_info,
                            st.seg_start, pb.n_req, st.bad, st.seg_ds, st.ds, group_capacity(tu, el),

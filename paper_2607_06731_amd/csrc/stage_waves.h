@@ -337,6 +337,120 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, co
     return GP_PROG_OK;
 }
 
+// The same program by one lane, node by node: the words, class and cost of
+// stage_wave, a lane's worth of time instead of a wavefront's.  Returns
+// kLeftToWave for a program that holds back more than kLaneHeld constants or
+// that stage_program may reorder.  held: this lane's constants, kLaneStride
+// floats apart.
+constexpr int kLaneHeld = 8, kLaneStride = 64;
+constexpr int kLeftToWave = -1;
+template <bool EXT>
+__device__ __forceinline__ int stage_lane(const uint32_t* __restrict__ nodes, int32_t len,
+                                          const float* __restrict__ consts, int64_t n_consts,
+                                          uint32_t allowed, int32_t n_vars, uint2* __restrict__ dst,
+                                          lds_f32* held, int64_t n_cases, int* cls, int* n_words, int* cost)
+{
+    GclCheck gc;
+    int rt = 0, np = 0, n = 0, extra = 0;   // runtime depth, held constants, words, cost beyond a word each
+    uint2 last = make_uint2(0u, 0u);
+    bool joined = false;                   // the node before was a variable that took this operator
+    uint32_t w = nodes[0];
+    for (int32_t k = 0; k < len; ++k) {
+        const uint32_t nw = k + 1 < len ? nodes[k + 1] : 0xFFu;
+        const uint32_t op = w & 0xFFu, arg = w >> 8, nx = nw & 0xFFu;
+        w = nw;
+        uint32_t cells = 0u;                 // PASTE: where the variable was, and what moves there
+        if (EXT && op == GP_PASTE) {
+            const int q = gc.var_pos(arg & (GP_GCL_VARS - 1u)), low = gc.live - 1;
+            cells = (31u - (uint32_t)q) | (31u - (uint32_t)low) << 8;
+        }
+        const int code = gc.step(op, arg, allowed, n_vars, n_consts);
+        if (code != GP_PROG_OK) return code;
+        const bool bin = op - GP_ADD < 4u, un = op - GP_SIN < 6u, pw = EXT && op == GP_POW;
+        extra += op == GP_DIV ? 3 : (op - GP_SIN < 2u ? 4 : (op - GP_SIN - 2u < 3u ? 2 : 0));
+        if (EXT) extra += pw || (op >= GP_CBRT && op_is_unary(op)) ? 12 : 0;
+        if (joined) {
+            joined = false;
+            continue;
+        }
+        if (op == GP_CONST) {
+            if (np == kLaneHeld) return kLeftToWave;
+            held[np * kLaneStride] = consts[arg];
+            ++np;
+            continue;
+        }
+        if (bin && np >= 2) {
+            --np;
+            held[(np - 1) * kLaneStride] = binary_value(op, held[(np - 1) * kLaneStride], held[np * kLaneStride]);
+            continue;
+        }
+        if (un && np >= 1) {
+            held[(np - 1) * kLaneStride] = unary_value(op, held[(np - 1) * kLaneStride]);
+            continue;
+        }
+        if (!bin && !(pw && np == 1)) {      // (a folded function over no constant flushes none)
+            for (int i = 0; i < np; ++i) {
+                dst[n] = ThreadedWords::push_const(rt, __float_as_uint(held[i * kLaneStride]));
+                ++n;
+                ++rt;
+            }
+            np = 0;
+        }
+        int change = 0;
+        if (op == GP_LOAD) {
+            const uint32_t payload = arg * kVarPayload;
+            joined = true;
+            if (nx - GP_ADD < 4u) {
+                last = ThreadedWords::top_row(rt, nx - GP_ADD, payload);
+            } else if (EXT && nx == GP_POW) {
+                last = ThreadedWords::top_row(rt, kBinPow, payload);
+            } else {
+                joined = nx - GP_SIN < 6u;
+                last = joined ? ThreadedWords::push_unary(rt, nx - GP_SIN, payload)
+                              : ThreadedWords::push_row(rt, payload);
+                change = 1;
+            }
+        } else if (bin || pw) {
+            const uint32_t sel = pw ? kBinPow : op - GP_ADD;
+            last = np == 1 ? ThreadedWords::top_const(rt, sel, __float_as_uint(held[0])) : ThreadedWords::cells(rt, sel);
+            change = np == 1 ? 0 : -1;
+            np = 0;
+        } else if (EXT && op >= GP_DUP && !op_is_unary(op)) {
+            const uint32_t off = op == GP_DUP    ? kThDup
+                                 : op == GP_SWAP ? kThSwap
+                                 : op == GP_DEL  ? kThDel
+                                 : op == GP_COPY ? kThCopy
+                                                 : kThPaste;
+            if (op == GP_COPY) cells = 31u - (uint32_t)gc.var_pos(arg);
+            change = op == GP_DUP || op == GP_PASTE ? 1 : (op == GP_DEL ? -1 : 0);
+            if (op == GP_DEL && rt < 2) {    // the only element: nothing to move
+                --rt;
+                continue;
+            }
+            last = ThreadedWords::move(rt, off, cells);
+        } else {
+            last = ThreadedWords::unary(rt, uop_sel(op));
+        }
+        dst[n] = last;
+        ++n;
+        rt += change;
+    }
+    const int code = gc.finish();
+    if (code != GP_PROG_OK) return code;
+    const int c = gc.maxd > 16 ? 2 : (gc.maxd > 8 ? 1 : 0);
+    if (c != 0 && n_cases >= kReorderCases && len <= kReorderMax) return kLeftToWave;
+    if (np != 0) {
+        // what is left is a constant: its value is pushed
+        last = ThreadedWords::push_const(0, __float_as_uint(held[0]));
+        ++n;
+    }
+    dst[n - 1] = ThreadedWords::last(last);
+    *cls = c;
+    *n_words = n;
+    *cost = n + extra;
+    return GP_PROG_OK;
+}
+
 // Stages one program: in the order written, and where that needs more than 8
 // cells again in Sethi-Ullman order.  cls: the depth class by the order written
 // decides the unit in which cases are summed (class_k), so the class of a

@@ -55,8 +55,8 @@ def _run(exe, tmp, nodes, offsets, consts, X, data_cases, mask, seed=1):
     r = subprocess.run([exe, fin, fout], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     raw = np.fromfile(fout, np.uint8)
-    info = raw[:P * 64].view(np.int64).reshape(P, 8)
-    return info, raw[P * 64:].view(np.float32).reshape(P, X.shape[1])
+    info = raw[:P * 72].view(np.int64).reshape(P, 9)
+    return info, raw[P * 72:].view(np.float32).reshape(P, X.shape[1])
 
 
 def _check(info, nodes, offsets, n_consts, n_vars, mask, data_cases):
@@ -67,6 +67,7 @@ def _check(info, nodes, offsets, n_consts, n_vars, mask, data_cases):
     assert info[ok, 5].all(), "a word without a handler"
     assert not info[ok, 6].any(), "values"
     assert info[ok, 7].all(), "packed words"
+    assert (info[np.diff(offsets) > 0, 8] != 0).all(), "staged by one lane"
     cls = np.where(md <= 8, 0, np.where(md <= 16, 1, 2))
     if data_cases < REORDERED:
         assert np.array_equal(info[ok, 1], cls[ok]) and not info[ok, 3].any()

@@ -20,7 +20,9 @@
 // nodes[n_nodes]; int64 offsets[P + 1]; float consts[n_consts];
 // float X[n_vars][n_cases].
 // Output: per program int64 {status, class, words, narrow, kept_range,
-// words_ok, cases_differing, same_when_packed}; then float out[P][n_cases].
+// words_ok, cases_differing, same_when_packed, by_lane}; then float
+// out[P][n_cases].  by_lane: 1 where stage_lane gives the same status, words,
+// class and cost, 2 where it leaves the program to a wavefront.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -433,13 +435,13 @@ int main(int argc, char** argv)
     c.mask = (uint32_t)hd[7];
     const uint2 blank = make_uint2(0xDEADBEEFu, 0xDEADBEEFu);
     auto is_blank = [&](const uint2& w) { return w.x == blank.x && w.y == blank.y; };
-    std::vector<int64_t> info(P * 8, 0);
+    std::vector<int64_t> info(P * 9, 0);
     std::vector<float> out(P * NC, NAN);
     std::vector<std::vector<uint2>> words((size_t)P);
     std::vector<int64_t> start((size_t)P + 1, 0);
     for (int64_t p = 0; p < P; ++p) {
         const int64_t len = off[p + 1] - off[p];
-        int64_t* I = &info[p * 8];
+        int64_t* I = &info[p * 9];
         start[p + 1] = start[p];
         if (len <= 0) {
             I[0] = GP_PROG_EMPTY;
@@ -453,7 +455,16 @@ int main(int argc, char** argv)
         c.packed = false;
         stage_call();
         I[0] = c.status[0];
-        if (c.status[0] != GP_PROG_OK) continue;
+        if (c.status[0] != GP_PROG_OK) {
+            std::vector<float> held(kLaneHeld * kLaneStride, NAN);
+            int cl, nw, co;
+            const int st = c.ext ? stage_lane<true>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, dst.data(),
+                                                    held.data(), c.data_cases, &cl, &nw, &co)
+                                 : stage_lane<false>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, dst.data(),
+                                                     held.data(), c.data_cases, &cl, &nw, &co);
+            I[8] = st == kLeftToWave ? 2 : st == c.status[0];
+            continue;
+        }
         const int n = c.n[0];
         I[1] = c.cls[0];
         I[2] = n;
@@ -461,6 +472,19 @@ int main(int argc, char** argv)
         I[4] = n >= 1 && n <= len;
         if (!I[4]) continue;
         words[(size_t)p].assign(dst.begin(), dst.begin() + n);
+        // the same by one lane, where it takes the program
+        {
+            std::vector<uint2> one((size_t)len, blank);
+            std::vector<float> held(kLaneHeld * kLaneStride, NAN);
+            int cl = -1, nw = -1, co = -1;
+            const int st = c.ext ? stage_lane<true>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, one.data(),
+                                                    held.data(), c.data_cases, &cl, &nw, &co)
+                                 : stage_lane<false>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, one.data(),
+                                                     held.data(), c.data_cases, &cl, &nw, &co);
+            I[8] = st == kLeftToWave ? 2 : (st == GP_PROG_OK && cl == c.cls[0] && nw == n && co == c.cost[0]);
+            for (int k = 0; k < n && I[8] == 1; ++k)
+                I[8] = one[(size_t)k].x == dst[(size_t)k].x && one[(size_t)k].y == dst[(size_t)k].y;
+        }
         const Words w{words[(size_t)p].data(), n, c.narrow[0] ? 8 : 8 << c.cls[0]};
         I[5] = 1;
         for (int64_t k = 0; k < NC; ++k) {
@@ -496,7 +520,7 @@ int main(int argc, char** argv)
             const uint2& v = all[(size_t)start[p] + k];
             eq = eq && v.x == w[k].x && v.y == w[k].y;
         }
-        info[p * 8 + 7] = eq;
+        info[p * 9 + 7] = eq;
     }
     FILE* o = fopen(argv[2], "wb");
     if (!o) return 2;
