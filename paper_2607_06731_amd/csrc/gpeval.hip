@@ -543,7 +543,13 @@ constexpr int kRunWG = 64 * kRunWaves;
 constexpr double kGpuWaves = 6144.0;     // evaluation wavefronts resident on the GPU
 constexpr int kListed = 192;             // programs a workgroup lists between two barriers
 constexpr uint32_t kManyRuns = 8u, kFewItems = 8u;      // runs of tiles; items per workgroup
-constexpr int kRunOn = 16;               // programs of an item that the next one may follow
+// Programs of an item that the next one may follow, at least; up to 64 where they
+// run over few cases each: the next items' programs are listed meanwhile, which
+// takes about 5 us, and 16 programs over one sub-tile are over before that
+// (1,000,000 programs of 3-8 nodes x 100 cases: k_run 730 us with 16, 433 with 64;
+// x 1,000 cases 823 and 811).
+constexpr int kRunOn = 16;
+constexpr int64_t kRunOnCases = 64 * 256;    // an item's programs times their cases
 constexpr int kChunkMax = 64;            // programs of an item, at most
 constexpr int kWarmLines = 6;
 // prog_tiles: the class's (program, tile) pairs
@@ -1052,8 +1058,10 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
             // (items over the same cases follow each other without a barrier, so
             // small ones cost nothing and end the launch evenly)
             const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars + so.y_row);
+            const int64_t cases = min((int64_t)m * a.one_ds.passes[t] * sub_cases(t), (a.one_ds.n_cases + 255) & ~(int64_t)255);
             int32_t G = cut_programs((double)count * (double)groups,
-                                           whole && so.g_max > kRunOn ? kRunOn : so.g_max, so.target_items);
+                                     whole ? min(so.g_max, max(kRunOn, (int32_t)(kRunOnCases / cases))) : so.g_max,
+                                     so.target_items);
             so.seg_cnt[t] = count;
             const int32_t split = so.split && whole && m == 1 ? split_programs(a.one_ds, t, count, so) : 0;
             if (split) G = split;
