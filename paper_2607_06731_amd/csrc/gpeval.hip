@@ -2489,6 +2489,17 @@ struct Tuning {
     int tile_max = kMaxTiles;   // case tiles per program, at most
 };
 
+// Case tiles per program of gp_predict, at most.  Outputs are not summed, so a tile
+// can be as small as a window, and few programs over many cases need that to fill
+// the GPU: about four (program, tile) pairs per wavefront (32 tiles: 1 program x
+// 1,000,000 cases 310 us, 8 programs 728; so many: 36 and 69.  As many as
+// windows whatever the programs: 1,000 x 10,000 with 20 variables 95 -> 111).
+inline int32_t predict_tiles(int64_t n_programs)
+{
+    const int64_t t = 4 * (int64_t)kGpuWaves / (n_programs < 1 ? 1 : n_programs);
+    return (int32_t)(t < kMaxTiles ? kMaxTiles : t);
+}
+
 // Whether a call's op mask reaches beyond the benchmark set (its staging then
 // follows named variables and stack moves).
 inline bool pb_ext(uint32_t allowed) { return (allowed & ~GP_BASE_OPS) != 0u; }
@@ -3377,6 +3388,7 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
     pb.need_out = 0;
     pb.fit = kFitPredict;
     Tuning tu;
+    tu.tile_max = predict_tiles(n_programs);
     EvalLaunch el;
     if ((rc = configure_eval(pb, tu, &el)) != GP_OK) return rc;
     Workspace* w = nullptr;
