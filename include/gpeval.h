@@ -185,7 +185,8 @@ int gp_eval(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs,
  * kind.  Every depth class runs on `stream` (no side streams) and no
  * timing events are recorded.  Returns GP_E_TOO_LARGE, before any device
  * work, when the call needs more workspace than the array holds (about 8
- * bytes per node plus 27 per program plus 9 per (program, case tile);
+ * bytes per node plus 21 per program plus 9 per (program, case tile), or
+ * 34 per program where that is more;
  * gp_workspace_size reports the need, with 25% slack); other errors as
  * gp_eval.  Every call on one GPU shares that GPU's array: calls that
  * overlap in time on one GPU (several streams or host threads) race, and

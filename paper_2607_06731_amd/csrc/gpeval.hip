@@ -687,7 +687,7 @@ struct StageArgs {
     int32_t* bad;
     ProgMeta* meta;
     uint8_t* cls;
-    int32_t* pds;
+    int32_t* pds;                   // request of each program (NULL: one request)
     int32_t* order;
     uint2* code;
     StageRow* rows;
@@ -769,7 +769,7 @@ __device__ __forceinline__ int put_program(const StageArgs& a, int64_t p, const 
     m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
     m.slen = narrow ? n | kNarrow : n;
     a.meta[p] = m;
-    a.pds[p] = g.r;
+    if (a.pds) a.pds[p] = g.r;
     const uint32_t w = (uint32_t)(cost > 1 ? cost : 1), z = __clz(w);
     int lb = (int)(((31u - z) << 2) + ((w << z) >> 29 & 3u)) - 12;      // 4 log2(w / 8)
     lb = lb < 0 ? 0 : (lb < kLenBuckets ? lb : kLenBuckets - 1);
@@ -1037,9 +1037,10 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         for (int64_t p = p0 + t; p < p1; p += kOrderWG) {
             if (a.cls[p] >= kKeys) continue;
             a.cls[p] = kKeyInvalid;
-            int32_t* st = a.single ? a.one_req.out_status : a.reqs[a.pds[p]].out_status;
-            const int64_t q = a.single ? p : p - a.seg_start[a.pds[p]];
-            if (st && (a.single || q < a.reqs[a.pds[p]].n_programs)) st[q] = GP_PROG_BAD_OFFSETS;
+            const int r = a.pds ? a.pds[p] : 0;
+            int32_t* st = a.single ? a.one_req.out_status : a.reqs[r].out_status;
+            const int64_t q = a.single ? p : p - a.seg_start[r];
+            if (st && (a.single || q < a.reqs[r].n_programs)) st[q] = GP_PROG_BAD_OFFSETS;
         }
         return;
     }
@@ -2132,7 +2133,7 @@ __global__ __launch_bounds__(256) void k_fill_invalid(const uint8_t* __restrict_
 struct ReduceArgs {
     const ProgMeta* meta;
     const uint8_t* cls;
-    const int32_t* pds;             // request of each program
+    const int32_t* pds;             // request of each program (NULL: one request)
     const DevRequest* reqs;
     const int64_t* seg_start;
     const DevDataset* ds;
@@ -2148,7 +2149,7 @@ __global__ __launch_bounds__(256) void k_reduce(ReduceArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
-    const int r = a.pds[p];
+    const int r = a.pds ? a.pds[p] : 0;
     const DevRequest& R = a.reqs[r];
     const int64_t q = p - a.seg_start[r];
     if (!R.out || q >= R.n_programs) return;     // only for inconsistent tables
@@ -2177,7 +2178,7 @@ __global__ __launch_bounds__(256) void k_reduce_corr(ReduceArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
-    const int r = a.pds[p];
+    const int r = a.pds ? a.pds[p] : 0;
     const DevRequest& R = a.reqs[r];
     const int64_t q = p - a.seg_start[r];
     if (!R.out || q >= R.n_programs) return;     // only for inconsistent tables
@@ -2209,7 +2210,7 @@ __global__ __launch_bounds__(256) void k_reduce_reward(ReduceArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.n_programs) return;
-    const int r = a.pds[p];
+    const int r = a.pds ? a.pds[p] : 0;
     const DevRequest& R = a.reqs[r];
     const int64_t q = p - a.seg_start[r];
     if (!R.out || q >= R.n_programs) return;     // only for inconsistent tables
@@ -2228,6 +2229,7 @@ struct Layout {
     size_t code, meta, cls, order, class_info, class_g, counter, rows;
     size_t part, part_bad;
     size_t ds, req, seg_ds, seg_start, seg_cnt, seg_pos, item_pre, pds, bad, total;
+    bool many;                      // several requests: each program's is kept (pds)
 };
 
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
@@ -2237,6 +2239,7 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
 {
     Layout L;
     size_t off = 0;
+    L.many = n_seg > 1;
     // a staged program never holds more instructions than nodes
     L.code = off;       off = align_up(off + (size_t)(n_nodes + 1) * sizeof(uint2));
     L.meta = off;       off = align_up(off + (size_t)n_programs * sizeof(ProgMeta));
@@ -2250,6 +2253,11 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     const size_t part_elem = fit == kFitCorr ? sizeof(CorrPart) : sizeof(float2);
     L.part = off;       off = align_up(off + (size_t)n_programs * part_stride * part_elem);
     L.part_bad = off;   off = align_up(off + (fit != kFitMse ? 0 : (size_t)n_programs * part_stride));
+    // the staging blocks' counts are read for the last time before the first
+    // partial is written: the same memory
+    L.rows = L.part;
+    const size_t rows_end = align_up(L.rows + (size_t)stage_blocks(n_programs) * sizeof(StageRow));
+    off = off < rows_end ? rows_end : off;
     L.ds = off;         off = align_up(off + (size_t)n_ds * sizeof(DevDataset));
     L.req = off;        off = align_up(off + (size_t)n_seg * sizeof(DevRequest));
     L.seg_ds = off;     off = align_up(off + (size_t)n_seg * 4);
@@ -2257,9 +2265,8 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.seg_cnt = off;    off = align_up(off + (size_t)kClasses * n_seg * 4);
     L.seg_pos = off;    off = align_up(off + (size_t)kClasses * n_seg * 4);
     L.item_pre = off;   off = align_up(off + (size_t)kClasses * (n_seg + 1) * 4);
-    L.pds = off;        off = align_up(off + (size_t)n_programs * 4);
+    L.pds = off;        off = align_up(off + (n_seg > 1 ? (size_t)n_programs * 4 : 0));
     L.bad = off;        off = align_up(off + 4);
-    L.rows = off;       off = align_up(off + (size_t)stage_blocks(n_programs) * sizeof(StageRow));
     L.total = off;
     return L;
 }
@@ -2310,7 +2317,7 @@ Staged carve(void* base, const Layout& L)
     st.seg_cnt = reinterpret_cast<int32_t*>(ws + L.seg_cnt);
     st.seg_pos = reinterpret_cast<int32_t*>(ws + L.seg_pos);
     st.item_pre = reinterpret_cast<uint32_t*>(ws + L.item_pre);
-    st.pds = reinterpret_cast<int32_t*>(ws + L.pds);
+    st.pds = L.many ? reinterpret_cast<int32_t*>(ws + L.pds) : nullptr;
     st.bad = reinterpret_cast<int32_t*>(ws + L.bad);
     return st;
 }
@@ -2582,7 +2589,7 @@ int configure_eval(const Problem& pb, const Tuning& tu, EvalLaunch* el)
         tile_shape(pb.max_cases, class_k(0, pb.max_vars), pb.max_vars, tu.tile_lds, tu.tile_max).n_tiles;
     el->split = pb.req_dev == nullptr && pb.max_cases > 256 &&
                 (pb.fit == kFitPredict || (double)pb.n_programs * (double)tiles <= kGpuWaves);
-    if (pb.fit == kFitPredict) el->stride = 1;      // (only the staging blocks' counts)
+    if (pb.fit == kFitPredict) el->stride = 0;      // no partials
     if (pb.fit == kFitCorr) rc = run_grid_for<kFitCorr>(pb, tu, cus, el);
     else if (pb.fit == kFitReward) rc = run_grid_for<kFitReward>(pb, tu, cus, el);
     else if (pb.fit == kFitPredict) rc = run_grid_for<kFitPredict>(pb, tu, cus, el);
