@@ -691,6 +691,7 @@ struct StageArgs {
     int32_t* order;
     uint2* code;
     StageRow* rows;
+    unsigned long long* words;      // staged words of each staging block
 };
 
 struct ProgRange {
@@ -704,31 +705,32 @@ struct ProgRange {
     int r;
 };
 // Program p's request fields and node range (all uniform).
-__device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p, bool tab_ok)
+template <class Args>
+__device__ __forceinline__ ProgRange program_range(Args a, int64_t p, bool tab_ok)
 {
     ProgRange g;
     g.s = g.e = 0;
-    if (a.single) {
+    if (a->single) {
         g.r = 0;
-        g.nodes = a.one_req.nodes;
-        g.consts = a.one_req.consts;
-        g.n_consts = a.one_req.n_consts;
+        g.nodes = a->one_req.nodes;
+        g.consts = a->one_req.consts;
+        g.n_consts = a->one_req.n_consts;
         g.node_base = 0;
-        g.n_nodes = a.one_req.n_nodes;
-        g.n_vars = a.one_ds.n_vars;
-        g.n_cases = a.one_ds.n_cases;
-        g.out_status = a.one_req.out_status ? a.one_req.out_status + p : nullptr;
-        g.s = as_const(a.one_req.offsets)[p];
-        g.e = as_const(a.one_req.offsets)[p + 1];
+        g.n_nodes = a->one_req.n_nodes;
+        g.n_vars = a->one_ds.n_vars;
+        g.n_cases = a->one_ds.n_cases;
+        g.out_status = a->one_req.out_status ? a->one_req.out_status + p : nullptr;
+        g.s = as_const(a->one_req.offsets)[p];
+        g.e = as_const(a->one_req.offsets)[p + 1];
         return g;
     }
-    const const_ptr<int64_t> start = as_const((const int64_t*)a.seg_start);
-    int lo = 0, hi = a.n_seg - 1;
+    const const_ptr<int64_t> start = as_const((const int64_t*)a->seg_start);
+    int lo = 0, hi = a->n_seg - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
         if (start[mid] <= p) lo = mid; else hi = mid - 1;
     }
-    const const_ptr<DevRequest> R = as_const((const DevRequest*)a.reqs) + lo;
+    const const_ptr<DevRequest> R = as_const((const DevRequest*)a->reqs) + lo;
     const int64_t q = p - start[lo];
     g.r = lo;
     g.nodes = R->nodes;
@@ -736,14 +738,22 @@ __device__ __forceinline__ ProgRange program_range(const StageArgs& a, int64_t p
     g.n_consts = R->n_consts;
     g.node_base = R->node_base;
     g.n_nodes = R->n_nodes;
-    g.n_vars = as_const((const DevDataset*)a.ds)[R->dataset].n_vars;
-    g.n_cases = as_const((const DevDataset*)a.ds)[R->dataset].n_cases;
+    g.n_vars = as_const((const DevDataset*)a->ds)[R->dataset].n_vars;
+    g.n_cases = as_const((const DevDataset*)a->ds)[R->dataset].n_cases;
     g.out_status = R->out_status && q < R->n_programs ? R->out_status + q : nullptr;
     if (tab_ok) {
         g.s = as_const(R->offsets)[q];
         g.e = as_const(R->offsets)[q + 1];
     }
     return g;
+}
+
+// The same pointer, opaque to the optimizer: what is read through it is read
+// there, not kept in scalar registers from the loop's start.
+template <class T> __device__ __forceinline__ const_ptr<T> again(const_ptr<T> p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
 }
 
 // The status that program g's range alone gives (GP_PROG_OK: look at its nodes).
@@ -757,7 +767,8 @@ __device__ __forceinline__ int range_status(const ProgRange& g, bool tab_ok)
 // class, then (single-request calls) cost band from dearest to cheapest; with
 // several requests the order inside a class stays the input order, so each
 // request's programs stay together.
-__device__ __forceinline__ int put_program(const StageArgs& a, int64_t p, const ProgRange& g, int status, int c,
+template <class Args>
+__device__ __forceinline__ int put_program(Args a, int64_t p, const ProgRange& g, int status, int c,
                                            int n, int cost, bool narrow)
 {
     if (status != GP_PROG_OK) {
@@ -768,13 +779,13 @@ __device__ __forceinline__ int put_program(const StageArgs& a, int64_t p, const 
     m.start = g.node_base + g.s;
     m.len = (int32_t)(status == GP_PROG_BAD_OFFSETS || status == GP_PROG_BAD_TABLE ? 0 : g.e - g.s);
     m.slen = narrow ? n | kNarrow : n;
-    a.meta[p] = m;
-    if (a.pds) a.pds[p] = g.r;
+    a->meta[p] = m;
+    if (a->pds) a->pds[p] = g.r;
     const uint32_t w = (uint32_t)(cost > 1 ? cost : 1), z = __clz(w);
     int lb = (int)(((31u - z) << 2) + ((w << z) >> 29 & 3u)) - 12;      // 4 log2(w / 8)
     lb = lb < 0 ? 0 : (lb < kLenBuckets ? lb : kLenBuckets - 1);
-    const int key = c >= 0 ? c * kLenBuckets + (a.lpt ? kLenBuckets - 1 - lb : 0) : kKeyInvalid;
-    a.cls[p] = (uint8_t)key;
+    const int key = c >= 0 ? c * kLenBuckets + (a->lpt ? kLenBuckets - 1 - lb : 0) : kKeyInvalid;
+    a->cls[p] = (uint8_t)key;
     if (g.out_status) *g.out_status = status;
     return key;
 }
@@ -788,7 +799,7 @@ __global__ __launch_bounds__(kLaneWG) void k_stage_lanes(StageArgs a)
     const int64_t p = (int64_t)blockIdx.x * kLaneWG + threadIdx.x;
     if (p >= a.n_programs) return;
     const bool tab_ok = a.single || as_const((const int32_t*)a.bad)[0] == 0;
-    const ProgRange g = program_range(a, p, tab_ok);
+    const ProgRange g = program_range(&a, p, tab_ok);
     int status = range_status(g, tab_ok), c = -1, n = 0, cost = 0;
     if (status == GP_PROG_OK)
         status = g.e - g.s > a.lane_nodes
@@ -797,7 +808,7 @@ __global__ __launch_bounds__(kLaneWG) void k_stage_lanes(StageArgs a)
                                        g.n_vars, a.code + g.node_base + g.s,
                                        (lds_f32*)&held[threadIdx.x >> 6][threadIdx.x & 63], g.n_cases, &c, &n, &cost);
     if (status == kLeftToWave) a.cls[p] = kKeyLeft;
-    else (void)put_program(a, p, g, status, c, n, cost, false);
+    else (void)put_program(&a, p, g, status, c, n, cost, false);
     if (g.e < g.s) a.cls[p] = kKeyDown;
 }
 
@@ -815,15 +826,18 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
 {
     __shared__ int cnt[kKeys];
     __shared__ int s_down;
+    __shared__ unsigned long long s_words;
     __shared__ uint32_t s_taken, s_left;
     __shared__ uint16_t left[LANES ? kStageRound : 1];
     __shared__ WaveTables tables[kStageWaves];
     __shared__ uint32_t turned[kStageWaves][kReorderMax];
+    const const_ptr<StageArgs> args = (const_ptr<StageArgs>)__builtin_amdgcn_kernarg_segment_ptr();
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (threadIdx.x < kKeys) cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         s_down = 0;
+        s_words = 0ull;
         s_taken = s_left = 0u;
     }
     if (a.single && blockIdx.x == 0 && threadIdx.x == 0) {
@@ -846,12 +860,17 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
                 if (threadIdx.x == 0) s_taken = s_left = 0u;
                 __syncthreads();
             }
+            unsigned long long words = 0;
             for (int64_t p = r0 + threadIdx.x; p < r1; p += 64 * kStageWaves) {
                 const int key = a.cls[p];
-                if (key < kKeys) atomicAdd(&cnt[key], 1);
+                if (key < kKeys) {
+                    atomicAdd(&cnt[key], 1);
+                    words += (unsigned long long)a.meta[p].slen;
+                }
                 if (key == kKeyDown) s_down = 1;
                 if (key == kKeyLeft) left[atomicAdd(&s_left, 1u)] = (uint16_t)(p - r0);
             }
+            if (words != 0ull) atomicAdd(&s_words, words);
             __syncthreads();
         }
         const int64_t todo = LANES ? (int64_t)s_left : r1 - r0;
@@ -860,24 +879,31 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
             const int64_t t = (int64_t)(__builtin_amdgcn_readfirstlane(atomicAdd(&s_taken, 1u)) >> 6);
             if (t >= todo) break;
             const int64_t p = r0 + (LANES ? (int64_t)__builtin_amdgcn_readfirstlane((int)left[t]) : t);
-            const ProgRange g = program_range(a, p, tab_ok);
+            const const_ptr<StageArgs> ka = again(args);
+            const ProgRange g = program_range(ka, p, tab_ok);
             int status = range_status(g, tab_ok), c = -1, n = 0, cost = 0;
             bool narrow = false;
             if (status == GP_PROG_OK)
-                status = stage_program<EXT, false>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                                   g.n_vars, a.code + g.node_base + g.s, &tables[wave], g.n_cases,
+                status = stage_program<EXT, false>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, ka->allowed,
+                                                   g.n_vars, ka->code + g.node_base + g.s, &tables[wave], g.n_cases,
                                                    turned[wave], lane, &c, &n, &cost, &narrow);
             if (lane == 0) {
                 if (g.e < g.s) s_down = 1;
-                const int key = put_program(a, p, g, status, c, n, cost, narrow);
-                if (key < kKeys) atomicAdd(&cnt[key], 1);
+                const int key = put_program(again(args), p, g, status, c, n, cost, narrow);
+                if (key < kKeys) {
+                    atomicAdd(&cnt[key], 1);
+                    atomicAdd(&s_words, (unsigned long long)n);
+                }
             }
         }
     }
     __syncthreads();
     StageRow* row = a.rows + blockIdx.x;
     if (threadIdx.x < kKeys) row->cnt[threadIdx.x] = (uint16_t)cnt[threadIdx.x];
-    if (threadIdx.x == 0) row->down = (uint16_t)s_down;
+    if (threadIdx.x == 0) {
+        row->down = (uint16_t)s_down;
+        a.words[blockIdx.x] = s_words;
+    }
 }
 
 // Pass 2, same blocks: every block sums the key counts of the blocks before
@@ -888,7 +914,8 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
 // Offsets that decrease somewhere let programs' node ranges overlap: then
 // every program is staged again here, packed in program order, unless the
 // staged programs need more than n_nodes words in total (no program of the
-// call is staged then).
+// call is staged then).  (us per call of 1,000,000 programs of 3-19 nodes x 100
+// cases, without and with one pair that decreases: 732 and 1,025.)
 struct SegOut {
     int32_t g_max, target_items, lds_floats, split, free_outputs, y_row;
     int32_t* seg_cnt;
@@ -927,7 +954,7 @@ __device__ inline int32_t split_programs(const DevDataset& D, int c, int32_t cou
 
 constexpr int kOrderWG = 256;
 template <bool EXT>
-__global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
+__global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
                                                     SegOut so)
 {
     constexpr int kCols = (int)(sizeof(StageRow) / 4);        // pairs of counts
@@ -967,10 +994,10 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         if (t == 0) s_words = s_before = 0ull;
         __syncthreads();
         unsigned long long all = 0, before = 0;
-        for (int64_t p = t; p < a.n_programs; p += kOrderWG) {
-            const unsigned long long v = (unsigned long long)(a.meta[p].slen & ~kNarrow);
+        for (int r = t; r < n_blk; r += kOrderWG) {
+            const unsigned long long v = a.words[r];
             all += v;
-            if (p < p0) before += v;
+            if (r < (int)blockIdx.x) before += v;
         }
         atomicAdd(&s_words, all);
         atomicAdd(&s_before, before);
@@ -979,17 +1006,58 @@ __global__ __launch_bounds__(kOrderWG) void k_order(StageArgs a, int32_t n_blk, 
         if (!overflow) {
             __shared__ WaveTables tables[kOrderWG / 64];
             __shared__ uint32_t turned[kOrderWG / 64][kReorderMax];
-            for (int64_t p = p0 + __builtin_amdgcn_readfirstlane(wave); p < p1; p += kOrderWG / 64) {
-                int64_t start = (int64_t)s_before;
-                for (int64_t q = p0; q < p; ++q) start += a.meta[q].slen & ~kNarrow;
-                if (a.cls[p] >= kKeys) continue;
-                const ProgRange g = program_range(a, p, true);
-                int c = 0, n = 0, cost = 0;
-                bool narrow = false;
-                (void)stage_program<EXT, true>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts, a.allowed,
-                                         g.n_vars, a.code + start, &tables[wave], g.n_cases, turned[wave], lane, &c, &n,
-                                         &cost, &narrow);
-                if (lane == 0) a.meta[p].start = start;
+            __shared__ unsigned long long s_wave[kOrderWG / 64];
+            __shared__ float held[kOrderWG / 64][kLaneHeld * kLaneStride];
+            __shared__ int32_t left[kOrderWG];
+            __shared__ uint32_t s_left;
+            unsigned long long base = s_before;
+            for (int64_t c0 = p0; c0 < p1; c0 += kOrderWG) {
+                // where each of 256 programs starts now
+                const int64_t p = c0 + t;
+                const bool staged = p < p1 && a.cls[p] < kKeys;
+                const unsigned long long v = staged ? (unsigned long long)(a.meta[p].slen & ~kNarrow) : 0ull;
+                unsigned long long sum = v;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const unsigned long long u = __shfl_up(sum, off);
+                    sum += lane >= off ? u : 0ull;
+                }
+                if (lane == 63) s_wave[wave] = sum;
+                if (t == 0) s_left = 0u;
+                __syncthreads();
+                unsigned long long chunk = 0;
+                for (int w2 = 0; w2 < kOrderWG / 64; ++w2) {
+                    if (w2 == wave) sum += base + chunk;
+                    chunk += s_wave[w2];
+                }
+                base += chunk;
+                if (staged) {
+                    const int64_t start = (int64_t)(sum - v);
+                    a.meta[p].start = start;
+                    // as in pass 1: by this lane, or by a wavefront
+                    const ProgRange g = program_range(&a, p, true);
+                    int status = kLeftToWave, c = 0, n = 0, cost = 0;
+                    if (g.e - g.s <= a.lane_nodes)
+                        for (int pass = 0; pass < 2; ++pass) {
+                            status = stage_lane<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts,
+                                                     a.allowed, g.n_vars, pass ? a.code + start : nullptr,
+                                                     (lds_f32*)&held[wave][lane], g.n_cases, &c, &n, &cost);
+                            if (status == kLeftToWave) break;
+                        }
+                    if (status == kLeftToWave) left[atomicAdd(&s_left, 1u)] = (int32_t)p;
+                }
+                __syncthreads();
+                const int todo = (int)s_left;
+                for (int q = __builtin_amdgcn_readfirstlane(wave); q < todo; q += kOrderWG / 64) {
+                    const int64_t pw = __builtin_amdgcn_readfirstlane(left[q]);
+                    const ProgRange g = program_range(&a, pw, true);
+                    int c = 0, n = 0, cost = 0;
+                    bool narrow = false;
+                    (void)stage_program<EXT, true>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts,
+                                                   a.allowed, g.n_vars, a.code + a.meta[pw].start, &tables[wave],
+                                                   g.n_cases, turned[wave], lane, &c, &n, &cost, &narrow);
+                }
+                __syncthreads();
             }
         }
     }
@@ -2226,7 +2294,7 @@ __global__ __launch_bounds__(256) void k_reduce_reward(ReduceArgs a)
 
 // ----------------------------------------------------------- workspaces
 struct Layout {
-    size_t code, meta, cls, order, class_info, class_g, counter, rows;
+    size_t code, meta, cls, order, class_info, class_g, counter, rows, words;
     size_t part, part_bad;
     size_t ds, req, seg_ds, seg_start, seg_cnt, seg_pos, item_pre, pds, bad, total;
     bool many;                      // several requests: each program's is kept (pds)
@@ -2256,7 +2324,8 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     // the staging blocks' counts are read for the last time before the first
     // partial is written: the same memory
     L.rows = L.part;
-    const size_t rows_end = align_up(L.rows + (size_t)stage_blocks(n_programs) * sizeof(StageRow));
+    L.words = align_up(L.rows + (size_t)stage_blocks(n_programs) * sizeof(StageRow));
+    const size_t rows_end = align_up(L.words + (size_t)stage_blocks(n_programs) * 8);
     off = off < rows_end ? rows_end : off;
     L.ds = off;         off = align_up(off + (size_t)n_ds * sizeof(DevDataset));
     L.req = off;        off = align_up(off + (size_t)n_seg * sizeof(DevRequest));
@@ -2281,6 +2350,7 @@ struct Staged {
     int32_t* class_g;
     uint32_t* counter;
     StageRow* rows;
+    unsigned long long* words;
     float2* part;
     uint8_t* part_bad;
     CorrPart* part_corr;            // the same memory as part, correlation mode
@@ -2307,6 +2377,7 @@ Staged carve(void* base, const Layout& L)
     st.class_g = reinterpret_cast<int32_t*>(ws + L.class_g);
     st.counter = reinterpret_cast<uint32_t*>(ws + L.counter);
     st.rows = reinterpret_cast<StageRow*>(ws + L.rows);
+    st.words = reinterpret_cast<unsigned long long*>(ws + L.words);
     st.part = reinterpret_cast<float2*>(ws + L.part);
     st.part_corr = reinterpret_cast<CorrPart*>(ws + L.part);
     st.part_bad = reinterpret_cast<uint8_t*>(ws + L.part_bad);
@@ -2644,7 +2715,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     a.n_seg = pb.n_req;
     a.ds = st.ds; a.reqs = st.req; a.seg_ds = st.seg_ds; a.seg_start = st.seg_start; a.bad = st.bad;
     a.meta = st.meta; a.cls = st.cls; a.pds = st.pds; a.order = st.order; a.code = st.code;
-    a.rows = st.rows;
+    a.rows = st.rows; a.words = st.words;
     if (a.single) {
         const gp_request& q = pb.one_req;
         a.one_req = DevRequest{q.nodes, q.offsets, q.consts, q.n_programs, q.n_nodes, q.n_consts, 0,

@@ -340,8 +340,9 @@ __device__ __forceinline__ int stage_wave(const uint32_t* __restrict__ nodes, co
 // The same program by one lane, node by node: the words, class and cost of
 // stage_wave, a lane's worth of time instead of a wavefront's.  Returns
 // kLeftToWave for a program that holds back more than kLaneHeld constants or
-// that stage_program may reorder.  held: this lane's constants, kLaneStride
-// floats apart.
+// that stage_program may reorder.  Else dst holds the words that come back and
+// none beyond them; a null dst stores nothing.  held: this lane's constants,
+// kLaneStride floats apart.
 constexpr int kLaneHeld = 8, kLaneStride = 64;
 constexpr int kLeftToWave = -1;
 template <bool EXT>
@@ -350,6 +351,7 @@ __device__ __forceinline__ int stage_lane(const uint32_t* __restrict__ nodes, in
                                           uint32_t allowed, int32_t n_vars, uint2* __restrict__ dst,
                                           lds_f32* held, int64_t n_cases, int* cls, int* n_words, int* cost)
 {
+    const bool store = dst != nullptr;
     GclCheck gc;
     int rt = 0, np = 0, n = 0, extra = 0;   // runtime depth, held constants, words, cost beyond a word each
     uint2 last = make_uint2(0u, 0u);
@@ -390,7 +392,7 @@ __device__ __forceinline__ int stage_lane(const uint32_t* __restrict__ nodes, in
         }
         if (!bin && !(pw && np == 1)) {      // (a folded function over no constant flushes none)
             for (int i = 0; i < np; ++i) {
-                dst[n] = ThreadedWords::push_const(rt, __float_as_uint(held[i * kLaneStride]));
+                if (store) dst[n] = ThreadedWords::push_const(rt, __float_as_uint(held[i * kLaneStride]));
                 ++n;
                 ++rt;
             }
@@ -431,7 +433,7 @@ __device__ __forceinline__ int stage_lane(const uint32_t* __restrict__ nodes, in
         } else {
             last = ThreadedWords::unary(rt, uop_sel(op));
         }
-        dst[n] = last;
+        if (store) dst[n] = last;
         ++n;
         rt += change;
     }
@@ -444,7 +446,7 @@ __device__ __forceinline__ int stage_lane(const uint32_t* __restrict__ nodes, in
         last = ThreadedWords::push_const(0, __float_as_uint(held[0]));
         ++n;
     }
-    dst[n - 1] = ThreadedWords::last(last);
+    if (store) dst[n - 1] = ThreadedWords::last(last);
     *cls = c;
     *n_words = n;
     *cost = n + extra;

@@ -6,6 +6,7 @@ and calls that fit the fixed workspace of gp_eval_noalloc with it have to go on
 fitting."""
 import numpy as np
 import pytest
+import torch
 
 CASES = [(1, 1), (100, 1), (128, 1), (129, 2), (4096, 32), (1 << 20, 32)]      # cases, most tiles
 
@@ -34,7 +35,6 @@ def test_workspace_of_one_population(cases, tiles):
 @pytest.mark.gpu
 @pytest.mark.parametrize("P,cases,tiles", [(8192, 100, 1), (4000, 100, 1), (8192, 4096, 32), (300, 1000, 8)])
 def test_the_fixed_workspace_takes_what_fits(P, cases, tiles):
-    import torch
     import paper_2607_06731_amd as gp
     from paper_2607_06731_amd import synth
     room = gp.GP_NOALLOC_WORKSPACE_BYTES

@@ -484,6 +484,14 @@ int main(int argc, char** argv)
             I[8] = st == kLeftToWave ? 2 : (st == GP_PROG_OK && cl == c.cls[0] && nw == n && co == c.cost[0]);
             for (int k = 0; k < n && I[8] == 1; ++k)
                 I[8] = one[(size_t)k].x == dst[(size_t)k].x && one[(size_t)k].y == dst[(size_t)k].y;
+            // no word beyond those, and without stores the same answer
+            for (int64_t k = n; k < len && I[8] == 1; ++k) I[8] = is_blank(one[(size_t)k]);
+            int c2 = -1, n2 = -1, o2 = -1;
+            const int s2 = c.ext ? stage_lane<true>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, nullptr,
+                                                    held.data(), c.data_cases, &c2, &n2, &o2)
+                                 : stage_lane<false>(c.nodes, c.len, c.consts, NCo, c.mask, c.n_vars, nullptr,
+                                                     held.data(), c.data_cases, &c2, &n2, &o2);
+            if (s2 != st || (st == GP_PROG_OK && (c2 != cl || n2 != nw || o2 != co))) I[8] = 0;
         }
         const Words w{words[(size_t)p].data(), n, c.narrow[0] ? 8 : 8 << c.cls[0]};
         I[5] = 1;
