@@ -125,12 +125,12 @@ def oracle_threads(n_programs):
 
 
 def kernel_source_digest():
-    """SHA-256 over the code of the kernel sources (gpeval.hip, staging.h, stage_waves.h,
+    """SHA-256 over the code of the kernel sources (gpeval.hip, run_shape.h, staging.h, stage_waves.h,
     threaded.h, interp_gfx950.h) with comments and blank space left out, so an edit of a
     comment keeps the counters that were taken on the same code, and any
     change of the code drops them."""
     texts = []
-    for name in ("gpeval.hip", "staging.h", "stage_waves.h", "threaded.h", "interp_gfx950.h"):
+    for name in ("gpeval.hip", "run_shape.h", "staging.h", "stage_waves.h", "threaded.h", "interp_gfx950.h"):
         with open(os.path.join(ROOT, "paper_2607_06731_amd", "csrc", name)) as f:
             texts.append(f.read())
     return code_digest(texts)

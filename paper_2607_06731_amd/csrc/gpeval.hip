@@ -96,14 +96,14 @@ namespace {
     } while (0)
 
 // ------------------------------------------------------------------ layout
-constexpr int kClasses = 3;              // max depth <= 8, <= 16, <= 32
+#include "run_shape.h"
+
 // Bands of a program's cost, four per octave from 8 to 128 words' worth: an
 // item's programs are of one band, so its wavefronts end together.  (Eight
 // bands of one octave of length each: at 10,000 programs x 4,096 cases the
 // wavefronts waited 14% of the time at barriers for the longest.)
 constexpr int kLenBuckets = 16;
 constexpr int kKeys = kClasses * kLenBuckets;
-constexpr int kMaxTiles = 32;            // case tiles per program (cap)
 // The serial staging walks' limits (staging.h): constants held back for
 // folding per program, and their stride.
 constexpr int kHeldConsts = 16;
@@ -118,65 +118,6 @@ struct ProgMeta {
 };
 constexpr int32_t kNarrow = INT32_MIN;   // class 2, but the words need at most 8 cells
 static_assert(sizeof(ProgMeta) == 16, "ProgMeta layout");
-
-// Cases per lane of a class's sub-tile, the unit in which its cases are
-// grouped into windows and tiles (and so its summation order).  Depends only
-// on the class, never on the rest of the population.  (Lane t holds cases t,
-// t + 64, t + 128, ... whatever the unit, so the interpreter may run two
-// sub-tiles at once.)
-__host__ __device__ inline int class_k(int c, int n_vars) { return c == 2 ? 2 : 4; }
-
-// Tile geometry for one class.  A sub-tile is 64*K cases (one wavefront, K
-// per lane).  The inputs and targets of `window` sub-tiles fit the LDS tile
-// budget together ((n_vars + 1) rows of 64*K floats each), so a wavefront
-// runs a program over a whole window without a barrier.  A tile is `passes`
-// consecutive sub-tiles (a whole number of windows where the case count
-// allows, at most 32 tiles per program); a work item covers one tile of G
-// programs.  Depends only on (n_cases, K, n_vars) -- the dataset -- so a
-// program's summation order never depends on the rest of the population or
-// the batch.
-constexpr int kTileLds = 24 * 1024;      // LDS bytes for input windows (6 workgroups per CU)
-constexpr int kMaxWindow = 8;
-
-struct TileShape {
-    int32_t sub;        // cases per sub-tile (64 * K)
-    int32_t passes;     // sub-tiles per tile
-    int32_t n_tiles;    // tiles covering n_cases
-    int32_t window;     // sub-tiles staged in LDS at once
-};
-
-__host__ __device__ inline int32_t tile_window(int k, int n_vars, int32_t lds_bytes)
-{
-    const int64_t block = (int64_t)(n_vars + 1) * 64 * k * 4;
-    int64_t w = lds_bytes / block;
-    return (int32_t)(w < 1 ? 1 : (w > kMaxWindow ? kMaxWindow : w));
-}
-
-__host__ __device__ inline TileShape tile_shape(int64_t n_cases, int k, int n_vars,
-                                               int32_t lds_bytes, int32_t max_t)
-{
-    TileShape t;
-    t.sub = 64 * k;
-    const int64_t n_sub = (n_cases + t.sub - 1) / t.sub;
-    t.window = tile_window(k, n_vars, lds_bytes);
-    int64_t passes = (n_sub + max_t - 1) / max_t;
-    if (passes < t.window) passes = t.window < n_sub ? t.window : n_sub;
-    if (passes < 1) passes = 1;
-    t.passes = (int32_t)passes;
-    t.n_tiles = (int32_t)((n_sub + passes - 1) / passes);
-    return t;
-}
-
-// Partial slots per program that any dataset of at most max_cases cases
-// can need: n_tiles never exceeds kMaxTiles or the sub-tile count, and the
-// sub-tile count grows with n_cases, so a smaller dataset can need more
-// tiles than the largest one (33 sub-tiles make 17 tiles, 32 make 32).
-__host__ __device__ inline int32_t max_tiles(int64_t max_cases, int k, int32_t max_t)
-{
-    const int64_t n_sub = (max_cases + 64 * k - 1) / (64 * k);
-    return (int32_t)(n_sub < max_t ? (n_sub < 1 ? 1 : n_sub) : max_t);
-}
-
 
 // Power-of-two pre-scale s = 2^-e with 4^e >= n: every scaled partial sum
 // of squared residuals is then <= MSE, so it overflows fp32 only when the
@@ -530,67 +471,6 @@ typedef __attribute__((address_space(3))) float lds_f32;
 #include "threaded.h"
 #include "interp_gfx950.h"
 
-// How a class's work is cut into items.  An item is G programs over m
-// consecutive case tiles, one workgroup's work between two barriers.
-// m is as large as the workgroup's LDS holds (item_tiles), capped so that at
-// least four (program, tiles) runs remain per wavefront of the GPU.
-// G (programs) is as large as g_max allows while the class still has about
-// target_items items, and at least one program per wavefront: larger groups
-// balance a workgroup's wavefronts (each takes the next program).  Neither
-// changes a result.
-constexpr int kRunWaves = 8;             // wavefronts of an evaluation workgroup
-constexpr int kRunWG = 64 * kRunWaves;
-constexpr double kGpuWaves = 6144.0;     // evaluation wavefronts resident on the GPU
-constexpr int kListed = 192;             // programs a workgroup lists between two barriers
-constexpr uint32_t kManyRuns = 8u, kFewItems = 8u;      // runs of tiles; items per workgroup
-// Programs of an item that the next one may follow, at least; up to 64 where they
-// run over few cases each: the next items' programs are listed meanwhile, which
-// takes about 5 us, and 16 programs over one sub-tile are over before that
-// (1,000,000 programs of 3-8 nodes x 100 cases: k_run 730 us with 16, 433 with 64;
-// x 1,000 cases 823 and 811).
-constexpr int kRunOn = 16;
-constexpr int64_t kRunOnCases = 64 * 256;    // an item's programs times their cases
-constexpr int kChunkMax = 64;            // programs of an item, at most
-constexpr int kWarmLines = 6;
-// prog_tiles: the class's (program, tile) pairs
-__device__ __forceinline__ int32_t cut_tiles(double prog_tiles)
-{
-    const double cap = prog_tiles / (4.0 * kGpuWaves);
-    return cap >= (double)kMaxTiles ? kMaxTiles : (cap < 1.0 ? 1 : (int32_t)cap);
-}
-// runs: the class's (program, m tiles) pairs
-__device__ __forceinline__ int32_t cut_programs(double runs, int32_t g_max, int32_t target_items)
-{
-    int32_t G = g_max;
-    while (G > kRunWaves && runs / (double)G < (double)target_items) G >>= 1;
-    return G < 1 ? 1 : G;
-}
-
-// Cases of a class's sub-tile (64 per case held by a lane).
-__host__ __device__ constexpr int sub_cases(int c) { return c == 2 ? 128 : 256; }
-
-// Cases (a multiple of 256) whose rows (the inputs, and the targets) fit the
-// staged memory.
-__host__ __device__ inline int64_t staged_cases(int32_t lds_floats, int32_t rows)
-{
-    const int64_t n = lds_floats / (rows < 1 ? 1 : rows) / 256 * 256;
-    return n < 256 ? 256 : n;
-}
-
-// Case tiles per item of one dataset: what the staged memory holds, spread
-// evenly over the dataset's tiles; 1 when a tile is larger than that (the
-// item then stages it piece by piece).
-__host__ __device__ inline int32_t item_tiles(int32_t passes, int32_t n_tiles, int c, int32_t rows,
-                                              int32_t lds_floats, int32_t m_cap)
-{
-    int64_t m = staged_cases(lds_floats, rows) / ((int64_t)passes * sub_cases(c));
-    m = m < m_cap ? m : m_cap;
-    m = m < 1 ? 1 : (m < n_tiles ? m : n_tiles);
-    const int32_t groups = (int32_t)((n_tiles + m - 1) / m);
-    return (n_tiles + groups - 1) / groups;
-}
-__host__ __device__ inline int32_t item_groups(int32_t n_tiles, int32_t m) { return (n_tiles + m - 1) / m; }
-
 // ------------------------------------------------ wavefront primitives
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask)
 {
@@ -926,32 +806,6 @@ struct SegOut {
     uint32_t* counter;
 };
 
-// A class of fewer (program, tile) pairs than the GPU holds wavefronts ends
-// with its longest program: its pairs are split into units of 256 cases, which
-// wavefronts take one by one, leaving the program's outputs in LDS; the one
-// that finishes a program's last unit sums them up, in the order of a whole
-// run.  gp_predict has nothing to sum and splits always.  Returns the programs
-// per item, 0 for no split.  (us per call: 1,000 programs x 1,024 cases 44 ->
-// 35; the whole command table, 2,000 x 2,048, 94 -> 74; outputs of 1,000 x 16,384
-// 110 -> 101.  10,000 x 4,096, 6.5 pairs per wavefront: 268 either way.)
-constexpr int kSplitMax = 8;             // programs per item
-__device__ inline int32_t split_programs(const DevDataset& D, int c, int32_t count, const SegOut& so)
-{
-    const int64_t tile = (int64_t)D.passes[c] * sub_cases(c);
-    const int32_t stride = (int32_t)((min(tile, D.n_cases) + 255) & ~(int64_t)255), units = stride >> 8;
-    if (units < 2) return 0;
-    int32_t most = min(so.g_max, kSplitMax);
-    if (!so.free_outputs) {
-        if ((double)count * (double)D.n_tiles[c] > kGpuWaves) return 0;
-        most = min(most, (so.lds_floats - (D.n_vars + 1) * stride) / stride);
-        if (most < 1) return 0;
-    }
-    int32_t G = max(kRunWaves / units, 1);
-    while (G > most) G >>= 1;
-    while (2 * G <= most && (double)count * (double)D.n_tiles[c] / G > (double)(so.target_items / 4)) G *= 2;
-    return G;
-}
-
 constexpr int kOrderWG = 256;
 template <bool EXT>
 __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
@@ -1079,26 +933,16 @@ __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_bl
         so.class_info[2 * t + 1] = count;
         if (t == 0) *so.counter = 0u;
         if (a.single) {
-            const int32_t tiles = a.one_ds.n_tiles[t];
-            const int32_t m_cap = cut_tiles((double)count * (double)tiles);
-            const int32_t m = item_tiles(a.one_ds.passes[t], tiles, t, a.one_ds.n_vars + so.y_row, so.lds_floats, m_cap);
-            const int32_t groups = item_groups(tiles, m);
-            // (items over the same cases follow each other without a barrier, so
-            // small ones cost nothing and end the launch evenly)
-            const bool whole = (int64_t)a.one_ds.passes[t] * sub_cases(t) <= staged_cases(so.lds_floats, a.one_ds.n_vars + so.y_row);
-            const int64_t cases = min((int64_t)m * a.one_ds.passes[t] * sub_cases(t), (a.one_ds.n_cases + 255) & ~(int64_t)255);
-            int32_t G = cut_programs((double)count * (double)groups,
-                                     whole ? min(so.g_max, max(kRunOn, (int32_t)(kRunOnCases / cases))) : so.g_max,
-                                     so.target_items);
+            const ClassCut cut = class_cut(t, count, a.one_ds.passes[t], a.one_ds.n_tiles[t], a.one_ds.n_cases,
+                                           a.one_ds.n_vars + so.y_row, so.g_max, so.target_items, so.lds_floats,
+                                           so.split != 0, so.free_outputs != 0);
             so.seg_cnt[t] = count;
-            const int32_t split = so.split && whole && m == 1 ? split_programs(a.one_ds, t, count, so) : 0;
-            if (split) G = split;
-            so.class_g[t] = G;
-            so.class_g[kClasses + t] = m_cap;
-            so.class_g[2 * kClasses + t] = split != 0;
+            so.class_g[t] = cut.G;
+            so.class_g[kClasses + t] = cut.m_cap;
+            so.class_g[2 * kClasses + t] = cut.split;
             so.seg_pos[t] = 0;
             so.item_pre[2 * t] = 0u;
-            so.item_pre[2 * t + 1] = (uint32_t)((count + G - 1) / G) * (uint32_t)groups;
+            so.item_pre[2 * t + 1] = cut.items;
         }
     }
     if (overflow) {
@@ -1932,7 +1776,7 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
 template <int FIT, bool SPLIT, bool WIDE>
 __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs a)
 {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     float* xt = lds;                              // [n_vars + 1][stride]: inputs, then targets
     char* accs = reinterpret_cast<char*>(lds + a.lds_floats);
     __shared__ uint32_t s_next, s_end, s_pending; // programs taken and listed; the next item
@@ -1998,7 +1842,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int64_t last = min(first + tile_cases * min(m, n_tiles - it.tile), n_cases);
         const int64_t cap = staged_cases(a.lds_floats, n_vars + kRowY);
         const bool whole = tile_cases <= cap;
-        const int64_t step = whole ? last - first : max(cap / it.window, (int64_t)1) * it.window;
+        const int64_t step = whole ? last - first : piece_cases(cap, it.window);
         it.tile_cases = whole ? (int)tile_cases : 0;
         if (!whole && FIT != kFitPredict) {
             // running sums of the chunk's programs over the tile's pieces
@@ -2567,17 +2411,6 @@ struct Tuning {
     int tile_max = kMaxTiles;   // case tiles per program, at most
 };
 
-// Case tiles per program of gp_predict, at most.  Outputs are not summed, so a tile
-// can be as small as a window, and few programs over many cases need that to fill
-// the GPU: about four (program, tile) pairs per wavefront (32 tiles: 1 program x
-// 1,000,000 cases 310 us, 8 programs 728; so many: 36 and 69.  As many as
-// windows whatever the programs: 1,000 x 10,000 with 20 variables 95 -> 111).
-inline int32_t predict_tiles(int64_t n_programs)
-{
-    const int64_t t = 4 * (int64_t)kGpuWaves / (n_programs < 1 ? 1 : n_programs);
-    return (int32_t)(t < kMaxTiles ? kMaxTiles : t);
-}
-
 // Whether a call's op mask reaches beyond the benchmark set (its staging then
 // follows named variables and stack moves).
 inline bool pb_ext(uint32_t allowed) { return (allowed & ~GP_BASE_OPS) != 0u; }
@@ -2600,22 +2433,15 @@ struct EvalLaunch {
 // running sums.
 int group_capacity(const Tuning& tu, const EvalLaunch& el) { return std::min(tu.G, el.chunk); }
 
-// LDS for staged inputs that leaves room for three workgroups per CU (160 KB).
-constexpr int kRunLds = 48 * 1024;
-
 // Grid and LDS of the evaluation kernel (LDS attribute set outside any
 // capture).
 template <int FIT, bool SPLIT, bool WIDE>
 int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
-    // at least one sub-tile of the widest dataset, and every window (a
-    // window of sub-tiles of 128 cases may round up by a third)
     el->y_row = WIDE && FIT == kFitPredict ? 0 : 1;
     el->wide = WIDE;
     el->chunk = chunk_max(FIT, WIDE);
-    const int64_t one = (int64_t)std::max(pb.max_vars + el->y_row, 1) * 256;
-    const int64_t want = std::max<int64_t>(kRunLds / 4, (int64_t)tu.tile_lds / 3);
-    el->lds_floats = (int32_t)std::max(one, want);
+    el->lds_floats = run_lds_floats(pb.max_vars + el->y_row, tu.tile_lds);
     el->lds = (size_t)el->lds_floats * sizeof(float) + acc_bytes(FIT, WIDE);
     if (el->lds > 64 * 1024) {
         GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT, SPLIT, WIDE>),
@@ -2632,7 +2458,6 @@ int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 
 // (Classes are split one by one, see split_programs; a kernel of its own, as
 // the forms for units cost the ordinary ones 3% in registers.)
-constexpr int32_t kWideVars = 128;       // from here on a sub-tile takes most of the LDS
 template <int FIT>
 int run_grid_for(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
