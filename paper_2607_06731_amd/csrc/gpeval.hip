@@ -797,7 +797,7 @@ __global__ __launch_bounds__(64 * kStageWaves, 8) void k_stage_waves(StageArgs a
 // call is staged then).  (us per call of 1,000,000 programs of 3-19 nodes x 100
 // cases, without and with one pair that decreases: 732 and 1,025.)
 struct SegOut {
-    int32_t g_max, target_items, lds_floats, split, free_outputs, y_row;
+    int32_t g_max, target_items, lds_floats, split, free_outputs;
     int32_t* seg_cnt;
     int32_t* seg_pos;
     uint32_t* item_pre;
@@ -934,7 +934,7 @@ __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_bl
         if (t == 0) *so.counter = 0u;
         if (a.single) {
             const ClassCut cut = class_cut(t, count, a.one_ds.passes[t], a.one_ds.n_tiles[t], a.one_ds.n_cases,
-                                           a.one_ds.n_vars + so.y_row, so.g_max, so.target_items, so.lds_floats,
+                                           staged_rows(so.free_outputs != 0, a.one_ds.n_vars), so.g_max, so.target_items, so.lds_floats,
                                            so.split != 0, so.free_outputs != 0);
             so.seg_cnt[t] = count;
             so.class_g[t] = cut.G;
@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(kSegWG) void k_seg_tables(
     const int32_t m_cap = cut_tiles(seg_sum(sc, v));
     auto groups = [&](int s) {
         const DevDataset& D = ds[seg_ds[s]];
-        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, D.n_vars + 1, lds_floats, m_cap);
+        const int32_t m = item_tiles(D.passes[c], D.n_tiles[c], c, staged_rows(false, D.n_vars), lds_floats, m_cap);
         return item_groups(D.n_tiles[c], m);
     };
     v = 0;
@@ -1769,7 +1769,7 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
 // every item left 44% of the wavefronts' time waiting; a class's kernel of its
 // own left the GPU to each tail in turn and cost 13 us when it was empty.)
 // WIDE: datasets of so many variables that a sub-tile leaves no room for the
-// long list (and, for gp_predict, for the targets).
+// long list.
 // Bound by vector issue (threaded.h): 80 registers hold 32 of stack, 16 of
 // temporaries and the epilogue's, for six wavefronts per SIMD; the
 // correlation sums take more.
@@ -1781,7 +1781,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
     char* accs = reinterpret_cast<char*>(lds + a.lds_floats);
     __shared__ uint32_t s_next, s_end, s_pending; // programs taken and listed; the next item
     constexpr int kList = WIDE ? 2 * kRunWaves : kListed, kChunk = chunk_max(FIT, WIDE);
-    constexpr int kRowY = WIDE && FIT == kFitPredict ? 0 : 1;     // the targets are staged
+    constexpr bool kNoTargets = FIT == kFitPredict;
     __shared__ uint4 s_prog[kList];             // listed programs: code, id, words
     __shared__ uint32_t s_done[kSplitMax];        // units of a program that are done
     const ThreadConsts tc = thread_consts();
@@ -1812,7 +1812,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int passes = D->passes[c], n_tiles = D->n_tiles[c], n_vars = D->n_vars;
         const int sub = sub_cases(c);
         const int64_t n_cases = D->n_cases;
-        const int m = item_tiles(passes, n_tiles, c, n_vars + kRowY, a.lds_floats, m_cap);
+        const int m = item_tiles(passes, n_tiles, c, staged_rows(kNoTargets, n_vars), a.lds_floats, m_cap);
         const int count = as_const(a.seg_cnt)[c * ns + sl];
         const uint32_t groups = (uint32_t)((count + G - 1) / G);
         const uint32_t local = ci - pre_c[sl];
@@ -1840,7 +1840,7 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         const int64_t tile_cases = (int64_t)passes * sub;
         const int64_t first = tile_cases * it.tile;
         const int64_t last = min(first + tile_cases * min(m, n_tiles - it.tile), n_cases);
-        const int64_t cap = staged_cases(a.lds_floats, n_vars + kRowY);
+        const int64_t cap = staged_cases(a.lds_floats, staged_rows(kNoTargets, n_vars));
         const bool whole = tile_cases <= cap;
         const int64_t step = whole ? last - first : piece_cases(cap, it.window);
         it.tile_cases = whole ? (int)tile_cases : 0;
@@ -1872,11 +1872,11 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
                 const float* __restrict__ X = D->X;
                 const float* __restrict__ y = D->y;
                 const int64_t ld_x = D->ld_x;
-                const int nb = it.stride >> 8, units = (n_vars + kRowY) * nb;
+                const int nb = it.stride >> 8, units = staged_rows(kNoTargets, n_vars) * nb;
                 int nf = 0;
                 for (int u = wave; u < units; u += kRunWaves) {
                     const int v = u / nb, b = u - v * nb;
-                    const bool target = v == n_vars;
+                    const bool target = !kNoTargets && v == n_vars;
                     const float* __restrict__ src = (target ? y : X + (int64_t)v * ld_x) + f0 + b * 256;
                     const int left = it.cases - b * 256;
                     float val[4];
@@ -2422,7 +2422,6 @@ struct EvalLaunch {
     int32_t lds_floats = 0;     // staged inputs and targets
     int32_t split = 0;          // cases may be split over wavefronts
     int32_t wide = 0;           // a sub-tile takes nearly all LDS (k_run's WIDE)
-    int32_t y_row = 1;          // the targets are staged
     int32_t chunk = 0;          // programs per work item, at most
     int grid = 0;
     size_t lds = 0;
@@ -2438,10 +2437,9 @@ int group_capacity(const Tuning& tu, const EvalLaunch& el) { return std::min(tu.
 template <int FIT, bool SPLIT, bool WIDE>
 int run_grid(const Problem& pb, const Tuning& tu, int cus, EvalLaunch* el)
 {
-    el->y_row = WIDE && FIT == kFitPredict ? 0 : 1;
     el->wide = WIDE;
     el->chunk = chunk_max(FIT, WIDE);
-    el->lds_floats = run_lds_floats(pb.max_vars + el->y_row, tu.tile_lds);
+    el->lds_floats = run_lds_floats(staged_rows(FIT == kFitPredict, pb.max_vars), tu.tile_lds);
     el->lds = (size_t)el->lds_floats * sizeof(float) + acc_bytes(FIT, WIDE);
     if (el->lds > 64 * 1024) {
         GP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_run<FIT, SPLIT, WIDE>),
@@ -2550,7 +2548,7 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
         return rc;
     }
     const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
-    const SegOut so{group_capacity(tu, el), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, el.y_row, st.seg_cnt, st.seg_pos,
+    const SegOut so{group_capacity(tu, el), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
     if (pb_ext(pb.allowed)) rc = launch_stage<true>(a, n_blk, pb.n_nodes, so, stream);
     else rc = launch_stage<false>(a, n_blk, pb.n_nodes, so, stream);
@@ -3281,7 +3279,7 @@ int gp_predict(const uint32_t* nodes, const int64_t* offsets, int64_t n_programs
     pb.one_req.n_programs = n_programs; pb.one_req.n_nodes = n_nodes;
     pb.one_req.n_consts = n_consts; pb.one_req.out_status = out_status;
     pb.n_req = 1;
-    pb.one.X = X; pb.one.y = reinterpret_cast<const float*>(out);   // any non-null: unused
+    pb.one.X = X; pb.one.y = nullptr;
     pb.one.ld_x = ld_x; pb.one.n_cases = n_cases; pb.one.tax_on_length = 0.0;
     pb.one.n_vars = n_vars;
     pb.n_ds = 1;

@@ -106,10 +106,11 @@ __host__ __device__ inline int32_t cut_programs(double runs, int32_t g_max, int3
 // Cases of a class's sub-tile (64 per case held by a lane).
 __host__ __device__ constexpr int sub_cases(int c) { return c == 2 ? 128 : 256; }
 
-// Rows of the staged memory: the inputs, and the targets.
+// Rows of the staged memory: the inputs, and the targets where there are any
+// (gp_predict has none).
 __host__ __device__ constexpr int32_t staged_rows(bool outputs_only, int32_t n_vars)
 {
-    return n_vars + (outputs_only && n_vars >= 128 ? 0 : 1);
+    return n_vars + (outputs_only ? 0 : 1);
 }
 
 // Cases (a multiple of 256) whose rows (the inputs, and the targets) fit the

@@ -54,6 +54,7 @@ int main(int argc, char** argv)
         const int32_t list = wide ? 2 * kRunWaves : kListed;
         for (int c = 0; c < kClasses; ++c) {
             CHECK(lds_floats % 4 == 0);
+            CHECK(rows == n_vars + (fit != 3));          // outputs have no targets
             CHECK((int64_t)rows * 256 <= lds_floats);
             const TileShape t = tile_shape(n_cases, class_k(c, n_vars), n_vars, tile_lds, tile_max);
             CHECK(t.sub == sub_cases(c) && t.n_tiles >= 1 && t.n_tiles <= tile_max);

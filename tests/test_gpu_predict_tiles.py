@@ -32,3 +32,31 @@ def test_sums_of_variables(n_programs, n_cases, n_vars):
         for v in use[p][-2::-1]:
             f = X[v] + f
         assert torch.equal(out[p], f)
+
+
+def test_the_output_rows_are_only_written():
+    """Rows of programs and the columns beyond the cases: what the buffer held
+    does not matter, and stays where nothing is written."""
+    import torch
+    import paper_2607_06731_amd as gp
+    n, ld = 5000, 5120
+    X = torch.rand((2, n), device="cuda", dtype=torch.float32)
+    nodes = np.array([L, L | 256, synth.ADD, L], np.uint32)
+    pop = gp.DevicePopulation(nodes, np.array([0, 3, 4]), np.ones(1, np.float32))
+    for fill in (float("nan"), float("inf"), 7.0):
+        buf = torch.full((2, ld), fill, device="cuda", dtype=torch.float32)
+        gp.gp_predict(pop.nodes, pop.offsets, pop.consts, X, buf, allowed_op_mask=synth.MASK_2)
+        assert torch.equal(buf[0, :n], X[0] + X[1]) and torch.equal(buf[1, :n], X[0])
+        rest = torch.full((2, ld - n), fill, device="cuda")
+        assert torch.equal(buf[:, n:].nan_to_num(1.5), rest.nan_to_num(1.5))
+
+
+def test_programs_without_variables():
+    import torch
+    import paper_2607_06731_amd as gp
+    X = torch.empty((0, 300), device="cuda", dtype=torch.float32)
+    pop = gp.DevicePopulation(np.array([synth.CONST, synth.CONST | 256, synth.SUB], np.uint32), np.array([0, 3]),
+                              np.array([3.5, 1.25], np.float32))
+    out = torch.empty((1, 300), device="cuda", dtype=torch.float32)
+    gp.gp_predict(pop.nodes, pop.offsets, pop.consts, X, out, allowed_op_mask=synth.MASK_2, n_cases=300)
+    assert torch.equal(out, torch.full_like(out, 2.25))
