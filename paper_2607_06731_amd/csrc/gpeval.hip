@@ -807,7 +807,7 @@ struct SegOut {
 };
 
 constexpr int kOrderWG = 256;
-template <bool EXT>
+template <bool EXT, bool LANES>
 __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_blk, int64_t code_capacity,
                                                     SegOut so)
 {
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_bl
             __shared__ WaveTables tables[kOrderWG / 64];
             __shared__ uint32_t turned[kOrderWG / 64][kReorderMax];
             __shared__ unsigned long long s_wave[kOrderWG / 64];
-            __shared__ float held[kOrderWG / 64][kLaneHeld * kLaneStride];
+            __shared__ float held[LANES ? kOrderWG / 64 : 1][kLaneHeld * kLaneStride];
             __shared__ int32_t left[kOrderWG];
             __shared__ uint32_t s_left;
             unsigned long long base = s_before;
@@ -889,15 +889,18 @@ __global__ __launch_bounds__(kOrderWG, 4) void k_order(StageArgs a, int32_t n_bl
                     const int64_t start = (int64_t)(sum - v);
                     a.meta[p].start = start;
                     // as in pass 1: by this lane, or by a wavefront
-                    const ProgRange g = program_range(&a, p, true);
-                    int status = kLeftToWave, c = 0, n = 0, cost = 0;
-                    if (g.e - g.s <= a.lane_nodes)
-                        for (int pass = 0; pass < 2; ++pass) {
-                            status = stage_lane<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts,
-                                                     a.allowed, g.n_vars, pass ? a.code + start : nullptr,
-                                                     (lds_f32*)&held[wave][lane], g.n_cases, &c, &n, &cost);
-                            if (status == kLeftToWave) break;
-                        }
+                    int status = kLeftToWave;
+                    if constexpr (LANES) {
+                        const ProgRange g = program_range(&a, p, true);
+                        int c = 0, n = 0, cost = 0;
+                        if (g.e - g.s <= a.lane_nodes)
+                            for (int pass = 0; pass < 2; ++pass) {
+                                status = stage_lane<EXT>(g.nodes + g.s, (int32_t)(g.e - g.s), g.consts, g.n_consts,
+                                                         a.allowed, g.n_vars, pass ? a.code + start : nullptr,
+                                                         (lds_f32*)&held[wave][lane], g.n_cases, &c, &n, &cost);
+                                if (status == kLeftToWave) break;
+                            }
+                    }
                     if (status == kLeftToWave) left[atomicAdd(&s_left, 1u)] = (int32_t)p;
                 }
                 __syncthreads();
@@ -2505,19 +2508,17 @@ int enqueue_tables(const Problem& pb, const Tuning& tu, const Staged& st, hipStr
     return GP_OK;
 }
 
-template <bool EXT>
+template <bool EXT, bool LANES>
 int launch_stage(const StageArgs& a, int32_t n_blk, int64_t n_nodes, const SegOut& so, hipStream_t stream)
 {
-    if (a.lane_nodes > 0) {
+    if (LANES) {
         hipLaunchKernelGGL((k_stage_lanes<EXT>), dim3((unsigned)((a.n_programs + kLaneWG - 1) / kLaneWG)), dim3(kLaneWG),
                            0, stream, a);
         GP_HIP_TRY(hipGetLastError());
-        hipLaunchKernelGGL((k_stage_waves<EXT, true>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
-    } else {
-        hipLaunchKernelGGL((k_stage_waves<EXT, false>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
     }
+    hipLaunchKernelGGL((k_stage_waves<EXT, LANES>), dim3(n_blk), dim3(64 * kStageWaves), 0, stream, a);
     GP_HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL((k_order<EXT>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, n_nodes, so);
+    hipLaunchKernelGGL((k_order<EXT, LANES>), dim3(n_blk), dim3(kOrderWG), 0, stream, a, n_blk, n_nodes, so);
     GP_HIP_TRY(hipGetLastError());
     return GP_OK;
 }
@@ -2550,8 +2551,12 @@ int enqueue_stage(const Problem& pb, const Tuning& tu, const EvalLaunch& el, con
     const int32_t n_blk = (int32_t)stage_blocks(pb.n_programs);
     const SegOut so{group_capacity(tu, el), el.target_items, el.lds_floats, el.split, pb.fit == kFitPredict, st.seg_cnt, st.seg_pos,
                     st.item_pre, st.class_g, st.class_info, st.counter};
-    if (pb_ext(pb.allowed)) rc = launch_stage<true>(a, n_blk, pb.n_nodes, so, stream);
-    else rc = launch_stage<false>(a, n_blk, pb.n_nodes, so, stream);
+    if (pb_ext(pb.allowed))
+        rc = a.lane_nodes > 0 ? launch_stage<true, true>(a, n_blk, pb.n_nodes, so, stream)
+                              : launch_stage<true, false>(a, n_blk, pb.n_nodes, so, stream);
+    else
+        rc = a.lane_nodes > 0 ? launch_stage<false, true>(a, n_blk, pb.n_nodes, so, stream)
+                              : launch_stage<false, false>(a, n_blk, pb.n_nodes, so, stream);
     if (rc != GP_OK) return rc;
     if (pb.req_dev) {
         hipLaunchKernelGGL(k_seg_tables, dim3(kClasses), dim3(kSegWG), 0, stream, st.order, st.class_info,
