@@ -1196,7 +1196,7 @@ typedef float f32x32 __attribute__((ext_vector_type(32)));
                    "{v25}"(tc.theta)                                                       \
                  : "v8", "v9", "v10", "v11", "v16", "v17", "v18", "s68", "s69", "s70",     \
                    "s71", "s72", "s73", "s74", "s75", "s90", "s91", "s92", "s93", "s94",   \
-                   "s95", "s96", "s97", "s98", "vcc", "scc", "memory")
+                   "s95", "s96", "s97", "s98", "m0", "vcc", "scc", "memory")
 
 // The function a result code asks for, on the K values v (u: the exponents).
 template <int K>

@@ -8,7 +8,7 @@
 //   s82 staged cases / 256 (the scale of a row's byte offset)
 //   s[68:75] compare masks         s[96:98] scratch     vcc, m0
 //   v22..v25 constants             v31 LDS address of the lane's first case
-//   v4..v19 temporaries (v4..v7 carry values to and from the caller, v12..v15
+//   v4..v18 temporaries (v4..v7 carry values to and from the caller, v12..v15
 //   a second operand to it)
 //   v36..v67 stack cells, K registers each (case j of cell i: v[36 + K i + j])
 // A handler takes its payload (s89), loads the next word into s[88:89] and
