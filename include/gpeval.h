@@ -534,9 +534,10 @@ int gp_workspace_size(int64_t n_programs, int64_t n_nodes, int32_t n_requests,
  * gp_eval calls on the calling thread record HIP events on their stream
  * around each phase; gp_timing_read() synchronizes on the recorded events
  * and accumulates milliseconds per phase since the last reset:
- *   ms[0] prepare + depth-class partition, ms[1] evaluation (one launch for
- *   every depth class; ms[2] and ms[3] are empty), ms[4] fp64 reduction,
- *   ms[5] whole call.
+ *   ms[0] prepare + depth-class partition, ms[1..3] evaluation of depth
+ *   classes <= 8, <= 16, <= 32, ms[4] fp64 reduction, ms[5] whole call.
+ * (One launch evaluates every depth class of an untimed call; a timed one has
+ * a launch for each, so its evaluation takes a little longer.)
  * *n_calls gets the number of timed calls.  gp_timing_enable(0) stops
  * recording; gp_timing_reset() clears the sums.  Returns GP_OK or GP_E_HIP.
  */

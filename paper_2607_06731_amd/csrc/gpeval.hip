@@ -2034,6 +2034,19 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
     }
 }
 
+// Timed calls: the next k_run takes depth class c alone.  The classes' item counts
+// (the ends of their prefixes) are kept in `counts` from the first of the three on.
+__global__ __launch_bounds__(64) void k_pick_class(int32_t c, int32_t n_seg, uint32_t* __restrict__ item_pre,
+                                                   int32_t* __restrict__ counts, uint32_t* __restrict__ counter)
+{
+    const int k = threadIdx.x;
+    if (k == 0) *counter = 0u;
+    if (k >= kClasses) return;
+    uint32_t* end = item_pre + k * (n_seg + 1) + n_seg;
+    if (c == 0) counts[k] = (int32_t)*end;
+    *end = k == c ? (uint32_t)counts[k] : 0u;
+}
+
 // NaN rows for programs that failed validation (one workgroup per program).
 __global__ __launch_bounds__(256) void k_fill_invalid(const uint8_t* __restrict__ cls,
                                                       int64_t n_cases, float* __restrict__ out,
@@ -2161,7 +2174,7 @@ Layout make_layout(int64_t n_programs, int64_t n_nodes, int32_t part_stride, int
     L.cls = off;        off = align_up(off + (size_t)n_programs);
     L.order = off;      off = align_up(off + (size_t)n_programs * 4);
     L.class_info = off; off = align_up(off + 2 * kClasses * 4);
-    L.class_g = off;    off = align_up(off + 3 * kClasses * 4);
+    L.class_g = off;    off = align_up(off + 4 * kClasses * 4);      // (k_pick_class: the last three)
     L.counter = off;    off = align_up(off + 4);
     // per (program, tile) partials: a compensated pair and a bad flag
     // (MSE), the correlation sums, or an int64 reward total
@@ -2609,11 +2622,19 @@ int enqueue_eval(const Problem& pb, const Tuning& tu, const EvalLaunch& el, cons
     int rc;
     if ((rc = ce.mark(0, stream)) != GP_OK) return rc;
     if ((rc = enqueue_stage(pb, tu, el, st, stream)) != GP_OK) return rc;
-    if ((rc = ce.mark(1, stream)) != GP_OK) return rc;
-    if ((rc = enqueue_run(pb, el, st, stream)) != GP_OK) return rc;
-    // one launch evaluates every class: the class phases share its time
-    for (int i = 2; i <= 4; ++i)
-        if ((rc = ce.mark(i, stream)) != GP_OK) return rc;
+    if (ce.on) {
+        // timed: a launch per depth class, so that each has its phase
+        for (int c = 0; c < kClasses; ++c) {
+            if ((rc = ce.mark(1 + c, stream)) != GP_OK) return rc;
+            hipLaunchKernelGGL(k_pick_class, dim3(1), dim3(64), 0, stream, c, pb.n_req, st.item_pre,
+                               st.class_g + 3 * kClasses, st.counter);
+            GP_HIP_TRY(hipGetLastError());
+            if ((rc = enqueue_run(pb, el, st, stream)) != GP_OK) return rc;
+        }
+        if ((rc = ce.mark(4, stream)) != GP_OK) return rc;
+    } else if ((rc = enqueue_run(pb, el, st, stream)) != GP_OK) {
+        return rc;
+    }
     ReduceArgs ra{};
     ra.meta = st.meta; ra.cls = st.cls; ra.pds = st.pds; ra.reqs = st.req;
     ra.seg_start = st.seg_start; ra.ds = st.ds;
