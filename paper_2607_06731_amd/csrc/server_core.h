@@ -153,8 +153,10 @@ struct Entry {
     size_t chunk;
 };
 
-// Node evaluations below which launches wait for each other (Core::hold).
+// Launches wait for each other below so many node evaluations together, and while
+// those in flight are younger than this (Core::hold).
 constexpr double kHoldNodeEvals = 2147483648.0;
+constexpr double kHoldMs = 0.3;
 
 // One launch as the device sees it.
 struct Batch {
@@ -511,16 +513,26 @@ struct Core {
     }
 
     // Whether what is ready waits for the launches in flight: while both are
-    // small (about 0.2 ms of the GPU together) requests that arrive meanwhile
-    // share the next launch; a launch of its own for each would leave most of
-    // the GPU idle (24 requests submitted in a row: 15-21 launches without
-    // this rule, since each ends before the next few are submitted).
+    // small, requests that arrive meanwhile share the next launch; a launch of
+    // its own for each leaves most of the GPU idle.  Small is a node count (0.2 ms
+    // of a full GPU), which says little about a few programs over very many cases,
+    // so nothing waits longer than kHoldMs for one launch.
+    // (Closed-loop clients of 20-1,000 programs x 500-8,000 cases, requests per
+    // second: 64 clients 14,800 without waiting, 34,000 waiting, 35,800-40,000 with
+    // the limit; 16 clients 15,500, 26,500, 27,000.  Four clients of 50 programs x
+    // 500 cases beside one of 8 programs of 127 nodes x 1,048,576 cases, p50: 0.24 ms
+    // without, 1.72 waiting for each 1.7 ms launch, 0.32 with the limit; a limit of
+    // 0.1 ms: 64 clients 28,800.)
     bool hold() const
     {
         if (busy_slots == 0 || cfg.one_launch_per_request || ready.front()->solo) return false;
         double work = 0.0;
-        for (const Slot& S : slots)
-            if (S.busy) work += S.work;
+        const double now = dev.now_ms();
+        for (const Slot& S : slots) {
+            if (!S.busy) continue;
+            if (now - S.t_launch_ms >= kHoldMs) return false;
+            work += S.work;
+        }
         size_t chunks = 0;
         for (const ReqPtr& R : ready) {
             const double cases = (double)datasets[(size_t)R->ds].n_cases;
