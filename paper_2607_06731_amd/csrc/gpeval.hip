@@ -104,10 +104,6 @@ namespace {
 // wavefronts waited 14% of the time at barriers for the longest.)
 constexpr int kLenBuckets = 16;
 constexpr int kKeys = kClasses * kLenBuckets;
-// The serial staging walks' limits (staging.h): constants held back for
-// folding per program, and their stride.
-constexpr int kHeldConsts = 16;
-constexpr int kBucketBlock = 1;
 constexpr int kMaxRequests = 4096;       // requests per batched call (tables are scanned by one workgroup)
 
 // Per-program record written by the staging passes.
@@ -466,7 +462,6 @@ template <class T> __device__ __forceinline__ const_ptr<T> as_const(const T* p)
 
 // ------------------------------------------------------------- staging
 typedef __attribute__((address_space(3))) float lds_f32;
-#define GP_STAGING_FN __device__
 #include "staging.h"
 #include "threaded.h"
 #include "interp_gfx950.h"

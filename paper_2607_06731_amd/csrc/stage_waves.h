@@ -10,8 +10,8 @@
 #pragma once
 
 // One wavefront stages one program: lane l holds node l of a 64-node chunk
-// (longer programs take several chunks), and what the serial walk of
-// staging.h decides node by node has a form over lanes.
+// (longer programs take several chunks), and what a serial walk (stage_lane)
+// decides node by node has a form over lanes.
 //   depth after a node   pushes minus pops up to it (two ballots)
 //   elements that depend on a variable (the runtime depth)
 //                        the smallest depth since the last variable or
@@ -22,11 +22,11 @@
 // From those each node knows the word it emits, if any, and the words before
 // it.  Serial, uniform in the wavefront, are only the folded operators (their
 // operands are the values at the last node of each depth) and, with the
-// whole command table (EXT), the named variables' cells.  (The serial walk, a
+// whole command table (EXT), the named variables' cells.  (A serial walk, a
 // program per lane, cost 275 instructions a node for every wavefront, the
 // union of what its 64 lanes were doing: 33 us for 32 programs, 70 us for
 // 10,000; with the whole table 64 + 75 us for 2,000.)  Statuses, depths and
-// values are the serial walk's; constants are held without its limit of 16.
+// values are the serial walk's; constants are held without a limit.
 //
 // LDS per wavefront: for each depth, one past the last node that left the
 // stack there in the chunks before, and the constant at it.

@@ -69,7 +69,7 @@ enum : uint32_t {
 };
 
 // Words of the threaded form, made from the runtime depth `rt` before the
-// instruction (staging.h's walk asks for them through this interface).
+// instruction.
 struct ThreadedWords {
     static __host__ __device__ uint32_t at(int rt, uint32_t off)
     {
