@@ -113,9 +113,8 @@ enum gp_op {
  * For the scoring entry points (gp_eval, gp_eval_noalloc,
  * gp_eval_correlation, gp_eval_reward, gp_eval_batched, plans, the server)
  * 0 means GP_BASE_OPS; for gp_validate and gp_predict 0 means GP_ALL_OPS.
- * A mask that reaches beyond GP_BASE_OPS runs an interpreter built for the
- * whole command table (same values for the benchmark set's commands; more
- * registers, so fewer wavefronts per SIMD). */
+ * A mask that reaches beyond GP_BASE_OPS has programs staged with the named
+ * variables and stack moves followed; one interpreter runs every command. */
 #define GP_BASE_OPS ((1u << 12) - 1u)
 /* COPY/PASTE variable names: @0 .. @15.  A valid program copies into a free
  * variable only, pastes a held one only, and ends with every variable
@@ -334,8 +333,7 @@ int gp_eval_batched(const gp_request* requests_dev, int32_t n_requests,
  * out: float32, out[p * ld_out + i] for i < n_cases, ld_out >= n_cases,
  * caller-owned device memory of n_programs * ld_out floats.  Values are the
  * fp32 results of the same interpreter gp_eval runs (NaN and +-inf kept).
- * allowed_op_mask may reach beyond GP_BASE_OPS (0 means GP_ALL_OPS): then
- * the interpreter built for the whole command table runs.
+ * allowed_op_mask may reach beyond GP_BASE_OPS (0 means GP_ALL_OPS).
  * Programs that fail validation get a NaN row and a nonzero out_status.
  * Asynchronous on `stream`; shares gp_eval's per-stream workspace.
  */
@@ -381,9 +379,14 @@ typedef struct {
 } gp_problem;                                       /* same meaning as gp_eval's arguments */
 
 typedef struct {
-    int32_t programs_per_item;   /* most programs per work item, 1..128 (default 64);
-                                    a depth class with few programs uses fewer */
-    int32_t wg_per_cu;           /* persistent workgroups per CU, 0 = occupancy limit */
+    int32_t programs_per_item;   /* most programs per work item, 1..128 (default 64;
+                                    above 64 as 64).  A depth class with few
+                                    programs uses fewer, and where a case tile
+                                    fits the staged memory an item holds up to 16
+                                    (more over fewer than 1,024 cases): the next
+                                    ones follow without a barrier */
+    int32_t wg_per_cu;           /* persistent workgroups per CU, 0 = occupancy limit
+                                    (three, or what the LDS allows) */
     int32_t concurrent_classes;  /* 0..2, accepted and reported: every depth class
                                     runs in one launch, so it changes nothing */
     int32_t tile_lds_bytes;      /* LDS budget of an input window, 4096..65536

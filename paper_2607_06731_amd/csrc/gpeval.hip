@@ -2796,8 +2796,9 @@ int time_config(gp_plan* p, const Tuning& t, hipStream_t stream, hipEvent_t e0, 
 
 // Time candidate knobs on the real inputs and keep the fastest: coordinate
 // descent over the axes (programs per work item, workgroups per CU, the LDS
-// budget of an input window, the cap on case tiles per program; the classes
-// share one launch, so `concurrent` has nothing to try), each axis tried in turn with the others at their
+// budget of an input window, the cap on case tiles per program), at values that
+// differ (an item holds at most 64 programs, a CU three workgroups, and a window of
+// up to 36 KB costs none of them), each axis tried in turn with the others at their
 // best so far, two sweeps, each candidate the median of five runs; then the
 // three fastest candidates are timed again in turns (five rounds, one run
 // each per round, so drift hits them alike) and the lowest median wins.
@@ -2819,12 +2820,10 @@ int plan_autotune(gp_plan* p, hipStream_t stream)
     hipEvent_t e0, e1;
     GP_HIP_TRY(hipEventCreate(&e0));
     GP_HIP_TRY(hipEventCreate(&e1));
-    const int kAxes = 5;
-    const std::vector<int> values[kAxes] = {{32, 64, 128}, {0, 3, 4}, {0},
-                                            {12 * 1024, 24 * 1024, 40 * 1024}, {2, 8, 32}};
+    const int kAxes = 4;
+    const std::vector<int> values[kAxes] = {{16, 32, 64}, {0, 2}, {12 * 1024, 24 * 1024, 36 * 1024}, {2, 8, 32}};
     auto field = [](Tuning& t, int a) -> int& {
-        return a == 0 ? t.G : a == 1 ? t.wg_per_cu : a == 2 ? t.concurrent
-                                                            : a == 3 ? t.tile_lds : t.tile_max;
+        return a == 0 ? t.G : a == 1 ? t.wg_per_cu : a == 2 ? t.tile_lds : t.tile_max;
     };
     Tuning best = p->tu;
     float best_ms = 1e30f;

@@ -12,12 +12,7 @@ constexpr uint32_t kVarPayload = 1024u;
 // Op kinds of the command table.  Unary selectors: the benchmark set's six
 // (SIN..ABS) first, then SQUARE..SQRT_RAW; POW's selector follows ADD..DIV.
 // (bit tables over the 28 opcodes: one shift per test)
-constexpr uint32_t kBinaryOps = 0x3Cu | (1u << GP_POW);                    // ADD..DIV, POW
 constexpr uint32_t kUnaryOps = 0xFC0u | (((1u << 10) - 1u) << GP_SQUARE);  // SIN..ABS, SQUARE..SQRT_RAW
-__host__ __device__ constexpr bool op_is_binary(uint32_t op)
-{
-    return op < 32u && ((kBinaryOps >> op) & 1u);
-}
 __host__ __device__ constexpr bool op_is_unary(uint32_t op)
 {
     return op < 32u && ((kUnaryOps >> op) & 1u);

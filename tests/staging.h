@@ -59,6 +59,11 @@ __host__ __device__ inline int depth_class(int maxd)
     return maxd <= 8 ? 0 : (maxd <= 16 ? 1 : 2);
 }
 
+constexpr uint32_t kBinaryOps = 0x3Cu | (1u << GP_POW);                    // ADD..DIV, POW
+__host__ __device__ constexpr bool op_is_binary(uint32_t op)
+{
+    return op < 32u && ((kBinaryOps >> op) & 1u);
+}
 __host__ __device__ constexpr uint32_t bop_sel(uint32_t op) { return op == GP_POW ? 4u : op - GP_ADD; }
 
 // Emits the staged instructions of one valid program (the check counts
