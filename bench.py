@@ -42,17 +42,17 @@ if ROOT not in sys.path:
 # operation as two flops).  One node evaluation needs at least one such
 # operation.
 PEAK_LANE_OPS = 256 * 128 * 2.4e9
-# fp32 VALU instructions per case of each operator as the interpreter
-# computes it in its common path (opcodes LOAD, CONST, ADD, SUB, MUL, DIV,
-# SIN, COS, EXP, LOG, SQRT, ABS): the operator's own arithmetic counted in
-# the AMD assembly of the library's operator functions compiled alone for
-# gfx950 (tests/test_op_costs.py recounts them), plus one for the
-# wavefront's range compare where the interpreter makes one (sin, cos and
-# exp: the fast formula; square root: the hardware root of |a|, the
-# denormal-safe scaling only when some case is tiny).  Protected division:
-# IEEE division plus the guard's compare and select; ln: hardware log2,
-# the split ln 2 product and the guard.  Leaves are LDS reads, no VALU
-# arithmetic.
+# fp32 VALU instructions per case of each operator in the interpreter's fast
+# handlers (opcodes LOAD, CONST, ADD, SUB, MUL, DIV, SIN, COS, EXP, LOG, SQRT,
+# ABS): the operator's own arithmetic, counted in the macros of interp_gfx950.h
+# (tests/test_handler_costs.py recounts them).  The range tests in front of
+# division and the functions, two to thirteen instructions for all of a lane's
+# cases together, are not in it.  Leaves are LDS reads, no VALU arithmetic.
+HANDLER_VALU = (0, 0, 1, 1, 1, 6, 12, 14, 9, 3, 1, 1)
+# The same of the library's general forms, which take any value (constant
+# folding, and cases outside the fast ranges), counted in the AMD assembly of the
+# operator functions compiled alone for gfx950 (tests/test_op_costs.py), plus
+# one for the range compare of sin, cos, exp and the square root.
 OP_VALU = (0, 0, 1, 1, 1, 13, 15, 17, 10, 5, 2, 1)
 
 
@@ -149,8 +149,8 @@ def code_digest(texts):
 
 
 def measured_counters(workload):
-    """Counter figures of the dominant kernel (HBM bytes per launch, VALU busy
-    fraction, VALU lane-slots per node evaluation, scalar instructions per
+    """Counter figures of the dominant kernel (HBM bytes per launch,
+    VALU lane-slots per node evaluation, scalar instructions per
     interpreted instruction, scalar-cache miss rate) from the committed
     counter summary, while the kernel source is the one the counters were
     taken on; an empty dict otherwise."""
@@ -168,7 +168,7 @@ def measured_counters(workload):
     if not m or m.group(1) != digest:
         return {}
     out = {}
-    for key, cast in (("traffic_bytes_per_launch", int), ("valu_busy", float),
+    for key, cast in (("traffic_bytes_per_launch", int),
                       ("valu_lane_slots_per_node_eval", float),
                       ("salu_per_dispatch", float), ("scalar_cache_miss_rate", float)):
         v = re.search(r"%s: ([0-9.]+)" % key, text)
@@ -360,9 +360,9 @@ def throughput(args):
     # once per program at staging)
     ex = executed_node_counts(w.pop.nodes, w.pop.offsets)
     ex0 = int(ex[cls0].sum()) * w.data.n_cases
-    # the operators' own arithmetic (OP_VALU lane operations per case)
+    # the operators' own arithmetic (HANDLER_VALU lane operations per case)
     mix0 = executed_operator_mix(w.pop.nodes, w.pop.offsets, cls0)
-    math0 = int(sum(int(mix0[k]) * OP_VALU[k] for k in range(12))) * w.data.n_cases
+    math0 = int(sum(int(mix0[k]) * HANDLER_VALU[k] for k in range(12))) * w.data.n_cases
     # algorithmic bytes of the launch: each input read once (the programs'
     # nodes, offsets, the cases and targets) and one value per program out
     algo0 = (4 * int(lens[cls0].sum()) + 16 * int(cls0.sum())
@@ -379,7 +379,6 @@ def throughput(args):
                 "algorithmic_bytes_per_launch": algo0,
                 "traffic_over_algorithmic": (round(traffic / algo0, 2) if traffic else None),
                 "traffic": traffic,
-                "valu_busy": counters.get("valu_busy"),
                 "valu_lane_slots_per_node_eval": counters.get("valu_lane_slots_per_node_eval"),
                 "salu_per_dispatch": counters.get("salu_per_dispatch"),
                 "scalar_cache_miss_rate": counters.get("scalar_cache_miss_rate"),
