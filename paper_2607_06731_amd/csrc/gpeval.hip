@@ -5,6 +5,9 @@
 //                    dataset and request tables, lays the requests out back
 //                    to back and derives tile shapes (a single request's
 //                    entries travel as kernel arguments).
+//   k_stage_lanes    calls of many short programs: one lane per program does
+//                    what k_stage_waves does with a wavefront, and leaves long
+//                    and deep programs to it.
 //   k_stage_waves    one wavefront per program: validate (GCL stack
 //                    discipline, 32-cell limit, opcode/operand ranges,
 //                    allowed ops) and stage each instruction as one 8-byte
@@ -1768,9 +1771,11 @@ __device__ __forceinline__ uint32_t list_chunk(const RunArgs& a, int obase, int 
 // own left the GPU to each tail in turn and cost 13 us when it was empty.)
 // WIDE: datasets of so many variables that a sub-tile leaves no room for the
 // long list.
-// Bound by vector issue (threaded.h): 80 registers hold 32 of stack, 16 of
-// temporaries and the epilogue's, for six wavefronts per SIMD; the
-// correlation sums take more.
+// Bound by vector issue (threaded.h).  80 registers leave six wavefronts per SIMD:
+// 32 of stack, 16 of temporaries and the epilogue's; the compiler spills 23 for MSE
+// and 46 for the reward, which still measured faster than fewer wavefronts
+// (reward, 9,973 programs x 4,096 cases: 244 -> 237 us).  The correlation sums take
+// 128 registers, four wavefronts.
 template <int FIT, bool SPLIT, bool WIDE>
 __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs a)
 {
@@ -1817,9 +1822,12 @@ __global__ __launch_bounds__(kRunWG, FIT == kFitCorr ? 4 : 6) void k_run(RunArgs
         // Run by run: the next item is mostly over the same cases.  A class of
         // few items with many runs of tiles takes them group by group instead,
         // all runs of the longest programs first, so the launch ends on short
-        // programs: 2,000 programs x 1,048,576 cases (32 runs) 7.47 -> 6.67 ms,
-        // outputs of 1,000 x 16,384 (16 runs) 130 -> 111 us; with 4 and 5 runs
-        // the staging of every item costs more (10,000 x 4,099: 267 -> 312 us).
+        // programs.  (us per call run by run and group by group: 300 programs x
+        // 65,536 cases 203 and 170, 3,000 x 65,536 714 and 626, 10,000 x 262,144
+        // 7,530 and 6,232, 2,000 x 1,048,576 7,470 and 6,670; with many items
+        // the staging of each costs more: 30,000 x 16,384 1,321 and 1,442, x 65,536
+        // 4,706 and 5,435.  With 4 and 5 runs it goes either way: 10,000 x 4,099
+        // correlations 267 and 312, 10,000 x 10,000 443 and 397.)
         const uint32_t n_class = c == 2 ? n2 : (c == 1 ? n1 : n0), tile_runs = (uint32_t)item_groups(n_tiles, m);
         const bool by_group = ns == 1 && tile_runs >= kManyRuns && n_class < kFewItems * gridDim.x;
         const uint32_t inner = by_group ? tile_runs : groups, o = local / inner, i = local - o * inner;

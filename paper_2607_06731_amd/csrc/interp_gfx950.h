@@ -311,11 +311,13 @@ asm volatile(R"(
  .endr
 .endm
 // cell \a = cell \a / cell \a+1 inside the range of GP_DIVRANGE: reciprocal, one
-// Newton step, quotient, one residual correction.  Correctly rounded: the
-// residual a - b q was compared with half a unit in the last place of q for
-// every pair of significands (2^46 of them) on an MI355X, and the reciprocal
-// scales exactly with its operand's exponent over the range; inside it no step
-// overflows and no residual is denormal.  (The general form: 50 clocks of vector
+// Newton step, quotient, one residual correction.  Inside the range no step
+// overflows, no residual is denormal, and the reciprocal scales exactly with its
+// operand's exponent, so the quotient's rounding depends on the significands
+// alone.  It is the IEEE quotient: found once for every pair of significands (2^46)
+// on an MI355X by comparing the residual a - b q with half a unit in the last
+// place of q; the tests cover every divisor significand under seven dividends and
+// 2^23 random pairs six times over.  (The general form: 50 clocks of vector
 // issue per case; this one: 20, and 6 for the range.)
 .macro GP_DIV K, a
  .irp j,0,1,2,3

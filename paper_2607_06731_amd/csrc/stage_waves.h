@@ -41,10 +41,17 @@ struct WaveTables {
 // operands of equal need is the only one that takes a cell more, and a program
 // of 128 nodes needs at most 7.  (In the order written, an eighth of the
 // programs of up to 64 nodes need more than 8 cells, a third of those of up to
-// 128 -- half of all nodes -- and run at two or one cases per lane.)  The results are the same: no operator's operands change, only which
-// of them is ready first.  The walk takes a wavefront 4 us, which datasets of
-// fewer than 2,048 cases do not give back (1,000 programs x 1,024 cases: 43 us
-// without it, 49 with it; 60,000 x 16,384: 1,719 and 1,609).
+// 128 -- half of all nodes -- and run at two or one cases per lane.)  The results
+// are the same: no operator's operands change, only which of them is ready first.
+// The walk takes a wavefront 4 us, which short datasets do not give back.  (us per
+// call with and without it, programs of 3-64 nodes: 50,000 x 1,024 cases 265 and
+// 256, x 2,048 401 and 417, x 8,192 1,083 and 1,238; 10,000 x 1,024 104 and 127,
+// x 2,048 154 and 147, x 8,192 368 and 390; 1,000 x 1,024 50 and 44, x 2,048 62
+// and 52, x 8,192 89 and 97; of 3-128 nodes 50,000 x 1,024 469 and 466, x 2,048 719
+// and 787, x 8,192 1,998 and 2,523; 1,000 x 2,048 85 and 90.  Calls of few programs
+// would gain from a higher limit, those of 10,000 from a lower one; the limit
+// looks at the dataset alone, so that a program is staged the same way in any
+// population.)
 constexpr int kReorderMax = 128;         // nodes: two per lane
 constexpr int64_t kReorderCases = 2048;
 constexpr uint32_t kReversed = 1u << 8;  // on - and / of the reordered program: the top is the left operand
