@@ -127,7 +127,9 @@ enum gp_op {
 enum gp_prog_status {
     GP_PROG_OK = 0, GP_PROG_EMPTY = 1, GP_PROG_BAD_OP = 2, GP_PROG_BAD_VAR = 3,
     GP_PROG_BAD_CONST = 4, GP_PROG_UNDERFLOW = 5, GP_PROG_TOO_DEEP = 6,
-    GP_PROG_FINAL_DEPTH = 7, GP_PROG_BAD_OFFSETS = 8,
+    GP_PROG_FINAL_DEPTH = 7,
+    GP_PROG_BAD_OFFSETS = 8,  /* offsets decrease or leave the nodes, or (on the
+                                 device) the program has over 2^29 - 16 nodes */
     GP_PROG_BAD_TABLE = 9,    /* gp_eval_batched: invalid dataset/request table */
     GP_PROG_BAD_PAIR = 10     /* COPY/PASTE not paired (see GP_GCL_VARS) */
 };

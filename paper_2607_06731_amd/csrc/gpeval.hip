@@ -634,10 +634,14 @@ template <class T> __device__ __forceinline__ const_ptr<T> again(const_ptr<T> p)
     return p;
 }
 
+// Nodes of a program, at most: the interpreter's offset of the word after the next
+// (8 bytes each, never more words than nodes) has 32 bits.
+constexpr int64_t kMaxNodes = (int64_t(1) << 29) - 16;
+
 // The status that program g's range alone gives (GP_PROG_OK: look at its nodes).
 __device__ __forceinline__ int range_status(const ProgRange& g, bool tab_ok)
 {
-    const bool ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= INT32_MAX - 1;
+    const bool ok = g.s >= 0 && g.e >= g.s && g.e <= g.n_nodes && g.e - g.s <= kMaxNodes;
     return !tab_ok ? GP_PROG_BAD_TABLE : (!ok ? GP_PROG_BAD_OFFSETS : (g.e == g.s ? GP_PROG_EMPTY : GP_PROG_OK));
 }
 
