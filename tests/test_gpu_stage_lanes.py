@@ -73,19 +73,41 @@ def test_scores_equal_those_of_small_calls(gcl, broken, n_cases):
 
 
 @pytest.mark.parametrize("n_cases", [37, 2048])
-def test_offsets_that_step_back(n_cases):
+@pytest.mark.parametrize("gcl", [False, True])
+def test_offsets_that_step_back(gcl, n_cases):
     gp = _gp()
     rng = np.random.default_rng(5)
-    nodes, offsets, consts = _mixed(rng, 60000, False, False)
+    nodes, offsets, consts = _mixed(rng, 60000, gcl, False)
+    mask = synth.MASK_GCL if gcl else synth.MASK_2
     P = offsets.size - 1
     X = rng.uniform(-2, 2, (3, n_cases)).astype(np.float32)
-    ref = gp.evaluate(nodes, offsets, consts, X, X[1], 0.0, synth.MASK_2)
+    ref = gp.evaluate(nodes, offsets, consts, X, X[1], 0.0, mask)
     full = np.concatenate([nodes, np.zeros(400, np.uint32)])
-    F, st = gp.evaluate(full, np.concatenate([offsets, offsets[:41]]), consts, X, X[1], 0.0, synth.MASK_2,
+    F, st = gp.evaluate(full, np.concatenate([offsets, offsets[:41]]), consts, X, X[1], 0.0, mask,
                         return_status=True)
     assert st[P] == 8 and (np.delete(st, P) == 0).all()
     got, want = np.delete(F, P), np.concatenate([ref, ref[:40]])
     assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
+
+
+def test_blocks_of_more_programs_than_a_round():
+    """Over 1,024 programs per staging block: k_stage_waves looks them through in
+    rounds."""
+    gp = _gp()
+    rng = np.random.default_rng(8)
+    nodes, offsets, consts = _mixed(rng, 120000, False, True)
+    k = 11
+    lens = np.tile(np.diff(offsets), k)
+    all_nodes, all_off = np.tile(nodes, k), np.concatenate([[0], np.cumsum(lens)])
+    assert all_off.size - 1 > 1024 * 1024
+    X = rng.uniform(-2, 2, (3, 37)).astype(np.float32)
+    ref, s0 = gp.evaluate(nodes, offsets, consts, X, X[1], 0.0, synth.MASK_2, return_status=True)
+    F, st = gp.evaluate(all_nodes, all_off, consts, X, X[1], 0.0, synth.MASK_2, return_status=True)
+    assert np.array_equal(st, np.tile(s0, k))
+    want = np.tile(ref, k)
+    nan = np.isnan(want)
+    assert np.array_equal(np.isnan(F), nan)
+    assert np.array_equal(F.view(np.uint64)[~nan], want.view(np.uint64)[~nan])
 
 
 def test_requests_of_one_launch():
