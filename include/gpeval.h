@@ -385,7 +385,7 @@ typedef struct {
                                     above 64 as 64).  A depth class with few
                                     programs uses fewer, and where a case tile
                                     fits the staged memory an item holds up to 16
-                                    (more over fewer than 1,024 cases): the next
+                                    (32 or 64 over at most 512 or 256 cases): the next
                                     ones follow without a barrier */
     int32_t wg_per_cu;           /* persistent workgroups per CU, 0 = occupancy limit
                                     (three, or what the LDS allows) */

@@ -186,7 +186,8 @@ __host__ __device__ inline ClassCut class_cut(int c, int32_t count, int32_t pass
     if (whole) {
         const int64_t all = (n_cases + 255) & ~(int64_t)255;
         const int64_t cases = m * tile < all ? m * tile : all;
-        const int32_t on = kRunOnCases / cases > kRunOn ? (int32_t)(kRunOnCases / cases) : kRunOn;
+        int32_t on = kRunOn;
+        while (2 * on * cases <= kRunOnCases) on *= 2;
         most = most < on ? most : on;
     }
     r.G = cut_programs((double)count * (double)groups, most, target_items);

@@ -61,6 +61,8 @@ int main(int argc, char** argv)
             const ClassCut cut = class_cut(c, count, t.passes, t.n_tiles, n_cases, rows, g_max, 4 * 3 * 256, lds_floats,
                                            !wide && rng() % 2, fit == 3);
             CHECK(cut.G >= 1 && cut.G <= g_max);
+            CHECK(cut.split || (int64_t)t.passes * t.sub > staged_cases(lds_floats, rows) || cut.G <= kRunOn ||
+                  cut.G * std::min<int64_t>((int64_t)t.passes * t.sub, (n_cases + 255) / 256 * 256) <= kRunOnCases);
             const int32_t m = item_tiles(t.passes, t.n_tiles, c, rows, lds_floats, cut.m_cap);
             const int32_t runs = item_groups(t.n_tiles, m), groups = (count + cut.G - 1) / cut.G;
             CHECK(cut.items == (uint32_t)groups * (uint32_t)runs);
